@@ -735,7 +735,7 @@ void launch_adj_reverse_step(const void* A, const void* lamB, void* lamA, const 
                              const AdjBufs& a, const double* mdt, const double* upt,
                              const double* Jt, uint32_t step, double kT, int ntiles, int tile_nodes, int nslots,
                              int nb, int n_sub, hipStream_t s) {
-  launch_bead_prep(d, nslots, s);
+  launch_bead_prep(d, nslots, 0, s);
   hipLaunchKernelGGL((k_adj_spread_t<T>), dim3(nblk(nb, 64)), dim3(64), 0, s, (const T*)lamB, d, a, Jt, nb);
   // neighbour lists at the step's start positions (d.r is the tape's r_n),
   // checked against every sub-step's force positions

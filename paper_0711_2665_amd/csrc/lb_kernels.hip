@@ -93,10 +93,12 @@ __global__ __launch_bounds__(64) void k_lb_forced(const T* __restrict__ A, T* __
 // Start of a coupled step: remember r(n), link every bead into the list of
 // its base node, clear J, and mark the stencil nodes of r(n) as carrying bead
 // force this step (solid ones are dropped by the spreading; every writer of
-// a node stores the same byte).
+// a node stores the same byte).  Also opens the flags of the MD sub-cycle, of
+// nrep replicas.
 // ---------------------------------------------------------------------------
-__global__ void k_bead_prep(Dev d, int nslots) {
+__global__ void k_bead_prep(Dev d, int nslots, int nrep) {
   int slot = blockIdx.x * blockDim.x + threadIdx.x;
+  if (blockIdx.x == 0 && nrep > 0) md_begin(d, nrep, threadIdx.x, blockDim.x);
   if (slot >= nslots) return;
   const Rep& R = d.reps[d.slot_rep[slot]];
   if (slot - R.slot_off >= R.mp.nb) return;
@@ -623,8 +625,8 @@ void launch_gather(const void* A, const Dev& d, int nslots, int start, hipStream
                        nslots, start);
 }
 
-void launch_bead_prep(const Dev& d, int nslots, hipStream_t s) {
-  if (nslots > 0) hipLaunchKernelGGL(k_bead_prep, dim3(blocks_for(nslots, 64)), dim3(64), 0, s, d, nslots);
+void launch_bead_prep(const Dev& d, int nslots, int nrep, hipStream_t s) {
+  if (nslots > 0) hipLaunchKernelGGL(k_bead_prep, dim3(blocks_for(nslots, 64)), dim3(64), 0, s, d, nslots, nrep);
 }
 
 template <typename T>

@@ -75,6 +75,7 @@ struct Packing {
   long obs_tiles = 0;
   long wl_blocks_max = 0;           // wall-link list blocks (LEDGER_BLOCK entries each), upper bound
   int nseg = 0;                     // chain segments of the fused sub-cycle (FUSED_OWN beads each)
+  int nrseg = 0;                    // chain segments of the resident sub-cycle (RES_OWN beads each)
 };
 
 // Fluid nodes with a solid upstream neighbour lie in the three planes around
@@ -98,6 +99,7 @@ Packing packing(const lb_desc* d, int nrep) {
     pk.obs_tiles += (N + OBS_TILE - 1) / OBS_TILE;
     pk.wl_blocks_max += (wall_link_bound(d[r]) + LEDGER_BLOCK - 1) / LEDGER_BLOCK;
     pk.nseg += (d[r].nb + FUSED_OWN - 1) / FUSED_OWN;
+    pk.nrseg += (d[r].nb + RES_OWN - 1) / RES_OWN;
   }
   pk.slots_alloc = pk.slots > 0 ? pk.slots : 1;
   return pk;
@@ -105,7 +107,7 @@ Packing packing(const lb_desc* d, int nrep) {
 
 struct WorkLayout {
   size_t ctrl, reps, tiles, otiles, slot_rep, head, next, base, touched, nbr, ncnt, rb, rmid0, rmid1, ref, part, xi,
-      tX, notdone, ccount, cbuf, rbin, cst, wlinks, ledger, lpart, lsp, fseg, rmS, vS, JS, fang, redo;
+      tX, notdone, ccount, cbuf, rbin, cst, wlinks, ledger, lpart, lsp, fseg, rmS, vS, JS, fang, redo, rseg, xring, xflag;
   size_t nbuckets;
   size_t total;
 };
@@ -151,6 +153,9 @@ WorkLayout work_layout(const lb_desc* d, int nrep, const Packing& pk) {
   w.JS = take(sizeof(double) * 3 * ns);
   w.fang = take(sizeof(double) * 9 * ns);
   w.redo = take(sizeof(int) * R);
+  w.rseg = take(sizeof(FusedSeg) * (size_t)(pk.nrseg > 0 ? pk.nrseg : 1));
+  w.xring = take(sizeof(uint64_t) * 4 * 2 * 3 * ns);
+  w.xflag = take(sizeof(uint64_t) * 2 * 2 * (size_t)(pk.nrseg > 0 ? pk.nrseg : 1));
   w.total = o;
   return w;
 }
@@ -350,6 +355,10 @@ struct SweepCfg {
   int cap = 0;        // 0, or at most this many sweep workgroups per CU (LDS reserved)
 };
 
+// A wait inside the resident sub-cycle normally lasts microseconds; longer
+// ones mean that the GPU is shared.
+constexpr uint64_t RES_WAIT = 10000000;   // 0.1 s
+
 struct lb_ctx {
   std::vector<lb_desc> d;
   int nrep = 1;
@@ -380,6 +389,9 @@ struct lb_ctx {
   int fusedK = 0;            // sub-steps per fused block of the uniform sub-cycle (0: one launch per sub-step)
   int fusedK_max = 0;        // the block length the context supports (0: none)
   FusedBufs fb{};
+  bool resident = false;     // the uniform sub-cycle runs in one launch of co-resident workgroups
+  const FusedSeg* rseg = nullptr;
+  uint64_t md_wait = RES_WAIT;   // longest wait inside it, ticks of the 100 MHz clock
   int64_t steps = 0;
   // second stream for the sweep over the nodes without bead force, which
   // runs concurrently with the bead phase; fork/join events
@@ -567,22 +579,30 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
   ev_record(c, c->fork, st);
   ev_wait(c, sb, c->fork);
   prof_mark(c, 0, sb);
-  launch_bead_prep(D, c->nslots, sb);
-  ev_record(c, c->prep, sb);
-  ev_wait(c, c->s2, c->prep);
-  prof_mark(c, 2, c->s2);
-  sweep_ab(c, A, B, 1, c->s2);
-  prof_mark(c, 3, c->s2);
-  // the wall's bounce-back momentum of this step (reads A, which no kernel
-  // of this step writes), and the next step's noise, into the other slot,
-  // after the sweep: off the bead stream's path
-  ledger_bb(c, A, c->s2);
-  if (c->any_noise) launch_md_noise(with_noise_slot(c, c->cur ^ 1), c->nslots, c->n_sub, 1, c->s2);
   // the lists of this step were built at the end of the previous one
-  // (beside the spreading), unless the positions changed since
+  // (beside the spreading), unless the positions changed since; their validity
+  // flags are read when the preparation opens the sub-cycle
   if (c->step_lists && c->lists_stale) launch_nbr_build(D, c->nslots, c->nrep, sb);
-  // the gather also opens the sub-cycle (after its flag reset)
-  launch_md_begin(D, c->nrep, sb);
+  launch_bead_prep(D, c->nslots, c->nrep, sb);
+  ev_record(c, c->prep, sb);
+  const bool resident = c->resident && c->mts == 0 && (c->fusedK == 0 || D.mdtape);
+  auto sweep_side = [&]() {
+    ev_wait(c, c->s2, c->prep);
+    if (resident) launch_md_gate(D, c->pk.nrseg, c->s2);
+    prof_mark(c, 2, c->s2);
+    sweep_ab(c, A, B, 1, c->s2);
+    prof_mark(c, 3, c->s2);
+    // the wall's bounce-back momentum of this step (reads A, which no kernel
+    // of this step writes), and the next step's noise, into the other slot,
+    // after the sweep: off the bead stream's path
+    ledger_bb(c, A, c->s2);
+    if (c->any_noise) launch_md_noise(with_noise_slot(c, c->cur ^ 1), c->nslots, c->n_sub, 1, c->s2);
+  };
+  // enqueued before the sub-cycle's many launches, but after the resident
+  // cycle's two: where both streams share a hardware queue, the gate before
+  // the sweep then follows the workgroups it waits for
+  if (!resident) sweep_side();
+  // the gather also opens the sub-cycle
   const int start = c->mts > 0 ? 2 : 1;
   if (c->dev) launch_gather<float, true>(A, D, c->nslots, start, sb);
   else launch_gather<double, false>(A, D, c->nslots, start, sb);
@@ -590,7 +610,10 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
   if (c->mts > 0) launch_md_cycle_mts(D, c->nslots, c->nrep, c->n_sub, c->mts, sb, false);
   else if (c->fusedK > 0 && !D.mdtape)
     launch_md_cycle_fused(D, c->fb, c->pk.nseg, c->nslots, c->nrep, c->n_sub, c->fusedK, sb);
+  else if (resident)
+    launch_md_cycle_resident(D, c->fb, c->rseg, c->pk.nrseg, c->nslots, c->nrep, c->n_sub, none, c->md_wait, sb);
   else launch_md_cycle(D, c->nslots, c->nrep, c->n_sub, none, sb, false, c->any_constrained);
+  if (resident) sweep_side();
   ev_record(c, c->mdone, sb);
   if (c->dev) launch_spread_lb<float, true>(A, B, D, c->nslots, sb);
   else launch_spread_lb<double, false>(A, B, D, c->nslots, sb);
@@ -880,6 +903,10 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
       for (int K = FUSED_K; K >= 2; --K)
         if (d[0].n_sub % K == 0) { c->fusedK_max = K; break; }
     c->fusedK = 0;
+    c->resident = d[0].mts_outer == 0 && !rigid && c->pk.nrseg > 0 && c->pk.nrseg <= RES_MAX_WG &&
+                  c->n_sub >= RES_MIN_SUB;
+    // a shorter limit sends every wait to the redo (tests)
+    if (const char* e = std::getenv("LBMD_MD_WAIT_TICKS")) c->md_wait = std::strtoull(e, nullptr, 10);
   }
   const double skin = SKIN_STEP;
   const size_t ns = (size_t)c->pk.slots_alloc;
@@ -962,6 +989,9 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   D.lpart = (double*)(w + c->wl.lpart);
   D.lsp = (double*)(w + c->wl.lsp);
   D.redo = (int*)(w + c->wl.redo);
+  D.xring = (unsigned long long*)(w + c->wl.xring);
+  D.xflag = (unsigned long long*)(w + c->wl.xflag);
+  c->rseg = (const FusedSeg*)(w + c->wl.rseg);
   c->fb.seg = (const FusedSeg*)(w + c->wl.fseg);
   c->fb.rmS = (double*)(w + c->wl.rmS);
   c->fb.vS = (double*)(w + c->wl.vS);
@@ -986,6 +1016,11 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
     for (int a = 0; a < d[r].nb; a += FUSED_OWN) segs.push_back(FusedSeg{r, a, std::min(a + FUSED_OWN, d[r].nb), 0});
   if (!segs.empty())
     acc(hipMemcpyAsync(w + c->wl.fseg, segs.data(), sizeof(FusedSeg) * segs.size(), hipMemcpyHostToDevice, s));
+  std::vector<FusedSeg> rsegs;
+  for (int r = 0; r < nrep; ++r)
+    for (int a = 0; a < d[r].nb; a += RES_OWN) rsegs.push_back(FusedSeg{r, a, std::min(a + RES_OWN, d[r].nb), 0});
+  if (!rsegs.empty())
+    acc(hipMemcpyAsync(w + c->wl.rseg, rsegs.data(), sizeof(FusedSeg) * rsegs.size(), hipMemcpyHostToDevice, s));
   launch_fill_i32(D.redo, nrep, -1, s);
   launch_fill_f64(D.ledger, (long)NLEDGER * nrep, 0.0, s);
   // rest populations, replica by replica ([19][N_r] from element 19 node_off)
@@ -1164,7 +1199,14 @@ int md_relax(lb_ctx* c, int nsub_total, double gamma_relax) {
   int left = nsub_total;
   while (left > 0) {
     int n = left < c->n_sub ? left : c->n_sub;
-    launch_md_cycle(c->D, c->nslots, c->nrep, n, ov, c->s, true, c->any_constrained);
+    if (c->resident && n >= RES_MIN_SUB) {
+      launch_nbr_build(c->D, c->nslots, c->nrep, c->s);
+      launch_md_begin(c->D, c->nrep, c->s);
+      launch_md_start(c->D, c->nslots, ov, c->s);
+      launch_md_cycle_resident(c->D, c->fb, c->rseg, c->pk.nrseg, c->nslots, c->nrep, n, ov, c->md_wait, c->s);
+    } else {
+      launch_md_cycle(c->D, c->nslots, c->nrep, n, ov, c->s, true, c->any_constrained);
+    }
     left -= n;
   }
   launch_zero_v(c->D, c->nslots, c->s);

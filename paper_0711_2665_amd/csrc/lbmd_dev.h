@@ -115,7 +115,9 @@ struct Ctrl {
   // the displacement bound
   uint32_t fused_why[5];
   uint32_t nbr_max;          // longest neighbour list a per-step build found (diagnostic)
-  uint32_t pad[42];
+  uint64_t cycles;           // sub-cycles opened so far: the tag of the resident cycle's exchanges
+  uint32_t placed[2];        // workgroups of the current resident cycle (its first, its second launch) that have started
+  uint32_t pad[38];
 };
 static_assert(sizeof(Ctrl) == 256, "control block is one 256-byte line");
 
@@ -150,12 +152,20 @@ __host__ __device__ inline bool site_solid(const Geom& g, int sx, int sy, int sz
 }
 
 // Wrap an unwrapped coordinate into [0, n): w = x - n floor(x / n), reduced
-// once more if rounding lands on n.  For 0 <= x < n - 1 the quotient is
-// certainly in [0, 1) so the result is x itself; that case skips the
-// division and returns the same bits.
-__device__ inline double wrapc(double x, int n) {
+// once more if rounding lands on n.  Within a period of the box the floor is
+// known, so the division (a third of the wall wave's time for a chain that
+// sits across a boundary) is skipped and the same bits returned: 0 on [0, n)
+// (the rounded quotient of x < n is below 1), 1 on [n, 2n), -1 on [-n, 0)
+// but for magnitudes whose quotient might underflow to zero.
+__host__ __device__ inline double wrapc(double x, int n) {
   double dn = (double)n;
-  if (x >= 0.0 && x < dn - 1.0) return x;
+  if (x >= 0.0 && x < dn) return x;
+  if (x >= dn && x < 2.0 * dn) return x - dn;
+  if (x >= -dn && x < -1e-200) {
+    double w = x + dn;
+    if (w >= dn) w = w - dn;
+    return w;
+  }
   double q = floor(x / dn);
   double w = x - dn * q;
   if (w >= dn) w = w - dn;

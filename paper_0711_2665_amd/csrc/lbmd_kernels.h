@@ -119,6 +119,10 @@ struct Dev {
   uint32_t* cst;    // per replica, 3 rotating words: some bead is farther than CELL_MARGIN
                     // from its binned position at that sub-step (the table is not usable)
   uint32_t cmask;   // buckets - 1 (a power of two minus one)
+  unsigned long long* xring;   // [4][slots][3][2]: positions exchanged inside a resident cycle, each as its
+                    // bits and its bits XOR the sub-step's tag (slots 0, 1: every sub-step; 2, 3: the
+                    // start of a block)
+  unsigned long long* xflag;   // [2][segments][2]: a word per segment at the start of a block, likewise
   Ctrl* ctrl;
   int* redo;        // per replica: first sub-step the fused sub-cycle leaves to the per-sub-step
                     // launches (-1: none); reset at every cycle's opening
@@ -150,10 +154,11 @@ void launch_lb(const void* A, void* B, const Dev& d, int ntiles, int tile_nodes,
 template <typename T, bool DEV>
 void launch_lb_forced(const void* A, void* B, const Dev& d, int maxlist, hipStream_t s);
 // start: 0, or also open the MD sub-cycle (what k_md_start does: 1 for
-// uniform sub-steps, 2 for the multiple-time-step cycle) after launch_md_begin
+// uniform sub-steps, 2 for the multiple-time-step cycle) after its flags
 template <typename T, bool DEV>
 void launch_gather(const void* A, const Dev& d, int nslots, int start, hipStream_t s);
-void launch_bead_prep(const Dev& d, int nslots, hipStream_t s);
+// nrep > 0: also opens the MD sub-cycle's flags (launch_md_begin)
+void launch_bead_prep(const Dev& d, int nslots, int nrep, hipStream_t s);
 template <typename T>
 void launch_spread(const Dev& d, int nslots, hipStream_t s);
 // Spreading fused with the update of the nodes it writes (forward step).
@@ -211,6 +216,7 @@ void launch_adj_finish(const AdjBufs& a, double* grads, int nb, hipStream_t s);
 void launch_md_cycle(const Dev& d, int nslots, int nrep, int n_sub, const MdOverride& ov, hipStream_t s,
                      bool prologue = true, bool constrained = false);
 void launch_md_begin(const Dev& d, int nrep, hipStream_t s);
+void launch_md_start(const Dev& d, int nslots, const MdOverride& ov, hipStream_t s);
 // The multiple-time-step sub-cycle of a coupled step: M outer steps of
 // n_sub / M SPV sub-steps with the bonded forces, between kicks of the slow
 // forces (bead LJ, wall, field); noise from d.xi as in launch_md_cycle.
@@ -245,6 +251,32 @@ constexpr int FUSED_K = 10;                  // sub-steps per block (the largest
 constexpr double FUSED_DELTA = 0.1;          // displacement bound within a block
 void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslots, int nrep, int n_sub, int K,
                            hipStream_t s);
+
+// The uniform sub-cycle (harmonic bonds) in one launch: workgroup w owns the
+// chain segment [a, b) of up to RES_OWN beads for the whole cycle and
+// exchanges the positions its neighbours need through d.xring (see
+// k_md_resident).  Measured per coupled step against one launch per sub-step:
+// 20 beads on 32^3 0.23 against 0.75 ms, 400 beads on 128^3 0.29 against 0.78,
+// 8000 beads on 512 x 256 x 256 (FP32) 1.12 against 1.66, 64 uneven replicas
+// 0.97 against 1.66.
+// Its workgroups wait for each other, so all of them have to be on the GPU at
+// once: 768 fit (three per CU by registers), at most RES_MAX_WG are used, so
+// that contexts of up to 256 segments fit beside any other.  A wait that
+// lasts longer than `wait` ticks of the 100 MHz clock, or RES_PLACE while some
+// workgroup has not found room, hands the replica to one workgroup that
+// redoes the cycle from its start; a bead that leaves the range of the step's
+// neighbour lists, to a second pass with new lists every RES_BLOCK sub-steps
+// (8000 beads of a walk that was not relaxed, step by step: 3.1 ms, as with one
+// launch per sub-step; the one workgroup takes 94).  At n_sub = 1 and 2 the
+// single launches cost no more than the cycle's three.
+constexpr int RES_OWN = 32;
+constexpr int RES_BLOCK = 10;
+constexpr int RES_MAX_WG = 512;
+constexpr int RES_MIN_SUB = 3;
+constexpr uint64_t RES_PLACE = 200000;   // 2 ms
+void launch_md_cycle_resident(const Dev& d, const FusedBufs& fb, const FusedSeg* seg, int nseg, int nslots, int nrep,
+                              int n_sub, const MdOverride& ov, uint64_t wait, hipStream_t s);
+void launch_md_gate(const Dev& d, int nseg, hipStream_t s);
 // Noise of one sub-cycle into d.xi, for the step counter + step_offset.
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s);
 void launch_md_invalidate(const Dev& d, int nrep, hipStream_t s);
@@ -252,6 +284,28 @@ void launch_md_invalidate(const Dev& d, int nrep, hipStream_t s);
 // positions (once per coupled step); marks the lists valid.
 void launch_nbr_build(const Dev& d, int nslots, int nrep, hipStream_t s);
 void launch_zero_v(const Dev& d, int nslots, hipStream_t s);
+
+// Opens a sub-cycle's flags, thread t of nt.  Per replica r, rb[4 r + 0..2]
+// are the three rotating rebuild flags and rb[4 r + 3] the "lists invalid"
+// request from the host (initialisation, restored state).
+__device__ inline void md_begin(const Dev& d, int nrep, int t, int nt) {
+  if (t == 0) {
+    d.ctrl->cycles += 1u;
+    d.ctrl->placed[0] = 0u;
+    d.ctrl->placed[1] = 0u;
+  }
+  for (int r = t; r < nrep; r += nt) {
+    if (d.redo) d.redo[r] = -1;
+    uint32_t* w = d.rb + 4 * r;
+    w[0] = w[3];
+    w[1] = 0u;
+    w[2] = 0u;
+    w[3] = 0u;
+    d.cst[4 * r] = 0u;
+    d.cst[4 * r + 1] = 0u;
+    d.cst[4 * r + 2] = 0u;
+  }
+}
 
 // Spread-on-solid ledger of one bead slot: the share W_k J_p of the step's
 // impulse that the spreading drops because corner k of the bead's stencil

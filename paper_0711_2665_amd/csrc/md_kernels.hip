@@ -23,22 +23,7 @@
 
 namespace lbmd {
 
-// Per replica r, rb[4 r + 0..2] are the three rotating rebuild flags and
-// rb[4 r + 3] the "lists invalid" request from the host (initialisation,
-// restored state).
-__global__ void k_md_begin(uint32_t* rb, uint32_t* cst, int nrep, int* redo) {
-  for (int r = threadIdx.x; r < nrep; r += blockDim.x) {
-    if (redo) redo[r] = -1;
-    uint32_t* w = rb + 4 * r;
-    w[0] = w[3];
-    w[1] = 0u;
-    w[2] = 0u;
-    w[3] = 0u;
-    cst[4 * r] = 0u;
-    cst[4 * r + 1] = 0u;
-    cst[4 * r + 2] = 0u;
-  }
-}
+__global__ void k_md_begin(Dev d, int nrep) { md_begin(d, nrep, threadIdx.x, blockDim.x); }
 
 __global__ void k_md_invalidate(uint32_t* rb, int nrep) {
   for (int r = threadIdx.x; r < nrep; r += blockDim.x) rb[4 * r + 3] = 1u;
@@ -1147,7 +1132,11 @@ __global__ __launch_bounds__(CON_WG) void k_md_constraint(Dev d, int nslots, int
 }
 
 void launch_md_begin(const Dev& d, int nrep, hipStream_t s) {
-  hipLaunchKernelGGL(k_md_begin, dim3(1), dim3(256), 0, s, d.rb, d.cst, nrep, d.redo);
+  hipLaunchKernelGGL(k_md_begin, dim3(1), dim3(256), 0, s, d, nrep);
+}
+
+void launch_md_start(const Dev& d, int nslots, const MdOverride& ov, hipStream_t s) {
+  hipLaunchKernelGGL(k_md_start, dim3((nslots + 255) / 256), dim3(256), 0, s, d, nslots, ov, 0);
 }
 
 void launch_md_cycle(const Dev& d, int nslots, int nrep, int n_sub, const MdOverride& ov, hipStream_t s,
@@ -1155,7 +1144,7 @@ void launch_md_cycle(const Dev& d, int nslots, int nrep, int n_sub, const MdOver
   if (nslots <= 0 || n_sub <= 0) return;
   unsigned nblk = (unsigned)(nslots / MD_BPB);
   if (prologue) {
-    hipLaunchKernelGGL(k_md_begin, dim3(1), dim3(256), 0, s, d.rb, d.cst, nrep, d.redo);
+    hipLaunchKernelGGL(k_md_begin, dim3(1), dim3(256), 0, s, d, nrep);
     hipLaunchKernelGGL(k_md_start, dim3((nslots + 255) / 256), dim3(256), 0, s, d, nslots, ov, 0);
   }
   if (constrained)
@@ -1177,7 +1166,7 @@ void launch_md_cycle_mts(const Dev& d, int nslots, int nrep, int n_sub, int M, h
   const unsigned nin = (unsigned)((nslots + own - 1) / own);
   MdOverride none{};
   if (prologue) {
-    hipLaunchKernelGGL(k_md_begin, dim3(1), dim3(256), 0, s, d.rb, d.cst, nrep, d.redo);
+    hipLaunchKernelGGL(k_md_begin, dim3(1), dim3(256), 0, s, d, nrep);
     hipLaunchKernelGGL(k_md_start, dim3((nslots + 255) / 256), dim3(256), 0, s, d, nslots, none, 1);
   }
   for (int o = 0; o < M; ++o) {
@@ -1717,28 +1706,34 @@ __global__ __launch_bounds__(FU_WG) void k_md_fused(Dev d, FusedBufs fb, int nsl
   }
 }
 
-// After the fused blocks, one workgroup per replica.  A replica whose block
-// failed at sub-step sp is redone from that block's start state to the end
-// of the cycle, sub-step by sub-step, with barriers: the angles of every
-// centre, then every bead's force, kick and drifts; the positions alternate
-// between r_mid0 and r_mid1.  A bead's pair partners within r_c, in
-// ascending order, come from the step's neighbour lists while every bead
-// lies within half the skin of where they were built, else from the cell
-// table while every bead lies within CELL_MARGIN of where it was binned,
-// else from all beads of the chain.  A replica whose last block wrote the
-// shadow set gets v and J copied back.
+// After the fused blocks or the resident cycle, one workgroup per replica.
+// A replica whose block failed at sub-step sp (the resident cycle: marker 1,
+// from sub-step 0) is
+// redone from that block's start state to the end of the cycle, sub-step by
+// sub-step, with barriers: the angles of every centre, then every bead's
+// force, kick and drifts; the positions alternate between r_mid0 and r_mid1.
+// A bead's pair partners come from the neighbour lists; when a bead is
+// farther than half the skin from where they were built, every list is built
+// anew at the sub-step's positions -- from the cell table while every bead
+// lies within CELL_MARGIN of where it was binned, else from all beads of the
+// chain.  With the fused blocks, a replica whose last block wrote the shadow
+// set gets v and J copied back; the resident cycle leaves the cycle's start
+// (r, v, J) in the shadow set.
 constexpr int RD_WG = 1024;
 constexpr int RD_NC = 32;          // pair partners within r_c of one bead
 
-__global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* ang, int nslots, int n_sub, int K) {
+__global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* ang, int nslots, int n_sub, int K,
+                                                   MdOverride ov, int resident) {
   __shared__ int any_far, any_off;
   const int rep = blockIdx.x;
+  int sp = fb.redo[rep];                          // constant during this launch
+  if (resident && sp < 1) return;                 // the resident cycle succeeded
+  if (resident) sp = 0;
   const Rep& R = d.reps[rep];
-  const MdParams P = R.mp;
+  const MdParams P = md_params(R, ov);
   const Geom g = R.g;
   const int so = R.slot_off, nb = P.nb;
   const int t = threadIdx.x;
-  const int sp = fb.redo[rep];                    // constant during this launch
   const int M = n_sub / K;
   if (sp < 0) {
     if (M & 1)
@@ -1750,22 +1745,24 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
     return;
   }
   // the failed block's start state into r_mid0, v, J
-  if ((sp / K) & 1)
+  if (resident || ((sp / K) & 1))
     for (int q = t; q < nb; q += RD_WG)
       for (int a = 0; a < 3; ++a) {
         const int i = 3 * (so + q) + a;
-        d.rmid0[i] = fb.rmS[i];
+        d.rmid0[i] = resident ? fb.rmS[i] + P.hh * fb.vS[i] : fb.rmS[i];
         d.v[i] = fb.vS[i];
         d.J[i] = fb.JS[i];
       }
-  if (t == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)(n_sub - sp));
-  bool fin = true, over = false;
+  if (t == 0) {
+    if (!resident) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)(n_sub - sp));
+  }
+  bool fin = true, over = false, valid = d.rb[4 * rep] == 0u;   // the lists, at the cycle's start
   for (int s = sp; s < n_sub; ++s) {
     const double* cur = ((s - sp) & 1) ? d.rmid1 : d.rmid0;
     double* nxt = ((s - sp) & 1) ? d.rmid0 : d.rmid1;
     // every bead near the position the lists were built at, the position
     // the table binned it at?
-    bool near = true, held = d.rb[4 * rep] == 0u;
+    bool near = true, held = valid;
     for (int q = t; q < nb; q += RD_WG) {
       double b2 = 0.0, f2 = 0.0;
       for (int a = 0; a < 3; ++a) {
@@ -1786,34 +1783,51 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
         fu_angle(P, &cur[3 * (so + q - 1)], &cur[3 * (so + q)], &cur[3 * (so + q + 1)], &ang[9 * (size_t)(so + q)]);
     __syncthreads();
     const bool lists = any_off == 0, table = any_far == 0;
+    if (!lists) {
+      // each thread builds the lists of its own beads, which it alone reads
+      for (int q = t; q < nb; q += RD_WG) {
+        const int sl = so + q;
+        const double rp[3] = {cur[3 * sl], cur[3 * sl + 1], cur[3 * sl + 2]};
+        int L[MAXNBR];
+        int n = 0;
+        if (table) {
+          n = cell_partners(d, R, rep, cur, q, rp, P.rlist2, L, MAXNBR);
+        } else {
+          for (int j = 0; j < nb && n <= MAXNBR; ++j) {
+            if (j == q) continue;
+            const double e0 = min_image(rp[0] - cur[3 * (so + j)], g.nx);
+            const double e1 = min_image(rp[1] - cur[3 * (so + j) + 1], g.ny);
+            const double e2 = min_image(rp[2] - cur[3 * (so + j) + 2], g.nz);
+            if (!(e0 * e0 + e1 * e1 + e2 * e2 < P.rlist2)) continue;
+            if (n < MAXNBR) L[n] = j;
+            ++n;
+          }
+        }
+        if (n > MAXNBR) { over = true; n = MAXNBR; }
+        for (int k = 0; k < n; ++k) d.nbr[(size_t)sl * MAXNBR + k] = so + L[k];
+        d.ncnt[sl] = n;
+        for (int a = 0; a < 3; ++a) d.ref[3 * sl + a] = rp[a];
+      }
+      if (t == 0) {
+        atomicAdd((unsigned long long*)&d.ctrl->rebuilds, 1ull);
+        if (table) atomicAdd((unsigned long long*)&d.ctrl->cell_rebuilds, 1ull);
+      }
+      valid = true;
+    }
     for (int q = t; q < nb; q += RD_WG) {
       const int sl = so + q;
       const double rp[3] = {cur[3 * sl], cur[3 * sl + 1], cur[3 * sl + 2]};
       int part[RD_NC];
       int np = 0;
-      if (lists) {
-        const int cnt = d.ncnt[sl];
-        for (int k = 0; k < cnt && np <= RD_NC; ++k) {
-          const int j = d.nbr[(size_t)sl * MAXNBR + k] - so;   // list entries are slots
-          const double e0 = min_image(rp[0] - cur[3 * (so + j)], g.nx);
-          const double e1 = min_image(rp[1] - cur[3 * (so + j) + 1], g.ny);
-          const double e2 = min_image(rp[2] - cur[3 * (so + j) + 2], g.nz);
-          if (!(e0 * e0 + e1 * e1 + e2 * e2 < P.rc2)) continue;
-          if (np < RD_NC) part[np] = j;
-          ++np;
-        }
-      } else if (table) {
-        np = cell_partners(d, R, rep, cur, q, rp, P.rc2, part, RD_NC);
-      } else {
-        for (int j = 0; j < nb && np <= RD_NC; ++j) {
-          if (j == q) continue;
-          const double e0 = min_image(rp[0] - cur[3 * (so + j)], g.nx);
-          const double e1 = min_image(rp[1] - cur[3 * (so + j) + 1], g.ny);
-          const double e2 = min_image(rp[2] - cur[3 * (so + j) + 2], g.nz);
-          if (!(e0 * e0 + e1 * e1 + e2 * e2 < P.rc2)) continue;
-          if (np < RD_NC) part[np] = j;
-          ++np;
-        }
+      const int cnt = d.ncnt[sl];
+      for (int k = 0; k < cnt && np <= RD_NC; ++k) {
+        const int j = d.nbr[(size_t)sl * MAXNBR + k] - so;   // list entries are slots
+        const double e0 = min_image(rp[0] - cur[3 * (so + j)], g.nx);
+        const double e1 = min_image(rp[1] - cur[3 * (so + j) + 1], g.ny);
+        const double e2 = min_image(rp[2] - cur[3 * (so + j) + 2], g.nz);
+        if (!(e0 * e0 + e1 * e1 + e2 * e2 < P.rc2)) continue;
+        if (np < RD_NC) part[np] = j;
+        ++np;
       }
       if (np > RD_NC) { over = true; np = RD_NC; }
       const double* a3 = (q - 1 >= 1 && q - 1 <= nb - 2) ? &ang[9 * (size_t)(sl - 1)] : nullptr;
@@ -1828,6 +1842,11 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
       double xi[3] = {0.0, 0.0, 0.0};
       if (P.sig != 0.0)
         for (int a = 0; a < 3; ++a) xi[a] = d.xi[(size_t)3 * ((size_t)s * nslots + sl) + a];
+      if (d.mdtape)
+        for (int a = 0; a < 3; ++a) {
+          d.mdtape[((size_t)s * nb + q) * 6 + a] = rp[a];
+          d.mdtape[((size_t)s * nb + q) * 6 + 3 + a] = v[a];
+        }
       const bool fl = s == n_sub - 1;
       double x[3];
       fin = fu_kick(P, F, u, xi, v, J, rp, fl, x) && fin;
@@ -1844,6 +1863,736 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
   if (over) atomicOr(&d.ctrl->err, E_NBRLIST);
 }
 
+// ---------------------------------------------------------------------------
+// The resident sub-cycle: one launch advances every chain through the whole
+// uniform sub-cycle.
+//
+// One launch per sub-step costs 7.4 us alone and 12.5 us beside the sweep for
+// 2 to 3 us of dependent arithmetic: the kernel's end writes the L2 back (full
+// of the sweep's lines) and the next one's start reads everything again from
+// memory.  Here workgroup w owns the chain segment [a, b) (up to RES_OWN
+// beads) for the whole cycle, holds its beads' state in registers and its
+// positions in LDS, and per sub-step exchanges only what its neighbours need:
+// it publishes its beads' new positions and polls those of its remote beads
+// (the two chain neighbours at each end, and the partners in its beads'
+// neighbour lists that other segments own, usually none).
+//
+// The exchange has no fence and no flag (an agent-scope release would write
+// the L2 back).  A position component travels as two 64-bit words, its bits and
+// its bits XOR a tag that no other sub-step of any cycle uses, written and
+// read by relaxed agent-scope atomics, which bypass the L2s that the XCDs do
+// not share: a reader takes the pair when the two words differ by the tag, so
+// it needs no order between them.  Two slots suffice: segments depend on each
+// other symmetrically, so a segment publishes x(s + 2) over x(s) only after
+// it has read x(s + 1) of a segment that has read its x(s).  A round trip
+// between workgroups takes 1.1 us alone, 2.4 us beside a streaming kernel.
+//
+// A wave issues one dependent FP64 instruction in about five cycles, so a
+// sub-step's time is the longest instruction count of a wave between two
+// barriers plus the exchange; eight waves split the force terms by kind so
+// that each is one pass over its lanes, and the two waves that share a SIMD
+// (w and w + 4) are a long and a short one.  Phase 1: waves 0 and 1 the angles
+// centred at a - 1 .. b without their kappa phi factor (one lane per angle and
+// component); wave 2 the factors kappa phi; wave 3 the wall sites (one lane
+// per site of the beads near the plane) and the field indicator; wave 4 stages
+// the noise; wave 5 the bonds and the displacement check; waves 6 and 7 the
+// pair forces (four lanes per bead, each a quarter of its list).  Phase 2:
+// waves 0 and 1 (one lane per bead and component) add every contribution in
+// the order of the sub-step kernel, move the beads and publish, while wave 4
+// polls.  32 beads per workgroup fill one pass of the lanes; three such
+// workgroups fit on a CU (79 registers).
+//
+// The workgroups announce themselves in ctrl->placed, and the sweep starts
+// only then (k_md_gate): its small workgroups would otherwise refill every gap
+// they leave, and a late segment holds up its neighbours until the sweep ends.
+//
+// The lists hold every pair within r_c while no bead is farther than half
+// the skin from where they were built.  A workgroup whose bead leaves that
+// range, whose lists are not valid at the start, whose remote beads exceed
+// RES_REM, or whose wait exceeds its limit sets the replica's redo marker
+// (-1 -> 0); the others see it while they poll, and all return.  A second
+// launch (BLOCKS; it returns at once where the first succeeded) takes such a
+// replica from the cycle's start state, which every workgroup saved first
+// (rmS, vS, JS), in blocks of RES_BLOCK sub-steps with new lists for each, so
+// a bead may travel half the skin per block instead of per cycle.  What fails
+// there too (marker 1) is advanced by one workgroup (k_md_redo).  Every wait
+// ends: the polled value arrives, the marker is set, or the clock runs out.
+//
+// New lists need the beads' positions at the block's start: each segment
+// publishes them (xblk, tagged like the exchange) and a word that says
+// whether its beads are within CELL_MARGIN of where the cell table binned
+// them, and reads every segment's word -- so no segment enters a block before
+// all have left the one before, and two slots suffice here as well.  The
+// candidates come from the cell table if every word allows it, else from all
+// beads of the chain.
+// ---------------------------------------------------------------------------
+constexpr int RES_WG = 512;
+constexpr int RES_HALO = 4;                    // local indices RES_OWN + 0..3: chain beads a-2, a-1, b, b+1
+constexpr int RES_REM = 144;                   // other remote beads
+constexpr int RES_IDX = RES_OWN + RES_HALO + RES_REM;
+constexpr int RES_PL = 4;                      // lanes per bead of the pair waves
+constexpr int RES_PH = 4;                      // pair forces kept per lane
+constexpr int RES_WH = 512;                    // wall-site forces kept (13 per bead at most for r_c <= 2)
+constexpr int RES_HASH = 512;
+constexpr int RES_TILE = 256;                  // beads scanned together by a full list build
+static_assert(RES_IDX <= 255, "local indices fit in a byte");
+static_assert(3 * (RES_OWN + 2) <= 128 && RES_OWN + 2 <= 64 && RES_PL * RES_OWN == 128, "one pass over the lanes");
+
+struct ResShared {
+  double pos[2][RES_IDX][3];                   // by parity of the sub-step and local index
+  double dd[2][RES_OWN + 2][3];                // row k: d1, d2 of the angle centred at a - 1 + k (see res_angle_d)
+  double kp[RES_OWN + 2];                      // its kappa phi
+  double bnd[RES_OWN + 1][3];                  // row k: force on a + k of its bond to a + k - 1
+  double xi[3 * RES_OWN];                      // the sub-step's noise
+  union {
+    struct {
+      double pairF[RES_PL][RES_PH][RES_OWN][3];   // pair forces of each lane's part of the list, in order
+      double wallF[RES_WH][3];                 // wall-site forces, bead by bead in site order
+    };
+    struct {                                   // set-up
+      int key[RES_HASH], val[RES_HASH];        // local index of a remote chain bead
+      int list[RES_OWN][MAXNBR];               // new lists (partner slots)
+      uint32_t bk[RES_OWN][27];                // the 27 buckets around a bead
+      double tile[RES_TILE][3];                // positions of RES_TILE chain beads
+    } h;
+  };
+  uint8_t lst[RES_OWN][MAXNBR];                // the beads' lists as local indices, ascending chain order
+  int lcnt[RES_OWN];
+  uint8_t pcnt[RES_OWN][RES_PL];               // pair forces found (one beyond RES_PH: the sum evaluates them again)
+  int wall[RES_OWN];                           // first wall-site force << 8 | their number
+  int fld[RES_OWN];                            // in the pore channel
+  int rslot[RES_IDX - RES_OWN];                // bead slot of remote local index RES_OWN + k, -1: none
+  int nrem;
+  int dead[2];                                 // by parity of the sub-step
+  int lost;                                    // a set-up failed
+  int ncand[RES_OWN];
+};
+static_assert(4 * sizeof(ResShared) <= (size_t)LDS_PER_CU, "four resident workgroups per CU");
+
+// A workgroup barrier that orders LDS only: __syncthreads would also wait for
+// every outstanding global access (the published positions on their way to
+// memory, the next sub-step's noise), none of which another wave of the
+// workgroup reads.
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+__device__ inline unsigned long long res_load(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void res_store(unsigned long long* p, unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline unsigned long long res_tag(uint64_t cycle, int n_sub, int s) {
+  return (cycle * (uint64_t)(n_sub + 1) + (uint64_t)s) * 0x9E3779B97F4A7C15ull;
+}
+
+// Bond vectors u (first) and w (second), cross product n, its length s and
+// c = u.w of the angle at (ra, rb, rc): the first operations of
+// angle_component.  Scalars, so that a lane's selection of a component is one
+// of registers.
+struct ResAngle {
+  double u0, u1, u2, w0, w1, w2, n0, n1, n2, s, c;
+};
+__device__ inline ResAngle res_angle(const double* ra, const double* rb, const double* rc) {
+  ResAngle A;
+  A.u0 = rb[0] - ra[0]; A.u1 = rb[1] - ra[1]; A.u2 = rb[2] - ra[2];
+  A.w0 = rc[0] - rb[0]; A.w1 = rc[1] - rb[1]; A.w2 = rc[2] - rb[2];
+  A.n0 = A.u1 * A.w2 - A.u2 * A.w1;
+  A.n1 = A.u2 * A.w0 - A.u0 * A.w2;
+  A.n2 = A.u0 * A.w1 - A.u1 * A.w0;
+  A.s = sqrt(A.n0 * A.n0 + A.n1 * A.n1 + A.n2 * A.n2);
+  A.c = A.u0 * A.w0 + A.u1 * A.w1 + A.u2 * A.w2;
+  return A;
+}
+__device__ inline double sel3(int a, double x, double y, double z) { return a == 0 ? x : (a == 1 ? y : z); }
+// d1, d2 of component a (angle_component's; the forces are kp d1 on the first
+// bead, -(kp (d1 - d2)) on the centre, -(kp d2) on the third).  0 for a straight
+// or folded angle, whose kp is 0 too.
+__device__ inline void res_angle_d(const ResAngle& A, int a, double& d1, double& d2) {
+  const double wa = sel3(a, A.w1, A.w2, A.w0), wb = sel3(a, A.w2, A.w0, A.w1);
+  const double ua = sel3(a, A.u1, A.u2, A.u0), ub = sel3(a, A.u2, A.u0, A.u1);
+  const double na = sel3(a, A.n1, A.n2, A.n0), nb = sel3(a, A.n2, A.n0, A.n1);
+  const double den = A.s * A.s + A.c * A.c;
+  const double g1 = wa * nb - wb * na;
+  const double g2 = na * ub - nb * ua;
+  d1 = (A.c * g1 / A.s - A.s * sel3(a, A.w0, A.w1, A.w2)) / den;
+  d2 = (A.c * g2 / A.s - A.s * sel3(a, A.u0, A.u1, A.u2)) / den;
+  if (A.s == 0.0) d1 = d2 = 0.0;
+}
+
+// A tagged pair's value, waiting for it until the tag matches; false when the
+// marker reached STOP or the wait its limit (RES_PLACE while some workgroup
+// of the launch has not started: another context's cycle may hold its place
+// and wait for one that this cycle holds).
+template <int STOP>
+__device__ inline bool res_poll(const unsigned long long* o, uint64_t tag, const int* marker, const Ctrl* ctrl,
+                                uint64_t wait, unsigned long long& val) {
+  unsigned long long w1;
+  val = res_load(o);
+  w1 = res_load(o + 1);
+  if ((val ^ w1) == tag) return true;
+  const uint64_t t0 = wall_clock64();
+  for (int spin = 0;; ++spin) {
+    val = res_load(o);
+    w1 = res_load(o + 1);
+    if ((val ^ w1) == tag) return true;
+    if ((spin & 15) == 15 || wait == 0) {
+      const uint64_t dt = wall_clock64() - t0;
+      if (__hip_atomic_load(marker, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= STOP || dt >= wait ||
+          (dt >= RES_PLACE &&
+           __hip_atomic_load(&ctrl->placed[STOP], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x))
+        return false;
+    }
+  }
+}
+
+template <bool BLOCKS>
+__global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, const FusedSeg* __restrict__ segs,
+                                                           int nslots, int n_sub, MdOverride ov, uint64_t wait) {
+  __shared__ ResShared sh;
+  const FusedSeg seg = segs[blockIdx.x];
+  const int rep = seg.rep;
+  if (BLOCKS && fb.redo[rep] < 0) {              // the whole cycle succeeded (0 or 1 from here on)
+    if (threadIdx.x == 0)
+      __hip_atomic_fetch_add(&d.ctrl->placed[BLOCKS], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  const Rep& R = d.reps[rep];
+  const MdParams P = md_params(R, ov);
+  const Geom g = R.g;
+  const int so = R.slot_off, nb = P.nb;
+  const int p0 = seg.a, n = seg.b - seg.a;
+  const int t = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(t) >> 6, lane = t & 63;
+  int* marker = &fb.redo[rep];
+  constexpr int STOP = BLOCKS ? 1 : 0;           // the marker of a failure here
+  auto fail = [&](int s) {
+    atomicCAS(marker, STOP - 1, STOP);
+    sh.dead[s & 1] = 1;
+  };
+  auto lose = [&]() {
+    atomicCAS(marker, STOP - 1, STOP);
+    sh.lost = 1;
+  };
+  // the tag of sub-step s of this cycle is (cycle (n_sub + 1) + s) TAG, and
+  // those of a block's start differ by MARK
+  constexpr uint64_t TAG = 0x9E3779B97F4A7C15ull, MARK = 0x5851F42D4C957F2Dull;
+  const uint64_t tag0 = d.ctrl->cycles * (uint64_t)(n_sub + 1) * TAG;
+
+  // ---- the lanes of the sum: component c of bead i
+  const int i = 16 * wave + lane / 3, c = lane % 3;
+  const bool mine = wave < 2 && lane < 48 && i < n;
+  const int slot = so + p0 + (mine ? i : 0), p = p0 + i;
+  double x = 0.0, v = 0.0, J = 0.0, u = 0.0;
+  if (mine) {
+    x = d.rmid0[3 * slot + c];
+    v = BLOCKS ? fb.vS[3 * slot + c] : d.v[3 * slot + c];
+    J = BLOCKS ? fb.JS[3 * slot + c] : d.J[3 * slot + c];
+    u = P.couple ? d.up[3 * slot + c] : 0.0;
+    if (!BLOCKS) {                               // the cycle's start state
+      fb.rmS[3 * slot + c] = d.r[3 * slot + c];
+      fb.vS[3 * slot + c] = v;
+      fb.JS[3 * slot + c] = J;
+    }
+    sh.pos[0][i][c] = x;
+  }
+  if (t < 2) sh.dead[t] = 0;
+  if (t == 0) {
+    sh.lost = 0;
+    __hip_atomic_fetch_add(&d.ctrl->placed[BLOCKS], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!BLOCKS) {
+      if (*marker >= 0 || d.rb[4 * rep] != 0u) lose();   // failed already, or lists not valid at the start
+      if (blockIdx.x == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)n_sub);
+    }
+  }
+  bool fin = true;
+  const int len = BLOCKS ? RES_BLOCK : n_sub;
+  for (int s0 = 0, blk = 0;; s0 += len, ++blk) {
+  const int s1 = BLOCKS ? min(s0 + len, n_sub) : n_sub;
+  const int sp = s0 & 1;                         // parity of the block's first sub-step
+  // ---- set-up: the lists as local indices
+  __syncthreads();                               // the positions at s0 are there, the forces' memory is free
+  constexpr int LL = RES_WG / RES_OWN, LE = MAXNBR / LL;   // 16 lanes per bead
+  const int lb = t / LL, ll = t % LL;
+  const bool fresh = BLOCKS && (s0 > 0 || d.rb[4 * rep] != 0u);   // build new lists
+  const unsigned long long* xb = nullptr;
+  const uint64_t tagb = tag0 + (uint64_t)s0 * TAG + MARK;
+  int cnt = lb < n && !fresh ? d.ncnt[so + p0 + lb] : 0;
+  if (BLOCKS && fresh) {
+    unsigned long long* xw = d.xring + (size_t)(2 + (blk & 1)) * 6 * nslots;
+    xb = xw;
+    unsigned long long* words = d.xflag + (size_t)2 * (blk & 1) * gridDim.x;
+    if (mine) {
+      const unsigned long long bits = (unsigned long long)__double_as_longlong(x);
+      res_store(xw + ((size_t)slot * 3 + c) * 2, bits);
+      res_store(xw + ((size_t)slot * 3 + c) * 2 + 1, bits ^ tagb);
+    }
+    bool near = true;
+    if (t < n) {
+      double b2 = 0.0;
+      for (int a = 0; a < 3; ++a) { const double db = sh.pos[sp][t][a] - d.rbin[3 * (so + p0 + t) + a]; b2 += db * db; }
+      near = b2 <= CELL_MARGIN * CELL_MARGIN;
+      sh.ncand[t] = 0;
+    }
+    const int all_near = __syncthreads_and(near ? 1 : 0);
+    if (t == 0) {
+      res_store(words + 2 * blockIdx.x, (unsigned long long)all_near);
+      res_store(words + 2 * blockIdx.x + 1, (unsigned long long)all_near ^ tagb);
+    }
+    // every segment's word
+    const int g0 = (int)blockIdx.x - p0 / RES_OWN, ng = (nb + RES_OWN - 1) / RES_OWN;
+    bool table = true;
+    for (int k = t; k < ng; k += RES_WG) {
+      unsigned long long w = 0;
+      if (!res_poll<STOP>(words + 2 * (g0 + k), tagb, marker, d.ctrl, wait, w)) { lose(); break; }
+      table = table && w != 0;
+    }
+    table = __syncthreads_and(table ? 1 : 0) != 0;
+    if (__syncthreads_or(sh.lost)) return;       // uniform, and read by all before the next write
+    auto partner = [&](int q, const double* y) {
+      if (q == so + p0 + lb) return;
+      const double* rp = sh.pos[sp][lb];
+      const double d0 = min_image(rp[0] - y[0], g.nx);
+      const double d1 = min_image(rp[1] - y[1], g.ny);
+      const double d2 = min_image(rp[2] - y[2], g.nz);
+      if (!(d0 * d0 + d1 * d1 + d2 * d2 < P.rlist2)) return;
+      const int o = atomicAdd(&sh.ncand[lb], 1);
+      if (o < MAXNBR) sh.h.list[lb][o] = q;
+    };
+    bool ok = true;
+    if (table) {
+      if (lb < n) {
+        int cell[3];
+        bead_cell(R, sh.pos[sp][lb], cell);
+        for (int k = ll; k < 27; k += LL) {
+          const int dx = k % 3 - 1, dy = (k / 3) % 3 - 1, dz = k / 9 - 1;
+          sh.h.bk[lb][k] = cell_bucket(rep, (cell[0] + dx + R.ncell[0]) % R.ncell[0],
+                                       (cell[1] + dy + R.ncell[1]) % R.ncell[1],
+                                       (cell[2] + dz + R.ncell[2]) % R.ncell[2], d.cmask);
+        }
+      }
+      __syncthreads();
+      if (lb < n)
+        for (int k = ll; k < 27 && ok; k += LL) {
+          const uint32_t b = sh.h.bk[lb][k];
+          bool dup = false;
+          for (int k2 = 0; k2 < k; ++k2) dup = dup || sh.h.bk[lb][k2] == b;
+          const int m = dup ? 0 : min(d.ccount[b], CELL_CAP);
+          for (int q = 0; q < m && ok; ++q) {
+            const int sl = d.cbuf[(size_t)b * CELL_CAP + q];
+            if (d.slot_rep[sl] != rep) continue;
+            double y[3];
+            for (int a = 0; a < 3 && ok; ++a) {
+              unsigned long long w = 0;
+              ok = res_poll<STOP>(xb + ((size_t)sl * 3 + a) * 2, tagb, marker, d.ctrl, wait, w);
+              y[a] = __longlong_as_double((long long)w);
+            }
+            if (ok) partner(sl, y);
+          }
+        }
+      if (!ok) lose();
+    } else {
+      for (int base = 0; base < nb; base += RES_TILE) {
+        const int m = min(RES_TILE, nb - base);
+        for (int k = t; k < 3 * m && ok; k += RES_WG) {
+          unsigned long long w = 0;
+          ok = res_poll<STOP>(xb + ((size_t)(so + base + k / 3) * 3 + k % 3) * 2, tagb, marker, d.ctrl, wait, w);
+          sh.h.tile[k / 3][k % 3] = __longlong_as_double((long long)w);
+        }
+        if (!ok) lose();
+        __syncthreads();
+        if (lb < n)
+          for (int k = ll; k < m; k += LL) partner(so + base + k, sh.h.tile[k]);
+        __syncthreads();
+      }
+    }
+    __syncthreads();
+    if (lb < n) cnt = min(sh.ncand[lb], MAXNBR);
+    if (lb < n && ll == 0) {                     // ascending order
+      int* L = sh.h.list[lb];
+      for (int k = 1; k < cnt; ++k) {
+        const int q = L[k];
+        int m = k;
+        while (m > 0 && L[m - 1] > q) { L[m] = L[m - 1]; --m; }
+        L[m] = q;
+      }
+    }
+    if (t == 0 && p0 == 0) {
+      atomicAdd((unsigned long long*)&d.ctrl->rebuilds, 1ull);
+      if (table) atomicAdd((unsigned long long*)&d.ctrl->cell_rebuilds, 1ull);
+    }
+    __syncthreads();
+  }
+  if (t == 0) sh.nrem = 0;
+  for (int k = t; k < RES_IDX - RES_OWN; k += RES_WG) {
+    // chain beads a - 2, a - 1, b, b + 1 first
+    const int q = k < 2 ? p0 - 2 + k : seg.b + (k - 2);
+    sh.rslot[k] = k < RES_HALO && q >= 0 && q < nb ? so + q : -1;
+  }
+  for (int k = t; k < RES_HASH; k += RES_WG) { sh.h.key[k] = -1; sh.h.val[k] = -1; }
+  __syncthreads();
+  // a remote bead's first finder gives it an index
+  if (cnt >= MAXNBR) lose();                     // a full list may have lost partners: segments need not depend on each other
+  int e[LE];
+#pragma unroll
+  for (int m = 0; m < LE; ++m) {
+    const int k = LL * m + ll;
+    e[m] = k < cnt ? (fresh ? sh.h.list[lb][k] : d.nbr[(size_t)(so + p0 + lb) * MAXNBR + k]) : -1;
+  }
+#pragma unroll 1
+  for (int m = 0; m < LE; ++m) {
+    const int em = m == 0 ? e[0] : (m == 1 ? e[1] : e[2]);
+    const int q = em - so;
+    if (em < 0 || (q >= p0 - 2 && q < seg.b + 2)) continue;
+    uint32_t h = ((uint32_t)q * 2654435761u) >> 23;          // RES_HASH = 2^9
+    for (int tries = 0; tries < RES_HASH; ++tries, h = (h + 1) & (RES_HASH - 1)) {
+      const int was = atomicCAS(&sh.h.key[h], -1, q);
+      if (was == -1) {
+        const int at = atomicAdd(&sh.nrem, 1);
+        if (at < RES_REM) {
+          sh.h.val[h] = RES_OWN + RES_HALO + at;
+          sh.rslot[RES_HALO + at] = em;
+        } else {
+          lose();
+        }
+        break;
+      }
+      if (was == q) break;
+      if (tries == RES_HASH - 1) lose();
+    }
+  }
+  __syncthreads();
+  if (lb < n && ll == 0) sh.lcnt[lb] = cnt;
+#pragma unroll 1
+  for (int m = 0; m < LE; ++m) {
+    const int em = m == 0 ? e[0] : (m == 1 ? e[1] : e[2]);
+    if (em < 0) continue;
+    const int q = em - so;
+    int li;
+    if (q >= p0 && q < seg.b) li = q - p0;
+    else if (q >= p0 - 2 && q < p0) li = RES_OWN + (q - p0 + 2);
+    else if (q >= seg.b && q < seg.b + 2) li = RES_OWN + 2 + (q - seg.b);
+    else {
+      uint32_t h = ((uint32_t)q * 2654435761u) >> 23;
+      for (int tries = 0; tries < RES_HASH && sh.h.key[h] != q; ++tries) h = (h + 1) & (RES_HASH - 1);
+      li = sh.h.key[h] == q ? sh.h.val[h] : -1;
+    }
+    sh.lst[lb][LL * m + ll] = (uint8_t)(li >= 0 ? li : 0);   // -1 only when lost
+  }
+  const int nrem = RES_HALO + min(sh.nrem, RES_REM);
+  for (int k = t; k < 3 * nrem; k += RES_WG) {
+    const int sl = sh.rslot[k / 3];
+    double y = 0.0;
+    if (sl >= 0) {
+      if (fresh) {
+        unsigned long long w = 0;
+        if (!res_poll<STOP>(xb + ((size_t)sl * 3 + k % 3) * 2, tagb, marker, d.ctrl, wait, w)) lose();
+        y = __longlong_as_double((long long)w);
+      } else {
+        y = d.rmid0[3 * sl + k % 3];
+      }
+    }
+    sh.pos[sp][RES_OWN + k / 3][k % 3] = y;
+  }
+  __syncthreads();
+  if (sh.lost) return;                           // uniform: the next writes follow many barriers
+
+  constexpr int HL = RES_OWN, HR = RES_OWN + 2;  // local indices of a - 2 and b
+  // local index of chain bead a + j, -2 <= j <= n + 1
+  auto at = [&](int j) { return j < 0 ? HL + 2 + j : (j < n ? j : HR + (j - n)); };
+  const bool multi = n < nb;                     // other segments exist
+  const size_t half = (size_t)6 * nslots;        // words of one slot of the ring
+  const bool noisy = P.sig != 0.0;
+  const uint64_t tags = tag0 + (uint64_t)s0 * TAG;
+  __builtin_amdgcn_s_setprio(2);
+  // Each kind of wave has a loop of its own (its registers then hold only
+  // what it needs), with the same two barriers per sub-step.  The test of
+  // sh.dead is uniform: sub-step s writes dead[s & 1] before its second
+  // barrier only, and s + 2 writes it again after two more.
+  if (wave < 2) {
+    // ---- angles; the sum
+    const int k = t / 3, ka = t % 3;             // component ka of the angle centred at a - 1 + k
+    const bool ang = k < n + 2 && p0 - 1 + k >= 1 && p0 - 1 + k <= nb - 2;
+    const int j0 = ang ? at(k - 2) : 0, j1 = ang ? at(k - 1) : 0, j2 = ang ? at(k) : 0;
+    const bool bm = !P.constrained && p > 0, bp = !P.constrained && p < nb - 1;
+    const bool am = p - 1 >= 1 && p - 1 <= nb - 2, ac = p >= 1 && p <= nb - 2, ap = p + 1 >= 1 && p + 1 <= nb - 2;
+    double* tape = mine && d.mdtape ? d.mdtape + (size_t)p * 6 + c : nullptr;
+    unsigned long long* ring = d.xring + ((size_t)slot * 3 + c) * 2;
+    uint64_t tag = tags;
+    for (int s = s0; s < s1; ++s) {
+      const int cb = s & 1;
+      const bool last = s == n_sub - 1;
+      tag += TAG;                                // of sub-step s + 1
+      if (ang) {
+        const ResAngle A = res_angle(sh.pos[cb][j0], sh.pos[cb][j1], sh.pos[cb][j2]);
+        double d1, d2;
+        res_angle_d(A, ka, d1, d2);
+        sh.dd[0][k][ka] = d1;
+        sh.dd[1][k][ka] = d2;
+      }
+      lds_barrier();
+      // every contribution in the fixed order, the kick and the drifts
+      if (mine) {
+        const uint32_t pc = *reinterpret_cast<const uint32_t*>(sh.pcnt[i]);
+        const int wl = sh.wall[i], fl = sh.fld[i];
+        const double xi = noisy ? sh.xi[3 * i + c] : 0.0;
+        const double f0 = sh.pairF[0][0][i][c], f1 = sh.pairF[1][0][i][c], f2 = sh.pairF[2][0][i][c],
+                     f3 = sh.pairF[3][0][i][c];
+        const double kp0 = sh.kp[i], kp1 = sh.kp[i + 1], kp2 = sh.kp[i + 2];
+        const double e2 = sh.dd[1][i][c], m1 = sh.dd[0][i + 1][c], m2 = sh.dd[1][i + 1][c], q1 = sh.dd[0][i + 2][c];
+        const double fb0 = sh.bnd[i][c], fb1 = sh.bnd[i + 1][c];
+        double F = 0.0;
+        if (bm) F += fb0;
+        if (bp) F += -fb1;
+        if (am) F += 0.0 + -(kp0 * e2);
+        if (ac) F += 0.0 + -(kp1 * (m1 - m2));
+        if (ap) F += 0.0 + kp2 * q1;
+        if ((pc & 0xfefefefeu) == 0u) {          // at most one pair force per lane
+          if (pc & 0xffu) F += f0;
+          if (pc & 0xff00u) F += f1;
+          if (pc & 0xff0000u) F += f2;
+          if (pc & 0xff000000u) F += f3;
+        } else {
+          bool kept = true;
+          for (int l = 0; l < RES_PL; ++l) kept = kept && (int)((pc >> (8 * l)) & 0xffu) <= RES_PH;
+          if (kept) {
+            for (int l = 0; l < RES_PL; ++l)
+              for (int m = 0; m < (int)((pc >> (8 * l)) & 0xffu); ++m) F += sh.pairF[l][m][i][c];
+          } else {
+            const double* rp = sh.pos[cb][i];
+            for (int m = 0; m < sh.lcnt[i]; ++m) {
+              const double* q = sh.pos[cb][sh.lst[i][m]];
+              const double d0 = min_image(rp[0] - q[0], g.nx);
+              const double d1 = min_image(rp[1] - q[1], g.ny);
+              const double d2 = min_image(rp[2] - q[2], g.nz);
+              if (!(d0 * d0 + d1 * d1 + d2 * d2 < P.rc2)) continue;
+              double Fp[3] = {0.0, 0.0, 0.0};
+              lj_add(P, d0, d1, d2, Fp);
+              F += c == 0 ? Fp[0] : (c == 1 ? Fp[1] : Fp[2]);
+            }
+          }
+        }
+        for (int m = wl >> 8; m < (wl >> 8) + (wl & 0xff); ++m) F += sh.wallF[m][c];
+        if (fl && c == g.wall_axis) F += P.f_drive;
+        if (tape) {
+          double* tp = tape + (size_t)s * nb * 6;
+          tp[0] = x;
+          tp[3] = v;
+        }
+        const double sx = P.sig * xi;
+        const double vn = P.e * v + P.cf * (F + P.gamma * u) + sx;
+        J = J - P.m * (P.omE * (u - v) + sx);
+        v = vn;
+        fin = fin && isfinite(vn);
+        const double re = x + P.hh * vn;
+        if (last) {
+          x = re;
+        } else {
+          x = re + P.hh * vn;
+          sh.pos[cb ^ 1][i][c] = x;
+          if (multi) {
+            unsigned long long* o = ring + (cb ? 0 : half);
+            const unsigned long long bits = (unsigned long long)__double_as_longlong(x);
+            res_store(o, bits);
+            res_store(o + 1, bits ^ tag);
+          }
+        }
+      }
+      lds_barrier();
+      if (sh.dead[cb]) return;
+    }
+  } else if (wave >= 6) {
+    // ---- pair forces: part [k0, k1) of bead pb's list
+    const int pb = (t - 384) / RES_PL, pl = t % RES_PL;
+    int k0 = 0, k1 = 0, first = 0;
+    if (pb < n) {
+      const int m = sh.lcnt[pb], per = (m + RES_PL - 1) / RES_PL;
+      k0 = min(pl * per, m);
+      k1 = min(k0 + per, m);
+      first = k0 < k1 ? sh.lst[pb][k0] : 0;
+    }
+    for (int s = s0; s < s1; ++s) {
+      const int cb = s & 1;
+      if (pb < n) {
+        const double* rp = sh.pos[cb][pb];
+        const double r0 = rp[0], r1 = rp[1], r2 = rp[2];
+        int hits = 0;
+        for (int m = k0; m < k1; ++m) {
+          const double* q = sh.pos[cb][m == k0 ? first : sh.lst[pb][m]];
+          const double d0 = min_image(r0 - q[0], g.nx);
+          const double d1 = min_image(r1 - q[1], g.ny);
+          const double d2 = min_image(r2 - q[2], g.nz);
+          if (!(d0 * d0 + d1 * d1 + d2 * d2 < P.rc2)) continue;
+          double Fp[3] = {0.0, 0.0, 0.0};
+          lj_add(P, d0, d1, d2, Fp);
+          if (hits < RES_PH) {
+            double* o = sh.pairF[pl][hits][pb];
+            o[0] = Fp[0]; o[1] = Fp[1]; o[2] = Fp[2];
+          }
+          ++hits;
+        }
+        sh.pcnt[pb][pl] = (uint8_t)min(hits, RES_PH + 1);
+      }
+      lds_barrier();
+      lds_barrier();
+      if (sh.dead[cb]) return;
+    }
+  } else if (wave == 2) {
+    // ---- kappa phi of the angle centred at a - 1 + lane
+    const bool ang = lane < n + 2 && p0 - 1 + lane >= 1 && p0 - 1 + lane <= nb - 2;
+    const int j0 = ang ? at(lane - 2) : 0, j1 = ang ? at(lane - 1) : 0, j2 = ang ? at(lane) : 0;
+    for (int s = s0; s < s1; ++s) {
+      const int cb = s & 1;
+      if (ang) {
+        const ResAngle A = res_angle(sh.pos[cb][j0], sh.pos[cb][j1], sh.pos[cb][j2]);
+        sh.kp[lane] = A.s == 0.0 ? 0.0 : P.kappa * atan2(A.s, A.c);
+      }
+      lds_barrier();
+      lds_barrier();
+      if (sh.dead[cb]) return;
+    }
+  } else if (wave == 5) {
+    // ---- bonds: the force on a + lane of its bond to a + lane - 1 (the
+    // other bead takes its exact negative); the displacement check
+    const bool bond = !P.constrained && lane <= n && p0 + lane > 0 && p0 + lane < nb;
+    double ref[3] = {0.0, 0.0, 0.0};
+    if (lane < n) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) ref[a] = fresh ? sh.pos[sp][lane][a] : d.ref[3 * (so + p0 + lane) + a];
+    }
+    for (int s = s0; s < s1; ++s) {
+      const int cb = s & 1;
+      if (bond) {
+        double Fb[3] = {0.0, 0.0, 0.0};
+        bond_add(P, sh.pos[cb][lane < n ? lane : HR], sh.pos[cb][lane ? lane - 1 : HL + 1], Fb);
+        sh.bnd[lane][0] = Fb[0]; sh.bnd[lane][1] = Fb[1]; sh.bnd[lane][2] = Fb[2];
+      }
+      if (lane < n && s > s0) {
+        double d2 = 0.0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) { const double dd = sh.pos[cb][lane][a] - ref[a]; d2 += dd * dd; }
+        if (d2 > P.halfskin2) fail(s);
+      }
+      lds_barrier();
+      lds_barrier();
+      if (sh.dead[cb]) return;
+    }
+  } else if (wave == 3) {
+    // ---- the wall sites of wall_row and the field indicator
+    const int wa = g.wall_axis, na = wa >= 0 ? ext(g, wa) : 0;
+    const int nw = P.whi - P.wlo + 1, per = nw <= 4 ? 16 : 64;
+    // nw x nw sites per bead in site order (o1 outer, o0 inner): 16 lanes
+    // per bead and 4 beads at once for the 4 x 4 window, else 64 lanes
+    const int num = lane % per, o1 = P.wlo + num / nw, o0 = P.wlo + num % nw;
+    const int n0 = wa == 0 ? g.ny : g.nx, n1 = wa == 2 ? g.ny : g.nz;   // transverse extents
+    for (int s = s0; s < s1; ++s) {
+      const int cb = s & 1;
+      int fl = 0, off = 0;
+      double w[3] = {0.0, 0.0, 0.0};             // wrapped: normal, then the transverse axes in order
+      bool near = false;                         // the bead's window reaches the plane
+      if (wa >= 0 && lane < n) {
+        const double* rp = sh.pos[cb][lane];
+        const double wn = wrapc(rp[wa], na);
+        off = g.wall_pos - (int)floor(wn);
+        if (off < WLO) off += na;
+        if (off > WHI) off -= na;
+        near = off >= P.wlo && off <= P.whi;
+        if (near) {
+          w[0] = wn;
+          w[1] = wrapc(rp[g.t0], n0);
+          w[2] = wrapc(rp[g.t1], n1);
+          fl = P.field_on && wn >= g.wall_pos - 1.5 && wn < g.wall_pos + 1.5 && w[1] >= g.lo0 - 0.5 &&
+               w[1] < g.hi0 + 0.5 && w[2] >= g.lo1 - 0.5 && w[2] < g.hi1 + 0.5 ? 1 : 0;
+        }
+      }
+      if (lane < n) {
+        sh.fld[lane] = fl;
+        sh.wall[lane] = 0;
+      }
+      uint64_t todo = __ballot(near);
+      int total = 0;
+      while (todo) {
+        uint64_t m = todo;                       // the (lane / per)-th of the beads left
+        for (int q = lane / per; q > 0; --q) m &= m - 1;
+        const bool on = m != 0 && num < nw * nw;
+        const int b = m ? __builtin_ctzll(m) : 0;
+        const double wn = __shfl(w[0], b, 64), wt0 = __shfl(w[1], b, 64), wt1 = __shfl(w[2], b, 64);
+        const int of = __shfl(off, b, 64);
+        bool hit = false;
+        double Fs[3] = {0.0, 0.0, 0.0};
+        if (on) {
+          const int u1 = (int)floor(wt1) + o1, u0 = (int)floor(wt0) + o0;
+          const int v1 = u1 < 0 ? u1 + n1 : (u1 >= n1 ? u1 - n1 : u1);
+          const int v0 = u0 < 0 ? u0 + n0 : (u0 >= n0 ? u0 - n0 : u0);
+          const bool pore = v1 >= g.lo1 && v1 <= g.hi1 && v0 >= g.lo0 && v0 <= g.hi0;
+          const double dn = wn - (double)((int)floor(wn) + of), dt0 = wt0 - (double)u0, dt1 = wt1 - (double)u1;
+          const double d0 = wa == 0 ? dn : dt0, d1 = wa == 1 ? dn : (wa == 0 ? dt0 : dt1), d2 = wa == 2 ? dn : dt1;
+          hit = !pore && d0 * d0 + d1 * d1 + d2 * d2 < P.rc2;
+          if (hit) lj_add(P, d0, d1, d2, Fs);
+        }
+        const uint64_t hm = __ballot(hit), below = (1ull << lane) - 1ull;
+        if (hit) {
+          const int o = total + __builtin_popcountll(hm & below);
+          if (o < RES_WH) { sh.wallF[o][0] = Fs[0]; sh.wallF[o][1] = Fs[1]; sh.wallF[o][2] = Fs[2]; }
+          else fail(s);
+        }
+        if (on && num == 0) {
+          const uint64_t own = per == 64 ? hm : (hm >> lane) & 0xffffull;
+          sh.wall[b] = ((total + __builtin_popcountll(hm & below)) << 8) | __builtin_popcountll(own);
+        }
+        total += __builtin_popcountll(hm);
+        for (int q = 0; q < 64 / per && todo; ++q) todo &= todo - 1;
+      }
+      lds_barrier();
+      lds_barrier();
+      if (sh.dead[cb]) return;
+    }
+  } else {
+    // ---- the noise of the workgroup's beads, one sub-step ahead (up to two
+    // of its 3 n values per lane); the remote positions
+    const int nx = noisy ? 3 * n : 0;
+    const double* xsrc = d.xi + (size_t)3 * (so + p0);
+    const double* x0 = xsrc + (size_t)s0 * 3 * nslots;
+    double xa = lane < nx ? x0[lane] : 0.0, xc = lane + 64 < nx ? x0[lane + 64] : 0.0;
+    const int rs0 = lane < 3 * nrem ? sh.rslot[lane / 3] : -1;
+    uint64_t tag = tags;
+    for (int s = s0; s < s1; ++s) {
+      const int cb = s & 1;
+      tag += TAG;
+      if (lane < nx) sh.xi[lane] = xa;
+      if (lane + 64 < nx) sh.xi[lane + 64] = xc;
+      lds_barrier();
+      if (s < s1 - 1) {
+        const double* q = xsrc + (size_t)(s + 1) * 3 * nslots;
+        if (lane < nx) xa = q[lane];
+        if (lane + 64 < nx) xc = q[lane + 64];
+        for (int m = lane; m < 3 * nrem; m += 64) {
+          const int sl = m == lane ? rs0 : sh.rslot[m / 3];
+          if (sl < 0) continue;
+          const unsigned long long* o = d.xring + (cb ? 0 : half) + ((size_t)sl * 3 + m % 3) * 2;
+          unsigned long long w = 0;
+          if (!res_poll<STOP>(o, tag, marker, d.ctrl, wait, w)) {
+            fail(s);
+            break;
+          }
+          sh.pos[cb ^ 1][RES_OWN + m / 3][m % 3] = __longlong_as_double((long long)w);
+        }
+      }
+      lds_barrier();
+      if (sh.dead[cb]) return;
+    }
+  }
+  if (!BLOCKS || s1 == n_sub) break;
+  }
+  if (!mine) return;
+  d.r[3 * slot + c] = x;
+  d.v[3 * slot + c] = v;
+  d.J[3 * slot + c] = J;
+  if (!fin) atomicOr(&d.ctrl->err, E_BEADS);
+}
+
 void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslots, int nrep, int n_sub, int K,
                            hipStream_t s) {
   if (nslots <= 0 || n_sub <= 0 || nseg <= 0) return;
@@ -1851,7 +2600,29 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
   for (int j = 0; j < M; ++j)
     hipLaunchKernelGGL(k_md_fused, dim3((unsigned)nseg), dim3(FU_WG), 0, s, d, fb, nslots, j * K, K,
                        j == M - 1 ? 1 : 0, j & 1);
-  hipLaunchKernelGGL(k_md_redo, dim3((unsigned)nrep), dim3(RD_WG), 0, s, d, fb, fb.ang, nslots, n_sub, K);
+  MdOverride none{};
+  hipLaunchKernelGGL(k_md_redo, dim3((unsigned)nrep), dim3(RD_WG), 0, s, d, fb, fb.ang, nslots, n_sub, K, none, 0);
+}
+
+// Holds the stream until the resident cycle's nseg workgroups run (they never
+// wait for this stream), at most RES_GATE ticks of the 100 MHz clock: 0.3 ms.
+constexpr uint64_t RES_GATE = 30000;
+__global__ void k_md_gate(const Ctrl* ctrl, uint32_t nseg) {
+  const uint64_t t0 = wall_clock64();
+  while (__hip_atomic_load(&ctrl->placed[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < nseg &&
+         wall_clock64() - t0 < RES_GATE)
+    __builtin_amdgcn_s_sleep(8);
+}
+void launch_md_gate(const Dev& d, int nseg, hipStream_t s) {
+  hipLaunchKernelGGL(k_md_gate, dim3(1), dim3(1), 0, s, d.ctrl, (uint32_t)nseg);
+}
+
+void launch_md_cycle_resident(const Dev& d, const FusedBufs& fb, const FusedSeg* seg, int nseg, int nslots, int nrep,
+                              int n_sub, const MdOverride& ov, uint64_t wait, hipStream_t s) {
+  if (nslots <= 0 || n_sub <= 0 || nseg <= 0) return;
+  hipLaunchKernelGGL(k_md_resident<false>, dim3((unsigned)nseg), dim3(RES_WG), 0, s, d, fb, seg, nslots, n_sub, ov, wait);
+  hipLaunchKernelGGL(k_md_resident<true>, dim3((unsigned)nseg), dim3(RES_WG), 0, s, d, fb, seg, nslots, n_sub, ov, wait);
+  hipLaunchKernelGGL(k_md_redo, dim3((unsigned)nrep), dim3(RD_WG), 0, s, d, fb, fb.ang, nslots, n_sub, n_sub, ov, 1);
 }
 
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s) {
