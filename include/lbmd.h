@@ -27,7 +27,7 @@
  *     lb_destroy; the library borrows the pointers and allocates no device
  *     memory (scratch areas such as the autotuner's state snapshot or the
  *     adjoint's checkpoints are buffers of the caller too).  It owns host
- *     objects only: two streams of its own, events, and the captured graph
+ *     objects only: a stream of its own, events, and the captured graph
  *     of lb_ensemble_run.
  *   - Streams: every call enqueues work on the stream given to lb_init and
  *     returns without synchronising, except where a call says that it

@@ -32,7 +32,7 @@ __global__ void k_fill_f64(double* __restrict__ p, long n, double v) {
 // K1: the sweep over a table of tiles (each tile_nodes consecutive nodes of
 // one replica); workgroups stride over the table.  Solid nodes are skipped,
 // and so are nodes carrying a bead force when skip_forced is set (they are
-// updated by k_lb_forced once the force is known).
+// updated by k_spread_lb once the force is known).
 // ---------------------------------------------------------------------------
 template <typename T, bool DEV, int U, bool FL>
 __global__ __launch_bounds__(256) void k_lb(const T* __restrict__ A, T* __restrict__ B,
@@ -72,21 +72,6 @@ __global__ __launch_bounds__(256) void k_lb(const T* __restrict__ A, T* __restri
     t = tn;
     tl = next;
   }
-}
-
-// The nodes that carry a bead force this step (the list written by the
-// spreading kernel).
-template <typename T, bool DEV>
-__global__ __launch_bounds__(64) void k_lb_forced(const T* __restrict__ A, T* __restrict__ B, Dev d, int maxlist) {
-  int k = blockIdx.x * blockDim.x + threadIdx.x;
-  int nt = (int)d.ctrl->touched;
-  if (k >= nt || k >= maxlist) return;
-  const int2 e = d.touched[k];
-  const Rep& R = d.reps[e.x];
-  const long no = R.node_off;
-  const uint8_t* fr = d.flags + no;
-  lb_node<T, DEV>(A + (size_t)Q * no, B + (size_t)Q * no, fr, (const T*)d.force + (size_t)3 * no, R.lp, d.ctrl, e.y,
-                  fr[e.y]);
 }
 
 // ---------------------------------------------------------------------------
@@ -247,9 +232,20 @@ __global__ void k_spread(Dev d, int nslots) {
 
 // Spreading fused with the LB update of the node it writes: the owner of a
 // node (see k_spread) sums its force, stores it, and updates the node at
-// once -- the same operations as k_spread followed by k_lb_forced.
+// once.
+//
+// The workgroups after the first nspread need J as well, and nothing else of
+// this step: they empty the buckets of the neighbour search, validate the
+// replicas' lists, and write each bead's spread-on-solid share.
 template <typename T, bool DEV>
-__global__ void k_spread_lb(const T* __restrict__ A, T* __restrict__ B, Dev d, int nslots) {
+__global__ void k_spread_lb(const T* __restrict__ A, T* __restrict__ B, Dev d, int nslots, int nspread, int nrep) {
+  if ((int)blockIdx.x >= nspread) {
+    const int k = ((int)blockIdx.x - nspread) * (int)blockDim.x + (int)threadIdx.x;
+    if (k <= (int)d.cmask) d.ccount[k] = 0;
+    if (k < nrep) d.rb[4 * k + 3] = 0u;
+    if (k < nslots) ledger_sp_share(d, k);
+    return;
+  }
   int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= 8 * nslots) return;
   int slot = e >> 3, k = e & 7;
@@ -310,42 +306,6 @@ __global__ void k_spread_lb(const T* __restrict__ A, T* __restrict__ B, Dev d, i
   d.touched[s] = make_int2(rep, n);
   const long no = R.node_off;
   lb_node<T, DEV>(A + (size_t)Q * no, B + (size_t)Q * no, fr, Fr, R.lp, d.ctrl, n, fr[n]);
-}
-
-// End of a coupled step: clear the forced bits, empty the node lists, note
-// replicas with a bead still on the cis side of the wall.
-__global__ void k_step_end(Dev d, int nslots, int maxlist) {
-  int k = blockIdx.x * blockDim.x + threadIdx.x;
-  int nt = (int)d.ctrl->touched;
-  if (k < nt && k < maxlist) {
-    int2 e = d.touched[k];
-    uint8_t* f = d.flags + d.reps[e.x].node_off + e.y;
-    *f = *f & (uint8_t)~F_FORCED;
-  }
-  if (k < nslots) {
-    const int rep = d.slot_rep[k];
-    const Rep& R = d.reps[rep];
-    if (k - R.slot_off < R.mp.nb) {
-      d.head[R.node_off + d.base[k]] = -1;
-      if (R.g.wall_axis >= 0 && !(d.r[3 * k + R.g.wall_axis] > (double)R.g.wall_pos)) d.notdone[rep] = 1u;
-    }
-  }
-}
-// Advance the step counter; record the translocation step of replicas whose
-// whole chain is past the wall plane for the first time.  One block.
-__global__ void k_step_tick(Dev d, int nrep, int with_beads) {
-  const uint64_t next = d.ctrl->step + 1u;
-  for (int r = threadIdx.x; r < nrep && with_beads; r += blockDim.x) {
-    const Rep& R = d.reps[r];
-    if (R.g.wall_axis >= 0 && R.mp.nb > 0 && d.notdone[r] == 0u && d.tX[r] < 0) d.tX[r] = (int64_t)next;
-    d.notdone[r] = 0u;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    d.ctrl->forced_total += d.ctrl->touched;
-    d.ctrl->touched = 0u;
-    d.ctrl->step = next;
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -501,8 +461,8 @@ __global__ __launch_bounds__(256) void k_observables(Dev d, double* __restrict__
 // solid upstream node x - c_i returns as f_i(x), so the wall takes
 // 2 f_opp(i)(x) c_opp(i); f from the post-collision array A the step pulls
 // from (f = A + w_i in deviation storage).  Block b of the wall-link list
-// sums its entries (fixed tree order) into lpart[3 b + a]; k_ledger_sum
-// then adds each replica's blocks in a fixed order to its cumulative ledger.
+// sums its entries (fixed tree order) into lpart[3 b + a]; k_step_end then
+// adds each replica's blocks in a fixed order to its cumulative ledger.
 // ---------------------------------------------------------------------------
 template <typename T, bool DEV>
 __global__ __launch_bounds__(LEDGER_BLOCK) void k_ledger_bb(const T* __restrict__ A, Dev d) {
@@ -531,41 +491,47 @@ __global__ __launch_bounds__(LEDGER_BLOCK) void k_ledger_bb(const T* __restrict_
   }
 }
 
-// One workgroup per replica: the step's bounce-back momentum, the replica's
-// block sums added in a fixed order (strided per thread, then a tree), added
-// to its ledger.
-__global__ __launch_bounds__(256) void k_ledger_sum(Dev d) {
+// End of a step, once every kernel of it is done: the first nend workgroups
+// clear the forced bits of the beads' stencils and empty their node lists (the
+// stencils again, rather than the list of forced nodes, so that one thread
+// can close the step in the same launch); then one workgroup per replica adds
+// the step's bounce-back momentum to its ledger, the replica's block sums in
+// a fixed order (strided per thread, then a tree).
+__global__ __launch_bounds__(256) void k_step_end(Dev d, int nslots, int nend, int links) {
   __shared__ double sh[256];
-  const Rep& R = d.reps[blockIdx.x];
+  if ((int)blockIdx.x < nend) {
+    const int slot = blockIdx.x * blockDim.x + threadIdx.x;
+    if (slot < nslots) {
+      const Rep& R = d.reps[d.slot_rep[slot]];
+      if (slot - R.slot_off < R.mp.nb) {
+        d.head[R.node_off + d.base[slot]] = -1;
+        const double rp[3] = {d.rs[3 * slot], d.rs[3 * slot + 1], d.rs[3 * slot + 2]};
+        const Stencil st = make_stencil(R.g, rp);
+        uint8_t* fr = d.flags + R.node_off;
+        uint8_t fl[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) fl[k] = fr[corner_node(R.g, st, k)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (fl[k] & F_FORCED) fr[corner_node(R.g, st, k)] = fl[k] & (uint8_t)~F_FORCED;
+      }
+    }
+    return;
+  }
+  const int rep = (int)blockIdx.x - nend;
+  if (rep == 0 && threadIdx.x == 0) {
+    d.ctrl->forced_total += d.ctrl->touched;
+    d.ctrl->touched = 0u;
+    d.ctrl->step += 1u;
+  }
+  if (!links) return;
+  const Rep& R = d.reps[rep];
   double s[3] = {0.0, 0.0, 0.0};
   for (int b = R.wl_begin + (int)threadIdx.x; b < R.wl_end; b += 256)
     for (int a = 0; a < 3; ++a) s[a] += d.lpart[3 * (size_t)b + a];
   for (int a = 0; a < 3; ++a) {
     const double v = block_sum(s[a], sh);
-    if (threadIdx.x == 0) d.ledger[NLEDGER * blockIdx.x + a] += v;
-  }
-}
-
-// Spread-on-solid: the share W_k J_p of the step's impulse that the
-// spreading drops because corner k of bead p is solid.  One thread per bead
-// slot writes its share (corners in order) to lsp; k_ledger_sp_sum then adds
-// each replica's beads in a fixed order (strided per thread, then a tree).
-__global__ void k_ledger_sp(Dev d, int nslots) {
-  const int slot = blockIdx.x * blockDim.x + threadIdx.x;
-  if (slot < nslots) ledger_sp_share(d, slot);
-}
-
-__global__ __launch_bounds__(1024) void k_ledger_sp_sum(Dev d) {
-  __shared__ double sh[1024];
-  const int rep = blockIdx.x;
-  const Rep& R = d.reps[rep];
-  double s[3] = {0.0, 0.0, 0.0};
-  if (R.g.wall_axis >= 0)
-    for (int p = threadIdx.x; p < R.mp.nb; p += 1024)
-      for (int a = 0; a < 3; ++a) s[a] += d.lsp[3 * (size_t)(R.slot_off + p) + a];
-  for (int a = 0; a < 3; ++a) {
-    const double v = block_sum<1024>(s[a], sh);
-    if (threadIdx.x == 0) d.ledger[NLEDGER * rep + 3 + a] += v;
+    if (threadIdx.x == 0) d.ledger[NLEDGER * rep + a] += v;
   }
 }
 
@@ -612,13 +578,6 @@ void launch_lb(const void* A, void* B, const Dev& d, int ntiles, int tile_nodes,
 }
 
 template <typename T, bool DEV>
-void launch_lb_forced(const void* A, void* B, const Dev& d, int maxlist, hipStream_t s) {
-  if (maxlist > 0)
-    hipLaunchKernelGGL((k_lb_forced<T, DEV>), dim3(blocks_for(maxlist, 64)), dim3(64), 0, s, (const T*)A, (T*)B, d,
-                       maxlist);
-}
-
-template <typename T, bool DEV>
 void launch_gather(const void* A, const Dev& d, int nslots, int start, hipStream_t s) {
   if (nslots > 0)
     hipLaunchKernelGGL((k_gather<T, DEV>), dim3(blocks_for(8L * nslots, 64)), dim3(64), 0, s, (const T*)A, d,
@@ -635,16 +594,20 @@ void launch_spread(const Dev& d, int nslots, hipStream_t s) {
 }
 
 template <typename T, bool DEV>
-void launch_spread_lb(const void* A, void* B, const Dev& d, int nslots, hipStream_t s) {
-  if (nslots > 0)
-    hipLaunchKernelGGL((k_spread_lb<T, DEV>), dim3(blocks_for(8L * nslots, 64)), dim3(64), 0, s, (const T*)A,
-                       (T*)B, d, nslots);
+void launch_spread_lb(const void* A, void* B, const Dev& d, int nslots, int nrep, hipStream_t s) {
+  if (nslots <= 0) return;
+  const unsigned nspread = blocks_for(8L * nslots, 64);
+  long n = (long)d.cmask + 1;
+  if (nslots > n) n = nslots;
+  if (nrep > n) n = nrep;
+  hipLaunchKernelGGL((k_spread_lb<T, DEV>), dim3(nspread + blocks_for(n, 64)), dim3(64), 0, s, (const T*)A, (T*)B, d,
+                     nslots, (int)nspread, nrep);
 }
 
-void launch_step_end(const Dev& d, int nslots, int maxlist, int nrep, hipStream_t s) {
-  long n = nslots > maxlist ? nslots : maxlist;
-  if (n > 0) hipLaunchKernelGGL(k_step_end, dim3(blocks_for(n, 256)), dim3(256), 0, s, d, nslots, maxlist);
-  hipLaunchKernelGGL(k_step_tick, dim3(1), dim3(256), 0, s, d, nrep, nslots > 0 ? 1 : 0);
+void launch_step_end(const Dev& d, int nslots, int nrep, int nblk, hipStream_t s) {
+  const unsigned nend = nslots > 0 ? blocks_for(nslots, 256) : 0u;
+  hipLaunchKernelGGL(k_step_end, dim3(nend + (unsigned)(nblk > 0 ? nrep : 1)), dim3(256), 0, s, d, nslots, (int)nend,
+                     nblk > 0 ? 1 : 0);
 }
 
 template <typename T, bool DEV>
@@ -656,34 +619,24 @@ void launch_observables(const void* A, const Dev& d, int n_otiles, int nrep, dou
 }
 
 template <typename T, bool DEV>
-void launch_ledger_bb(const void* A, const Dev& d, int nblk, int nrep, hipStream_t s) {
-  if (nblk <= 0) return;
-  hipLaunchKernelGGL((k_ledger_bb<T, DEV>), dim3((unsigned)nblk), dim3(LEDGER_BLOCK), 0, s, (const T*)A, d);
-  hipLaunchKernelGGL(k_ledger_sum, dim3((unsigned)nrep), dim3(256), 0, s, d);
-}
-
-void launch_ledger_sp(const Dev& d, int nslots, int nrep, hipStream_t s) {
-  if (nslots <= 0) return;
-  hipLaunchKernelGGL(k_ledger_sp, dim3(blocks_for(nslots, 64)), dim3(64), 0, s, d, nslots);
-  hipLaunchKernelGGL(k_ledger_sp_sum, dim3((unsigned)nrep), dim3(1024), 0, s, d);
+void launch_ledger_bb(const void* A, const Dev& d, int nblk, hipStream_t s) {
+  if (nblk > 0) hipLaunchKernelGGL((k_ledger_bb<T, DEV>), dim3((unsigned)nblk), dim3(LEDGER_BLOCK), 0, s, (const T*)A, d);
 }
 
 template void launch_fill_rest<double, false>(void*, long, hipStream_t);
 template void launch_fill_rest<float, true>(void*, long, hipStream_t);
 template void launch_lb<double, false>(const void*, void*, const Dev&, int, int, int, int, int, bool, hipStream_t);
 template void launch_lb<float, true>(const void*, void*, const Dev&, int, int, int, int, int, bool, hipStream_t);
-template void launch_lb_forced<double, false>(const void*, void*, const Dev&, int, hipStream_t);
-template void launch_lb_forced<float, true>(const void*, void*, const Dev&, int, hipStream_t);
 template void launch_gather<double, false>(const void*, const Dev&, int, int, hipStream_t);
 template void launch_gather<float, true>(const void*, const Dev&, int, int, hipStream_t);
 template void launch_spread<double>(const Dev&, int, hipStream_t);
-template void launch_spread_lb<double, false>(const void*, void*, const Dev&, int, hipStream_t);
-template void launch_spread_lb<float, true>(const void*, void*, const Dev&, int, hipStream_t);
+template void launch_spread_lb<double, false>(const void*, void*, const Dev&, int, int, hipStream_t);
+template void launch_spread_lb<float, true>(const void*, void*, const Dev&, int, int, hipStream_t);
 template void launch_spread<float>(const Dev&, int, hipStream_t);
 template void launch_observables<double, false>(const void*, const Dev&, int, int, double*, int, double*,
                                                 hipStream_t);
 template void launch_observables<float, true>(const void*, const Dev&, int, int, double*, int, double*, hipStream_t);
-template void launch_ledger_bb<double, false>(const void*, const Dev&, int, int, hipStream_t);
-template void launch_ledger_bb<float, true>(const void*, const Dev&, int, int, hipStream_t);
+template void launch_ledger_bb<double, false>(const void*, const Dev&, int, hipStream_t);
+template void launch_ledger_bb<float, true>(const void*, const Dev&, int, hipStream_t);
 
 }  // namespace lbmd

@@ -107,7 +107,7 @@ Packing packing(const lb_desc* d, int nrep) {
 
 struct WorkLayout {
   size_t ctrl, reps, tiles, otiles, slot_rep, head, next, base, touched, nbr, ncnt, rb, rmid0, rmid1, ref, part, xi,
-      tX, notdone, ccount, cbuf, rbin, cst, wlinks, ledger, lpart, lsp, fseg, rmS, vS, JS, fang, redo, rseg, xring, xflag;
+      tX, ccount, cbuf, rbin, cst, wlinks, ledger, lpart, lsp, fseg, rmS, vS, JS, fang, redo, rseg, xring, xflag, rsync;
   size_t nbuckets;
   size_t total;
 };
@@ -136,7 +136,6 @@ WorkLayout work_layout(const lb_desc* d, int nrep, const Packing& pk) {
   w.part = take(sizeof(double) * 4 * (size_t)pk.obs_tiles);
   w.xi = take(sizeof(double) * 3 * ns * (size_t)d[0].n_sub * 2);   // two sub-cycles: this step's and the next
   w.tX = take(sizeof(int64_t) * R);
-  w.notdone = take(sizeof(uint32_t) * R);
   w.nbuckets = 64;
   while (w.nbuckets < 2 * ns) w.nbuckets *= 2;
   w.ccount = take(sizeof(int) * w.nbuckets);
@@ -153,6 +152,7 @@ WorkLayout work_layout(const lb_desc* d, int nrep, const Packing& pk) {
   w.JS = take(sizeof(double) * 3 * ns);
   w.fang = take(sizeof(double) * 9 * ns);
   w.redo = take(sizeof(int) * R);
+  w.rsync = take(sizeof(uint32_t) * 2 * R);
   w.rseg = take(sizeof(FusedSeg) * (size_t)(pk.nrseg > 0 ? pk.nrseg : 1));
   w.xring = take(sizeof(uint64_t) * 4 * 2 * 3 * ns);
   w.xflag = take(sizeof(uint64_t) * 2 * 2 * (size_t)(pk.nrseg > 0 ? pk.nrseg : 1));
@@ -375,7 +375,6 @@ struct lb_ctx {
   std::vector<Rep> reps;
   Dev D;
   int nslots = 0;
-  int maxlist = 0;
   bool step_lists = false;   // neighbour lists built from a cell list at every coupled step
   bool lists_stale = true;   // the positions changed outside a coupled step since the last build
   bool any_noise = false;
@@ -394,11 +393,10 @@ struct lb_ctx {
   uint64_t md_wait = RES_WAIT;   // longest wait inside it, ticks of the 100 MHz clock
   int64_t steps = 0;
   // second stream for the sweep over the nodes without bead force, which
-  // runs concurrently with the bead phase; fork/join events
-  hipStream_t s1 = nullptr, s2 = nullptr;
-  hipEvent_t fork = nullptr, prep = nullptr, join = nullptr, join1 = nullptr, mdone = nullptr;
+  // runs concurrently with the bead phase on the caller's; fork/join events
+  hipStream_t s2 = nullptr;
+  hipEvent_t prep = nullptr, join = nullptr;
   // graph of two coupled steps, starting at population parity graph_cur
-  hipStream_t scap = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
   int graph_cur = -1;
@@ -408,9 +406,7 @@ struct lb_ctx {
   // graph would depend on nodes of another (possibly destroyed) graph
   uint64_t cap_gen = 0;
   std::map<hipEvent_t, uint64_t> ev_gen;
-  std::map<hipEvent_t, hipStream_t> ev_stream;   // the stream of each event's last record
   bool stale_wait = false;
-  bool back_wait = false;      // inside a capture, the bead stream waited on the sweep stream
   // adjoint: the forward pass recorded by lb_adjoint_forward
   int adj_n = 0, adj_K = 0;
   bool adj_taped = false;   // the forward pass recorded the whole horizon's tape
@@ -500,15 +496,11 @@ void prof_next(lb_ctx* c) {
 void ev_record(lb_ctx* c, hipEvent_t e, hipStream_t st) {
   acc(hipEventRecord(e, st));
   c->ev_gen[e] = c->capturing ? c->cap_gen : 0;
-  c->ev_stream[e] = st;
 }
 void ev_wait(lb_ctx* c, hipStream_t st, hipEvent_t e) {
   if (c->capturing) {
     auto it = c->ev_gen.find(e);
     if (it == c->ev_gen.end() || it->second != c->cap_gen) c->stale_wait = true;
-    // the forked streams depend on each other in one direction only: the
-    // sweep stream waits on the bead stream, never the reverse
-    if (st == c->s1 && c->ev_stream[e] == c->s2) c->back_wait = true;
   }
   acc(hipStreamWaitEvent(st, e, 0));
 }
@@ -548,8 +540,8 @@ void ensure_lists(lb_ctx* c, hipStream_t st) {
 
 // The bounce-back ledger of a step that pulls from A, on stream st.
 void ledger_bb(lb_ctx* c, const void* A, hipStream_t st) {
-  if (c->dev) launch_ledger_bb<float, true>(A, c->D, c->wl_blocks, c->nrep, st);
-  else launch_ledger_bb<double, false>(A, c->D, c->wl_blocks, c->nrep, st);
+  if (c->dev) launch_ledger_bb<float, true>(A, c->D, c->wl_blocks, st);
+  else launch_ledger_bb<double, false>(A, c->D, c->wl_blocks, st);
 }
 
 // One fluid-only step on stream st.
@@ -561,7 +553,7 @@ void enqueue_lb_step(lb_ctx* c, hipStream_t st) {
   sweep(c, 0, st);
   prof_mark(c, 3, st);
   ledger_bb(c, cur_pops(c), st);
-  launch_step_end(c->D, 0, 0, c->nrep, st);
+  launch_step_end(c->D, 0, c->nrep, c->wl_blocks, st);
   c->cur ^= 1;
   prof_next(c);
 }
@@ -569,22 +561,19 @@ void enqueue_lb_step(lb_ctx* c, hipStream_t st) {
 // One coupled step on stream st: the stencil nodes of r(n) are marked first;
 // the sweep over all other nodes then runs on the second stream while the
 // beads move; the marked nodes are updated once the bead force is spread.
-// The bead phase runs on the library's bead stream s1 and the sweep over the
-// nodes without bead force on s2, both forked from and joined back to st, so
-// that the overlap does not depend on the kind of stream the caller uses.
+// The bead phase and what follows from it (the next step's lists and noise)
+// stay on st, which waits for the sweep only at the step's last launch: a step
+// bound by the sweep then has nothing but that launch after it.
 void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) {
   ensure_noise(c, st);
   const Dev D = with_noise_slot(c, c->cur);
-  hipStream_t sb = c->s1;
-  ev_record(c, c->fork, st);
-  ev_wait(c, sb, c->fork);
-  prof_mark(c, 0, sb);
-  // the lists of this step were built at the end of the previous one
-  // (beside the spreading), unless the positions changed since; their validity
-  // flags are read when the preparation opens the sub-cycle
-  if (c->step_lists && c->lists_stale) launch_nbr_build(D, c->nslots, c->nrep, sb);
-  launch_bead_prep(D, c->nslots, c->nrep, sb);
-  ev_record(c, c->prep, sb);
+  prof_mark(c, 0, st);
+  // the lists of this step were built at the end of the previous one, unless
+  // the positions changed since; their validity flags are read when the
+  // preparation opens the sub-cycle
+  if (c->step_lists && c->lists_stale) launch_nbr_build(D, c->nslots, c->nrep, st);
+  launch_bead_prep(D, c->nslots, c->nrep, st);
+  ev_record(c, c->prep, st);
   const bool resident = c->resident && c->mts == 0 && (c->fusedK == 0 || D.mdtape);
   auto sweep_side = [&]() {
     ev_wait(c, c->s2, c->prep);
@@ -593,48 +582,34 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
     sweep_ab(c, A, B, 1, c->s2);
     prof_mark(c, 3, c->s2);
     // the wall's bounce-back momentum of this step (reads A, which no kernel
-    // of this step writes), and the next step's noise, into the other slot,
-    // after the sweep: off the bead stream's path
+    // of this step writes)
     ledger_bb(c, A, c->s2);
-    if (c->any_noise) launch_md_noise(with_noise_slot(c, c->cur ^ 1), c->nslots, c->n_sub, 1, c->s2);
+    ev_record(c, c->join, c->s2);
   };
   // enqueued before the sub-cycle's many launches, but after the resident
-  // cycle's two: where both streams share a hardware queue, the gate before
-  // the sweep then follows the workgroups it waits for
+  // cycle: where both streams share a hardware queue, the gate before the
+  // sweep then follows the workgroups it waits for
   if (!resident) sweep_side();
   // the gather also opens the sub-cycle
   const int start = c->mts > 0 ? 2 : 1;
-  if (c->dev) launch_gather<float, true>(A, D, c->nslots, start, sb);
-  else launch_gather<double, false>(A, D, c->nslots, start, sb);
+  if (c->dev) launch_gather<float, true>(A, D, c->nslots, start, st);
+  else launch_gather<double, false>(A, D, c->nslots, start, st);
   MdOverride none{};
-  if (c->mts > 0) launch_md_cycle_mts(D, c->nslots, c->nrep, c->n_sub, c->mts, sb, false);
+  if (c->mts > 0) launch_md_cycle_mts(D, c->nslots, c->nrep, c->n_sub, c->mts, st, false);
   else if (c->fusedK > 0 && !D.mdtape)
-    launch_md_cycle_fused(D, c->fb, c->pk.nseg, c->nslots, c->nrep, c->n_sub, c->fusedK, sb);
+    launch_md_cycle_fused(D, c->fb, c->pk.nseg, c->nslots, c->nrep, c->n_sub, c->fusedK, st);
   else if (resident)
-    launch_md_cycle_resident(D, c->fb, c->rseg, c->pk.nrseg, c->nslots, c->nrep, c->n_sub, none, c->md_wait, sb);
-  else launch_md_cycle(D, c->nslots, c->nrep, c->n_sub, none, sb, false, c->any_constrained);
+    launch_md_cycle_resident(D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, c->n_sub, none, c->md_wait, st);
+  else launch_md_cycle(D, c->nslots, c->nrep, c->n_sub, none, st, false, c->any_constrained);
   if (resident) sweep_side();
-  ev_record(c, c->mdone, sb);
-  if (c->dev) launch_spread_lb<float, true>(A, B, D, c->nslots, sb);
-  else launch_spread_lb<double, false>(A, B, D, c->nslots, sb);
-  prof_mark(c, 1, sb);
-  // on the sweep stream (done by now) once J is final, beside the
-  // spreading, which writes none of their arrays, and enqueued after it so
-  // that a replayed graph issues the spreading first: the share of the
-  // impulse that falls on solid nodes; for long chains the next step's
-  // lists from r(n+1)
-  ev_wait(c, c->s2, c->mdone);
-  if (c->step_lists) {
-    launch_step_tail(D, c->nslots, c->nrep, true, c->s2);
-    c->lists_stale = false;
-  } else {
-    launch_ledger_sp(D, c->nslots, c->nrep, c->s2);
-  }
-  ev_record(c, c->join, c->s2);
-  ev_record(c, c->join1, sb);
+  if (c->dev) launch_spread_lb<float, true>(A, B, D, c->nslots, c->nrep, st);
+  else launch_spread_lb<double, false>(A, B, D, c->nslots, c->nrep, st);
+  prof_mark(c, 1, st);
+  // the next step's lists from r(n+1) and, into the other slot, its noise
+  launch_step_tail(D, c->nslots, c->nrep, c->any_noise ? with_noise_slot(c, c->cur ^ 1).xi : nullptr, c->n_sub, st);
+  c->lists_stale = false;
   ev_wait(c, st, c->join);
-  ev_wait(c, st, c->join1);
-  launch_step_end(D, c->nslots, c->maxlist, c->nrep, st);
+  launch_step_end(D, c->nslots, c->nrep, c->wl_blocks, st);
   c->noise_ready = c->any_noise;
   prof_next(c);
 }
@@ -665,41 +640,40 @@ int build_graph(lb_ctx* c) {
   ensure_noise(c, c->s);
   ensure_lists(c, c->s);
   const int cur0 = c->cur;
+  // a stream for the capture alone: one that lived on would hold a place among
+  // the few hardware queues, which the streams of other contexts then share
+  hipStream_t scap = nullptr;
+  hipError_t e = hipStreamCreateWithFlags(&scap, hipStreamNonBlocking);
+  if (e != hipSuccess) return fail(LB_ERR_DEVICE, "graph capture: %s", hipGetErrorString(e));
   c->capturing = true;
   ++c->cap_gen;
   c->stale_wait = false;
-  c->back_wait = false;
-  hipError_t e = hipStreamBeginCapture(c->scap, hipStreamCaptureModeThreadLocal);
+  e = hipStreamBeginCapture(scap, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) {
     c->capturing = false;
+    (void)hipStreamDestroy(scap);
     return fail(LB_ERR_DEVICE, "graph capture: %s", hipGetErrorString(e));
   }
-  enqueue_coupled_step(c, c->scap);
-  enqueue_coupled_step(c, c->scap);
+  enqueue_coupled_step(c, scap);
+  enqueue_coupled_step(c, scap);
   hipGraph_t g = nullptr;
-  hipError_t e2 = hipStreamEndCapture(c->scap, &g);
+  hipError_t e2 = hipStreamEndCapture(scap, &g);
   c->capturing = false;
+  (void)hipStreamDestroy(scap);
   c->cur = cur0;
   int rc = take_acc("graph capture");
   // every wait inside the capture used a record made inside it
   if (!rc && c->stale_wait)
     rc = fail(LB_ERR_DEVICE, "graph capture: a stream waited on an event recorded outside the capture");
-  if (!rc && c->back_wait)
-    rc = fail(LB_ERR_DEVICE, "graph capture: the bead stream waited on the sweep stream (the forked streams "
-                             "may depend on each other in one direction only)");
-  // every stream the steps forked joined back before the end of the capture:
-  // none of them may still be capturing (work enqueued on it later would
-  // otherwise belong to a graph that no longer exists)
+  // the stream the steps forked joined back before the end of the capture:
+  // it may not still be capturing (work enqueued on it later would otherwise
+  // belong to a graph that no longer exists)
   if (!rc && e2 == hipSuccess) {
-    for (hipStream_t side : {c->s1, c->s2}) {
-      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-      hipError_t e3 = hipStreamIsCapturing(side, &cs);
-      if (e3 != hipSuccess || cs != hipStreamCaptureStatusNone) {
-        rc = fail(LB_ERR_DEVICE, "graph capture: a forked stream is still capturing (%s)",
-                  e3 != hipSuccess ? hipGetErrorString(e3) : "status not none");
-        break;
-      }
-    }
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    hipError_t e3 = hipStreamIsCapturing(c->s2, &cs);
+    if (e3 != hipSuccess || cs != hipStreamCaptureStatusNone)
+      rc = fail(LB_ERR_DEVICE, "graph capture: the forked stream is still capturing (%s)",
+                e3 != hipSuccess ? hipGetErrorString(e3) : "status not none");
   }
   if (e2 != hipSuccess || rc) {
     if (g) (void)hipGraphDestroy(g);
@@ -868,15 +842,9 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   c->s = (hipStream_t)stream;
   {
     hipError_t e1 = hipStreamCreateWithFlags(&c->s2, hipStreamNonBlocking);
-    hipError_t e2 = hipEventCreateWithFlags(&c->fork, hipEventDisableTiming);
     hipError_t e3 = hipEventCreateWithFlags(&c->join, hipEventDisableTiming);
-    hipError_t e4 = hipStreamCreateWithFlags(&c->scap, hipStreamNonBlocking);
-    hipError_t e5 = hipStreamCreateWithFlags(&c->s1, hipStreamNonBlocking);
     hipError_t e6 = hipEventCreateWithFlags(&c->prep, hipEventDisableTiming);
-    hipError_t e7 = hipEventCreateWithFlags(&c->join1, hipEventDisableTiming);
-    hipError_t e8 = hipEventCreateWithFlags(&c->mdone, hipEventDisableTiming);
-    if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess || e4 != hipSuccess || e5 != hipSuccess ||
-        e6 != hipSuccess || e7 != hipSuccess || e8 != hipSuccess) {
+    if (e1 != hipSuccess || e3 != hipSuccess || e6 != hipSuccess) {
       lb_destroy(c);
       return fail(LB_ERR_DEVICE, "stream/event creation failed");
     }
@@ -889,7 +857,6 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   c->wl = work_layout(d, nrep, c->pk);
   c->sl = state_layout(d, nrep, c->pk);
   c->nslots = c->pk.slots;
-  c->maxlist = 8 * c->nslots;
   // every chain's neighbour lists are built from the cell table at every
   // coupled step, beside the spreading, with a skin wide enough that a
   // step's motion rarely forces a rebuild inside the sub-cycle
@@ -977,7 +944,6 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   D.xi = (double*)(w + c->wl.xi);
   D.part = (double*)(w + c->wl.part);
   D.tX = (int64_t*)(w + c->wl.tX);
-  D.notdone = (uint32_t*)(w + c->wl.notdone);
   D.ccount = (int*)(w + c->wl.ccount);
   D.cbuf = (int*)(w + c->wl.cbuf);
   D.rbin = (double*)(w + c->wl.rbin);
@@ -991,6 +957,7 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   D.redo = (int*)(w + c->wl.redo);
   D.xring = (unsigned long long*)(w + c->wl.xring);
   D.xflag = (unsigned long long*)(w + c->wl.xflag);
+  D.rsync = (uint32_t*)(w + c->wl.rsync);
   c->rseg = (const FusedSeg*)(w + c->wl.rseg);
   c->fb.seg = (const FusedSeg*)(w + c->wl.fseg);
   c->fb.rmS = (double*)(w + c->wl.rmS);
@@ -1041,7 +1008,6 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   acc(hipMemsetAsync(D.cst, 0, sizeof(uint32_t) * 4 * nrep, s));
   acc(hipMemsetAsync(D.ncnt, 0, sizeof(int) * ns, s));
   acc(hipMemsetAsync(D.rb, 0, sizeof(uint32_t) * 4 * nrep, s));
-  acc(hipMemsetAsync(D.notdone, 0, sizeof(uint32_t) * nrep, s));
   {
     std::vector<int64_t> tx((size_t)nrep, -1);
     acc(hipMemcpyAsync(D.tX, tx.data(), sizeof(int64_t) * nrep, hipMemcpyHostToDevice, s));
@@ -1079,18 +1045,12 @@ int lb_init(const lb_desc* d, const lb_buffers* b, const double* r0_host, const 
 void lb_destroy(lb_ctx* ctx) {
   if (!ctx) return;
   if (ctx->s) (void)hipStreamSynchronize(ctx->s);
-  if (ctx->s1) (void)hipStreamSynchronize(ctx->s1);
   if (ctx->s2) (void)hipStreamSynchronize(ctx->s2);
   drop_graph(ctx);
   for (hipEvent_t e : ctx->ev) (void)hipEventDestroy(e);
-  if (ctx->fork) (void)hipEventDestroy(ctx->fork);
   if (ctx->prep) (void)hipEventDestroy(ctx->prep);
   if (ctx->join) (void)hipEventDestroy(ctx->join);
-  if (ctx->join1) (void)hipEventDestroy(ctx->join1);
-  if (ctx->mdone) (void)hipEventDestroy(ctx->mdone);
-  if (ctx->s1) (void)hipStreamDestroy(ctx->s1);
   if (ctx->s2) (void)hipStreamDestroy(ctx->s2);
-  if (ctx->scap) (void)hipStreamDestroy(ctx->scap);
   delete ctx;
 }
 
@@ -1124,7 +1084,6 @@ int lb_profile_stop(lb_ctx* c, double* mean_lb_ms, double* mean_bead_ms, int* ns
   if (!c->prof_on) return fail(LB_ERR_ARG, "profiling not active");
   c->prof_on = false;
   hipError_t r = hipStreamSynchronize(c->s);
-  if (r == hipSuccess) r = hipStreamSynchronize(c->s1);
   if (r == hipSuccess) r = hipStreamSynchronize(c->s2);
   if (r != hipSuccess) return fail(LB_ERR_DEVICE, "stream: %s", hipGetErrorString(r));
   double tl = 0.0, tb = 0.0;
@@ -1203,7 +1162,7 @@ int md_relax(lb_ctx* c, int nsub_total, double gamma_relax) {
       launch_nbr_build(c->D, c->nslots, c->nrep, c->s);
       launch_md_begin(c->D, c->nrep, c->s);
       launch_md_start(c->D, c->nslots, ov, c->s);
-      launch_md_cycle_resident(c->D, c->fb, c->rseg, c->pk.nrseg, c->nslots, c->nrep, n, ov, c->md_wait, c->s);
+      launch_md_cycle_resident(c->D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, n, ov, c->md_wait, c->s);
     } else {
       launch_md_cycle(c->D, c->nslots, c->nrep, n, ov, c->s, true, c->any_constrained);
     }
@@ -1282,7 +1241,6 @@ void* lb_current_pops(lb_ctx* c) { return c ? cur_pops(c) : nullptr; }
 int lb_check(lb_ctx* c) {
   if (!c) return fail(LB_ERR_ARG, "null context");
   hipError_t e = hipStreamSynchronize(c->s);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->s1);
   if (e == hipSuccess) e = hipStreamSynchronize(c->s2);
   if (e != hipSuccess) return fail(LB_ERR_DEVICE, "stream: %s", hipGetErrorString(e));
   uint32_t err = 0;

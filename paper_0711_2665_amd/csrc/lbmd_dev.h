@@ -116,8 +116,8 @@ struct Ctrl {
   uint32_t fused_why[5];
   uint32_t nbr_max;          // longest neighbour list a per-step build found (diagnostic)
   uint64_t cycles;           // sub-cycles opened so far: the tag of the resident cycle's exchanges
-  uint32_t placed[2];        // workgroups of the current resident cycle (its first, its second launch) that have started
-  uint32_t pad[38];
+  uint32_t placed;           // workgroups of the current resident cycle that have started
+  uint32_t pad[39];
 };
 static_assert(sizeof(Ctrl) == 256, "control block is one 256-byte line");
 

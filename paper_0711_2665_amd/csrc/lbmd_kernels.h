@@ -110,7 +110,6 @@ struct Dev {
   // reductions and per-replica bookkeeping
   double* part;     // [reduction tiles][4] fluid partial sums
   int64_t* tX;      // per replica: first step with the whole chain translocated, -1 before
-  uint32_t* notdone;// per replica: some bead still on the cis side this step
   double* mdtape;   // when set: per sub-step s and bead p, r_mid and v at the start,
                     // [s][p][2][3] (recorded for the adjoint, one replica)
   int* ccount;      // neighbour search: beads per bucket of the hashed cell table
@@ -123,6 +122,7 @@ struct Dev {
                     // bits and its bits XOR the sub-step's tag (slots 0, 1: every sub-step; 2, 3: the
                     // start of a block)
   unsigned long long* xflag;   // [2][segments][2]: a word per segment at the start of a block, likewise
+  uint32_t* rsync;  // [R][2]: per pass of the resident cycle, segments done and the failure bit
   Ctrl* ctrl;
   int* redo;        // per replica: first sub-step the fused sub-cycle leaves to the per-sub-step
                     // launches (-1: none); reset at every cycle's opening
@@ -151,8 +151,6 @@ void launch_fill_f64(double* p, long n, double v, hipStream_t s);
 template <typename T, bool DEV>
 void launch_lb(const void* A, void* B, const Dev& d, int ntiles, int tile_nodes, int grid, int cap, int skip_forced,
                bool fluct, hipStream_t s);
-template <typename T, bool DEV>
-void launch_lb_forced(const void* A, void* B, const Dev& d, int maxlist, hipStream_t s);
 // start: 0, or also open the MD sub-cycle (what k_md_start does: 1 for
 // uniform sub-steps, 2 for the multiple-time-step cycle) after its flags
 template <typename T, bool DEV>
@@ -161,10 +159,12 @@ void launch_gather(const void* A, const Dev& d, int nslots, int start, hipStream
 void launch_bead_prep(const Dev& d, int nslots, int nrep, hipStream_t s);
 template <typename T>
 void launch_spread(const Dev& d, int nslots, hipStream_t s);
-// Spreading fused with the update of the nodes it writes (forward step).
+// Spreading fused with the update of the nodes it writes (forward step), and
+// the first part of the step's tail (launch_step_tail).
 template <typename T, bool DEV>
-void launch_spread_lb(const void* A, void* B, const Dev& d, int nslots, hipStream_t s);
-void launch_step_end(const Dev& d, int nslots, int maxlist, int nrep, hipStream_t s);
+void launch_spread_lb(const void* A, void* B, const Dev& d, int nslots, int nrep, hipStream_t s);
+// The last launch of a step (nblk: wall-link list blocks).
+void launch_step_end(const Dev& d, int nslots, int nrep, int nblk, hipStream_t s);
 // Observables into out[NOBS * r + k]; groups of the lb_observables mask
 // (bit 0 fluid sums, 1 bead quantities, 2 wall ledgers, 3 step count); the
 // entries of groups not asked for are left as they are.  part: the fluid
@@ -172,12 +172,10 @@ void launch_step_end(const Dev& d, int nslots, int maxlist, int nrep, hipStream_
 template <typename T, bool DEV>
 void launch_observables(const void* A, const Dev& d, int n_otiles, int nrep, double* out, int mask, double* part,
                         hipStream_t s);
-// Wall ledgers of one step: the bounce-back momentum of the links in the
-// wall-link list (from the populations A the step reads; nblk list blocks),
-// and the bead impulse of the step's spreading that falls on solid nodes.
+// The bounce-back momentum of the links in the wall-link list, per list block
+// (from the populations A the step reads; nblk list blocks).
 template <typename T, bool DEV>
-void launch_ledger_bb(const void* A, const Dev& d, int nblk, int nrep, hipStream_t s);
-void launch_ledger_sp(const Dev& d, int nslots, int nrep, hipStream_t s);
+void launch_ledger_bb(const void* A, const Dev& d, int nblk, hipStream_t s);
 
 // Adjoint pass (one replica, chains of at most MAX_ADJ_BEADS beads).
 constexpr int MAX_ADJ_BEADS = 16384;
@@ -265,17 +263,17 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
 // lasts longer than `wait` ticks of the 100 MHz clock, or RES_PLACE while some
 // workgroup has not found room, hands the replica to one workgroup that
 // redoes the cycle from its start; a bead that leaves the range of the step's
-// neighbour lists, to a second pass with new lists every RES_BLOCK sub-steps
+// neighbour lists, to a second pass with new lists where one needs them, every RES_BLOCK sub-steps
 // (8000 beads of a walk that was not relaxed, step by step: 3.1 ms, as with one
 // launch per sub-step; the one workgroup takes 94).  At n_sub = 1 and 2 the
-// single launches cost no more than the cycle's three.
+// single launches cost no more.
 constexpr int RES_OWN = 32;
 constexpr int RES_BLOCK = 10;
 constexpr int RES_MAX_WG = 512;
 constexpr int RES_MIN_SUB = 3;
 constexpr uint64_t RES_PLACE = 200000;   // 2 ms
-void launch_md_cycle_resident(const Dev& d, const FusedBufs& fb, const FusedSeg* seg, int nseg, int nslots, int nrep,
-                              int n_sub, const MdOverride& ov, uint64_t wait, hipStream_t s);
+void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int nseg, int nslots, int n_sub,
+                              const MdOverride& ov, uint64_t wait, hipStream_t s);
 void launch_md_gate(const Dev& d, int nseg, hipStream_t s);
 // Noise of one sub-cycle into d.xi, for the step counter + step_offset.
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s);
@@ -291,11 +289,12 @@ void launch_zero_v(const Dev& d, int nslots, hipStream_t s);
 __device__ inline void md_begin(const Dev& d, int nrep, int t, int nt) {
   if (t == 0) {
     d.ctrl->cycles += 1u;
-    d.ctrl->placed[0] = 0u;
-    d.ctrl->placed[1] = 0u;
+    d.ctrl->placed = 0u;
   }
   for (int r = t; r < nrep; r += nt) {
-    if (d.redo) d.redo[r] = -1;
+    d.redo[r] = -1;
+    d.rsync[2 * r] = 0u;
+    d.rsync[2 * r + 1] = 0u;
     uint32_t* w = d.rb + 4 * r;
     w[0] = w[3];
     w[1] = 0u;
@@ -338,10 +337,9 @@ __device__ inline void ledger_sp_share(const Dev& d, int slot) {
   for (int a = 0; a < 3; ++a) d.lsp[3 * (size_t)slot + a] = s[a];
 }
 
-// The end of a coupled step on the sweep stream, once J is final: the
-// spread-on-solid ledger (shares per slot, then each replica's beads added
-// in a fixed order into its ledger) fused with the next step's neighbour
-// lists (cell table cleared, beads binned, lists built): three launches.
-void launch_step_tail(const Dev& d, int nslots, int nrep, bool ledger, hipStream_t s);
+// What follows the spreading, from r(n+1) and J: the cell table (emptied by
+// launch_spread_lb), the spread-on-solid ledger and the translocation record,
+// then the next step's neighbour lists and its noise (into `noise`, NULL: none).
+void launch_step_tail(const Dev& d, int nslots, int nrep, double* noise, int n_sub, hipStream_t s);
 
 }  // namespace lbmd

@@ -29,10 +29,24 @@ __global__ void k_md_invalidate(uint32_t* rb, int nrep) {
   for (int r = threadIdx.x; r < nrep; r += blockDim.x) rb[4 * r + 3] = 1u;
 }
 
+// A copy of *p through the constant address space: scalar loads for a
+// workgroup-uniform p, also where the compiler cannot rule out that a store
+// of the kernel aliases it.  For tables that no kernel writes.
+template <typename T>
+__device__ inline T load_uniform(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  typedef const __attribute__((address_space(4))) uint32_t Word;
+  Word* q = (Word*)(uintptr_t)p;
+  T out;
+  uint32_t* o = reinterpret_cast<uint32_t*>(&out);
+#pragma unroll
+  for (size_t k = 0; k < sizeof(T) / 4; ++k) o[k] = q[k];
+  return out;
+}
+
 // Coefficients of the sub-cycle for one replica: its own, or the
 // relaxation's (no coupling, no field, no noise).
-__device__ inline MdParams md_params(const Rep& R, const MdOverride& ov) {
-  MdParams P = R.mp;
+__device__ inline MdParams md_override(MdParams P, const MdOverride& ov) {
   if (ov.on) {
     P.gamma = ov.gamma; P.e = ov.e; P.omE = ov.omE;
     P.cf = ov.gamma == 0.0 ? (2.0 * P.hh) / P.m : ov.omE / (P.m * ov.gamma);
@@ -40,6 +54,7 @@ __device__ inline MdParams md_params(const Rep& R, const MdOverride& ov) {
   }
   return P;
 }
+__device__ inline MdParams md_params(const Rep& R, const MdOverride& ov) { return md_override(R.mp, ov); }
 
 // Neighbour-search cells: side >= r_c + skin + CELL_MARGIN per replica; each
 // cell hashes to one bucket of a power-of-two table of fixed-capacity buckets
@@ -90,8 +105,7 @@ __global__ void k_md_start(Dev d, int nslots, MdOverride ov, int mts) {
 // the transcendental functions run in one wide launch instead of on the
 // critical path of every sub-step.  The step counter word is the control
 // block's step plus step_offset (1: the sub-cycle of the next step).
-__global__ void k_md_noise(Dev d, int nslots, int n_sub, int step_offset) {
-  long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ inline void md_noise(const Dev& d, long k, int nslots, int n_sub, int step_offset) {
   if (k >= (long)n_sub * nslots) return;
   int sidx = (int)(k / nslots), slot = (int)(k - (long)sidx * nslots);
   const Rep& R = d.reps[d.slot_rep[slot]];
@@ -100,6 +114,9 @@ __global__ void k_md_noise(Dev d, int nslots, int n_sub, int step_offset) {
   double x[3];
   gauss3(R.mp.seed, R.mp.replica, (uint32_t)(d.ctrl->step + (uint64_t)step_offset), (uint32_t)sidx, (uint32_t)p, x);
   d.xi[3 * k] = x[0]; d.xi[3 * k + 1] = x[1]; d.xi[3 * k + 2] = x[2];
+}
+__global__ void k_md_noise(Dev d, int nslots, int n_sub, int step_offset) {
+  md_noise(d, (long)blockIdx.x * blockDim.x + threadIdx.x, nslots, n_sub, step_offset);
 }
 
 // The bending angle at (ra, rb, rc) and what its forces need: the bond
@@ -749,7 +766,16 @@ constexpr int LB_LANES = 32;                 // lanes per bead in the list build
 constexpr int LB_BEADS = 2;                  // beads per 64-lane workgroup
 constexpr int LB_CAND = 96;                  // candidates a bead may collect
 
-__global__ __launch_bounds__(LB_LANES * LB_BEADS) void k_list_build(Dev d, int nslots) {
+// The workgroups after the first nbuild draw the next step's noise (noise: its
+// buffer, NULL for none).
+__global__ __launch_bounds__(LB_LANES * LB_BEADS) void k_list_build(Dev d, int nslots, int nbuild, double* noise,
+                                                                    int n_sub) {
+  if ((int)blockIdx.x >= nbuild) {
+    Dev dn = d;
+    dn.xi = noise;
+    md_noise(dn, ((long)blockIdx.x - nbuild) * (LB_LANES * LB_BEADS) + threadIdx.x, nslots, n_sub, 1);
+    return;
+  }
   __shared__ int cand[LB_BEADS][LB_CAND];
   __shared__ int ncand[LB_BEADS];
   __shared__ uint32_t bkt[LB_BEADS][LB_LANES];
@@ -823,55 +849,51 @@ __global__ __launch_bounds__(LB_LANES * LB_BEADS) void k_list_build(Dev d, int n
   d.ref[3 * slot] = rp[0]; d.ref[3 * slot + 1] = rp[1]; d.ref[3 * slot + 2] = rp[2];
 }
 
-// k_cell_clear with the spread-on-solid shares: k < nbuckets clears a bucket,
-// k < nrep validates a replica's lists, k < nslots writes a slot's share.
-__global__ void k_tail_clear(Dev d, int nbuckets, int nrep, int nslots, int ledger) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < nbuckets) d.ccount[k] = 0;
-  if (k < nrep) d.rb[4 * k + 3] = 0u;
-  if (ledger && k < nslots) ledger_sp_share(d, k);
-}
-
 // k_cell_insert in the first `nins` workgroups; after them one workgroup per
-// replica adds its beads' shares (strided per thread, then a fixed tree)
-// into its ledger.
-constexpr int TAIL_WG = 1024;
+// replica adds its beads' spread-on-solid shares (TAIL_SUM strided sums, then a
+// fixed tree) into its ledger, and records the translocation step when every
+// bead is past the wall plane for the first time.  Small workgroups, which find
+// room beside the sweep.
+constexpr int TAIL_WG = 256, TAIL_SUM = 1024;
 __global__ __launch_bounds__(TAIL_WG) void k_tail_insert(Dev d, int nslots, int nins) {
   if ((int)blockIdx.x < nins) {                  // uniform in the workgroup
     const int slot = blockIdx.x * blockDim.x + threadIdx.x;
     if (slot < nslots) cell_insert_slot(d, slot);
     return;
   }
-  __shared__ double sh[TAIL_WG];
+  __shared__ double sh[TAIL_SUM];
   const int rep = blockIdx.x - nins;
   const Rep& R = d.reps[rep];
-  double s[3] = {0.0, 0.0, 0.0};
-  if (R.g.wall_axis >= 0)
-    for (int p = threadIdx.x; p < R.mp.nb; p += TAIL_WG)
-      for (int a = 0; a < 3; ++a) s[a] += d.lsp[3 * (size_t)(R.slot_off + p) + a];
+  if (R.g.wall_axis < 0 || R.mp.nb == 0) return; // uniform; nothing to add
+  const int t = threadIdx.x;
+  bool past = true;
+  for (int p = t; p < R.mp.nb; p += TAIL_WG)
+    past = past && d.r[3 * (size_t)(R.slot_off + p) + R.g.wall_axis] > (double)R.g.wall_pos;
+  if (__syncthreads_and(past ? 1 : 0) && t == 0 && d.tX[rep] < 0) d.tX[rep] = (int64_t)d.ctrl->step + 1;
   for (int a = 0; a < 3; ++a) {
+    for (int k = t; k < TAIL_SUM; k += TAIL_WG) {
+      double s = 0.0;
+      for (int p = k; p < R.mp.nb; p += TAIL_SUM) s += d.lsp[3 * (size_t)(R.slot_off + p) + a];
+      sh[k] = s;
+    }
     __syncthreads();
-    sh[threadIdx.x] = s[a];
-    __syncthreads();
-    for (int w = TAIL_WG / 2; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+    for (int w = TAIL_SUM / 2; w > 0; w >>= 1) {
+      for (int k = t; k < w; k += TAIL_WG) sh[k] += sh[k + w];
       __syncthreads();
     }
-    if (threadIdx.x == 0) d.ledger[NLEDGER * rep + 3 + a] += sh[0];
+    if (t == 0) d.ledger[NLEDGER * rep + 3 + a] += sh[0];
+    __syncthreads();
   }
 }
 
-void launch_step_tail(const Dev& d, int nslots, int nrep, bool ledger, hipStream_t s) {
+void launch_step_tail(const Dev& d, int nslots, int nrep, double* noise, int n_sub, hipStream_t s) {
   if (nslots <= 0) return;
-  const int nb = (int)d.cmask + 1;
-  int n = nb > nrep ? nb : nrep;
-  if (nslots > n) n = nslots;
-  hipLaunchKernelGGL(k_tail_clear, dim3((n + 255) / 256), dim3(256), 0, s, d, nb, nrep, nslots, ledger ? 1 : 0);
   const int nins = (nslots + TAIL_WG - 1) / TAIL_WG;
-  hipLaunchKernelGGL(k_tail_insert, dim3((unsigned)(nins + (ledger ? nrep : 0))), dim3(TAIL_WG), 0, s, d, nslots,
-                     nins);
-  hipLaunchKernelGGL(k_list_build, dim3((nslots + LB_BEADS - 1) / LB_BEADS), dim3(LB_LANES * LB_BEADS), 0, s, d,
-                     nslots);
+  hipLaunchKernelGGL(k_tail_insert, dim3((unsigned)(nins + nrep)), dim3(TAIL_WG), 0, s, d, nslots, nins);
+  const unsigned nbuild = (unsigned)((nslots + LB_BEADS - 1) / LB_BEADS);
+  const unsigned nn = noise ? (unsigned)(((long)n_sub * nslots + LB_LANES * LB_BEADS - 1) / (LB_LANES * LB_BEADS)) : 0u;
+  hipLaunchKernelGGL(k_list_build, dim3(nbuild + nn), dim3(LB_LANES * LB_BEADS), 0, s, d, nslots, (int)nbuild, noise,
+                     n_sub);
 }
 
 void launch_nbr_build(const Dev& d, int nslots, int nrep, hipStream_t s) {
@@ -880,8 +902,9 @@ void launch_nbr_build(const Dev& d, int nslots, int nrep, hipStream_t s) {
   const int nclr = nb > nrep ? nb : nrep;
   hipLaunchKernelGGL(k_cell_clear, dim3((nclr + 255) / 256), dim3(256), 0, s, d.ccount, nb, d.rb, nrep);
   hipLaunchKernelGGL(k_cell_insert, dim3((nslots + 255) / 256), dim3(256), 0, s, d, nslots);
-  hipLaunchKernelGGL(k_list_build, dim3((nslots + LB_BEADS - 1) / LB_BEADS), dim3(LB_LANES * LB_BEADS), 0, s, d,
-                     nslots);
+  const unsigned nbuild = (unsigned)((nslots + LB_BEADS - 1) / LB_BEADS);
+  hipLaunchKernelGGL(k_list_build, dim3(nbuild), dim3(LB_LANES * LB_BEADS), 0, s, d, nslots, (int)nbuild,
+                     (double*)nullptr, 0);
 }
 
 void launch_md_invalidate(const Dev& d, int nrep, hipStream_t s) {
@@ -1706,56 +1729,28 @@ __global__ __launch_bounds__(FU_WG) void k_md_fused(Dev d, FusedBufs fb, int nsl
   }
 }
 
-// After the fused blocks or the resident cycle, one workgroup per replica.
-// A replica whose block failed at sub-step sp (the resident cycle: marker 1,
-// from sub-step 0) is
-// redone from that block's start state to the end of the cycle, sub-step by
-// sub-step, with barriers: the angles of every centre, then every bead's
-// force, kick and drifts; the positions alternate between r_mid0 and r_mid1.
-// A bead's pair partners come from the neighbour lists; when a bead is
-// farther than half the skin from where they were built, every list is built
-// anew at the sub-step's positions -- from the cell table while every bead
-// lies within CELL_MARGIN of where it was binned, else from all beads of the
-// chain.  With the fused blocks, a replica whose last block wrote the shadow
-// set gets v and J copied back; the resident cycle leaves the cycle's start
-// (r, v, J) in the shadow set.
+// After the fused blocks, one workgroup per replica (and one workgroup of a
+// replica that the resident cycle could not take).  A replica whose block
+// failed at sub-step sp is redone from that block's start state to the end of
+// the cycle, sub-step by sub-step, with barriers: the angles of every centre,
+// then every bead's force, kick and drifts; the positions alternate between
+// r_mid0 and r_mid1.  A bead's pair partners come from the neighbour lists;
+// when a bead is farther than half the skin from where they were built, every
+// list is built anew at the sub-step's positions -- from the cell table while
+// every bead lies within CELL_MARGIN of where it was binned, else from all
+// beads of the chain.  A replica whose last block wrote the shadow set gets v
+// and J copied back.
 constexpr int RD_WG = 1024;
 constexpr int RD_NC = 32;          // pair partners within r_c of one bead
 
-__global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* ang, int nslots, int n_sub, int K,
-                                                   MdOverride ov, int resident) {
-  __shared__ int any_far, any_off;
-  const int rep = blockIdx.x;
-  int sp = fb.redo[rep];                          // constant during this launch
-  if (resident && sp < 1) return;                 // the resident cycle succeeded
-  if (resident) sp = 0;
-  const Rep& R = d.reps[rep];
-  const MdParams P = md_params(R, ov);
+// Sub-steps sp .. n_sub - 1 of replica rep by one workgroup of WG threads, from
+// r_mid of sub-step sp in r_mid0, and v, J.
+template <int WG>
+__device__ inline void md_redo(const Dev& d, const Rep& R, const MdParams& P, int rep, double* ang, int nslots,
+                               int sp, int n_sub, int& any_far, int& any_off) {
   const Geom g = R.g;
   const int so = R.slot_off, nb = P.nb;
   const int t = threadIdx.x;
-  const int M = n_sub / K;
-  if (sp < 0) {
-    if (M & 1)
-      for (int q = t; q < nb; q += RD_WG)
-        for (int a = 0; a < 3; ++a) {
-          d.v[3 * (so + q) + a] = fb.vS[3 * (so + q) + a];
-          d.J[3 * (so + q) + a] = fb.JS[3 * (so + q) + a];
-        }
-    return;
-  }
-  // the failed block's start state into r_mid0, v, J
-  if (resident || ((sp / K) & 1))
-    for (int q = t; q < nb; q += RD_WG)
-      for (int a = 0; a < 3; ++a) {
-        const int i = 3 * (so + q) + a;
-        d.rmid0[i] = resident ? fb.rmS[i] + P.hh * fb.vS[i] : fb.rmS[i];
-        d.v[i] = fb.vS[i];
-        d.J[i] = fb.JS[i];
-      }
-  if (t == 0) {
-    if (!resident) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)(n_sub - sp));
-  }
   bool fin = true, over = false, valid = d.rb[4 * rep] == 0u;   // the lists, at the cycle's start
   for (int s = sp; s < n_sub; ++s) {
     const double* cur = ((s - sp) & 1) ? d.rmid1 : d.rmid0;
@@ -1763,7 +1758,7 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
     // every bead near the position the lists were built at, the position
     // the table binned it at?
     bool near = true, held = valid;
-    for (int q = t; q < nb; q += RD_WG) {
+    for (int q = t; q < nb; q += WG) {
       double b2 = 0.0, f2 = 0.0;
       for (int a = 0; a < 3; ++a) {
         const double x = cur[3 * (so + q) + a];
@@ -1778,14 +1773,14 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
     __syncthreads();                              // also orders the previous sub-step's writes
     if (!near) any_far = 1;
     if (!held) any_off = 1;
-    for (int q = t; q < nb; q += RD_WG)
+    for (int q = t; q < nb; q += WG)
       if (q >= 1 && q <= nb - 2)
         fu_angle(P, &cur[3 * (so + q - 1)], &cur[3 * (so + q)], &cur[3 * (so + q + 1)], &ang[9 * (size_t)(so + q)]);
     __syncthreads();
     const bool lists = any_off == 0, table = any_far == 0;
     if (!lists) {
       // each thread builds the lists of its own beads, which it alone reads
-      for (int q = t; q < nb; q += RD_WG) {
+      for (int q = t; q < nb; q += WG) {
         const int sl = so + q;
         const double rp[3] = {cur[3 * sl], cur[3 * sl + 1], cur[3 * sl + 2]};
         int L[MAXNBR];
@@ -1814,7 +1809,7 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
       }
       valid = true;
     }
-    for (int q = t; q < nb; q += RD_WG) {
+    for (int q = t; q < nb; q += WG) {
       const int sl = so + q;
       const double rp[3] = {cur[3 * sl], cur[3 * sl + 1], cur[3 * sl + 2]};
       int part[RD_NC];
@@ -1863,6 +1858,37 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
   if (over) atomicOr(&d.ctrl->err, E_NBRLIST);
 }
 
+__global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* ang, int nslots, int n_sub, int K) {
+  __shared__ int any_far, any_off;
+  const int rep = blockIdx.x;
+  const Rep& R = d.reps[rep];
+  const MdParams P = R.mp;
+  const int so = R.slot_off, nb = P.nb;
+  const int t = threadIdx.x;
+  const int sp = fb.redo[rep];                    // constant during this launch
+  const int M = n_sub / K;
+  if (sp < 0) {
+    if (M & 1)
+      for (int q = t; q < nb; q += RD_WG)
+        for (int a = 0; a < 3; ++a) {
+          d.v[3 * (so + q) + a] = fb.vS[3 * (so + q) + a];
+          d.J[3 * (so + q) + a] = fb.JS[3 * (so + q) + a];
+        }
+    return;
+  }
+  // the failed block's start state into r_mid0, v, J
+  if ((sp / K) & 1)
+    for (int q = t; q < nb; q += RD_WG)
+      for (int a = 0; a < 3; ++a) {
+        const int i = 3 * (so + q) + a;
+        d.rmid0[i] = fb.rmS[i];
+        d.v[i] = fb.vS[i];
+        d.J[i] = fb.JS[i];
+      }
+  if (t == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)(n_sub - sp));
+  md_redo<RD_WG>(d, R, P, rep, ang, nslots, sp, n_sub, any_far, any_off);
+}
+
 // ---------------------------------------------------------------------------
 // The resident sub-cycle: one launch advances every chain through the whole
 // uniform sub-cycle.
@@ -1909,22 +1935,24 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
 // The lists hold every pair within r_c while no bead is farther than half
 // the skin from where they were built.  A workgroup whose bead leaves that
 // range, whose lists are not valid at the start, whose remote beads exceed
-// RES_REM, or whose wait exceeds its limit sets the replica's redo marker
-// (-1 -> 0); the others see it while they poll, and all return.  A second
-// launch (BLOCKS; it returns at once where the first succeeded) takes such a
-// replica from the cycle's start state, which every workgroup saved first
-// (rmS, vS, JS), in blocks of RES_BLOCK sub-steps with new lists for each, so
-// a bead may travel half the skin per block instead of per cycle.  What fails
-// there too (marker 1) is advanced by one workgroup (k_md_redo).  Every wait
-// ends: the polled value arrives, the marker is set, or the clock runs out.
+// RES_REM, or whose wait exceeds its limit sets the replica's failure bit;
+// the others see it while they poll, and leave the pass.  The segments store
+// their results only when all of them have finished.  Else a second pass takes
+// the replica from the cycle's start in blocks of RES_BLOCK sub-steps, with new
+// lists where one needs them, so a bead may travel half the skin per block
+// instead of per cycle.  When that fails too, the workgroup that set the bit advances the
+// replica alone (md_redo).  Every wait ends: the polled value arrives, the bit
+// is set, or the clock runs out.  All of this is one launch: a second one that
+// finds nothing to do would wait for room beside the sweep (0.49 ms of a
+// 1.1 ms step).
 //
-// New lists need the beads' positions at the block's start: each segment
-// publishes them (xblk, tagged like the exchange) and a word that says
-// whether its beads are within CELL_MARGIN of where the cell table binned
-// them, and reads every segment's word -- so no segment enters a block before
-// all have left the one before, and two slots suffice here as well.  The
-// candidates come from the cell table if every word allows it, else from all
-// beads of the chain.
+// At a block's start each segment publishes its positions (tagged like the
+// exchange) and a word that says whether its beads are within CELL_MARGIN of
+// where the cell table binned them and whether one may leave the lists' range
+// within the block, and reads every segment's word -- so no segment enters a
+// block before all have left the one before, and two slots suffice here as
+// well.  Where some word asks for new lists, their candidates come from the
+// cell table if every word allows it, else from all beads of the chain.
 // ---------------------------------------------------------------------------
 constexpr int RES_WG = 512;
 constexpr int RES_HALO = 4;                    // local indices RES_OWN + 0..3: chain beads a-2, a-1, b, b+1
@@ -1932,8 +1960,9 @@ constexpr int RES_REM = 144;                   // other remote beads
 constexpr int RES_IDX = RES_OWN + RES_HALO + RES_REM;
 constexpr int RES_PL = 4;                      // lanes per bead of the pair waves
 constexpr int RES_PH = 4;                      // pair forces kept per lane
-constexpr int RES_WH = 512;                    // wall-site forces kept (13 per bead at most for r_c <= 2)
+constexpr int RES_WH = 416;                    // wall-site forces kept (13 per bead at most for r_c <= 2)
 constexpr int RES_HASH = 512;
+constexpr uint32_t RES_FAIL = 0x80000000u;
 constexpr int RES_TILE = 256;                  // beads scanned together by a full list build
 static_assert(RES_IDX <= 255, "local indices fit in a byte");
 static_assert(3 * (RES_OWN + 2) <= 128 && RES_OWN + 2 <= 64 && RES_PL * RES_OWN == 128, "one pass over the lanes");
@@ -1943,28 +1972,34 @@ struct ResShared {
   double dd[2][RES_OWN + 2][3];                // row k: d1, d2 of the angle centred at a - 1 + k (see res_angle_d)
   double kp[RES_OWN + 2];                      // its kappa phi
   double bnd[RES_OWN + 1][3];                  // row k: force on a + k of its bond to a + k - 1
+  double ref[RES_OWN][3];                      // where the lists were built
   double xi[3 * RES_OWN];                      // the sub-step's noise
   union {
     struct {
       double pairF[RES_PL][RES_PH][RES_OWN][3];   // pair forces of each lane's part of the list, in order
-      double wallF[RES_WH][3];                 // wall-site forces, bead by bead in site order
+      double wallF[RES_WH + 3][3];             // wall-site forces, bead by bead in site order
     };
     struct {                                   // set-up
       int key[RES_HASH], val[RES_HASH];        // local index of a remote chain bead
       int list[RES_OWN][MAXNBR];               // new lists (partner slots)
       uint32_t bk[RES_OWN][27];                // the 27 buckets around a bead
       double tile[RES_TILE][3];                // positions of RES_TILE chain beads
+      double vel[RES_OWN][3];
     } h;
   };
   uint8_t lst[RES_OWN][MAXNBR];                // the beads' lists as local indices, ascending chain order
   int lcnt[RES_OWN];
   uint8_t pcnt[RES_OWN][RES_PL];               // pair forces found (one beyond RES_PH: the sum evaluates them again)
   int wall[RES_OWN];                           // first wall-site force << 8 | their number
+  double wrec[RES_OWN][3];                     // beads near the plane: distance to it, wrapped transverse coordinates
+  int wbead[RES_OWN];
   int fld[RES_OWN];                            // in the pore channel
   int rslot[RES_IDX - RES_OWN];                // bead slot of remote local index RES_OWN + k, -1: none
   int nrem;
   int dead[2];                                 // by parity of the sub-step
   int lost;                                    // a set-up failed
+  int owner;                                   // this workgroup set the failure bit
+  int done;
   int ncand[RES_OWN];
 };
 static_assert(4 * sizeof(ResShared) <= (size_t)LDS_PER_CU, "four resident workgroups per CU");
@@ -1978,6 +2013,8 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
+// Orders one wave's LDS accesses (which the LDS executes in order) for the compiler.
+__device__ inline void wave_lds() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 __device__ inline unsigned long long res_load(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -2023,11 +2060,10 @@ __device__ inline void res_angle_d(const ResAngle& A, int a, double& d1, double&
 }
 
 // A tagged pair's value, waiting for it until the tag matches; false when the
-// marker reached STOP or the wait its limit (RES_PLACE while some workgroup
-// of the launch has not started: another context's cycle may hold its place
-// and wait for one that this cycle holds).
-template <int STOP>
-__device__ inline bool res_poll(const unsigned long long* o, uint64_t tag, const int* marker, const Ctrl* ctrl,
+// replica's word has the failure bit or the wait reached its limit (RES_PLACE
+// while some workgroup of the launch has not started: another context's cycle
+// may hold its place and wait for one that this cycle holds).
+__device__ inline bool res_poll(const unsigned long long* o, uint64_t tag, const uint32_t* word, const Ctrl* ctrl,
                                 uint64_t wait, unsigned long long& val) {
   unsigned long long w1;
   val = res_load(o);
@@ -2040,46 +2076,50 @@ __device__ inline bool res_poll(const unsigned long long* o, uint64_t tag, const
     if ((val ^ w1) == tag) return true;
     if ((spin & 15) == 15 || wait == 0) {
       const uint64_t dt = wall_clock64() - t0;
-      if (__hip_atomic_load(marker, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= STOP || dt >= wait ||
+      if ((__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & RES_FAIL) || dt >= wait ||
           (dt >= RES_PLACE &&
-           __hip_atomic_load(&ctrl->placed[STOP], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x))
+           __hip_atomic_load(&ctrl->placed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x))
         return false;
     }
   }
 }
 
+// One pass of the cycle (see above); 0: done, 1: failed, 2: failed, by this
+// workgroup's decision.
 template <bool BLOCKS>
-__global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, const FusedSeg* __restrict__ segs,
-                                                           int nslots, int n_sub, MdOverride ov, uint64_t wait) {
-  __shared__ ResShared sh;
-  const FusedSeg seg = segs[blockIdx.x];
+__device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const Rep& R, const MdParams& P, ResShared& sh,
+                                        int nslots, int n_sub, uint64_t wait) {
   const int rep = seg.rep;
-  if (BLOCKS && fb.redo[rep] < 0) {              // the whole cycle succeeded (0 or 1 from here on)
-    if (threadIdx.x == 0)
-      __hip_atomic_fetch_add(&d.ctrl->placed[BLOCKS], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return;
-  }
-  const Rep& R = d.reps[rep];
-  const MdParams P = md_params(R, ov);
-  const Geom g = R.g;
-  const int so = R.slot_off, nb = P.nb;
+  const Geom g = load_uniform(&R.g);
+  const int so = load_uniform(&R.slot_off), nb = P.nb;
   const int p0 = seg.a, n = seg.b - seg.a;
   const int t = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(t) >> 6, lane = t & 63;
-  int* marker = &fb.redo[rep];
-  constexpr int STOP = BLOCKS ? 1 : 0;           // the marker of a failure here
+  uint32_t* word = &d.rsync[2 * rep + BLOCKS];
+  const uint32_t ng = (uint32_t)((nb + RES_OWN - 1) / RES_OWN);   // the replica's segments
+  // Failure ends the pass for the whole replica.  It is decided on one word:
+  // the number of segments that have finished, and a failure bit that can
+  // only be set while that number is below ng.
+  auto give_up = [&]() {
+    uint32_t w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (w < ng) {
+      const uint32_t was = atomicCAS(word, w, w | RES_FAIL);
+      if (was == w) { sh.owner = 1; break; }
+      w = was;
+    }
+  };
   auto fail = [&](int s) {
-    atomicCAS(marker, STOP - 1, STOP);
+    give_up();
     sh.dead[s & 1] = 1;
   };
   auto lose = [&]() {
-    atomicCAS(marker, STOP - 1, STOP);
+    give_up();
     sh.lost = 1;
   };
   // the tag of sub-step s of this cycle is (cycle (n_sub + 1) + s) TAG, and
   // those of a block's start differ by MARK
   constexpr uint64_t TAG = 0x9E3779B97F4A7C15ull, MARK = 0x5851F42D4C957F2Dull;
-  const uint64_t tag0 = d.ctrl->cycles * (uint64_t)(n_sub + 1) * TAG;
+  const uint64_t tag0 = load_uniform(&d.ctrl->cycles) * (uint64_t)(n_sub + 1) * TAG;
 
   // ---- the lanes of the sum: component c of bead i
   const int i = 16 * wave + lane / 3, c = lane % 3;
@@ -2088,26 +2128,23 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
   double x = 0.0, v = 0.0, J = 0.0, u = 0.0;
   if (mine) {
     x = d.rmid0[3 * slot + c];
-    v = BLOCKS ? fb.vS[3 * slot + c] : d.v[3 * slot + c];
-    J = BLOCKS ? fb.JS[3 * slot + c] : d.J[3 * slot + c];
+    v = d.v[3 * slot + c];
+    J = d.J[3 * slot + c];
     u = P.couple ? d.up[3 * slot + c] : 0.0;
-    if (!BLOCKS) {                               // the cycle's start state
-      fb.rmS[3 * slot + c] = d.r[3 * slot + c];
-      fb.vS[3 * slot + c] = v;
-      fb.JS[3 * slot + c] = J;
-    }
     sh.pos[0][i][c] = x;
   }
   if (t < 2) sh.dead[t] = 0;
   if (t == 0) {
     sh.lost = 0;
-    __hip_atomic_fetch_add(&d.ctrl->placed[BLOCKS], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sh.owner = 0;
     if (!BLOCKS) {
-      if (*marker >= 0 || d.rb[4 * rep] != 0u) lose();   // failed already, or lists not valid at the start
+      __hip_atomic_fetch_add(&d.ctrl->placed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (blockIdx.x == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)n_sub);
     }
+    if (!BLOCKS && d.rb[4 * rep] != 0u) lose();  // the lists are not valid at the start
+    if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & RES_FAIL) sh.lost = 1;
   }
-  bool fin = true;
+  bool fin = true, dead = false;
   const int len = BLOCKS ? RES_BLOCK : n_sub;
   for (int s0 = 0, blk = 0;; s0 += len, ++blk) {
   const int s1 = BLOCKS ? min(s0 + len, n_sub) : n_sub;
@@ -2116,11 +2153,10 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
   __syncthreads();                               // the positions at s0 are there, the forces' memory is free
   constexpr int LL = RES_WG / RES_OWN, LE = MAXNBR / LL;   // 16 lanes per bead
   const int lb = t / LL, ll = t % LL;
-  const bool fresh = BLOCKS && (s0 > 0 || d.rb[4 * rep] != 0u);   // build new lists
+  bool fresh = BLOCKS && s0 == 0 && d.rb[4 * rep] != 0u;   // build new lists
   const unsigned long long* xb = nullptr;
   const uint64_t tagb = tag0 + (uint64_t)s0 * TAG + MARK;
-  int cnt = lb < n && !fresh ? d.ncnt[so + p0 + lb] : 0;
-  if (BLOCKS && fresh) {
+  if (BLOCKS && (s0 > 0 || fresh)) {
     unsigned long long* xw = d.xring + (size_t)(2 + (blk & 1)) * 6 * nslots;
     xb = xw;
     unsigned long long* words = d.xflag + (size_t)2 * (blk & 1) * gridDim.x;
@@ -2129,28 +2165,44 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
       res_store(xw + ((size_t)slot * 3 + c) * 2, bits);
       res_store(xw + ((size_t)slot * 3 + c) * 2 + 1, bits ^ tagb);
     }
-    bool near = true;
+    // bit 0: every bead near where the table binned it; bit 1: some bead may
+    // leave the lists' range within the block (at twice its present speed)
+    bool near = true, need = s0 == 0;
+    if (mine) sh.h.vel[i][c] = v;
+    __syncthreads();
     if (t < n) {
-      double b2 = 0.0;
-      for (int a = 0; a < 3; ++a) { const double db = sh.pos[sp][t][a] - d.rbin[3 * (so + p0 + t) + a]; b2 += db * db; }
+      double b2 = 0.0, f2 = 0.0, v2 = 0.0;
+      for (int a = 0; a < 3; ++a) {
+        const double y = sh.pos[sp][t][a], w = sh.h.vel[t][a];
+        const double db = y - d.rbin[3 * (so + p0 + t) + a], df = y - sh.ref[t][a];
+        b2 += db * db;
+        f2 += df * df;
+        v2 += w * w;
+      }
       near = b2 <= CELL_MARGIN * CELL_MARGIN;
+      need = need || !(sqrt(f2) + 4.0 * P.hh * RES_BLOCK * sqrt(v2) <= 0.95 * sqrt(P.halfskin2));
       sh.ncand[t] = 0;
     }
-    const int all_near = __syncthreads_and(near ? 1 : 0);
+    const int all_near = __syncthreads_and(near ? 1 : 0), any_need = __syncthreads_or(need ? 1 : 0);
     if (t == 0) {
-      res_store(words + 2 * blockIdx.x, (unsigned long long)all_near);
-      res_store(words + 2 * blockIdx.x + 1, (unsigned long long)all_near ^ tagb);
+      const unsigned long long w = (all_near ? 1ull : 0ull) | (any_need ? 2ull : 0ull);
+      res_store(words + 2 * blockIdx.x, w);
+      res_store(words + 2 * blockIdx.x + 1, w ^ tagb);
     }
     // every segment's word
-    const int g0 = (int)blockIdx.x - p0 / RES_OWN, ng = (nb + RES_OWN - 1) / RES_OWN;
+    const int g0 = (int)blockIdx.x - p0 / RES_OWN;
     bool table = true;
-    for (int k = t; k < ng; k += RES_WG) {
+    need = false;
+    for (int k = t; k < (int)ng; k += RES_WG) {
       unsigned long long w = 0;
-      if (!res_poll<STOP>(words + 2 * (g0 + k), tagb, marker, d.ctrl, wait, w)) { lose(); break; }
-      table = table && w != 0;
+      if (!res_poll(words + 2 * (g0 + k), tagb, word, d.ctrl, wait, w)) { lose(); break; }
+      table = table && (w & 1ull);
+      need = need || (w & 2ull);
     }
     table = __syncthreads_and(table ? 1 : 0) != 0;
-    if (__syncthreads_or(sh.lost)) return;       // uniform, and read by all before the next write
+    fresh = __syncthreads_or(need ? 1 : 0) != 0;
+    if (__syncthreads_or(sh.lost)) { dead = true; break; }   // uniform, and read by all before the next write
+    if (fresh) {
     auto partner = [&](int q, const double* y) {
       if (q == so + p0 + lb) return;
       const double* rp = sh.pos[sp][lb];
@@ -2186,7 +2238,7 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
             double y[3];
             for (int a = 0; a < 3 && ok; ++a) {
               unsigned long long w = 0;
-              ok = res_poll<STOP>(xb + ((size_t)sl * 3 + a) * 2, tagb, marker, d.ctrl, wait, w);
+              ok = res_poll(xb + ((size_t)sl * 3 + a) * 2, tagb, word, d.ctrl, wait, w);
               y[a] = __longlong_as_double((long long)w);
             }
             if (ok) partner(sl, y);
@@ -2198,7 +2250,7 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
         const int m = min(RES_TILE, nb - base);
         for (int k = t; k < 3 * m && ok; k += RES_WG) {
           unsigned long long w = 0;
-          ok = res_poll<STOP>(xb + ((size_t)(so + base + k / 3) * 3 + k % 3) * 2, tagb, marker, d.ctrl, wait, w);
+          ok = res_poll(xb + ((size_t)(so + base + k / 3) * 3 + k % 3) * 2, tagb, word, d.ctrl, wait, w);
           sh.h.tile[k / 3][k % 3] = __longlong_as_double((long long)w);
         }
         if (!ok) lose();
@@ -2209,8 +2261,8 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
       }
     }
     __syncthreads();
-    if (lb < n) cnt = min(sh.ncand[lb], MAXNBR);
     if (lb < n && ll == 0) {                     // ascending order
+      const int cnt = min(sh.ncand[lb], MAXNBR);
       int* L = sh.h.list[lb];
       for (int k = 1; k < cnt; ++k) {
         const int q = L[k];
@@ -2224,7 +2276,12 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
       if (table) atomicAdd((unsigned long long*)&d.ctrl->cell_rebuilds, 1ull);
     }
     __syncthreads();
+    }
   }
+  if (!BLOCKS || s0 == 0 || fresh) {
+  const int cnt = lb >= n ? 0 : (BLOCKS && fresh ? min(sh.ncand[lb], MAXNBR) : d.ncnt[so + p0 + lb]);
+  if (t < n)
+    for (int a = 0; a < 3; ++a) sh.ref[t][a] = BLOCKS && fresh ? sh.pos[sp][t][a] : d.ref[3 * (so + p0 + t) + a];
   if (t == 0) sh.nrem = 0;
   for (int k = t; k < RES_IDX - RES_OWN; k += RES_WG) {
     // chain beads a - 2, a - 1, b, b + 1 first
@@ -2281,14 +2338,13 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
     }
     sh.lst[lb][LL * m + ll] = (uint8_t)(li >= 0 ? li : 0);   // -1 only when lost
   }
-  const int nrem = RES_HALO + min(sh.nrem, RES_REM);
-  for (int k = t; k < 3 * nrem; k += RES_WG) {
+  for (int k = t; k < 3 * (RES_HALO + min(sh.nrem, RES_REM)); k += RES_WG) {
     const int sl = sh.rslot[k / 3];
     double y = 0.0;
     if (sl >= 0) {
       if (fresh) {
         unsigned long long w = 0;
-        if (!res_poll<STOP>(xb + ((size_t)sl * 3 + k % 3) * 2, tagb, marker, d.ctrl, wait, w)) lose();
+        if (!res_poll(xb + ((size_t)sl * 3 + k % 3) * 2, tagb, word, d.ctrl, wait, w)) lose();
         y = __longlong_as_double((long long)w);
       } else {
         y = d.rmid0[3 * sl + k % 3];
@@ -2296,8 +2352,10 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
     }
     sh.pos[sp][RES_OWN + k / 3][k % 3] = y;
   }
+  }
   __syncthreads();
-  if (sh.lost) return;                           // uniform: the next writes follow many barriers
+  if (sh.lost) { dead = true; break; }           // uniform: the next writes follow many barriers
+  const int nrem = RES_HALO + min(sh.nrem, RES_REM);
 
   constexpr int HL = RES_OWN, HR = RES_OWN + 2;  // local indices of a - 2 and b
   // local index of chain bead a + j, -2 <= j <= n + 1
@@ -2374,7 +2432,13 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
             }
           }
         }
-        for (int m = wl >> 8; m < (wl >> 8) + (wl & 0xff); ++m) F += sh.wallF[m][c];
+        for (int m = wl >> 8, m1 = m + (wl & 0xff); m < m1; m += 4) {   // four loads in flight
+          const double w0 = sh.wallF[m][c], w1 = sh.wallF[m + 1][c], w2 = sh.wallF[m + 2][c], w3 = sh.wallF[m + 3][c];
+          F += w0;
+          if (m + 1 < m1) F += w1;
+          if (m + 2 < m1) F += w2;
+          if (m + 3 < m1) F += w3;
+        }
         if (fl && c == g.wall_axis) F += P.f_drive;
         if (tape) {
           double* tp = tape + (size_t)s * nb * 6;
@@ -2401,7 +2465,7 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
         }
       }
       lds_barrier();
-      if (sh.dead[cb]) return;
+      if (sh.dead[cb]) { dead = true; break; }
     }
   } else if (wave >= 6) {
     // ---- pair forces: part [k0, k1) of bead pb's list
@@ -2437,7 +2501,7 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
       }
       lds_barrier();
       lds_barrier();
-      if (sh.dead[cb]) return;
+      if (sh.dead[cb]) { dead = true; break; }
     }
   } else if (wave == 2) {
     // ---- kappa phi of the angle centred at a - 1 + lane
@@ -2451,7 +2515,7 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
       }
       lds_barrier();
       lds_barrier();
-      if (sh.dead[cb]) return;
+      if (sh.dead[cb]) { dead = true; break; }
     }
   } else if (wave == 5) {
     // ---- bonds: the force on a + lane of its bond to a + lane - 1 (the
@@ -2460,7 +2524,7 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
     double ref[3] = {0.0, 0.0, 0.0};
     if (lane < n) {
 #pragma unroll
-      for (int a = 0; a < 3; ++a) ref[a] = fresh ? sh.pos[sp][lane][a] : d.ref[3 * (so + p0 + lane) + a];
+      for (int a = 0; a < 3; ++a) ref[a] = sh.ref[lane][a];
     }
     for (int s = s0; s < s1; ++s) {
       const int cb = s & 1;
@@ -2469,7 +2533,7 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
         bond_add(P, sh.pos[cb][lane < n ? lane : HR], sh.pos[cb][lane ? lane - 1 : HL + 1], Fb);
         sh.bnd[lane][0] = Fb[0]; sh.bnd[lane][1] = Fb[1]; sh.bnd[lane][2] = Fb[2];
       }
-      if (lane < n && s > s0) {
+      if (lane < n && (s > s0 || (BLOCKS && s > 0))) {
         double d2 = 0.0;
 #pragma unroll
         for (int a = 0; a < 3; ++a) { const double dd = sh.pos[cb][lane][a] - ref[a]; d2 += dd * dd; }
@@ -2477,77 +2541,96 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
       }
       lds_barrier();
       lds_barrier();
-      if (sh.dead[cb]) return;
+      if (sh.dead[cb]) { dead = true; break; }
     }
   } else if (wave == 3) {
     // ---- the wall sites of wall_row and the field indicator
     const int wa = g.wall_axis, na = wa >= 0 ? ext(g, wa) : 0;
     const int nw = P.whi - P.wlo + 1, per = nw <= 4 ? 16 : 64;
-    // nw x nw sites per bead in site order (o1 outer, o0 inner): 16 lanes
-    // per bead and 4 beads at once for the 4 x 4 window, else 64 lanes
+    // Three passes, each with few idle lanes: a lane per bead finds the beads
+    // within r_c of the plane (the normal part of a distance alone: a sum of
+    // squares rounds to no less than one of them); a lane per site of those,
+    // in site order (o1 outer, o0 inner; 16 lanes per bead and 4 beads at once
+    // for the 4 x 4 window, else 64 lanes), finds the sites within r_c; a lane
+    // per site found evaluates its force.  With all of it in one pass a chain
+    // that lies along the plane made this the longest wave: 0.37 to 0.57
+    // against 0.29 ms per step (400 beads, 128^3), 0.48 to 0.62 against 0.38
+    // (32 x 100 beads).
     const int num = lane % per, o1 = P.wlo + num / nw, o0 = P.wlo + num % nw;
     const int n0 = wa == 0 ? g.ny : g.nx, n1 = wa == 2 ? g.ny : g.nz;   // transverse extents
+    const uint64_t below = (1ull << lane) - 1ull;
     for (int s = s0; s < s1; ++s) {
       const int cb = s & 1;
-      int fl = 0, off = 0;
-      double w[3] = {0.0, 0.0, 0.0};             // wrapped: normal, then the transverse axes in order
-      bool near = false;                         // the bead's window reaches the plane
+      int fl = 0;
+      bool near = false;
+      double dn = 0.0, wt0 = 0.0, wt1 = 0.0;
       if (wa >= 0 && lane < n) {
         const double* rp = sh.pos[cb][lane];
         const double wn = wrapc(rp[wa], na);
-        off = g.wall_pos - (int)floor(wn);
+        int off = g.wall_pos - (int)floor(wn);
         if (off < WLO) off += na;
         if (off > WHI) off -= na;
-        near = off >= P.wlo && off <= P.whi;
-        if (near) {
-          w[0] = wn;
-          w[1] = wrapc(rp[g.t0], n0);
-          w[2] = wrapc(rp[g.t1], n1);
-          fl = P.field_on && wn >= g.wall_pos - 1.5 && wn < g.wall_pos + 1.5 && w[1] >= g.lo0 - 0.5 &&
-               w[1] < g.hi0 + 0.5 && w[2] >= g.lo1 - 0.5 && w[2] < g.hi1 + 0.5 ? 1 : 0;
+        if (off >= P.wlo && off <= P.whi) {      // the bead's window reaches the plane
+          wt0 = wrapc(rp[g.t0], n0);
+          wt1 = wrapc(rp[g.t1], n1);
+          dn = wn - (double)((int)floor(wn) + off);
+          near = dn * dn < P.rc2;
+          fl = P.field_on && wn >= g.wall_pos - 1.5 && wn < g.wall_pos + 1.5 && wt0 >= g.lo0 - 0.5 &&
+               wt0 < g.hi0 + 0.5 && wt1 >= g.lo1 - 0.5 && wt1 < g.hi1 + 0.5 ? 1 : 0;
         }
       }
+      const uint64_t nm = __ballot(near);
+      const int nn = __builtin_popcountll(nm);
       if (lane < n) {
         sh.fld[lane] = fl;
         sh.wall[lane] = 0;
       }
-      uint64_t todo = __ballot(near);
+      if (near) {
+        const int r = __builtin_popcountll(nm & below);
+        sh.wrec[r][0] = dn; sh.wrec[r][1] = wt0; sh.wrec[r][2] = wt1;
+        sh.wbead[r] = lane;
+      }
       int total = 0;
-      while (todo) {
-        uint64_t m = todo;                       // the (lane / per)-th of the beads left
-        for (int q = lane / per; q > 0; --q) m &= m - 1;
-        const bool on = m != 0 && num < nw * nw;
-        const int b = m ? __builtin_ctzll(m) : 0;
-        const double wn = __shfl(w[0], b, 64), wt0 = __shfl(w[1], b, 64), wt1 = __shfl(w[2], b, 64);
-        const int of = __shfl(off, b, 64);
+      for (int r0 = 0; r0 < nn; r0 += 64 / per) {
+        wave_lds();
+        const int r = r0 + lane / per;
+        const bool on = r < nn && num < nw * nw;
         bool hit = false;
-        double Fs[3] = {0.0, 0.0, 0.0};
+        double d0 = 0.0, d1 = 0.0, d2 = 0.0;
         if (on) {
-          const int u1 = (int)floor(wt1) + o1, u0 = (int)floor(wt0) + o0;
+          const double x0 = sh.wrec[r][1], x1 = sh.wrec[r][2], xn = sh.wrec[r][0];
+          const int u1 = (int)floor(x1) + o1, u0 = (int)floor(x0) + o0;
           const int v1 = u1 < 0 ? u1 + n1 : (u1 >= n1 ? u1 - n1 : u1);
           const int v0 = u0 < 0 ? u0 + n0 : (u0 >= n0 ? u0 - n0 : u0);
           const bool pore = v1 >= g.lo1 && v1 <= g.hi1 && v0 >= g.lo0 && v0 <= g.hi0;
-          const double dn = wn - (double)((int)floor(wn) + of), dt0 = wt0 - (double)u0, dt1 = wt1 - (double)u1;
-          const double d0 = wa == 0 ? dn : dt0, d1 = wa == 1 ? dn : (wa == 0 ? dt0 : dt1), d2 = wa == 2 ? dn : dt1;
+          const double dt0 = x0 - (double)u0, dt1 = x1 - (double)u1;
+          d0 = wa == 0 ? xn : dt0;
+          d1 = wa == 1 ? xn : (wa == 0 ? dt0 : dt1);
+          d2 = wa == 2 ? xn : dt1;
           hit = !pore && d0 * d0 + d1 * d1 + d2 * d2 < P.rc2;
-          if (hit) lj_add(P, d0, d1, d2, Fs);
         }
-        const uint64_t hm = __ballot(hit), below = (1ull << lane) - 1ull;
+        const uint64_t hm = __ballot(hit);
+        const int o = total + __builtin_popcountll(hm & below);
         if (hit) {
-          const int o = total + __builtin_popcountll(hm & below);
-          if (o < RES_WH) { sh.wallF[o][0] = Fs[0]; sh.wallF[o][1] = Fs[1]; sh.wallF[o][2] = Fs[2]; }
+          if (o < RES_WH) { sh.wallF[o][0] = d0; sh.wallF[o][1] = d1; sh.wallF[o][2] = d2; }
           else fail(s);
         }
         if (on && num == 0) {
           const uint64_t own = per == 64 ? hm : (hm >> lane) & 0xffffull;
-          sh.wall[b] = ((total + __builtin_popcountll(hm & below)) << 8) | __builtin_popcountll(own);
+          sh.wall[sh.wbead[r]] = (o << 8) | __builtin_popcountll(own);
         }
         total += __builtin_popcountll(hm);
-        for (int q = 0; q < 64 / per && todo; ++q) todo &= todo - 1;
+      }
+      wave_lds();
+      for (int o = lane; o < min(total, RES_WH); o += 64) {
+        double* w = sh.wallF[o];
+        double Fs[3] = {0.0, 0.0, 0.0};
+        lj_add(P, w[0], w[1], w[2], Fs);
+        w[0] = Fs[0]; w[1] = Fs[1]; w[2] = Fs[2];
       }
       lds_barrier();
       lds_barrier();
-      if (sh.dead[cb]) return;
+      if (sh.dead[cb]) { dead = true; break; }
     }
   } else {
     // ---- the noise of the workgroup's beads, one sub-step ahead (up to two
@@ -2564,7 +2647,7 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
       if (lane < nx) sh.xi[lane] = xa;
       if (lane + 64 < nx) sh.xi[lane + 64] = xc;
       lds_barrier();
-      if (s < s1 - 1) {
+      if (s < n_sub - 1) {
         const double* q = xsrc + (size_t)(s + 1) * 3 * nslots;
         if (lane < nx) xa = q[lane];
         if (lane + 64 < nx) xc = q[lane + 64];
@@ -2573,7 +2656,7 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
           if (sl < 0) continue;
           const unsigned long long* o = d.xring + (cb ? 0 : half) + ((size_t)sl * 3 + m % 3) * 2;
           unsigned long long w = 0;
-          if (!res_poll<STOP>(o, tag, marker, d.ctrl, wait, w)) {
+          if (!res_poll(o, tag, word, d.ctrl, wait, w)) {
             fail(s);
             break;
           }
@@ -2581,16 +2664,69 @@ __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(Dev d, FusedBufs fb, 
         }
       }
       lds_barrier();
-      if (sh.dead[cb]) return;
+      if (sh.dead[cb]) { dead = true; break; }
     }
   }
-  if (!BLOCKS || s1 == n_sub) break;
+  if (dead || !BLOCKS || s1 == n_sub) break;
   }
-  if (!mine) return;
-  d.r[3 * slot + c] = x;
-  d.v[3 * slot + c] = v;
-  d.J[3 * slot + c] = J;
-  if (!fin) atomicOr(&d.ctrl->err, E_BEADS);
+  __builtin_amdgcn_s_setprio(0);
+  // every segment of the replica, or none, stores its result
+  if (t == 0) {
+    if (!dead && atomicAdd(word, 1u) + 1u != ng) {
+      const uint64_t t0 = wall_clock64();
+      while (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < ng)
+        if (wall_clock64() - t0 >= wait) give_up();          // the word reaches ng or gets the failure bit
+    }
+    sh.done = !dead && __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ng;
+  }
+  __syncthreads();
+  if (!sh.done) return sh.owner ? 2 : 1;
+  if (mine) {
+    d.r[3 * slot + c] = x;
+    d.v[3 * slot + c] = v;
+    d.J[3 * slot + c] = J;
+    if (!fin) atomicOr(&d.ctrl->err, E_BEADS);
+  }
+  return 0;
+}
+
+// The memory of a workgroup (sizeof(ResShared) bytes of dynamic LDS, so that
+// the kernel and the function below share it).
+extern __shared__ __align__(16) unsigned char res_lds[];
+
+struct ResArgs {
+  Dev d;
+  double* ang;
+  const FusedSeg* segs;
+  int nslots, n_sub;
+  MdOverride ov;
+  uint64_t wait;
+};
+
+// What follows a failed first pass.  Out of line: inlined, its registers
+// spill in the first pass (0.27 against 0.23 ms per step on 32^3).  a: the
+// kernel's arguments in memory, so that none is copied for this call.
+__device__ __attribute__((noinline)) void res_rescue(const ResArgs* a) {
+  ResShared& sh = *reinterpret_cast<ResShared*>(res_lds);
+  const Dev& d = a->d;
+  const FusedSeg seg = load_uniform(&a->segs[blockIdx.x]);
+  const Rep& R = d.reps[seg.rep];
+  const MdParams P = md_override(load_uniform(&R.mp), a->ov);
+  if (res_pass<true>(d, seg, R, P, sh, a->nslots, a->n_sub, a->wait) != 2) return;
+  // the pass's failure was this workgroup's decision: it alone goes on.  No
+  // other stores anything that the redo reads.
+  __syncthreads();
+  md_redo<RES_WG>(d, R, P, seg.rep, a->ang, a->nslots, 0, a->n_sub, sh.dead[0], sh.dead[1]);
+}
+
+__global__ __launch_bounds__(RES_WG, 6) void k_md_resident(ResArgs a) {
+  ResShared& sh = *reinterpret_cast<ResShared*>(res_lds);
+  const FusedSeg seg = load_uniform(&a.segs[blockIdx.x]);
+  const Rep& R = a.d.reps[seg.rep];
+  const MdParams P = md_override(load_uniform(&R.mp), a.ov);
+  if (__builtin_expect(res_pass<false>(a.d, seg, R, P, sh, a.nslots, a.n_sub, a.wait) == 0, 1)) return;
+  __syncthreads();                               // sh.done and sh.owner are read
+  res_rescue((const ResArgs*)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
 void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslots, int nrep, int n_sub, int K,
@@ -2600,8 +2736,7 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
   for (int j = 0; j < M; ++j)
     hipLaunchKernelGGL(k_md_fused, dim3((unsigned)nseg), dim3(FU_WG), 0, s, d, fb, nslots, j * K, K,
                        j == M - 1 ? 1 : 0, j & 1);
-  MdOverride none{};
-  hipLaunchKernelGGL(k_md_redo, dim3((unsigned)nrep), dim3(RD_WG), 0, s, d, fb, fb.ang, nslots, n_sub, K, none, 0);
+  hipLaunchKernelGGL(k_md_redo, dim3((unsigned)nrep), dim3(RD_WG), 0, s, d, fb, fb.ang, nslots, n_sub, K);
 }
 
 // Holds the stream until the resident cycle's nseg workgroups run (they never
@@ -2609,7 +2744,7 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
 constexpr uint64_t RES_GATE = 30000;
 __global__ void k_md_gate(const Ctrl* ctrl, uint32_t nseg) {
   const uint64_t t0 = wall_clock64();
-  while (__hip_atomic_load(&ctrl->placed[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < nseg &&
+  while (__hip_atomic_load(&ctrl->placed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < nseg &&
          wall_clock64() - t0 < RES_GATE)
     __builtin_amdgcn_s_sleep(8);
 }
@@ -2617,12 +2752,11 @@ void launch_md_gate(const Dev& d, int nseg, hipStream_t s) {
   hipLaunchKernelGGL(k_md_gate, dim3(1), dim3(1), 0, s, d.ctrl, (uint32_t)nseg);
 }
 
-void launch_md_cycle_resident(const Dev& d, const FusedBufs& fb, const FusedSeg* seg, int nseg, int nslots, int nrep,
-                              int n_sub, const MdOverride& ov, uint64_t wait, hipStream_t s) {
+void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int nseg, int nslots, int n_sub,
+                              const MdOverride& ov, uint64_t wait, hipStream_t s) {
   if (nslots <= 0 || n_sub <= 0 || nseg <= 0) return;
-  hipLaunchKernelGGL(k_md_resident<false>, dim3((unsigned)nseg), dim3(RES_WG), 0, s, d, fb, seg, nslots, n_sub, ov, wait);
-  hipLaunchKernelGGL(k_md_resident<true>, dim3((unsigned)nseg), dim3(RES_WG), 0, s, d, fb, seg, nslots, n_sub, ov, wait);
-  hipLaunchKernelGGL(k_md_redo, dim3((unsigned)nrep), dim3(RD_WG), 0, s, d, fb, fb.ang, nslots, n_sub, n_sub, ov, 1);
+  hipLaunchKernelGGL(k_md_resident, dim3((unsigned)nseg), dim3(RES_WG), sizeof(ResShared), s,
+                     (ResArgs{d, ang, seg, nslots, n_sub, ov, wait}));
 }
 
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s) {
