@@ -154,7 +154,7 @@ WorkLayout work_layout(const lb_desc* d, int nrep, const Packing& pk) {
   w.redo = take(sizeof(int) * R);
   w.rsync = take(sizeof(uint32_t) * 2 * R);
   w.rseg = take(sizeof(FusedSeg) * (size_t)(pk.nrseg > 0 ? pk.nrseg : 1));
-  w.xring = take(sizeof(uint64_t) * 4 * 2 * 3 * ns);
+  w.xring = take(sizeof(uint64_t) * XRING * 2 * 3 * ns);
   w.xflag = take(sizeof(uint64_t) * 2 * 2 * (size_t)(pk.nrseg > 0 ? pk.nrseg : 1));
   w.total = o;
   return w;
@@ -1002,6 +1002,9 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   acc(hipMemsetAsync(b->force, 0, elem_size(d) * 3 * (size_t)nodes, s));
   acc(hipMemsetAsync(b->beads, 0, sizeof(double) * 15 * ns, s));
   acc(hipMemsetAsync(D.ctrl, 0, sizeof(Ctrl), s));
+  // no tag of this context: the memory may hold the exchanges of an earlier one
+  acc(hipMemsetAsync(D.xring, 0, sizeof(uint64_t) * XRING * 2 * 3 * ns, s));
+  acc(hipMemsetAsync(D.xflag, 0, sizeof(uint64_t) * 2 * 2 * (size_t)std::max<long>(c->pk.nrseg, 1), s));
   launch_fill_i32(D.head, nodes, -1, s);
   launch_fill_f64(D.ref, 3L * (long)ns, 1e300, s);
   launch_fill_f64(D.rbin, 3L * (long)ns, 1e300, s);

@@ -267,6 +267,7 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
 // (8000 beads of a walk that was not relaxed, step by step: 3.1 ms, as with one
 // launch per sub-step; the one workgroup takes 94).  At n_sub = 1 and 2 the
 // single launches cost no more.
+constexpr int XRING = 4;                       // slots of xring
 constexpr int RES_OWN = 32;
 constexpr int RES_BLOCK = 10;
 constexpr int RES_MAX_WG = 512;

@@ -2021,9 +2021,6 @@ __device__ inline unsigned long long res_load(const unsigned long long* p) {
 __device__ inline void res_store(unsigned long long* p, unsigned long long v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ inline unsigned long long res_tag(uint64_t cycle, int n_sub, int s) {
-  return (cycle * (uint64_t)(n_sub + 1) + (uint64_t)s) * 0x9E3779B97F4A7C15ull;
-}
 
 // Bond vectors u (first) and w (second), cross product n, its length s and
 // c = u.w of the angle at (ra, rb, rc): the first operations of
@@ -2116,10 +2113,11 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     give_up();
     sh.lost = 1;
   };
-  // the tag of sub-step s of this cycle is (cycle (n_sub + 1) + s) TAG, and
-  // those of a block's start differ by MARK
+  // The tag of sub-step s of this cycle is (2^32 cycle + s) TAG, so that no two
+  // sub-steps share one, whatever the cycles' lengths; those of a block's
+  // start differ by MARK.
   constexpr uint64_t TAG = 0x9E3779B97F4A7C15ull, MARK = 0x5851F42D4C957F2Dull;
-  const uint64_t tag0 = load_uniform(&d.ctrl->cycles) * (uint64_t)(n_sub + 1) * TAG;
+  const uint64_t tag0 = ((uint64_t)load_uniform(&d.ctrl->cycles) << 32) * TAG;
 
   // ---- the lanes of the sum: component c of bead i
   const int i = 16 * wave + lane / 3, c = lane % 3;

@@ -201,6 +201,32 @@ def test_adjoint_tape_from_the_redo(monkeypatch):
     assert np.array_equal(grads[0], grads[1])
 
 
+def test_context_in_the_memory_of_an_earlier_one():
+    """The positions that an earlier context left in the exchange are not taken
+    for the new one's: every context runs one cycle of three sub-steps, the
+    last two of which stay in memory that the allocator hands out again."""
+    _torch()
+    from paper_0711_2665_amd import lbmd
+    cfg = scaled(C0, shape=(36, 36, 36), wall_pos=18, nb=200, init_seed=30)
+    s = lbmd.Simulation(cfg, initial_chain(cfg)[0], None)
+    s.relax(400, 1.0)
+    r = _state(s)[1]["r"]
+    cfg = scaled(cfg, n_sub=3, kT=0.0)
+    got = []
+    for fused in (0, 3):
+        got.append([])
+        for k in range(6):
+            s = lbmd.Simulation(cfg, r + np.array([0.37 * k, 0.0, 0.0]), None)
+            if fused:
+                s.md_fused(fused)
+            s.couple_step(1)
+            got[-1].append(_state(s)[1])
+            del s
+    for k, (a, b) in enumerate(zip(*got)):
+        for f in ("r", "v", "up", "J"):
+            assert np.array_equal(a[f], b[f]), (k, f)
+
+
 def test_more_segments_than_fit_use_single_launches():
     """16640 beads in 520 segments: one launch per sub-step, whose steps equal
     those of a chain alone in its context."""
