@@ -574,7 +574,7 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
   if (c->step_lists && c->lists_stale) launch_nbr_build(D, c->nslots, c->nrep, st);
   launch_bead_prep(D, c->nslots, c->nrep, st);
   ev_record(c, c->prep, st);
-  const bool resident = c->resident && c->mts == 0 && (c->fusedK == 0 || D.mdtape);
+  const bool resident = c->resident && (c->fusedK == 0 || D.mdtape);
   auto sweep_side = [&]() {
     ev_wait(c, c->s2, c->prep);
     if (resident) launch_md_gate(D, c->pk.nrseg, c->s2);
@@ -595,11 +595,11 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
   if (c->dev) launch_gather<float, true>(A, D, c->nslots, start, st);
   else launch_gather<double, false>(A, D, c->nslots, start, st);
   MdOverride none{};
-  if (c->mts > 0) launch_md_cycle_mts(D, c->nslots, c->nrep, c->n_sub, c->mts, st, false);
-  else if (c->fusedK > 0 && !D.mdtape)
+  if (c->fusedK > 0 && !D.mdtape)
     launch_md_cycle_fused(D, c->fb, c->pk.nseg, c->nslots, c->nrep, c->n_sub, c->fusedK, st);
   else if (resident)
-    launch_md_cycle_resident(D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, c->n_sub, none, c->md_wait, st);
+    launch_md_cycle_resident(D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, c->n_sub, c->mts, none, c->md_wait, st);
+  else if (c->mts > 0) launch_md_cycle_mts(D, c->nslots, c->n_sub, c->mts, st);
   else launch_md_cycle(D, c->nslots, c->nrep, c->n_sub, none, st, false, c->any_constrained);
   if (resident) sweep_side();
   if (c->dev) launch_spread_lb<float, true>(A, B, D, c->nslots, c->nrep, st);
@@ -870,7 +870,7 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
       for (int K = FUSED_K; K >= 2; --K)
         if (d[0].n_sub % K == 0) { c->fusedK_max = K; break; }
     c->fusedK = 0;
-    c->resident = d[0].mts_outer == 0 && !rigid && c->pk.nrseg > 0 && c->pk.nrseg <= RES_MAX_WG &&
+    c->resident = !rigid && c->pk.nrseg > 0 && c->pk.nrseg <= RES_MAX_WG &&
                   c->n_sub >= RES_MIN_SUB;
     // a shorter limit sends every wait to the redo (tests)
     if (const char* e = std::getenv("LBMD_MD_WAIT_TICKS")) c->md_wait = std::strtoull(e, nullptr, 10);
@@ -1165,7 +1165,7 @@ int md_relax(lb_ctx* c, int nsub_total, double gamma_relax) {
       launch_nbr_build(c->D, c->nslots, c->nrep, c->s);
       launch_md_begin(c->D, c->nrep, c->s);
       launch_md_start(c->D, c->nslots, ov, c->s);
-      launch_md_cycle_resident(c->D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, n, ov, c->md_wait, c->s);
+      launch_md_cycle_resident(c->D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, n, 0, ov, c->md_wait, c->s);
     } else {
       launch_md_cycle(c->D, c->nslots, c->nrep, n, ov, c->s, true, c->any_constrained);
     }

@@ -118,9 +118,9 @@ struct Dev {
   uint32_t* cst;    // per replica, 3 rotating words: some bead is farther than CELL_MARGIN
                     // from its binned position at that sub-step (the table is not usable)
   uint32_t cmask;   // buckets - 1 (a power of two minus one)
-  unsigned long long* xring;   // [4][slots][3][2]: positions exchanged inside a resident cycle, each as its
+  unsigned long long* xring;   // [6][slots][3][2]: positions exchanged inside a resident cycle, each as its
                     // bits and its bits XOR the sub-step's tag (slots 0, 1: every sub-step; 2, 3: the
-                    // start of a block)
+                    // start of a block; 4, 5: the kicks of the multiple-time-step cycle)
   unsigned long long* xflag;   // [2][segments][2]: a word per segment at the start of a block, likewise
   uint32_t* rsync;  // [R][2]: per pass of the resident cycle, segments done and the failure bit
   Ctrl* ctrl;
@@ -220,7 +220,7 @@ void launch_md_start(const Dev& d, int nslots, const MdOverride& ov, hipStream_t
 // forces (bead LJ, wall, field); noise from d.xi as in launch_md_cycle.
 constexpr int MTS_MAX_INNER = 40;
 constexpr int MAX_CONSTRAINED_BEADS = 1024;   // rigid bonds: one workgroup per chain   // inner sub-steps per outer step (the inner kernel's halo is 2 per sub-step)
-void launch_md_cycle_mts(const Dev& d, int nslots, int nrep, int n_sub, int M, hipStream_t s, bool prologue = true);
+void launch_md_cycle_mts(const Dev& d, int nslots, int n_sub, int M, hipStream_t s);
 
 // The uniform sub-cycle in blocks of K sub-steps, one launch per block:
 // workgroup w advances the chain segment [a, b) of replica rep through the
@@ -267,14 +267,14 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
 // (8000 beads of a walk that was not relaxed, step by step: 3.1 ms, as with one
 // launch per sub-step; the one workgroup takes 94).  At n_sub = 1 and 2 the
 // single launches cost no more.
-constexpr int XRING = 4;                       // slots of xring
+constexpr int XRING = 6;                       // slots of xring
 constexpr int RES_OWN = 32;
 constexpr int RES_BLOCK = 10;
 constexpr int RES_MAX_WG = 512;
 constexpr int RES_MIN_SUB = 3;
 constexpr uint64_t RES_PLACE = 200000;   // 2 ms
 void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int nseg, int nslots, int n_sub,
-                              const MdOverride& ov, uint64_t wait, hipStream_t s);
+                              int mts, const MdOverride& ov, uint64_t wait, hipStream_t s);
 void launch_md_gate(const Dev& d, int nseg, hipStream_t s);
 // Noise of one sub-cycle into d.xi, for the step counter + step_offset.
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s);

@@ -288,8 +288,9 @@ __global__ __launch_bounds__(3 * MD_WG) void k_md_substep(Dev d, MdOverride ov, 
   const int bslot = tb / MD_LANES, lane = tb % MD_LANES;
   const int slot0 = blockIdx.x * MD_BPB;
   const int slot = slot0 + bslot;            // the grid covers the nslots slots exactly
-  const double* rabs = SLOW ? d.r : ((s & 1) ? d.rmid1 : d.rmid0);
+  const double* rabs = (s & 1) ? d.rmid1 : d.rmid0;
   double* rout = (s & 1) ? d.rmid0 : d.rmid1;
+  const double* vin = (const double*)d.xring;   // SLOW: the inner cycle's velocities
   auto clampslot = [nslots](int q) { return q < 0 ? 0 : (q >= nslots ? nslots - 1 : q); };
 
   // ---- first-level loads, addressed by slot alone so that they are in
@@ -476,7 +477,7 @@ __global__ __launch_bounds__(3 * MD_WG) void k_md_substep(Dev d, MdOverride ov, 
     // other waves work; they are needed only at the end.
     if (SLOW) {
 #pragma unroll
-      for (int a = 0; a < 3; ++a) vo[a] = d.v[3 * slot + a];
+      for (int a = 0; a < 3; ++a) vo[a] = (s > 0 ? vin : d.v)[3 * slot + a];
     } else {
       const int sm = clampslot(slot - 1), sq = clampslot(slot + 1);
 #pragma unroll
@@ -577,6 +578,7 @@ __global__ __launch_bounds__(3 * MD_WG) void k_md_substep(Dev d, MdOverride ov, 
       double vn = vo[a] + P.kick * F[a];
       if (last == 2) vn = vn + P.kick * F[a];
       d.v[3 * slot + a] = vn;
+      if (s > 0 && last == 1) d.r[3 * slot + a] = rp[a];   // the cycle's end
       fin = fin && isfinite(vn);
     }
     if (!fin) atomicOr(&d.ctrl->err, E_BEADS);
@@ -646,12 +648,20 @@ __global__ void k_zero_v(double* v, int n) {
 // the definition's order: bonds to p-1 and p+1, then the angles centred at
 // p-1, p, p+1.  The last lane state also gives the displacement checks of the
 // slow kick that follows (index o + 1).
+// A halo slot is read while the workgroup that owns it may have ended, so
+// the results go to other arrays than those read: positions alternate between
+// r_mid0 and r_mid1, velocities go from v to the exchange memory of the
+// resident cycle (which runs instead of this kernel up to RES_MAX_WG segments),
+// and the kicks bring both back.
 // ---------------------------------------------------------------------------
 constexpr int IN_WG = 256;
 
 __global__ __launch_bounds__(IN_WG) void k_md_inner(Dev d, int nslots, int o, int Mb) {
   __shared__ double pos[2][IN_WG][3];
   const int j = threadIdx.x;
+  const double* rin = (o & 1) ? d.rmid1 : d.rmid0;
+  double* rout = (o & 1) ? d.rmid0 : d.rmid1;
+  double* vout = (double*)d.xring;
   const int H = 2 * Mb, own = IN_WG - 2 * H;
   const int gslot = (int)blockIdx.x * own - H + j;
   const bool valid = gslot >= 0 && gslot < nslots;
@@ -667,7 +677,7 @@ __global__ __launch_bounds__(IN_WG) void k_md_inner(Dev d, int nslots, int o, in
   if (active) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      r[a] = d.r[3 * slot + a];
+      r[a] = rin[3 * slot + a];
       v[a] = d.v[3 * slot + a];
       J[a] = d.J[3 * slot + a];
       u[a] = R.mp.couple ? d.up[3 * slot + a] : 0.0;
@@ -713,8 +723,8 @@ __global__ __launch_bounds__(IN_WG) void k_md_inner(Dev d, int nslots, int o, in
   double d2 = 0.0, b2 = 0.0;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    d.r[3 * slot + a] = r[a];
-    d.v[3 * slot + a] = v[a];
+    rout[3 * slot + a] = r[a];
+    vout[3 * slot + a] = v[a];
     d.J[3 * slot + a] = J[a];
     fin = fin && isfinite(v[a]) && isfinite(r[a]);
     const double dd = r[a] - d.ref[3 * slot + a];
@@ -1181,17 +1191,13 @@ void launch_md_cycle(const Dev& d, int nslots, int nrep, int n_sub, const MdOver
   }
 }
 
-void launch_md_cycle_mts(const Dev& d, int nslots, int nrep, int n_sub, int M, hipStream_t s, bool prologue) {
+void launch_md_cycle_mts(const Dev& d, int nslots, int n_sub, int M, hipStream_t s) {
   if (nslots <= 0 || n_sub <= 0 || M <= 0) return;
   const int Mb = n_sub / M;
   const unsigned nblk = (unsigned)(nslots / MD_BPB);
   const int own = IN_WG - 4 * Mb;
   const unsigned nin = (unsigned)((nslots + own - 1) / own);
   MdOverride none{};
-  if (prologue) {
-    hipLaunchKernelGGL(k_md_begin, dim3(1), dim3(256), 0, s, d, nrep);
-    hipLaunchKernelGGL(k_md_start, dim3((nslots + 255) / 256), dim3(256), 0, s, d, nslots, none, 1);
-  }
   for (int o = 0; o < M; ++o) {
     hipLaunchKernelGGL(k_md_substep<true>, dim3(nblk), dim3(3 * MD_WG), 0, s, d, none, nslots, o, o == 0 ? 1 : 2);
     hipLaunchKernelGGL(k_md_inner, dim3(nin), dim3(IN_WG), 0, s, d, nslots, o, Mb);
@@ -1410,7 +1416,7 @@ __device__ inline void fu_wall(const MdParams& P, const Geom& g, const double* r
 // chain order (terms within r_c only), the wall sites, the field.
 __device__ inline void fu_force(const MdParams& P, const Geom& g, int q, const double* rp, const double* rm,
                                 const double* rq, const double* a3, const double* ac, const double* a1,
-                                const double* base, const int* idx, int np, double F[3]) {
+                                const double* base, const int* idx, int np, double F[3], bool slow = true) {
   F[0] = 0.0; F[1] = 0.0; F[2] = 0.0;
   if (!P.constrained) {
     if (q > 0 && rm) bond_add(P, rp, rm, F);
@@ -1429,6 +1435,7 @@ __device__ inline void fu_force(const MdParams& P, const Geom& g, int q, const d
     lj_add(P, e0, e1, e2, Fp);
     F[0] += Fp[0]; F[1] += Fp[1]; F[2] += Fp[2];
   }
+  if (!slow) return;
   fu_wall(P, g, rp, F);
   if (P.field_on && in_field(g, rp)) F[g.wall_axis] += P.f_drive;
 }
@@ -1744,15 +1751,19 @@ constexpr int RD_WG = 1024;
 constexpr int RD_NC = 32;          // pair partners within r_c of one bead
 
 // Sub-steps sp .. n_sub - 1 of replica rep by one workgroup of WG threads, from
-// r_mid of sub-step sp in r_mid0, and v, J.
-template <int WG>
+// r_mid of sub-step sp in r_mid0, and v, J.  MTS: the n_sub + mts + 1 stages of
+// the multiple-time-step cycle (sp = 0; see the resident cycle).
+template <int WG, bool MTS>
 __device__ inline void md_redo(const Dev& d, const Rep& R, const MdParams& P, int rep, double* ang, int nslots,
-                               int sp, int n_sub, int& any_far, int& any_off) {
+                               int sp, int n_sub, int mts, int& any_far, int& any_off) {
   const Geom g = R.g;
   const int so = R.slot_off, nb = P.nb;
   const int t = threadIdx.x;
   bool fin = true, over = false, valid = d.rb[4 * rep] == 0u;   // the lists, at the cycle's start
-  for (int s = sp; s < n_sub; ++s) {
+  const int Mb = MTS ? n_sub / mts : 0, end = MTS ? n_sub + mts + 1 : n_sub;
+  for (int s = sp; s < end; ++s) {
+    const bool kick = MTS && s % (Mb + 1) == 0;
+    const int sub = MTS ? s - s / (Mb + 1) - 1 : s;       // index of the sub-step (no kick)
     const double* cur = ((s - sp) & 1) ? d.rmid1 : d.rmid0;
     double* nxt = ((s - sp) & 1) ? d.rmid0 : d.rmid1;
     // every bead near the position the lists were built at, the position
@@ -1774,10 +1785,10 @@ __device__ inline void md_redo(const Dev& d, const Rep& R, const MdParams& P, in
     if (!near) any_far = 1;
     if (!held) any_off = 1;
     for (int q = t; q < nb; q += WG)
-      if (q >= 1 && q <= nb - 2)
+      if (!kick && q >= 1 && q <= nb - 2)
         fu_angle(P, &cur[3 * (so + q - 1)], &cur[3 * (so + q)], &cur[3 * (so + q + 1)], &ang[9 * (size_t)(so + q)]);
     __syncthreads();
-    const bool lists = any_off == 0, table = any_far == 0;
+    const bool lists = (MTS && !kick) || any_off == 0, table = any_far == 0;
     if (!lists) {
       // each thread builds the lists of its own beads, which it alone reads
       for (int q = t; q < nb; q += WG) {
@@ -1814,7 +1825,7 @@ __device__ inline void md_redo(const Dev& d, const Rep& R, const MdParams& P, in
       const double rp[3] = {cur[3 * sl], cur[3 * sl + 1], cur[3 * sl + 2]};
       int part[RD_NC];
       int np = 0;
-      const int cnt = d.ncnt[sl];
+      const int cnt = !MTS || kick ? d.ncnt[sl] : 0;
       for (int k = 0; k < cnt && np <= RD_NC; ++k) {
         const int j = d.nbr[(size_t)sl * MAXNBR + k] - so;   // list entries are slots
         const double e0 = min_image(rp[0] - cur[3 * (so + j)], g.nx);
@@ -1829,22 +1840,34 @@ __device__ inline void md_redo(const Dev& d, const Rep& R, const MdParams& P, in
       const double* ac = (q >= 1 && q <= nb - 2) ? &ang[9 * (size_t)sl] : nullptr;
       const double* a1 = (q + 1 >= 1 && q + 1 <= nb - 2) ? &ang[9 * (size_t)(sl + 1)] : nullptr;
       double F[3];
-      fu_force(P, g, q, rp, q > 0 ? &cur[3 * (sl - 1)] : nullptr, q < nb - 1 ? &cur[3 * (sl + 1)] : nullptr, a3, ac,
-               a1, cur + 3 * (size_t)so, part, np, F);
+      const bool fast = !kick, slow = !MTS || kick;
+      fu_force(P, g, q, rp, fast && q > 0 ? &cur[3 * (sl - 1)] : nullptr,
+               fast && q < nb - 1 ? &cur[3 * (sl + 1)] : nullptr, fast ? a3 : nullptr, fast ? ac : nullptr,
+               fast ? a1 : nullptr, cur + 3 * (size_t)so, part, np, F, slow);
       double v[3] = {d.v[3 * sl], d.v[3 * sl + 1], d.v[3 * sl + 2]};
       double J[3] = {d.J[3 * sl], d.J[3 * sl + 1], d.J[3 * sl + 2]};
       double u[3] = {d.up[3 * sl], d.up[3 * sl + 1], d.up[3 * sl + 2]};
       double xi[3] = {0.0, 0.0, 0.0};
       if (P.sig != 0.0)
-        for (int a = 0; a < 3; ++a) xi[a] = d.xi[(size_t)3 * ((size_t)s * nslots + sl) + a];
+        for (int a = 0; a < 3; ++a) xi[a] = kick ? 0.0 : d.xi[(size_t)3 * ((size_t)sub * nslots + sl) + a];
       if (d.mdtape)
         for (int a = 0; a < 3; ++a) {
           d.mdtape[((size_t)s * nb + q) * 6 + a] = rp[a];
           d.mdtape[((size_t)s * nb + q) * 6 + 3 + a] = v[a];
         }
-      const bool fl = s == n_sub - 1;
+      const bool fl = s == end - 1;
       double x[3];
-      fin = fu_kick(P, F, u, xi, v, J, rp, fl, x) && fin;
+      if (kick) {
+        for (int a = 0; a < 3; ++a) {
+          v[a] = v[a] + P.kick * F[a];
+          if (s > 0 && !fl) v[a] = v[a] + P.kick * F[a];
+          x[a] = fl ? rp[a] : rp[a] + P.hh * v[a];
+          fin = fin && isfinite(v[a]) && isfinite(rp[a]);
+        }
+      } else {
+        // r itself where a kick follows
+        fin = fu_kick(P, F, u, xi, v, J, rp, MTS ? (s + 1) % (Mb + 1) == 0 : fl, x) && fin;
+      }
       for (int a = 0; a < 3; ++a) {
         d.v[3 * sl + a] = v[a];
         d.J[3 * sl + a] = J[a];
@@ -1886,7 +1909,7 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
         d.J[i] = fb.JS[i];
       }
   if (t == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)(n_sub - sp));
-  md_redo<RD_WG>(d, R, P, rep, ang, nslots, sp, n_sub, any_far, any_off);
+  md_redo<RD_WG, false>(d, R, P, rep, ang, nslots, sp, n_sub, 0, any_far, any_off);
 }
 
 // ---------------------------------------------------------------------------
@@ -1945,6 +1968,17 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
 // is set, or the clock runs out.  All of this is one launch: a second one that
 // finds nothing to do would wait for room beside the sweep (0.49 ms of a
 // 1.1 ms step).
+//
+// The multiple-time-step cycle (MTS) is the same loop over n_sub + M + 1
+// stages: kicks of the slow forces (pairs, walls, field) at r, and between two
+// of them Mb = n_sub / M sub-steps of the bonded forces.  Pair partners that are
+// no chain neighbours exchange positions for the kicks only, so those travel in
+// slots of their own (4, 5, by the kick's parity: the argument above holds
+// for the kicks alone, and for every stage between chain neighbours).  The
+// lists are checked at the kicks, and a block is a kick and the sub-steps up
+// to the next, so the second pass takes any displacement.  2000 beads, M = 5,
+// n_sub = 100: 0.47 ms per step; with a launch per kick and one for the
+// sub-steps between (k_md_inner) 0.63.
 //
 // At a block's start each segment publishes its positions (tagged like the
 // exchange) and a word that says whether its beads are within CELL_MARGIN of
@@ -2083,10 +2117,12 @@ __device__ inline bool res_poll(const unsigned long long* o, uint64_t tag, const
 
 // One pass of the cycle (see above); 0: done, 1: failed, 2: failed, by this
 // workgroup's decision.
-template <bool BLOCKS>
+template <bool BLOCKS, bool MTS>
 __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const Rep& R, const MdParams& P, ResShared& sh,
-                                        int nslots, int n_sub, uint64_t wait) {
+                                        int nslots, int n_sub, int mts, uint64_t wait) {
   const int rep = seg.rep;
+  const int Mb = MTS ? n_sub / mts : 0;          // sub-steps between two kicks
+  const int end = MTS ? n_sub + mts + 1 : n_sub; // stages; MTS: stage s is a kick where Mb + 1 divides it
   const Geom g = load_uniform(&R.g);
   const int so = load_uniform(&R.slot_off), nb = P.nb;
   const int p0 = seg.a, n = seg.b - seg.a;
@@ -2143,9 +2179,9 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & RES_FAIL) sh.lost = 1;
   }
   bool fin = true, dead = false;
-  const int len = BLOCKS ? RES_BLOCK : n_sub;
+  const int len = !BLOCKS ? end : (MTS ? Mb + 1 : RES_BLOCK);
   for (int s0 = 0, blk = 0;; s0 += len, ++blk) {
-  const int s1 = BLOCKS ? min(s0 + len, n_sub) : n_sub;
+  const int s1 = BLOCKS ? min(s0 + len, end) : end;
   const int sp = s0 & 1;                         // parity of the block's first sub-step
   // ---- set-up: the lists as local indices
   __syncthreads();                               // the positions at s0 are there, the forces' memory is free
@@ -2178,7 +2214,9 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         v2 += w * w;
       }
       near = b2 <= CELL_MARGIN * CELL_MARGIN;
-      need = need || !(sqrt(f2) + 4.0 * P.hh * RES_BLOCK * sqrt(v2) <= 0.95 * sqrt(P.halfskin2));
+      // (MTS: the lists serve the block's first stage only)
+      need = need || (MTS ? !(f2 <= P.halfskin2)
+                          : !(sqrt(f2) + 4.0 * P.hh * RES_BLOCK * sqrt(v2) <= 0.95 * sqrt(P.halfskin2)));
       sh.ncand[t] = 0;
     }
     const int all_near = __syncthreads_and(near ? 1 : 0), any_need = __syncthreads_or(need ? 1 : 0);
@@ -2366,7 +2404,8 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
   // Each kind of wave has a loop of its own (its registers then hold only
   // what it needs), with the same two barriers per sub-step.  The test of
   // sh.dead is uniform: sub-step s writes dead[s & 1] before its second
-  // barrier only, and s + 2 writes it again after two more.
+  // barrier only, and s + 2 writes it again after two more.  q: stages since
+  // the last kick (MTS).
   if (wave < 2) {
     // ---- angles; the sum
     const int k = t / 3, ka = t % 3;             // component ka of the angle centred at a - 1 + k
@@ -2377,11 +2416,14 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     double* tape = mine && d.mdtape ? d.mdtape + (size_t)p * 6 + c : nullptr;
     unsigned long long* ring = d.xring + ((size_t)slot * 3 + c) * 2;
     uint64_t tag = tags;
+    int q = 0, o = MTS ? s0 / (Mb + 1) : 0;
     for (int s = s0; s < s1; ++s) {
       const int cb = s & 1;
-      const bool last = s == n_sub - 1;
+      const bool last = s == end - 1;
+      const bool kick = MTS && q == 0;
+      if (MTS && q++ == Mb) { q = 0; ++o; }      // of stage s + 1
       tag += TAG;                                // of sub-step s + 1
-      if (ang) {
+      if (ang && !kick) {
         const ResAngle A = res_angle(sh.pos[cb][j0], sh.pos[cb][j1], sh.pos[cb][j2]);
         double d1, d2;
         res_angle_d(A, ka, d1, d2);
@@ -2400,11 +2442,14 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         const double e2 = sh.dd[1][i][c], m1 = sh.dd[0][i + 1][c], m2 = sh.dd[1][i + 1][c], q1 = sh.dd[0][i + 2][c];
         const double fb0 = sh.bnd[i][c], fb1 = sh.bnd[i + 1][c];
         double F = 0.0;
+        if (!kick) {
         if (bm) F += fb0;
         if (bp) F += -fb1;
         if (am) F += 0.0 + -(kp0 * e2);
         if (ac) F += 0.0 + -(kp1 * (m1 - m2));
         if (ap) F += 0.0 + kp2 * q1;
+        }
+        if (!MTS || kick) {
         if ((pc & 0xfefefefeu) == 0u) {          // at most one pair force per lane
           if (pc & 0xffu) F += f0;
           if (pc & 0xff00u) F += f1;
@@ -2419,10 +2464,10 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
           } else {
             const double* rp = sh.pos[cb][i];
             for (int m = 0; m < sh.lcnt[i]; ++m) {
-              const double* q = sh.pos[cb][sh.lst[i][m]];
-              const double d0 = min_image(rp[0] - q[0], g.nx);
-              const double d1 = min_image(rp[1] - q[1], g.ny);
-              const double d2 = min_image(rp[2] - q[2], g.nz);
+              const double* rq = sh.pos[cb][sh.lst[i][m]];
+              const double d0 = min_image(rp[0] - rq[0], g.nx);
+              const double d1 = min_image(rp[1] - rq[1], g.ny);
+              const double d2 = min_image(rp[2] - rq[2], g.nz);
               if (!(d0 * d0 + d1 * d1 + d2 * d2 < P.rc2)) continue;
               double Fp[3] = {0.0, 0.0, 0.0};
               lj_add(P, d0, d1, d2, Fp);
@@ -2438,27 +2483,33 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
           if (m + 3 < m1) F += w3;
         }
         if (fl && c == g.wall_axis) F += P.f_drive;
-        if (tape) {
+        }
+        if (!MTS && tape) {
           double* tp = tape + (size_t)s * nb * 6;
           tp[0] = x;
           tp[3] = v;
         }
-        const double sx = P.sig * xi;
-        const double vn = P.e * v + P.cf * (F + P.gamma * u) + sx;
-        J = J - P.m * (P.omE * (u - v) + sx);
-        v = vn;
-        fin = fin && isfinite(vn);
-        const double re = x + P.hh * vn;
-        if (last) {
-          x = re;
+        if (kick) {
+          v = v + P.kick * F;
+          if (s > 0 && !last) v = v + P.kick * F;
+          fin = fin && isfinite(v) && isfinite(x);
+          if (!last) x = x + P.hh * v;
         } else {
-          x = re + P.hh * vn;
+          const double sx = P.sig * xi;
+          const double vn = P.e * v + P.cf * (F + P.gamma * u) + sx;
+          J = J - P.m * (P.omE * (u - v) + sx);
+          v = vn;
+          fin = fin && isfinite(vn);
+          const double re = x + P.hh * vn;
+          x = (MTS ? q == 0 : last) ? re : re + P.hh * vn;   // a kick takes r itself
+        }
+        if (!last) {
           sh.pos[cb ^ 1][i][c] = x;
           if (multi) {
-            unsigned long long* o = ring + (cb ? 0 : half);
+            unsigned long long* w = ring + (MTS && q == 0 ? (4 + (o & 1)) * half : (cb ? 0 : half));
             const unsigned long long bits = (unsigned long long)__double_as_longlong(x);
-            res_store(o, bits);
-            res_store(o + 1, bits ^ tag);
+            res_store(w, bits);
+            res_store(w + 1, bits ^ tag);
           }
         }
       }
@@ -2475,17 +2526,20 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
       k1 = min(k0 + per, m);
       first = k0 < k1 ? sh.lst[pb][k0] : 0;
     }
+    int q = 0;
     for (int s = s0; s < s1; ++s) {
       const int cb = s & 1;
-      if (pb < n) {
+      const bool slow = !MTS || q == 0;
+      if (MTS && q++ == Mb) q = 0;
+      if (pb < n && slow) {
         const double* rp = sh.pos[cb][pb];
         const double r0 = rp[0], r1 = rp[1], r2 = rp[2];
         int hits = 0;
         for (int m = k0; m < k1; ++m) {
-          const double* q = sh.pos[cb][m == k0 ? first : sh.lst[pb][m]];
-          const double d0 = min_image(r0 - q[0], g.nx);
-          const double d1 = min_image(r1 - q[1], g.ny);
-          const double d2 = min_image(r2 - q[2], g.nz);
+          const double* rq = sh.pos[cb][m == k0 ? first : sh.lst[pb][m]];
+          const double d0 = min_image(r0 - rq[0], g.nx);
+          const double d1 = min_image(r1 - rq[1], g.ny);
+          const double d2 = min_image(r2 - rq[2], g.nz);
           if (!(d0 * d0 + d1 * d1 + d2 * d2 < P.rc2)) continue;
           double Fp[3] = {0.0, 0.0, 0.0};
           lj_add(P, d0, d1, d2, Fp);
@@ -2505,9 +2559,12 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     // ---- kappa phi of the angle centred at a - 1 + lane
     const bool ang = lane < n + 2 && p0 - 1 + lane >= 1 && p0 - 1 + lane <= nb - 2;
     const int j0 = ang ? at(lane - 2) : 0, j1 = ang ? at(lane - 1) : 0, j2 = ang ? at(lane) : 0;
+    int q = 0;
     for (int s = s0; s < s1; ++s) {
       const int cb = s & 1;
-      if (ang) {
+      const bool kick = MTS && q == 0;
+      if (MTS && q++ == Mb) q = 0;
+      if (ang && !kick) {
         const ResAngle A = res_angle(sh.pos[cb][j0], sh.pos[cb][j1], sh.pos[cb][j2]);
         sh.kp[lane] = A.s == 0.0 ? 0.0 : P.kappa * atan2(A.s, A.c);
       }
@@ -2524,14 +2581,17 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
 #pragma unroll
       for (int a = 0; a < 3; ++a) ref[a] = sh.ref[lane][a];
     }
+    int q = 0;
     for (int s = s0; s < s1; ++s) {
       const int cb = s & 1;
-      if (bond) {
+      const bool kick = MTS && q == 0;
+      if (MTS && q++ == Mb) q = 0;
+      if (bond && !kick) {
         double Fb[3] = {0.0, 0.0, 0.0};
         bond_add(P, sh.pos[cb][lane < n ? lane : HR], sh.pos[cb][lane ? lane - 1 : HL + 1], Fb);
         sh.bnd[lane][0] = Fb[0]; sh.bnd[lane][1] = Fb[1]; sh.bnd[lane][2] = Fb[2];
       }
-      if (lane < n && (s > s0 || (BLOCKS && s > 0))) {
+      if (lane < n && (MTS ? kick && s > s0 : s > s0 || (BLOCKS && s > 0))) {
         double d2 = 0.0;
 #pragma unroll
         for (int a = 0; a < 3; ++a) { const double dd = sh.pos[cb][lane][a] - ref[a]; d2 += dd * dd; }
@@ -2557,8 +2617,17 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     const int num = lane % per, o1 = P.wlo + num / nw, o0 = P.wlo + num % nw;
     const int n0 = wa == 0 ? g.ny : g.nx, n1 = wa == 2 ? g.ny : g.nz;   // transverse extents
     const uint64_t below = (1ull << lane) - 1ull;
+    int q = 0;
     for (int s = s0; s < s1; ++s) {
       const int cb = s & 1;
+      const bool slow = !MTS || q == 0;
+      if (MTS && q++ == Mb) q = 0;
+      if (!slow) {
+        lds_barrier();
+        lds_barrier();
+        if (sh.dead[cb]) { dead = true; break; }
+        continue;
+      }
       int fl = 0;
       bool near = false;
       double dn = 0.0, wt0 = 0.0, wt1 = 0.0;
@@ -2634,27 +2703,41 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     // ---- the noise of the workgroup's beads, one sub-step ahead (up to two
     // of its 3 n values per lane); the remote positions
     const int nx = noisy ? 3 * n : 0;
-    const double* xsrc = d.xi + (size_t)3 * (so + p0);
-    const double* x0 = xsrc + (size_t)s0 * 3 * nslots;
-    double xa = lane < nx ? x0[lane] : 0.0, xc = lane + 64 < nx ? x0[lane + 64] : 0.0;
+    const size_t row = (size_t)3 * nslots;
+    int left = n_sub - (MTS ? s0 - s0 / (Mb + 1) : s0);   // sub-steps from s0 on
+    const double* xn = d.xi + (size_t)3 * (so + p0) + (size_t)(n_sub - left) * row;
+    double xa = 0.0, xc = 0.0;
+    if (!MTS || left > 0) {
+      xa = lane < nx ? xn[lane] : 0.0;
+      xc = lane + 64 < nx ? xn[lane + 64] : 0.0;
+    }
     const int rs0 = lane < 3 * nrem ? sh.rslot[lane / 3] : -1;
     uint64_t tag = tags;
+    int q = 0, o = MTS ? s0 / (Mb + 1) : 0;
     for (int s = s0; s < s1; ++s) {
       const int cb = s & 1;
+      const bool kick = MTS && q == 0;
+      if (MTS && q++ == Mb) { q = 0; ++o; }      // of stage s + 1
       tag += TAG;
-      if (lane < nx) sh.xi[lane] = xa;
-      if (lane + 64 < nx) sh.xi[lane + 64] = xc;
+      if (!kick) {
+        if (lane < nx) sh.xi[lane] = xa;
+        if (lane + 64 < nx) sh.xi[lane + 64] = xc;
+        --left;
+      }
       lds_barrier();
-      if (s < n_sub - 1) {
-        const double* q = xsrc + (size_t)(s + 1) * 3 * nslots;
-        if (lane < nx) xa = q[lane];
-        if (lane + 64 < nx) xc = q[lane + 64];
-        for (int m = lane; m < 3 * nrem; m += 64) {
+      if (s < end - 1) {
+        if (!kick && left > 0) {
+          xn += row;
+          if (lane < nx) xa = xn[lane];
+          if (lane + 64 < nx) xc = xn[lane + 64];
+        }
+        const unsigned long long* from = d.xring + (MTS && q == 0 ? (4 + (o & 1)) * half : (cb ? 0 : half));
+        const int m1 = 3 * (MTS && q != 0 ? RES_HALO : nrem);   // a sub-step needs the chain neighbours only
+        for (int m = lane; m < m1; m += 64) {
           const int sl = m == lane ? rs0 : sh.rslot[m / 3];
           if (sl < 0) continue;
-          const unsigned long long* o = d.xring + (cb ? 0 : half) + ((size_t)sl * 3 + m % 3) * 2;
           unsigned long long w = 0;
-          if (!res_poll(o, tag, word, d.ctrl, wait, w)) {
+          if (!res_poll(from + ((size_t)sl * 3 + m % 3) * 2, tag, word, d.ctrl, wait, w)) {
             fail(s);
             break;
           }
@@ -2665,7 +2748,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
       if (sh.dead[cb]) { dead = true; break; }
     }
   }
-  if (dead || !BLOCKS || s1 == n_sub) break;
+  if (dead || !BLOCKS || s1 == end) break;
   }
   __builtin_amdgcn_s_setprio(0);
   // every segment of the replica, or none, stores its result
@@ -2696,7 +2779,7 @@ struct ResArgs {
   Dev d;
   double* ang;
   const FusedSeg* segs;
-  int nslots, n_sub;
+  int nslots, n_sub, mts;
   MdOverride ov;
   uint64_t wait;
 };
@@ -2704,27 +2787,29 @@ struct ResArgs {
 // What follows a failed first pass.  Out of line: inlined, its registers
 // spill in the first pass (0.27 against 0.23 ms per step on 32^3).  a: the
 // kernel's arguments in memory, so that none is copied for this call.
+template <bool MTS>
 __device__ __attribute__((noinline)) void res_rescue(const ResArgs* a) {
   ResShared& sh = *reinterpret_cast<ResShared*>(res_lds);
   const Dev& d = a->d;
   const FusedSeg seg = load_uniform(&a->segs[blockIdx.x]);
   const Rep& R = d.reps[seg.rep];
   const MdParams P = md_override(load_uniform(&R.mp), a->ov);
-  if (res_pass<true>(d, seg, R, P, sh, a->nslots, a->n_sub, a->wait) != 2) return;
+  if (res_pass<true, MTS>(d, seg, R, P, sh, a->nslots, a->n_sub, a->mts, a->wait) != 2) return;
   // the pass's failure was this workgroup's decision: it alone goes on.  No
   // other stores anything that the redo reads.
   __syncthreads();
-  md_redo<RES_WG>(d, R, P, seg.rep, a->ang, a->nslots, 0, a->n_sub, sh.dead[0], sh.dead[1]);
+  md_redo<RES_WG, MTS>(d, R, P, seg.rep, a->ang, a->nslots, 0, a->n_sub, a->mts, sh.dead[0], sh.dead[1]);
 }
 
+template <bool MTS>
 __global__ __launch_bounds__(RES_WG, 6) void k_md_resident(ResArgs a) {
   ResShared& sh = *reinterpret_cast<ResShared*>(res_lds);
   const FusedSeg seg = load_uniform(&a.segs[blockIdx.x]);
   const Rep& R = a.d.reps[seg.rep];
   const MdParams P = md_override(load_uniform(&R.mp), a.ov);
-  if (__builtin_expect(res_pass<false>(a.d, seg, R, P, sh, a.nslots, a.n_sub, a.wait) == 0, 1)) return;
+  if (__builtin_expect(res_pass<false, MTS>(a.d, seg, R, P, sh, a.nslots, a.n_sub, a.mts, a.wait) == 0, 1)) return;
   __syncthreads();                               // sh.done and sh.owner are read
-  res_rescue((const ResArgs*)__builtin_amdgcn_kernarg_segment_ptr());
+  res_rescue<MTS>((const ResArgs*)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
 void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslots, int nrep, int n_sub, int K,
@@ -2751,10 +2836,10 @@ void launch_md_gate(const Dev& d, int nseg, hipStream_t s) {
 }
 
 void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int nseg, int nslots, int n_sub,
-                              const MdOverride& ov, uint64_t wait, hipStream_t s) {
+                              int mts, const MdOverride& ov, uint64_t wait, hipStream_t s) {
   if (nslots <= 0 || n_sub <= 0 || nseg <= 0) return;
-  hipLaunchKernelGGL(k_md_resident, dim3((unsigned)nseg), dim3(RES_WG), sizeof(ResShared), s,
-                     (ResArgs{d, ang, seg, nslots, n_sub, ov, wait}));
+  hipLaunchKernelGGL(mts > 0 ? k_md_resident<true> : k_md_resident<false>, dim3((unsigned)nseg), dim3(RES_WG),
+                     sizeof(ResShared), s, (ResArgs{d, ang, seg, nslots, n_sub, mts, ov, wait}));
 }
 
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s) {

@@ -243,3 +243,51 @@ def test_more_segments_than_fit_use_single_launches():
         s.relax(200, 1.0)
         s.couple_step(2)
         _same((e, k), (s,), f"replica {k} of 520")
+
+
+@pytest.mark.parametrize("M", [4, 25, 100])
+def test_mts_against_single_launches(monkeypatch, M):
+    """The multiple-time-step cycle (25, 4 and 1 sub-steps between kicks): a
+    resident context, its redo, and the launches of a context with more
+    segments than stay resident (520 of them fill chains beside the compared
+    ones).  Chains of one, three and 22 segments, one that drifts out of its
+    lists' range, and a dense one."""
+    _torch()
+    from paper_0711_2665_amd import lbmd
+    kw = dict(mts_outer=M, n_sub=100)
+    folded = []                                    # rows and planes of six, neighbours 1.05 apart
+    for k in range(200):
+        row, x = divmod(k, 6)
+        z, y = divmod(row, 6)
+        folded.append((5 - x if row % 2 else x, 5 - y if z % 2 else y, z))
+    folded = np.asarray(folded, dtype=np.float64) * 1.05 + np.array([9.3, 9.1, 16.2])
+    test = [(scaled(C0, shape=(32, 32, 32), nb=20, seed=3, replica=0, **kw), None, 0.0),
+            (scaled(C0, shape=(36, 34, 30), wall_axis=1, wall_pos=17, nb=65, seed=4, replica=1, init_seed=4, **kw), None, 0.0),
+            (scaled(C0, shape=(40, 36, 44), wall_pos=22, nb=700, seed=5, replica=2, init_seed=4, **kw), None, 0.0),
+            (scaled(C0, shape=(40, 40, 40), wall_pos=20, nb=300, seed=6, replica=3, init_seed=9, **kw), None, 2.0),
+            (scaled(C0, shape=(24, 24, 30), wall_pos=15, nb=200, seed=7, replica=4, eps=0.05, r0=1.05, kappa=0.5, **kw),
+             folded, 0.0)]
+    r0 = [initial_chain(c)[0] if r is None else r for c, r, _ in test]
+    fill = [scaled(C0, shape=(32, 32, 32), nb=32, seed=k, replica=k, init_seed=k, **kw) for k in range(5, 525)]
+
+    p = lbmd.LB_FP32_DEV
+    e = lbmd.Ensemble([c for c, _, _ in test] + fill, r0 + [initial_chain(c)[0] for c in fill], precision=p)
+    sims = []
+    for wait in (None, "0"):
+        if wait is not None:
+            monkeypatch.setenv("LBMD_MD_WAIT_TICKS", wait)
+        sims.append([lbmd.Simulation(c, r, None, precision=p) for (c, _, _), r in zip(test, r0)])
+    monkeypatch.delenv("LBMD_MD_WAIT_TICKS")
+    for s in (e, *sims[0], *sims[1]):
+        s.relax(200, 1.0)
+    for k, (_, _, speed) in enumerate(test):
+        for v in [e.beads(k)["v"]] + [group[k].beads()["v"] for group in sims]:
+            v[:, 0] = speed
+    for n in (1, 2):
+        e.couple_step(n)
+        for k in range(len(test)):
+            for tag, group in zip(("resident", "redo"), sims):
+                group[k].couple_step(n)
+                _same((group[k],), (e, k), f"M {M}, chain {k}, {tag} against launches")
+    print({k: sims[0][3].diagnostics()[k] for k in ("nbr_max", "rebuilds")}, flush=True)
+    assert sims[0][3].diagnostics()["rebuilds"] > 0
