@@ -388,7 +388,8 @@ struct lb_ctx {
   int fusedK = 0;            // sub-steps per fused block of the uniform sub-cycle (0: one launch per sub-step)
   int fusedK_max = 0;        // the block length the context supports (0: none)
   FusedBufs fb{};
-  bool resident = false;     // the uniform sub-cycle runs in one launch of co-resident workgroups
+  bool resident = false;     // the sub-cycle runs in one launch of co-resident workgroups
+  bool resident_own = false; // each on a CU of its own
   const FusedSeg* rseg = nullptr;
   uint64_t md_wait = RES_WAIT;   // longest wait inside it, ticks of the 100 MHz clock
   int64_t steps = 0;
@@ -598,7 +599,8 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
   if (c->fusedK > 0 && !D.mdtape)
     launch_md_cycle_fused(D, c->fb, c->pk.nseg, c->nslots, c->nrep, c->n_sub, c->fusedK, st);
   else if (resident)
-    launch_md_cycle_resident(D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, c->n_sub, c->mts, none, c->md_wait, st);
+    launch_md_cycle_resident(D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, c->n_sub, c->mts, none, c->md_wait,
+                             c->resident_own, st);
   else if (c->mts > 0) launch_md_cycle_mts(D, c->nslots, c->n_sub, c->mts, st);
   else launch_md_cycle(D, c->nslots, c->nrep, c->n_sub, none, st, false, c->any_constrained);
   if (resident) sweep_side();
@@ -872,6 +874,9 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
     c->fusedK = 0;
     c->resident = !rigid && c->pk.nrseg > 0 && c->pk.nrseg <= RES_MAX_WG &&
                   c->n_sub >= RES_MIN_SUB;
+    // the sweep reads and writes every population once
+    c->resident_own = c->pk.nrseg <= RES_OWN_WG &&
+                      2.0 * Q * (double)elem_size(d) * (double)c->pk.nodes <= RES_OWN_BYTES * (c->n_sub + c->mts);
     // a shorter limit sends every wait to the redo (tests)
     if (const char* e = std::getenv("LBMD_MD_WAIT_TICKS")) c->md_wait = std::strtoull(e, nullptr, 10);
   }
@@ -1165,7 +1170,8 @@ int md_relax(lb_ctx* c, int nsub_total, double gamma_relax) {
       launch_nbr_build(c->D, c->nslots, c->nrep, c->s);
       launch_md_begin(c->D, c->nrep, c->s);
       launch_md_start(c->D, c->nslots, ov, c->s);
-      launch_md_cycle_resident(c->D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, n, 0, ov, c->md_wait, c->s);
+      launch_md_cycle_resident(c->D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, n, 0, ov, c->md_wait,
+                               c->resident_own, c->s);
     } else {
       launch_md_cycle(c->D, c->nslots, c->nrep, n, ov, c->s, true, c->any_constrained);
     }

@@ -267,14 +267,26 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
 // (8000 beads of a walk that was not relaxed, step by step: 3.1 ms, as with one
 // launch per sub-step; the one workgroup takes 94).  At n_sub = 1 and 2 the
 // single launches cost no more.
+// own: every workgroup takes a CU for itself.  An exchange beside the sweep's
+// waves on the same CU takes 2.4 to 2.8 us, on a CU of its own 1.4 to 1.8 (alone
+// 1.0 to 1.3).  That is worth while the beads outlast the sweep, which then has
+// fewer CUs: 400 beads on 128^3 0.26 against 0.28 ms per step, 32 x 100 beads
+// 0.34 against 0.38, 2000 beads with M = 5 on 256 x 256 x 128 (FP32) 0.35 against
+// 0.47; but 4000 beads there in FP64 0.64 against 0.60, 8000 beads on 512 x 256 x
+// 256 1.60 against 1.11, 64 uneven replicas (432 segments) 1.28 against 0.96.  So:
+// up to RES_OWN_WG segments (half of the CUs; two contexts fit beside each
+// other), and at most RES_OWN_BYTES of populations per sub-step (about what the
+// sweep moves in that time).
 constexpr int XRING = 6;                       // slots of xring
 constexpr int RES_OWN = 32;
 constexpr int RES_BLOCK = 10;
 constexpr int RES_MAX_WG = 512;
 constexpr int RES_MIN_SUB = 3;
+constexpr int RES_OWN_WG = 128;
+constexpr double RES_OWN_BYTES = 16e6;
 constexpr uint64_t RES_PLACE = 200000;   // 2 ms
 void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int nseg, int nslots, int n_sub,
-                              int mts, const MdOverride& ov, uint64_t wait, hipStream_t s);
+                              int mts, const MdOverride& ov, uint64_t wait, bool own, hipStream_t s);
 void launch_md_gate(const Dev& d, int nseg, hipStream_t s);
 // Noise of one sub-cycle into d.xi, for the step counter + step_offset.
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s);

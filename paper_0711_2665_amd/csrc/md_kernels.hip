@@ -2801,8 +2801,11 @@ __device__ __attribute__((noinline)) void res_rescue(const ResArgs* a) {
   md_redo<RES_WG, MTS>(d, R, P, seg.rep, a->ang, a->nslots, 0, a->n_sub, a->mts, sh.dead[0], sh.dead[1]);
 }
 
-template <bool MTS>
-__global__ __launch_bounds__(RES_WG, 6) void k_md_resident(ResArgs a) {
+// OWN: a workgroup takes the registers of a whole CU (8 waves of 256), so that
+// no wave of the sweep shares it; else three fit beside each other.
+template <bool MTS, bool OWN>
+__global__ __launch_bounds__(RES_WG, OWN ? 2 : 6) void k_md_resident(ResArgs a) {
+  if (OWN) asm volatile("" ::: "v255");
   ResShared& sh = *reinterpret_cast<ResShared*>(res_lds);
   const FusedSeg seg = load_uniform(&a.segs[blockIdx.x]);
   const Rep& R = a.d.reps[seg.rep];
@@ -2836,10 +2839,12 @@ void launch_md_gate(const Dev& d, int nseg, hipStream_t s) {
 }
 
 void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int nseg, int nslots, int n_sub,
-                              int mts, const MdOverride& ov, uint64_t wait, hipStream_t s) {
+                              int mts, const MdOverride& ov, uint64_t wait, bool own, hipStream_t s) {
   if (nslots <= 0 || n_sub <= 0 || nseg <= 0) return;
-  hipLaunchKernelGGL(mts > 0 ? k_md_resident<true> : k_md_resident<false>, dim3((unsigned)nseg), dim3(RES_WG),
-                     sizeof(ResShared), s, (ResArgs{d, ang, seg, nslots, n_sub, mts, ov, wait}));
+  const auto k = mts > 0 ? (own ? k_md_resident<true, true> : k_md_resident<true, false>)
+                         : (own ? k_md_resident<false, true> : k_md_resident<false, false>);
+  hipLaunchKernelGGL(k, dim3((unsigned)nseg), dim3(RES_WG), sizeof(ResShared), s,
+                     (ResArgs{d, ang, seg, nslots, n_sub, mts, ov, wait}));
 }
 
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s) {
