@@ -105,12 +105,50 @@ Packing packing(const lb_desc* d, int nrep) {
   return pk;
 }
 
+// slots of the exchange memory (without a resident cycle its first holds velocities)
+int xring_slots(const Packing& pk) { return pk.nrseg <= RES_MAX_WG ? XRING : 1; }
+
 struct WorkLayout {
   size_t ctrl, reps, tiles, otiles, slot_rep, head, next, base, touched, nbr, ncnt, rb, rmid0, rmid1, ref, part, xi,
       tX, ccount, cbuf, rbin, cst, wlinks, ledger, lpart, lsp, fseg, rmS, vS, JS, fang, redo, rseg, xring, xflag, rsync;
   size_t nbuckets;
   size_t total;
 };
+
+// The table of the resident sub-cycle: entry b is the segment of workgroup b, or
+// one with rep = -1.  Workgroups go to the XCDs in turn, so entries b with the
+// same b % XCDS share one: chains of up to RES_XCD segments take one XCD
+// (the least loaded, from one that depends on the seed, so that contexts side
+// by side choose different ones), longer ones every XCD in runs of neighbours.
+std::vector<FusedSeg> res_place(const lb_desc* d, int nrep, const Packing& pk) {
+  std::vector<FusedSeg> out;
+  if (pk.nrseg <= 0 || pk.nrseg > RES_MAX_WG) return out;
+  std::vector<FusedSeg> bin[XCDS];
+  std::vector<int> order(nrep), first(nrep);
+  for (int r = 0, id = 0; r < nrep; ++r) {
+    order[r] = r;
+    first[r] = id;
+    id += (d[r].nb + RES_OWN - 1) / RES_OWN;
+  }
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return d[a].nb > d[b].nb; });
+  const int start = pk.nrseg > 1 ? (int)(((uint32_t)d[0].seed * 2654435761u) >> 29) : 0;
+  for (int r : order) {
+    const int ng = (d[r].nb + RES_OWN - 1) / RES_OWN;
+    int least = start;
+    for (int k = 1; k < XCDS; ++k)
+      if (bin[(start + k) % XCDS].size() < bin[least].size()) least = (start + k) % XCDS;
+    for (int g = 0; g < ng; ++g)
+      bin[ng > RES_XCD ? (int)((long)g * XCDS / ng) : least].push_back(
+          FusedSeg{r, g * RES_OWN, std::min((g + 1) * RES_OWN, (int)d[r].nb), first[r] + g});
+  }
+  size_t rows = 0;
+  for (const auto& b : bin) rows = std::max(rows, b.size());
+  out.assign(rows * XCDS, FusedSeg{-1, 0, 0, 0});
+  for (int x = 0; x < XCDS; ++x)
+    for (size_t k = 0; k < bin[x].size(); ++k) out[k * XCDS + x] = bin[x][k];
+  while (out.back().rep < 0) out.pop_back();
+  return out;
+}
 
 WorkLayout work_layout(const lb_desc* d, int nrep, const Packing& pk) {
   WorkLayout w;
@@ -153,9 +191,9 @@ WorkLayout work_layout(const lb_desc* d, int nrep, const Packing& pk) {
   w.fang = take(sizeof(double) * 9 * ns);
   w.redo = take(sizeof(int) * R);
   w.rsync = take(sizeof(uint32_t) * 2 * R);
-  w.rseg = take(sizeof(FusedSeg) * (size_t)(pk.nrseg > 0 ? pk.nrseg : 1));
-  w.xring = take(sizeof(uint64_t) * XRING * 2 * 3 * ns);
-  w.xflag = take(sizeof(uint64_t) * 2 * 2 * (size_t)(pk.nrseg > 0 ? pk.nrseg : 1));
+  w.rseg = take(sizeof(FusedSeg) * std::max<size_t>(res_place(d, nrep, pk).size(), 1));
+  w.xring = take(sizeof(uint64_t) * xring_slots(pk) * 2 * 3 * ns);
+  w.xflag = take(sizeof(uint64_t) * XFLAG * 2 * (size_t)(pk.nrseg > 0 ? pk.nrseg : 1));
   w.total = o;
   return w;
 }
@@ -391,6 +429,7 @@ struct lb_ctx {
   bool resident = false;     // the sub-cycle runs in one launch of co-resident workgroups
   bool resident_own = false; // each on a CU of its own
   const FusedSeg* rseg = nullptr;
+  int nrtab = 0;             // its entries
   uint64_t md_wait = RES_WAIT;   // longest wait inside it, ticks of the 100 MHz clock
   int64_t steps = 0;
   // second stream for the sweep over the nodes without bead force, which
@@ -599,7 +638,7 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
   if (c->fusedK > 0 && !D.mdtape)
     launch_md_cycle_fused(D, c->fb, c->pk.nseg, c->nslots, c->nrep, c->n_sub, c->fusedK, st);
   else if (resident)
-    launch_md_cycle_resident(D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, c->n_sub, c->mts, none, c->md_wait,
+    launch_md_cycle_resident(D, c->fb.ang, c->rseg, c->nrtab, c->pk.nrseg, c->nslots, c->n_sub, c->mts, none, c->md_wait,
                              c->resident_own, st);
   else if (c->mts > 0) launch_md_cycle_mts(D, c->nslots, c->n_sub, c->mts, st);
   else launch_md_cycle(D, c->nslots, c->nrep, c->n_sub, none, st, false, c->any_constrained);
@@ -863,6 +902,7 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   // coupled step, beside the spreading, with a skin wide enough that a
   // step's motion rarely forces a rebuild inside the sub-cycle
   c->step_lists = c->nslots > 0;
+  std::vector<FusedSeg> rsegs;
   // the fused sub-cycle (uniform sub-steps, harmonic bonds) is available in
   // blocks of up to FUSED_K sub-steps; it is off until asked for
   {
@@ -875,7 +915,9 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
     c->resident = !rigid && c->pk.nrseg > 0 && c->pk.nrseg <= RES_MAX_WG &&
                   c->n_sub >= RES_MIN_SUB;
     // the sweep reads and writes every population once
-    c->resident_own = c->pk.nrseg <= RES_OWN_WG &&
+    rsegs = res_place(d, nrep, c->pk);
+    c->nrtab = (int)rsegs.size();
+    c->resident_own = c->pk.nrseg <= RES_OWN_WG && c->nrtab <= RES_OWN_XCD * XCDS &&
                       2.0 * Q * (double)elem_size(d) * (double)c->pk.nodes <= RES_OWN_BYTES * (c->n_sub + c->mts);
     // a shorter limit sends every wait to the redo (tests)
     if (const char* e = std::getenv("LBMD_MD_WAIT_TICKS")) c->md_wait = std::strtoull(e, nullptr, 10);
@@ -988,9 +1030,6 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
     for (int a = 0; a < d[r].nb; a += FUSED_OWN) segs.push_back(FusedSeg{r, a, std::min(a + FUSED_OWN, d[r].nb), 0});
   if (!segs.empty())
     acc(hipMemcpyAsync(w + c->wl.fseg, segs.data(), sizeof(FusedSeg) * segs.size(), hipMemcpyHostToDevice, s));
-  std::vector<FusedSeg> rsegs;
-  for (int r = 0; r < nrep; ++r)
-    for (int a = 0; a < d[r].nb; a += RES_OWN) rsegs.push_back(FusedSeg{r, a, std::min(a + RES_OWN, d[r].nb), 0});
   if (!rsegs.empty())
     acc(hipMemcpyAsync(w + c->wl.rseg, rsegs.data(), sizeof(FusedSeg) * rsegs.size(), hipMemcpyHostToDevice, s));
   launch_fill_i32(D.redo, nrep, -1, s);
@@ -1008,8 +1047,8 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   acc(hipMemsetAsync(b->beads, 0, sizeof(double) * 15 * ns, s));
   acc(hipMemsetAsync(D.ctrl, 0, sizeof(Ctrl), s));
   // no tag of this context: the memory may hold the exchanges of an earlier one
-  acc(hipMemsetAsync(D.xring, 0, sizeof(uint64_t) * XRING * 2 * 3 * ns, s));
-  acc(hipMemsetAsync(D.xflag, 0, sizeof(uint64_t) * 2 * 2 * (size_t)std::max<long>(c->pk.nrseg, 1), s));
+  acc(hipMemsetAsync(D.xring, 0, sizeof(uint64_t) * xring_slots(c->pk) * 2 * 3 * ns, s));
+  acc(hipMemsetAsync(D.xflag, 0, sizeof(uint64_t) * XFLAG * 2 * (size_t)std::max<long>(c->pk.nrseg, 1), s));
   launch_fill_i32(D.head, nodes, -1, s);
   launch_fill_f64(D.ref, 3L * (long)ns, 1e300, s);
   launch_fill_f64(D.rbin, 3L * (long)ns, 1e300, s);
@@ -1170,7 +1209,7 @@ int md_relax(lb_ctx* c, int nsub_total, double gamma_relax) {
       launch_nbr_build(c->D, c->nslots, c->nrep, c->s);
       launch_md_begin(c->D, c->nrep, c->s);
       launch_md_start(c->D, c->nslots, ov, c->s);
-      launch_md_cycle_resident(c->D, c->fb.ang, c->rseg, c->pk.nrseg, c->nslots, n, 0, ov, c->md_wait,
+      launch_md_cycle_resident(c->D, c->fb.ang, c->rseg, c->nrtab, c->pk.nrseg, c->nslots, n, 0, ov, c->md_wait,
                                c->resident_own, c->s);
     } else {
       launch_md_cycle(c->D, c->nslots, c->nrep, n, ov, c->s, true, c->any_constrained);

@@ -118,10 +118,11 @@ struct Dev {
   uint32_t* cst;    // per replica, 3 rotating words: some bead is farther than CELL_MARGIN
                     // from its binned position at that sub-step (the table is not usable)
   uint32_t cmask;   // buckets - 1 (a power of two minus one)
-  unsigned long long* xring;   // [6][slots][3][2]: positions exchanged inside a resident cycle, each as its
+  unsigned long long* xring;   // [10][slots][3][2]: positions exchanged inside a resident cycle, each as its
                     // bits and its bits XOR the sub-step's tag (slots 0, 1: every sub-step; 2, 3: the
-                    // start of a block; 4, 5: the kicks of the multiple-time-step cycle)
-  unsigned long long* xflag;   // [2][segments][2]: a word per segment at the start of a block, likewise
+                    // kicks of the multiple-time-step cycle; 4, 5: the start of a block; 6 to 9:
+                    // the copies of 0 to 3 for readers on the same XCD)
+  unsigned long long* xflag;   // [3][segments][2]: a word per segment, likewise (0, 1: the start of a block; 2: its XCD)
   uint32_t* rsync;  // [R][2]: per pass of the resident cycle, segments done and the failure bit
   Ctrl* ctrl;
   int* redo;        // per replica: first sub-step the fused sub-cycle leaves to the per-sub-step
@@ -234,7 +235,7 @@ void launch_md_cycle_mts(const Dev& d, int nslots, int n_sub, int M, hipStream_t
 // workgroup that redoes the cycle from that block's start (k_md_redo).
 // Results equal the per-sub-step cycle bit for bit.
 struct FusedSeg {
-  int rep, a, b, pad;
+  int rep, a, b, id;   // id: the segment's number (chains in order, beads ascending)
 };
 struct FusedBufs {
   const FusedSeg* seg;
@@ -254,7 +255,7 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
 // chain segment [a, b) of up to RES_OWN beads for the whole cycle and
 // exchanges the positions its neighbours need through d.xring (see
 // k_md_resident).  Measured per coupled step against one launch per sub-step:
-// 20 beads on 32^3 0.23 against 0.75 ms, 400 beads on 128^3 0.29 against 0.78,
+// 20 beads on 32^3 0.20 against 0.75 ms, 400 beads on 128^3 0.22 against 0.78,
 // 8000 beads on 512 x 256 x 256 (FP32) 1.12 against 1.66, 64 uneven replicas
 // 0.97 against 1.66.
 // Its workgroups wait for each other, so all of them have to be on the GPU at
@@ -270,22 +271,27 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
 // own: every workgroup takes a CU for itself.  An exchange beside the sweep's
 // waves on the same CU takes 2.4 to 2.8 us, on a CU of its own 1.4 to 1.8 (alone
 // 1.0 to 1.3).  That is worth while the beads outlast the sweep, which then has
-// fewer CUs: 400 beads on 128^3 0.26 against 0.28 ms per step, 32 x 100 beads
-// 0.34 against 0.38, 2000 beads with M = 5 on 256 x 256 x 128 (FP32) 0.35 against
-// 0.47; but 4000 beads there in FP64 0.64 against 0.60, 8000 beads on 512 x 256 x
+// fewer CUs: 400 beads on 128^3 0.27 against 0.29 ms per step (0.22 with the
+// exchange within an XCD), 32 x 100 beads 0.34 against 0.38 (0.30), 2000 beads
+// with M = 5 on 256 x 256 x 128 (FP32) 0.35 against 0.47; but 4000 beads there in FP64 0.64 against 0.60, 8000 beads on 512 x 256 x
 // 256 1.60 against 1.11, 64 uneven replicas (432 segments) 1.28 against 0.96.  So:
 // up to RES_OWN_WG segments (half of the CUs; two contexts fit beside each
-// other), and at most RES_OWN_BYTES of populations per sub-step (about what the
-// sweep moves in that time).
-constexpr int XRING = 6;                       // slots of xring
+// other) that leave a quarter of every XCD's CUs to the sweep, and at most
+// RES_OWN_BYTES of populations per sub-step (about what the sweep moves in that
+// time).
+constexpr int XRING = 10;                      // slots of xring
+constexpr int XFLAG = 3;
+constexpr int XCDS = 8;
 constexpr int RES_OWN = 32;
 constexpr int RES_BLOCK = 10;
 constexpr int RES_MAX_WG = 512;
 constexpr int RES_MIN_SUB = 3;
 constexpr int RES_OWN_WG = 128;
+constexpr int RES_OWN_XCD = 24;                // of the 32 CUs of an XCD
+constexpr int RES_XCD = 16;
 constexpr double RES_OWN_BYTES = 16e6;
 constexpr uint64_t RES_PLACE = 200000;   // 2 ms
-void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int nseg, int nslots, int n_sub,
+void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int ntab, int nseg, int nslots, int n_sub,
                               int mts, const MdOverride& ov, uint64_t wait, bool own, hipStream_t s);
 void launch_md_gate(const Dev& d, int nseg, hipStream_t s);
 // Noise of one sub-cycle into d.xi, for the step counter + step_offset.

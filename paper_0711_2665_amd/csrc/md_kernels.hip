@@ -1933,8 +1933,16 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
 // not share: a reader takes the pair when the two words differ by the tag, so
 // it needs no order between them.  Two slots suffice: segments depend on each
 // other symmetrically, so a segment publishes x(s + 2) over x(s) only after
-// it has read x(s + 1) of a segment that has read its x(s).  A round trip
-// between workgroups takes 1.1 us alone, 2.4 us beside a streaming kernel.
+// it has read x(s + 1) of a segment that has read its x(s).
+//
+// Workgroups on one XCD exchange through its L2: a second copy of the
+// positions is written with stores of workgroup scope, which stay there, and a
+// reader takes the copy that suits its owner's XCD (each workgroup publishes
+// its own at the start, so nothing depends on where the hardware puts them).
+// Per exchange, beside a streaming kernel, each workgroup on a CU of its own: 0.8
+// to 0.95 us within an XCD, 1.4 to 1.8 through memory (alone 0.69 and 1.0 to
+// 1.3).  The host orders the segments so that a short chain lands on one XCD
+// (res_place).
 //
 // A wave issues one dependent FP64 instruction in about five cycles, so a
 // sub-step's time is the longest instruction count of a wave between two
@@ -1973,7 +1981,7 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
 // stages: kicks of the slow forces (pairs, walls, field) at r, and between two
 // of them Mb = n_sub / M sub-steps of the bonded forces.  Pair partners that are
 // no chain neighbours exchange positions for the kicks only, so those travel in
-// slots of their own (4, 5, by the kick's parity: the argument above holds
+// slots of their own (2, 3, by the kick's parity: the argument above holds
 // for the kicks alone, and for every stage between chain neighbours).  The
 // lists are checked at the kicks, and a block is a kick and the sub-steps up
 // to the next, so the second pass takes any displacement.  2000 beads, M = 5,
@@ -2029,6 +2037,8 @@ struct ResShared {
   int wbead[RES_OWN];
   int fld[RES_OWN];                            // in the pore channel
   int rslot[RES_IDX - RES_OWN];                // bead slot of remote local index RES_OWN + k, -1: none
+  uint8_t rnear[RES_IDX - RES_OWN];            // its owner runs on this XCD
+  int links;                                   // bit 0: some owner runs on another XCD, bit 1: on this one
   int nrem;
   int dead[2];                                 // by parity of the sub-step
   int lost;                                    // a set-up failed
@@ -2055,6 +2065,12 @@ __device__ inline unsigned long long res_load(const unsigned long long* p) {
 __device__ inline void res_store(unsigned long long* p, unsigned long long v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// A store that stays in this XCD's L2, where an agent-scope load of another CU
+// of the XCD finds it (it misses the L1s only).
+__device__ inline void res_store_near(unsigned long long* p, unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ inline uint32_t res_xcd() { return __builtin_amdgcn_s_getreg(20 | 3 << 11); }   // HW_REG_XCC_ID, 4 bits
 
 // Bond vectors u (first) and w (second), cross product n, its length s and
 // c = u.w of the angle at (ra, rb, rc): the first operations of
@@ -2095,7 +2111,7 @@ __device__ inline void res_angle_d(const ResAngle& A, int a, double& d1, double&
 // while some workgroup of the launch has not started: another context's cycle
 // may hold its place and wait for one that this cycle holds).
 __device__ inline bool res_poll(const unsigned long long* o, uint64_t tag, const uint32_t* word, const Ctrl* ctrl,
-                                uint64_t wait, unsigned long long& val) {
+                                uint64_t wait, int nseg, unsigned long long& val) {
   unsigned long long w1;
   val = res_load(o);
   w1 = res_load(o + 1);
@@ -2109,7 +2125,7 @@ __device__ inline bool res_poll(const unsigned long long* o, uint64_t tag, const
       const uint64_t dt = wall_clock64() - t0;
       if ((__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & RES_FAIL) || dt >= wait ||
           (dt >= RES_PLACE &&
-           __hip_atomic_load(&ctrl->placed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x))
+           __hip_atomic_load(&ctrl->placed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)nseg))
         return false;
     }
   }
@@ -2119,7 +2135,7 @@ __device__ inline bool res_poll(const unsigned long long* o, uint64_t tag, const
 // workgroup's decision.
 template <bool BLOCKS, bool MTS>
 __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const Rep& R, const MdParams& P, ResShared& sh,
-                                        int nslots, int n_sub, int mts, uint64_t wait) {
+                                        int nslots, int nseg, int n_sub, int mts, uint64_t wait) {
   const int rep = seg.rep;
   const int Mb = MTS ? n_sub / mts : 0;          // sub-steps between two kicks
   const int end = MTS ? n_sub + mts + 1 : n_sub; // stages; MTS: stage s is a kick where Mb + 1 divides it
@@ -2168,12 +2184,16 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     sh.pos[0][i][c] = x;
   }
   if (t < 2) sh.dead[t] = 0;
+  const int g0 = seg.id - p0 / RES_OWN;          // the replica's first segment
   if (t == 0) {
     sh.lost = 0;
     sh.owner = 0;
     if (!BLOCKS) {
       __hip_atomic_fetch_add(&d.ctrl->placed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (blockIdx.x == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)n_sub);
+      if (seg.id == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)n_sub);
+      const unsigned long long w = res_xcd();
+      res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id, w);
+      res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id + 1, w ^ tag0);
     }
     if (!BLOCKS && d.rb[4 * rep] != 0u) lose();  // the lists are not valid at the start
     if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & RES_FAIL) sh.lost = 1;
@@ -2191,9 +2211,9 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
   const unsigned long long* xb = nullptr;
   const uint64_t tagb = tag0 + (uint64_t)s0 * TAG + MARK;
   if (BLOCKS && (s0 > 0 || fresh)) {
-    unsigned long long* xw = d.xring + (size_t)(2 + (blk & 1)) * 6 * nslots;
+    unsigned long long* xw = d.xring + (size_t)(4 + (blk & 1)) * 6 * nslots;
     xb = xw;
-    unsigned long long* words = d.xflag + (size_t)2 * (blk & 1) * gridDim.x;
+    unsigned long long* words = d.xflag + (size_t)2 * (blk & 1) * nseg;
     if (mine) {
       const unsigned long long bits = (unsigned long long)__double_as_longlong(x);
       res_store(xw + ((size_t)slot * 3 + c) * 2, bits);
@@ -2222,16 +2242,15 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     const int all_near = __syncthreads_and(near ? 1 : 0), any_need = __syncthreads_or(need ? 1 : 0);
     if (t == 0) {
       const unsigned long long w = (all_near ? 1ull : 0ull) | (any_need ? 2ull : 0ull);
-      res_store(words + 2 * blockIdx.x, w);
-      res_store(words + 2 * blockIdx.x + 1, w ^ tagb);
+      res_store(words + 2 * seg.id, w);
+      res_store(words + 2 * seg.id + 1, w ^ tagb);
     }
     // every segment's word
-    const int g0 = (int)blockIdx.x - p0 / RES_OWN;
     bool table = true;
     need = false;
     for (int k = t; k < (int)ng; k += RES_WG) {
       unsigned long long w = 0;
-      if (!res_poll(words + 2 * (g0 + k), tagb, word, d.ctrl, wait, w)) { lose(); break; }
+      if (!res_poll(words + 2 * (g0 + k), tagb, word, d.ctrl, wait, nseg, w)) { lose(); break; }
       table = table && (w & 1ull);
       need = need || (w & 2ull);
     }
@@ -2274,7 +2293,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
             double y[3];
             for (int a = 0; a < 3 && ok; ++a) {
               unsigned long long w = 0;
-              ok = res_poll(xb + ((size_t)sl * 3 + a) * 2, tagb, word, d.ctrl, wait, w);
+              ok = res_poll(xb + ((size_t)sl * 3 + a) * 2, tagb, word, d.ctrl, wait, nseg, w);
               y[a] = __longlong_as_double((long long)w);
             }
             if (ok) partner(sl, y);
@@ -2286,7 +2305,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         const int m = min(RES_TILE, nb - base);
         for (int k = t; k < 3 * m && ok; k += RES_WG) {
           unsigned long long w = 0;
-          ok = res_poll(xb + ((size_t)(so + base + k / 3) * 3 + k % 3) * 2, tagb, word, d.ctrl, wait, w);
+          ok = res_poll(xb + ((size_t)(so + base + k / 3) * 3 + k % 3) * 2, tagb, word, d.ctrl, wait, nseg, w);
           sh.h.tile[k / 3][k % 3] = __longlong_as_double((long long)w);
         }
         if (!ok) lose();
@@ -2318,7 +2337,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
   const int cnt = lb >= n ? 0 : (BLOCKS && fresh ? min(sh.ncand[lb], MAXNBR) : d.ncnt[so + p0 + lb]);
   if (t < n)
     for (int a = 0; a < 3; ++a) sh.ref[t][a] = BLOCKS && fresh ? sh.pos[sp][t][a] : d.ref[3 * (so + p0 + t) + a];
-  if (t == 0) sh.nrem = 0;
+  if (t == 0) { sh.nrem = 0; sh.links = 0; }
   for (int k = t; k < RES_IDX - RES_OWN; k += RES_WG) {
     // chain beads a - 2, a - 1, b, b + 1 first
     const int q = k < 2 ? p0 - 2 + k : seg.b + (k - 2);
@@ -2374,13 +2393,23 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     }
     sh.lst[lb][LL * m + ll] = (uint8_t)(li >= 0 ? li : 0);   // -1 only when lost
   }
+  // which remote beads are exchanged within this XCD
+  for (int k = t; k < RES_HALO + min(sh.nrem, RES_REM); k += RES_WG) {
+    const int sl = sh.rslot[k];
+    unsigned long long w = 0;
+    if (sl >= 0 && !res_poll(d.xflag + 4 * (size_t)nseg + 2 * (g0 + (sl - so) / RES_OWN), tag0, word, d.ctrl, wait, nseg, w))
+      lose();
+    const bool near = w == (unsigned long long)res_xcd();
+    sh.rnear[k] = near;
+    if (sl >= 0) atomicOr(&sh.links, near ? 2 : 1);
+  }
   for (int k = t; k < 3 * (RES_HALO + min(sh.nrem, RES_REM)); k += RES_WG) {
     const int sl = sh.rslot[k / 3];
     double y = 0.0;
     if (sl >= 0) {
       if (fresh) {
         unsigned long long w = 0;
-        if (!res_poll(xb + ((size_t)sl * 3 + k % 3) * 2, tagb, word, d.ctrl, wait, w)) lose();
+        if (!res_poll(xb + ((size_t)sl * 3 + k % 3) * 2, tagb, word, d.ctrl, wait, nseg, w)) lose();
         y = __longlong_as_double((long long)w);
       } else {
         y = d.rmid0[3 * sl + k % 3];
@@ -2396,29 +2425,35 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
   constexpr int HL = RES_OWN, HR = RES_OWN + 2;  // local indices of a - 2 and b
   // local index of chain bead a + j, -2 <= j <= n + 1
   auto at = [&](int j) { return j < 0 ? HL + 2 + j : (j < n ? j : HR + (j - n)); };
-  const bool multi = n < nb;                     // other segments exist
+  // no lane writes the angles and bonds beyond the chain's ends
+  if (t < n + 2 && !(p0 - 1 + t >= 1 && p0 - 1 + t <= nb - 2)) {
+    sh.kp[t] = 0.0;
+    for (int a = 0; a < 3; ++a) sh.dd[0][t][a] = sh.dd[1][t][a] = 0.0;
+  }
+  if (t <= n && (P.constrained || p0 + t == 0 || p0 + t == nb))
+    for (int a = 0; a < 3; ++a) sh.bnd[t][a] = 0.0;
+  const int links = sh.links;                    // 0: no other segment needs this one's positions
   const size_t half = (size_t)6 * nslots;        // words of one slot of the ring
   const bool noisy = P.sig != 0.0;
   const uint64_t tags = tag0 + (uint64_t)s0 * TAG;
   __builtin_amdgcn_s_setprio(2);
   // Each kind of wave has a loop of its own (its registers then hold only
-  // what it needs), with the same two barriers per sub-step.  The test of
-  // sh.dead is uniform: sub-step s writes dead[s & 1] before its second
-  // barrier only, and s + 2 writes it again after two more.  q: stages since
-  // the last kick (MTS).
+  // what it needs), with the same two barriers per sub-step.  A failure at
+  // sub-step s is seen before the first barrier of s + 1, by all waves: s writes
+  // dead[s & 1] before its second barrier, s + 2 after the first of s + 1 (the
+  // load is in flight with the sub-step's others; a test after the second
+  // barrier would wait for it).  q: stages since the last kick (MTS).
   if (wave < 2) {
     // ---- angles; the sum
     const int k = t / 3, ka = t % 3;             // component ka of the angle centred at a - 1 + k
     const bool ang = k < n + 2 && p0 - 1 + k >= 1 && p0 - 1 + k <= nb - 2;
     const int j0 = ang ? at(k - 2) : 0, j1 = ang ? at(k - 1) : 0, j2 = ang ? at(k) : 0;
-    const bool bm = !P.constrained && p > 0, bp = !P.constrained && p < nb - 1;
-    const bool am = p - 1 >= 1 && p - 1 <= nb - 2, ac = p >= 1 && p <= nb - 2, ap = p + 1 >= 1 && p + 1 <= nb - 2;
     double* tape = mine && d.mdtape ? d.mdtape + (size_t)p * 6 + c : nullptr;
     unsigned long long* ring = d.xring + ((size_t)slot * 3 + c) * 2;
     uint64_t tag = tags;
     int q = 0, o = MTS ? s0 / (Mb + 1) : 0;
     for (int s = s0; s < s1; ++s) {
-      const int cb = s & 1;
+      const int cb = s & 1, was = sh.dead[cb ^ 1];
       const bool last = s == end - 1;
       const bool kick = MTS && q == 0;
       if (MTS && q++ == Mb) { q = 0; ++o; }      // of stage s + 1
@@ -2430,9 +2465,11 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         sh.dd[0][k][ka] = d1;
         sh.dd[1][k][ka] = d2;
       }
+      if (__builtin_amdgcn_readfirstlane(was)) { dead = true; break; }
       lds_barrier();
       // every contribution in the fixed order, the kick and the drifts
       if (mine) {
+        // Absent contributions are zeros (F is never -0, which a zero would change).
         const uint32_t pc = *reinterpret_cast<const uint32_t*>(sh.pcnt[i]);
         const int wl = sh.wall[i], fl = sh.fld[i];
         const double xi = noisy ? sh.xi[3 * i + c] : 0.0;
@@ -2443,18 +2480,18 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         const double fb0 = sh.bnd[i][c], fb1 = sh.bnd[i + 1][c];
         double F = 0.0;
         if (!kick) {
-        if (bm) F += fb0;
-        if (bp) F += -fb1;
-        if (am) F += 0.0 + -(kp0 * e2);
-        if (ac) F += 0.0 + -(kp1 * (m1 - m2));
-        if (ap) F += 0.0 + kp2 * q1;
+        F += fb0;
+        F += -fb1;
+        F += -(kp0 * e2);
+        F += -(kp1 * (m1 - m2));
+        F += kp2 * q1;
         }
         if (!MTS || kick) {
-        if ((pc & 0xfefefefeu) == 0u) {          // at most one pair force per lane
-          if (pc & 0xffu) F += f0;
-          if (pc & 0xff00u) F += f1;
-          if (pc & 0xff0000u) F += f2;
-          if (pc & 0xff000000u) F += f3;
+        if (!__any((pc & 0xfefefefeu) != 0u)) {  // at most one pair force per lane
+          F += f0;
+          F += f1;
+          F += f2;
+          F += f3;
         } else {
           bool kept = true;
           for (int l = 0; l < RES_PL; ++l) kept = kept && (int)((pc >> (8 * l)) & 0xffu) <= RES_PH;
@@ -2475,6 +2512,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
             }
           }
         }
+        if (__any((wl & 0xff) != 0))
         for (int m = wl >> 8, m1 = m + (wl & 0xff); m < m1; m += 4) {   // four loads in flight
           const double w0 = sh.wallF[m][c], w1 = sh.wallF[m + 1][c], w2 = sh.wallF[m + 2][c], w3 = sh.wallF[m + 3][c];
           F += w0;
@@ -2505,16 +2543,19 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         }
         if (!last) {
           sh.pos[cb ^ 1][i][c] = x;
-          if (multi) {
-            unsigned long long* w = ring + (MTS && q == 0 ? (4 + (o & 1)) * half : (cb ? 0 : half));
-            const unsigned long long bits = (unsigned long long)__double_as_longlong(x);
+          unsigned long long* w = ring + (MTS && q == 0 ? (2 + (o & 1)) * half : (cb ? 0 : half));
+          const unsigned long long bits = (unsigned long long)__double_as_longlong(x);
+          if (links & 2) {
+            res_store_near(w + 6 * half, bits);
+            res_store_near(w + 6 * half + 1, bits ^ tag);
+          }
+          if (links & 1) {
             res_store(w, bits);
             res_store(w + 1, bits ^ tag);
           }
         }
       }
       lds_barrier();
-      if (sh.dead[cb]) { dead = true; break; }
     }
   } else if (wave >= 6) {
     // ---- pair forces: part [k0, k1) of bead pb's list
@@ -2528,7 +2569,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     }
     int q = 0;
     for (int s = s0; s < s1; ++s) {
-      const int cb = s & 1;
+      const int cb = s & 1, was = sh.dead[cb ^ 1];
       const bool slow = !MTS || q == 0;
       if (MTS && q++ == Mb) q = 0;
       if (pb < n && slow) {
@@ -2549,11 +2590,15 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
           }
           ++hits;
         }
+        if (hits == 0) {
+          double* o = sh.pairF[pl][0][pb];
+          o[0] = 0.0; o[1] = 0.0; o[2] = 0.0;
+        }
         sh.pcnt[pb][pl] = (uint8_t)min(hits, RES_PH + 1);
       }
+      if (__builtin_amdgcn_readfirstlane(was)) { dead = true; break; }
       lds_barrier();
       lds_barrier();
-      if (sh.dead[cb]) { dead = true; break; }
     }
   } else if (wave == 2) {
     // ---- kappa phi of the angle centred at a - 1 + lane
@@ -2561,16 +2606,16 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     const int j0 = ang ? at(lane - 2) : 0, j1 = ang ? at(lane - 1) : 0, j2 = ang ? at(lane) : 0;
     int q = 0;
     for (int s = s0; s < s1; ++s) {
-      const int cb = s & 1;
+      const int cb = s & 1, was = sh.dead[cb ^ 1];
       const bool kick = MTS && q == 0;
       if (MTS && q++ == Mb) q = 0;
       if (ang && !kick) {
         const ResAngle A = res_angle(sh.pos[cb][j0], sh.pos[cb][j1], sh.pos[cb][j2]);
         sh.kp[lane] = A.s == 0.0 ? 0.0 : P.kappa * atan2(A.s, A.c);
       }
+      if (__builtin_amdgcn_readfirstlane(was)) { dead = true; break; }
       lds_barrier();
       lds_barrier();
-      if (sh.dead[cb]) { dead = true; break; }
     }
   } else if (wave == 5) {
     // ---- bonds: the force on a + lane of its bond to a + lane - 1 (the
@@ -2583,7 +2628,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     }
     int q = 0;
     for (int s = s0; s < s1; ++s) {
-      const int cb = s & 1;
+      const int cb = s & 1, was = sh.dead[cb ^ 1];
       const bool kick = MTS && q == 0;
       if (MTS && q++ == Mb) q = 0;
       if (bond && !kick) {
@@ -2597,9 +2642,9 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         for (int a = 0; a < 3; ++a) { const double dd = sh.pos[cb][lane][a] - ref[a]; d2 += dd * dd; }
         if (d2 > P.halfskin2) fail(s);
       }
+      if (__builtin_amdgcn_readfirstlane(was)) { dead = true; break; }
       lds_barrier();
       lds_barrier();
-      if (sh.dead[cb]) { dead = true; break; }
     }
   } else if (wave == 3) {
     // ---- the wall sites of wall_row and the field indicator
@@ -2619,13 +2664,13 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     const uint64_t below = (1ull << lane) - 1ull;
     int q = 0;
     for (int s = s0; s < s1; ++s) {
-      const int cb = s & 1;
+      const int cb = s & 1, was = sh.dead[cb ^ 1];
       const bool slow = !MTS || q == 0;
       if (MTS && q++ == Mb) q = 0;
       if (!slow) {
+        if (__builtin_amdgcn_readfirstlane(was)) { dead = true; break; }
+      lds_barrier();
         lds_barrier();
-        lds_barrier();
-        if (sh.dead[cb]) { dead = true; break; }
         continue;
       }
       int fl = 0;
@@ -2695,9 +2740,9 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         lj_add(P, w[0], w[1], w[2], Fs);
         w[0] = Fs[0]; w[1] = Fs[1]; w[2] = Fs[2];
       }
+      if (__builtin_amdgcn_readfirstlane(was)) { dead = true; break; }
       lds_barrier();
       lds_barrier();
-      if (sh.dead[cb]) { dead = true; break; }
     }
   } else {
     // ---- the noise of the workgroup's beads, one sub-step ahead (up to two
@@ -2712,10 +2757,11 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
       xc = lane + 64 < nx ? xn[lane + 64] : 0.0;
     }
     const int rs0 = lane < 3 * nrem ? sh.rslot[lane / 3] : -1;
+    const bool rn0 = lane < 3 * nrem && sh.rnear[lane / 3];
     uint64_t tag = tags;
     int q = 0, o = MTS ? s0 / (Mb + 1) : 0;
     for (int s = s0; s < s1; ++s) {
-      const int cb = s & 1;
+      const int cb = s & 1, was = sh.dead[cb ^ 1];
       const bool kick = MTS && q == 0;
       if (MTS && q++ == Mb) { q = 0; ++o; }      // of stage s + 1
       tag += TAG;
@@ -2724,6 +2770,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         if (lane + 64 < nx) sh.xi[lane + 64] = xc;
         --left;
       }
+      if (__builtin_amdgcn_readfirstlane(was)) { dead = true; break; }
       lds_barrier();
       if (s < end - 1) {
         if (!kick && left > 0) {
@@ -2731,13 +2778,14 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
           if (lane < nx) xa = xn[lane];
           if (lane + 64 < nx) xc = xn[lane + 64];
         }
-        const unsigned long long* from = d.xring + (MTS && q == 0 ? (4 + (o & 1)) * half : (cb ? 0 : half));
+        const unsigned long long* from = d.xring + (MTS && q == 0 ? (2 + (o & 1)) * half : (cb ? 0 : half));
         const int m1 = 3 * (MTS && q != 0 ? RES_HALO : nrem);   // a sub-step needs the chain neighbours only
         for (int m = lane; m < m1; m += 64) {
           const int sl = m == lane ? rs0 : sh.rslot[m / 3];
           if (sl < 0) continue;
           unsigned long long w = 0;
-          if (!res_poll(from + ((size_t)sl * 3 + m % 3) * 2, tag, word, d.ctrl, wait, w)) {
+          const size_t off = ((size_t)sl * 3 + m % 3) * 2 + ((m == lane ? rn0 : sh.rnear[m / 3] != 0) ? 6 * half : 0);
+          if (!res_poll(from + off, tag, word, d.ctrl, wait, nseg, w)) {
             fail(s);
             break;
           }
@@ -2745,9 +2793,9 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         }
       }
       lds_barrier();
-      if (sh.dead[cb]) { dead = true; break; }
     }
   }
+  if (__builtin_amdgcn_readfirstlane(sh.dead[(s1 - 1) & 1])) dead = true;   // the last sub-step's
   if (dead || !BLOCKS || s1 == end) break;
   }
   __builtin_amdgcn_s_setprio(0);
@@ -2779,7 +2827,7 @@ struct ResArgs {
   Dev d;
   double* ang;
   const FusedSeg* segs;
-  int nslots, n_sub, mts;
+  int nslots, nseg, n_sub, mts;
   MdOverride ov;
   uint64_t wait;
 };
@@ -2794,7 +2842,7 @@ __device__ __attribute__((noinline)) void res_rescue(const ResArgs* a) {
   const FusedSeg seg = load_uniform(&a->segs[blockIdx.x]);
   const Rep& R = d.reps[seg.rep];
   const MdParams P = md_override(load_uniform(&R.mp), a->ov);
-  if (res_pass<true, MTS>(d, seg, R, P, sh, a->nslots, a->n_sub, a->mts, a->wait) != 2) return;
+  if (res_pass<true, MTS>(d, seg, R, P, sh, a->nslots, a->nseg, a->n_sub, a->mts, a->wait) != 2) return;
   // the pass's failure was this workgroup's decision: it alone goes on.  No
   // other stores anything that the redo reads.
   __syncthreads();
@@ -2808,9 +2856,10 @@ __global__ __launch_bounds__(RES_WG, OWN ? 2 : 6) void k_md_resident(ResArgs a) 
   if (OWN) asm volatile("" ::: "v255");
   ResShared& sh = *reinterpret_cast<ResShared*>(res_lds);
   const FusedSeg seg = load_uniform(&a.segs[blockIdx.x]);
+  if (seg.rep < 0) return;                       // fills the table (see res_place)
   const Rep& R = a.d.reps[seg.rep];
   const MdParams P = md_override(load_uniform(&R.mp), a.ov);
-  if (__builtin_expect(res_pass<false, MTS>(a.d, seg, R, P, sh, a.nslots, a.n_sub, a.mts, a.wait) == 0, 1)) return;
+  if (__builtin_expect(res_pass<false, MTS>(a.d, seg, R, P, sh, a.nslots, a.nseg, a.n_sub, a.mts, a.wait) == 0, 1)) return;
   __syncthreads();                               // sh.done and sh.owner are read
   res_rescue<MTS>((const ResArgs*)__builtin_amdgcn_kernarg_segment_ptr());
 }
@@ -2838,13 +2887,13 @@ void launch_md_gate(const Dev& d, int nseg, hipStream_t s) {
   hipLaunchKernelGGL(k_md_gate, dim3(1), dim3(1), 0, s, d.ctrl, (uint32_t)nseg);
 }
 
-void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int nseg, int nslots, int n_sub,
+void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int ntab, int nseg, int nslots, int n_sub,
                               int mts, const MdOverride& ov, uint64_t wait, bool own, hipStream_t s) {
-  if (nslots <= 0 || n_sub <= 0 || nseg <= 0) return;
+  if (nslots <= 0 || n_sub <= 0 || nseg <= 0 || ntab < nseg) return;
   const auto k = mts > 0 ? (own ? k_md_resident<true, true> : k_md_resident<true, false>)
                          : (own ? k_md_resident<false, true> : k_md_resident<false, false>);
-  hipLaunchKernelGGL(k, dim3((unsigned)nseg), dim3(RES_WG), sizeof(ResShared), s,
-                     (ResArgs{d, ang, seg, nslots, n_sub, mts, ov, wait}));
+  hipLaunchKernelGGL(k, dim3((unsigned)ntab), dim3(RES_WG), sizeof(ResShared), s,
+                     (ResArgs{d, ang, seg, nslots, nseg, n_sub, mts, ov, wait}));
 }
 
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s) {
