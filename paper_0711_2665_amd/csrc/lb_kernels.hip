@@ -3,6 +3,7 @@
 // deterministic spreading of the bead reaction onto the lattice, and the
 // fluid reductions.  All kernels serve every replica of a context.
 #include "lbmd_kernels.h"
+#include <algorithm>
 #include "lbmd_lattice.h"
 
 namespace lbmd {
@@ -28,26 +29,136 @@ __global__ void k_fill_f64(double* __restrict__ p, long n, double v) {
   if (k < n) p[k] = v;
 }
 
+// Block-wide sum of NT values (fixed tree order); every thread gets it.
+template <int NT = 256>
+__device__ inline double block_sum(double v, double* sh) {
+  int t = threadIdx.x;
+  __syncthreads();
+  sh[t] = v;
+  __syncthreads();
+  for (int w = NT / 2; w > 0; w >>= 1) {
+    if (t < w) sh[t] += sh[t + w];
+    __syncthreads();
+  }
+  double r = sh[0];
+  __syncthreads();
+  return r;
+}
+
+// ---------------------------------------------------------------------------
+// Wall momentum ledgers (the momentum the wall takes, for the bead-fluid
+// momentum balance of Sec. 2, Eq. (momentum_cons), with walls).
+// Bounce-back: the population f_opp(i)(x) that leaves fluid node x towards a
+// solid upstream node x - c_i returns as f_i(x), so the wall takes
+// 2 f_opp(i)(x) c_opp(i); f from the post-collision array A the step pulls
+// from (f = A + w_i in deviation storage).  Block b of the wall-link list
+// sums its entries (fixed tree order) into lpart[3 b + a]; the replica's block
+// that ends last adds them, in a fixed order, to the cumulative ledger.
+//
+// These blocks are workgroups of the sweep's launch: they read what the sweep
+// reads, and their scattered loads overlap its stream.  As launches of their
+// own, with the one that counts the step, they took 7 of the 18 us of a step
+// of 32^3 (11 now) and 13 of 55 on 201 x 97 x 53.  A step without beads ends
+// with the sweep, so they come first there (in a multiple of the XCD count, so
+// that a tile keeps its XCD: 11 against 13 us on 32^3; last, 201 x 97 x 53 takes
+// 49 against 42).  Beside beads they come last: first, they delay the nodes
+// that share the chip with the beads (64 uneven replicas 0.976 against 0.957 ms).
+//
+// The block sums travel by agent-scope accesses (no cache is written back or
+// invalidated for them): each is stored and acknowledged before its block
+// counts itself in lcount[rep], and read by the block that counts last.
+// ---------------------------------------------------------------------------
+struct LbLedger {
+  const WallLink* links;
+  double* lpart;
+  double* ledger;
+  uint32_t* lcount;       // [R], zero between launches
+  int nblk;
+  int lead;               // they are the launch's first workgroups (lead of them, some without work), 0: its last
+  int tick;               // the launch is a whole step: count it
+};
+
+template <typename T, bool DEV>
+__device__ inline void ledger_block(const T* __restrict__ A, const Rep* __restrict__ reps, const LbLedger& l, int b,
+                                    double* sh) {
+  const WallLink e = l.links[(size_t)b * LEDGER_BLOCK + threadIdx.x];
+  const int rep = __builtin_amdgcn_readfirstlane(e.rep);     // one replica per block
+  const Rep& R = reps[rep];
+  double s[3] = {0.0, 0.0, 0.0};
+  if (e.mask) {
+    const size_t N = (size_t)R.lp.N;
+    const T* Ar = A + (size_t)Q * R.node_off;
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+      if (!((e.mask >> i) & 1u)) continue;
+      const int o = opp(i);
+      double f = (double)Ar[(size_t)o * N + (size_t)e.node];
+      if (DEV) f += wgt(o);
+      const double f2 = 2.0 * f;
+      s[0] += f2 * (double)cx(o);
+      s[1] += f2 * (double)cy(o);
+      s[2] += f2 * (double)cz(o);
+    }
+  }
+  unsigned long long* part = (unsigned long long*)l.lpart;
+  for (int a = 0; a < 3; ++a) {
+    const double v = block_sum(s[a], sh);
+    if (threadIdx.x == 0)
+      __hip_atomic_store(part + 3 * (size_t)b + a, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (threadIdx.x == 0) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    const uint32_t was =
+        __hip_atomic_fetch_add(&l.lcount[rep], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sh[0] = was + 1u == (uint32_t)(R.wl_end - R.wl_begin) ? 1.0 : 0.0;
+  }
+  __syncthreads();
+  if (sh[0] == 0.0) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  for (int a = 0; a < 3; ++a) s[a] = 0.0;
+  for (int k = R.wl_begin + (int)threadIdx.x; k < R.wl_end; k += LEDGER_BLOCK)
+    for (int a = 0; a < 3; ++a)
+      s[a] += __longlong_as_double((long long)__hip_atomic_load(part + 3 * (size_t)k + a, __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT));
+  for (int a = 0; a < 3; ++a) {
+    const double v = block_sum(s[a], sh);
+    if (threadIdx.x == 0) l.ledger[NLEDGER * rep + a] += v;
+  }
+  if (threadIdx.x == 0) __hip_atomic_store(&l.lcount[rep], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ---------------------------------------------------------------------------
 // K1: the sweep over a table of tiles (each tile_nodes consecutive nodes of
 // one replica); workgroups stride over the table.  Solid nodes are skipped,
 // and so are nodes carrying a bead force when skip_forced is set (they are
-// updated by k_spread_lb once the force is known).
+// updated by k_spread_lb once the force is known).  led.nblk more
+// workgroups keep the bounce-back ledger.
 // ---------------------------------------------------------------------------
 template <typename T, bool DEV, int U, bool FL>
 __global__ __launch_bounds__(256) void k_lb(const T* __restrict__ A, T* __restrict__ B,
                                             const Tile* __restrict__ tiles, const Rep* __restrict__ reps,
                                             const uint8_t* __restrict__ flags, const T* __restrict__ force,
-                                            Ctrl* __restrict__ ctrl, int ntiles, int tile_nodes, int skip_forced) {
+                                            Ctrl* __restrict__ ctrl, int ntiles, int tile_nodes, int skip_forced,
+                                            LbLedger led) {
+  if (led.tick && blockIdx.x == 0 && threadIdx.x == 0) ctrl->step += 1u;
+  const int lead = led.lead, nsw = (int)gridDim.x - (lead > 0 ? lead : led.nblk);   // the sweep's workgroups
+  int t = (int)blockIdx.x - lead;
+  if (t < 0 || t >= nsw) {
+    extern __shared__ double lb_sh[];
+    const int b = t < 0 ? (int)blockIdx.x : t - nsw;
+    if (b < led.nblk) ledger_block<T, DEV>(A, reps, led, b, lb_sh);
+    return;
+  }
   // The tile and replica tables are read-only arguments that alias nothing
   // the sweep writes, so their workgroup-uniform reads become scalar loads;
   // the next tile's record is requested before this tile's work.
-  int t = blockIdx.x;
   if (t >= ntiles) return;
   const uint32_t n = FL ? (uint32_t)ctrl->step : 0u;   // LB step: counter word 0 of the fluid noise
   Tile tl = tiles[t];
   for (;;) {
-    const int tn = t + (int)gridDim.x;
+    const int tn = t + nsw;
     const Tile next = tiles[tn < ntiles ? tn : t];
     const Rep& R = reps[tl.rep];
     const long no = R.node_off;
@@ -346,22 +457,6 @@ __global__ __launch_bounds__(256) void k_fluid_sums(const T* __restrict__ A, Dev
   if (threadIdx.x < 4) part[4 * (size_t)blockIdx.x + threadIdx.x] = sh[threadIdx.x][0];
 }
 
-// Block-wide sum of NT values (fixed tree order); every thread gets it.
-template <int NT = 256>
-__device__ inline double block_sum(double v, double* sh) {
-  int t = threadIdx.x;
-  __syncthreads();
-  sh[t] = v;
-  __syncthreads();
-  for (int w = NT / 2; w > 0; w >>= 1) {
-    if (t < w) sh[t] += sh[t + w];
-    __syncthreads();
-  }
-  double r = sh[0];
-  __syncthreads();
-  return r;
-}
-
 // Observables of replica blockIdx.x (one block of 256 threads per replica),
 // out[NOBS * r + k] in the order documented in lbmd.h, for the groups in
 // mask (bit 0: fluid sums from part, 1: bead quantities, 2: wall ledgers,
@@ -454,51 +549,11 @@ __global__ __launch_bounds__(256) void k_observables(Dev d, double* __restrict__
   }
 }
 
-// ---------------------------------------------------------------------------
-// Wall momentum ledgers (the momentum the wall takes, for the bead-fluid
-// momentum balance of Sec. 2, Eq. (momentum_cons), with walls).
-// Bounce-back: the population f_opp(i)(x) that leaves fluid node x towards a
-// solid upstream node x - c_i returns as f_i(x), so the wall takes
-// 2 f_opp(i)(x) c_opp(i); f from the post-collision array A the step pulls
-// from (f = A + w_i in deviation storage).  Block b of the wall-link list
-// sums its entries (fixed tree order) into lpart[3 b + a]; k_step_end then
-// adds each replica's blocks in a fixed order to its cumulative ledger.
-// ---------------------------------------------------------------------------
-template <typename T, bool DEV>
-__global__ __launch_bounds__(LEDGER_BLOCK) void k_ledger_bb(const T* __restrict__ A, Dev d) {
-  __shared__ double sh[LEDGER_BLOCK];
-  const WallLink e = d.wlinks[(size_t)blockIdx.x * LEDGER_BLOCK + threadIdx.x];
-  double s[3] = {0.0, 0.0, 0.0};
-  if (e.mask) {
-    const Rep& R = d.reps[e.rep];
-    const size_t N = (size_t)R.lp.N;
-    const T* Ar = A + (size_t)Q * R.node_off;
-#pragma unroll
-    for (int i = 1; i < Q; ++i) {
-      if (!((e.mask >> i) & 1u)) continue;
-      const int o = opp(i);
-      double f = (double)Ar[(size_t)o * N + (size_t)e.node];
-      if (DEV) f += wgt(o);
-      const double f2 = 2.0 * f;
-      s[0] += f2 * (double)cx(o);
-      s[1] += f2 * (double)cy(o);
-      s[2] += f2 * (double)cz(o);
-    }
-  }
-  for (int a = 0; a < 3; ++a) {
-    const double v = block_sum(s[a], sh);
-    if (threadIdx.x == 0) d.lpart[3 * (size_t)blockIdx.x + a] = v;
-  }
-}
-
 // End of a step, once every kernel of it is done: the first nend workgroups
 // clear the forced bits of the beads' stencils and empty their node lists (the
 // stencils again, rather than the list of forced nodes, so that one thread
-// can close the step in the same launch); then one workgroup per replica adds
-// the step's bounce-back momentum to its ledger, the replica's block sums in
-// a fixed order (strided per thread, then a tree).
-__global__ __launch_bounds__(256) void k_step_end(Dev d, int nslots, int nend, int links) {
-  __shared__ double sh[256];
+// can close the step in the same launch).
+__global__ __launch_bounds__(256) void k_step_end(Dev d, int nslots, int nend) {
   if ((int)blockIdx.x < nend) {
     const int slot = blockIdx.x * blockDim.x + threadIdx.x;
     if (slot < nslots) {
@@ -518,20 +573,10 @@ __global__ __launch_bounds__(256) void k_step_end(Dev d, int nslots, int nend, i
     }
     return;
   }
-  const int rep = (int)blockIdx.x - nend;
-  if (rep == 0 && threadIdx.x == 0) {
+  if (threadIdx.x == 0) {
     d.ctrl->forced_total += d.ctrl->touched;
     d.ctrl->touched = 0u;
     d.ctrl->step += 1u;
-  }
-  if (!links) return;
-  const Rep& R = d.reps[rep];
-  double s[3] = {0.0, 0.0, 0.0};
-  for (int b = R.wl_begin + (int)threadIdx.x; b < R.wl_end; b += 256)
-    for (int a = 0; a < 3; ++a) s[a] += d.lpart[3 * (size_t)b + a];
-  for (int a = 0; a < 3; ++a) {
-    const double v = block_sum(s[a], sh);
-    if (threadIdx.x == 0) d.ledger[NLEDGER * rep + a] += v;
   }
 }
 
@@ -553,28 +598,31 @@ void launch_fill_f64(double* p, long n, double v, hipStream_t s) {
 
 template <typename T, bool DEV, bool FL>
 static void launch_lb_u(const void* A, void* B, const Dev& d, int ntiles, int tile_nodes, int gsz, size_t lds,
-                        int skip_forced, hipStream_t s) {
+                        int skip_forced, int nlb, int lead, int tick, hipStream_t s) {
+  const LbLedger led{d.wlinks, d.lpart, d.ledger, d.lcount, nlb, lead, tick};
   const int per = tile_nodes / 256;         // nodes per thread and tile
   if (per >= 4)
     hipLaunchKernelGGL((k_lb<T, DEV, 4, FL>), dim3((unsigned)gsz), dim3(256), lds, s, (const T*)A, (T*)B, d.tiles,
-                       d.reps, d.flags, (const T*)d.force, d.ctrl, ntiles, tile_nodes, skip_forced);
+                       d.reps, d.flags, (const T*)d.force, d.ctrl, ntiles, tile_nodes, skip_forced, led);
   else if (per >= 2)
     hipLaunchKernelGGL((k_lb<T, DEV, 2, FL>), dim3((unsigned)gsz), dim3(256), lds, s, (const T*)A, (T*)B, d.tiles,
-                       d.reps, d.flags, (const T*)d.force, d.ctrl, ntiles, tile_nodes, skip_forced);
+                       d.reps, d.flags, (const T*)d.force, d.ctrl, ntiles, tile_nodes, skip_forced, led);
   else
     hipLaunchKernelGGL((k_lb<T, DEV, 1, FL>), dim3((unsigned)gsz), dim3(256), lds, s, (const T*)A, (T*)B, d.tiles,
-                       d.reps, d.flags, (const T*)d.force, d.ctrl, ntiles, tile_nodes, skip_forced);
+                       d.reps, d.flags, (const T*)d.force, d.ctrl, ntiles, tile_nodes, skip_forced, led);
 }
 
 template <typename T, bool DEV>
 void launch_lb(const void* A, void* B, const Dev& d, int ntiles, int tile_nodes, int grid, int cap, int skip_forced,
-               bool fluct, hipStream_t s) {
-  int gsz = (grid > 0 && grid < ntiles) ? grid : ntiles;
+               bool fluct, int nlb, int tick, hipStream_t s) {
+  const int lead = skip_forced ? 0 : (nlb + XCDS - 1) / XCDS * XCDS;
+  const int gsz = std::max(nlb, lead) + ((grid > 0 && grid < ntiles) ? grid : ntiles);
   // LDS the kernel does not use, reserved so that at most `cap` sweep
   // workgroups share a CU
-  const size_t lds = cap > 0 ? (size_t)((LDS_PER_CU - LDS_KEEP) / cap) & ~(size_t)1023 : 0;
-  if (fluct) launch_lb_u<T, DEV, true>(A, B, d, ntiles, tile_nodes, gsz, lds, skip_forced, s);
-  else launch_lb_u<T, DEV, false>(A, B, d, ntiles, tile_nodes, gsz, lds, skip_forced, s);
+  size_t lds = cap > 0 ? (size_t)((LDS_PER_CU - LDS_KEEP) / cap) & ~(size_t)1023 : 0;
+  if (nlb > 0) lds = std::max(lds, sizeof(double) * LEDGER_BLOCK);
+  if (fluct) launch_lb_u<T, DEV, true>(A, B, d, ntiles, tile_nodes, gsz, lds, skip_forced, nlb, lead, tick, s);
+  else launch_lb_u<T, DEV, false>(A, B, d, ntiles, tile_nodes, gsz, lds, skip_forced, nlb, lead, tick, s);
 }
 
 template <typename T, bool DEV>
@@ -604,10 +652,9 @@ void launch_spread_lb(const void* A, void* B, const Dev& d, int nslots, int nrep
                      nslots, (int)nspread, nrep);
 }
 
-void launch_step_end(const Dev& d, int nslots, int nrep, int nblk, hipStream_t s) {
+void launch_step_end(const Dev& d, int nslots, hipStream_t s) {
   const unsigned nend = nslots > 0 ? blocks_for(nslots, 256) : 0u;
-  hipLaunchKernelGGL(k_step_end, dim3(nend + (unsigned)(nblk > 0 ? nrep : 1)), dim3(256), 0, s, d, nslots, (int)nend,
-                     nblk > 0 ? 1 : 0);
+  hipLaunchKernelGGL(k_step_end, dim3(nend + 1), dim3(256), 0, s, d, nslots, (int)nend);
 }
 
 template <typename T, bool DEV>
@@ -618,15 +665,12 @@ void launch_observables(const void* A, const Dev& d, int n_otiles, int nrep, dou
   hipLaunchKernelGGL(k_observables, dim3((unsigned)nrep), dim3(256), 0, s, d, out, mask, (const double*)part);
 }
 
-template <typename T, bool DEV>
-void launch_ledger_bb(const void* A, const Dev& d, int nblk, hipStream_t s) {
-  if (nblk > 0) hipLaunchKernelGGL((k_ledger_bb<T, DEV>), dim3((unsigned)nblk), dim3(LEDGER_BLOCK), 0, s, (const T*)A, d);
-}
-
 template void launch_fill_rest<double, false>(void*, long, hipStream_t);
 template void launch_fill_rest<float, true>(void*, long, hipStream_t);
-template void launch_lb<double, false>(const void*, void*, const Dev&, int, int, int, int, int, bool, hipStream_t);
-template void launch_lb<float, true>(const void*, void*, const Dev&, int, int, int, int, int, bool, hipStream_t);
+template void launch_lb<double, false>(const void*, void*, const Dev&, int, int, int, int, int, bool, int, int,
+                                      hipStream_t);
+template void launch_lb<float, true>(const void*, void*, const Dev&, int, int, int, int, int, bool, int, int,
+                                     hipStream_t);
 template void launch_gather<double, false>(const void*, const Dev&, int, int, hipStream_t);
 template void launch_gather<float, true>(const void*, const Dev&, int, int, hipStream_t);
 template void launch_spread<double>(const Dev&, int, hipStream_t);
@@ -636,7 +680,5 @@ template void launch_spread<float>(const Dev&, int, hipStream_t);
 template void launch_observables<double, false>(const void*, const Dev&, int, int, double*, int, double*,
                                                 hipStream_t);
 template void launch_observables<float, true>(const void*, const Dev&, int, int, double*, int, double*, hipStream_t);
-template void launch_ledger_bb<double, false>(const void*, const Dev&, int, hipStream_t);
-template void launch_ledger_bb<float, true>(const void*, const Dev&, int, hipStream_t);
 
 }  // namespace lbmd

@@ -110,7 +110,7 @@ int xring_slots(const Packing& pk) { return pk.nrseg <= RES_MAX_WG ? XRING : 1; 
 
 struct WorkLayout {
   size_t ctrl, reps, tiles, otiles, slot_rep, head, next, base, touched, nbr, ncnt, rb, rmid0, rmid1, ref, part, xi,
-      tX, ccount, cbuf, rbin, cst, wlinks, ledger, lpart, lsp, fseg, rmS, vS, JS, fang, redo, rseg, xring, xflag, rsync;
+      tX, ccount, cbuf, rbin, cst, wlinks, ledger, lpart, lcount, lsp, fseg, rmS, vS, JS, fang, redo, rseg, xring, xflag, rsync;
   size_t nbuckets;
   size_t total;
 };
@@ -183,6 +183,7 @@ WorkLayout work_layout(const lb_desc* d, int nrep, const Packing& pk) {
   w.wlinks = take(sizeof(WallLink) * LEDGER_BLOCK * (size_t)pk.wl_blocks_max);
   w.ledger = take(sizeof(double) * NLEDGER * R);
   w.lpart = take(sizeof(double) * 3 * (size_t)(pk.wl_blocks_max > 0 ? pk.wl_blocks_max : 1));
+  w.lcount = take(sizeof(uint32_t) * R);
   w.lsp = take(sizeof(double) * 3 * ns);
   w.fseg = take(sizeof(FusedSeg) * (size_t)(pk.nseg > 0 ? pk.nseg : 1));
   w.rmS = take(sizeof(double) * 3 * ns);
@@ -545,14 +546,18 @@ void ev_wait(lb_ctx* c, hipStream_t st, hipEvent_t e) {
   acc(hipStreamWaitEvent(st, e, 0));
 }
 
-void sweep_ab(lb_ctx* c, const void* A, void* B, int skip_forced, hipStream_t st) {
+// The sweep from A to B; ledger: with the wall's bounce-back momentum (which
+// reads A); tick: it also counts the step.
+void sweep_ab(lb_ctx* c, const void* A, void* B, int skip_forced, bool ledger, int tick, hipStream_t st) {
   const SweepCfg& w = c->sweep;
+  const int nlb = ledger ? c->wl_blocks : 0;
   if (c->dev)
-    launch_lb<float, true>(A, B, c->D, c->ntiles, w.tile_nodes, w.grid, w.cap, skip_forced, c->any_fluct, st);
+    launch_lb<float, true>(A, B, c->D, c->ntiles, w.tile_nodes, w.grid, w.cap, skip_forced, c->any_fluct, nlb, tick,
+                           st);
   else
-    launch_lb<double, false>(A, B, c->D, c->ntiles, w.tile_nodes, w.grid, w.cap, skip_forced, c->any_fluct, st);
+    launch_lb<double, false>(A, B, c->D, c->ntiles, w.tile_nodes, w.grid, w.cap, skip_forced, c->any_fluct, nlb, tick,
+                             st);
 }
-void sweep(lb_ctx* c, int skip_forced, hipStream_t st) { sweep_ab(c, cur_pops(c), other_pops(c), skip_forced, st); }
 
 // The device view with d.xi at noise slot k (two sub-cycles of noise, one
 // per population parity).
@@ -578,22 +583,16 @@ void ensure_lists(lb_ctx* c, hipStream_t st) {
   c->lists_stale = false;
 }
 
-// The bounce-back ledger of a step that pulls from A, on stream st.
-void ledger_bb(lb_ctx* c, const void* A, hipStream_t st) {
-  if (c->dev) launch_ledger_bb<float, true>(A, c->D, c->wl_blocks, st);
-  else launch_ledger_bb<double, false>(A, c->D, c->wl_blocks, st);
-}
-
 // One fluid-only step on stream st.
 void enqueue_lb_step(lb_ctx* c, hipStream_t st) {
   c->noise_ready = false;
   prof_mark(c, 0, st);
   prof_mark(c, 1, st);
   prof_mark(c, 2, st);
-  sweep(c, 0, st);
+  // the fluid noise's workgroups read the step counter
+  sweep_ab(c, cur_pops(c), other_pops(c), 0, true, c->any_fluct ? 0 : 1, st);
   prof_mark(c, 3, st);
-  ledger_bb(c, cur_pops(c), st);
-  launch_step_end(c->D, 0, c->nrep, c->wl_blocks, st);
+  if (c->any_fluct) launch_step_end(c->D, 0, st);
   c->cur ^= 1;
   prof_next(c);
 }
@@ -619,11 +618,8 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
     ev_wait(c, c->s2, c->prep);
     if (resident) launch_md_gate(D, c->pk.nrseg, c->s2);
     prof_mark(c, 2, c->s2);
-    sweep_ab(c, A, B, 1, c->s2);
+    sweep_ab(c, A, B, 1, true, 0, c->s2);
     prof_mark(c, 3, c->s2);
-    // the wall's bounce-back momentum of this step (reads A, which no kernel
-    // of this step writes)
-    ledger_bb(c, A, c->s2);
     ev_record(c, c->join, c->s2);
   };
   // enqueued before the sub-cycle's many launches, but after the resident
@@ -650,7 +646,7 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
   launch_step_tail(D, c->nslots, c->nrep, c->any_noise ? with_noise_slot(c, c->cur ^ 1).xi : nullptr, c->n_sub, st);
   c->lists_stale = false;
   ev_wait(c, st, c->join);
-  launch_step_end(D, c->nslots, c->nrep, c->wl_blocks, st);
+  launch_step_end(D, c->nslots, st);
   c->noise_ready = c->any_noise;
   prof_next(c);
 }
@@ -1000,6 +996,7 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   D.wlinks = (const WallLink*)(w + c->wl.wlinks);
   D.ledger = (double*)(w + c->wl.ledger);
   D.lpart = (double*)(w + c->wl.lpart);
+  D.lcount = (uint32_t*)(w + c->wl.lcount);
   D.lsp = (double*)(w + c->wl.lsp);
   D.redo = (int*)(w + c->wl.redo);
   D.xring = (unsigned long long*)(w + c->wl.xring);
@@ -1034,6 +1031,7 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
     acc(hipMemcpyAsync(w + c->wl.rseg, rsegs.data(), sizeof(FusedSeg) * rsegs.size(), hipMemcpyHostToDevice, s));
   launch_fill_i32(D.redo, nrep, -1, s);
   launch_fill_f64(D.ledger, (long)NLEDGER * nrep, 0.0, s);
+  launch_fill_i32((int*)D.lcount, nrep, 0, s);
   // rest populations, replica by replica ([19][N_r] from element 19 node_off)
   for (int r = 0; r < nrep; ++r) {
     const size_t off = elem_size(d) * Q * (size_t)c->reps[r].node_off;
@@ -1492,9 +1490,9 @@ int tune_layout(lb_ctx* c, int reps, bool coupled, char* snap, size_t snap_bytes
       } else {
         // into the other array, which the next step overwrites: the state
         // is unchanged
-        for (int j = 0; j < 2; ++j) sweep(c, 0, c->s);
+        for (int j = 0; j < 2; ++j) sweep_ab(c, cur_pops(c), other_pops(c), 0, false, 0, c->s);
         acc(hipEventRecord(e0, c->s));
-        for (int j = 0; j < reps; ++j) sweep(c, 0, c->s);
+        for (int j = 0; j < reps; ++j) sweep_ab(c, cur_pops(c), other_pops(c), 0, false, 0, c->s);
         acc(hipEventRecord(e1, c->s));
       }
       hipError_t e = hipEventSynchronize(e1);

@@ -133,6 +133,7 @@ struct Dev {
   const WallLink* wlinks;
   double* ledger;
   double* lpart;
+  uint32_t* lcount; // [R]: blocks of the replica's wall-link list done in this sweep
   double* lsp;      // per slot [3]: the step's spread-on-solid share of the bead
 };
 
@@ -148,10 +149,13 @@ template <typename T, bool DEV> void launch_fill_rest(void* pops, long N, hipStr
 void launch_fill_i32(int* p, long n, int v, hipStream_t s);
 void launch_fill_f64(double* p, long n, double v, hipStream_t s);
 // fluct: some replica has a fluctuating fluid (selects the sweep variant
-// that draws the fluid noise; replicas without it skip the draw)
+// that draws the fluid noise; replicas without it skip the draw).  The same
+// launch adds the bounce-back momentum of the nlb blocks of the wall-link list
+// to the ledgers, and with tick counts the step (not where workgroups read the
+// counter: with fluct, or beside beads).
 template <typename T, bool DEV>
 void launch_lb(const void* A, void* B, const Dev& d, int ntiles, int tile_nodes, int grid, int cap, int skip_forced,
-               bool fluct, hipStream_t s);
+               bool fluct, int nlb, int tick, hipStream_t s);
 // start: 0, or also open the MD sub-cycle (what k_md_start does: 1 for
 // uniform sub-steps, 2 for the multiple-time-step cycle) after its flags
 template <typename T, bool DEV>
@@ -164,8 +168,9 @@ void launch_spread(const Dev& d, int nslots, hipStream_t s);
 // the first part of the step's tail (launch_step_tail).
 template <typename T, bool DEV>
 void launch_spread_lb(const void* A, void* B, const Dev& d, int nslots, int nrep, hipStream_t s);
-// The last launch of a step (nblk: wall-link list blocks).
-void launch_step_end(const Dev& d, int nslots, int nrep, int nblk, hipStream_t s);
+// The last launch of a coupled step, or of a fluid-only one whose sweep does
+// not count it.
+void launch_step_end(const Dev& d, int nslots, hipStream_t s);
 // Observables into out[NOBS * r + k]; groups of the lb_observables mask
 // (bit 0 fluid sums, 1 bead quantities, 2 wall ledgers, 3 step count); the
 // entries of groups not asked for are left as they are.  part: the fluid
@@ -173,10 +178,6 @@ void launch_step_end(const Dev& d, int nslots, int nrep, int nblk, hipStream_t s
 template <typename T, bool DEV>
 void launch_observables(const void* A, const Dev& d, int n_otiles, int nrep, double* out, int mask, double* part,
                         hipStream_t s);
-// The bounce-back momentum of the links in the wall-link list, per list block
-// (from the populations A the step reads; nblk list blocks).
-template <typename T, bool DEV>
-void launch_ledger_bb(const void* A, const Dev& d, int nblk, hipStream_t s);
 
 // Adjoint pass (one replica, chains of at most MAX_ADJ_BEADS beads).
 constexpr int MAX_ADJ_BEADS = 16384;
