@@ -572,6 +572,352 @@ __global__ __launch_bounds__(AS_WG) void k_adj_sub(Dev d, AdjBufs a, const doubl
   a.gacc[3 * p + 1] = of;
 }
 
+// ---------------------------------------------------------------------------
+// The reversed sub-cycle of a chain of at most ADJ_CHAIN beads in two launches.
+//
+// The force positions of every sub-step are on the tape, and the derivative of
+// the force is linear in the directions: so everything but the product with
+// the directions is done for all sub-steps at once (k_adj_terms), and the
+// serial part (k_adj_chain, one workgroup) is a product with a band per
+// sub-step.  One launch per sub-step (k_adj_sub) evaluated the force law in
+// dual numbers between two directions: 8.5 us of latency each, at 100 beads
+// 0.85 of 1.5 ms per reversed step; the two launches take 14 and 125 us. From
+// 400 beads on, three components per thread spill and the launches are faster.
+//
+// The chain's directions enter as differences of neighbours, D_q = dir_q -
+// dir_{q-1}, as in the dual evaluation (a common translation of the beads then
+// cancels before it is multiplied by the large stiffness terms): the band holds
+// the 3 x 3 blocks of bead p for D_{p-1}, D_p, D_{p+1}, D_{p+2} -- bonds,
+// angles, and pairs of beads at most two links apart -- and the block of its
+// wall sites for dir_p itself.  Other pairs within r_c are kept apart, ADJ_NP
+// per bead and sub-step (a bead with more evaluates them again).
+// ---------------------------------------------------------------------------
+constexpr int AT_BPB = 12;                   // beads per workgroup
+constexpr int AT_WG = 256;
+static_assert(18 * (AT_BPB + 2) <= AT_WG && ADJ_LANES * AT_BPB <= AT_WG && 3 * (AT_BPB + 1) <= AT_WG, "one pass");
+
+struct AdjCoef {
+  double* M;       // [C][12][3 nb]: blocks of the band, 3 diff + k, for component c of bead p at 3 p + c
+  double* W;       // [C][3][3 nb]: walls
+  double* F;       // [C][3 nb]: force
+  int* np;         // [C][nb]: far pairs (-1: more than ADJ_NP), + 256 in the field
+  int* pj;         // [C][ADJ_NP][nb]: partner
+  double* pk;      // [C][ADJ_NP][5][nb]: coef, 2 dcoef / dr^2, separation
+};
+__host__ __device__ inline AdjCoef adj_coef(double* buf, int nb, int C) {
+  AdjCoef k;
+  const size_t n = (size_t)C * nb;
+  k.M = buf;
+  k.W = k.M + 36 * n;
+  k.F = k.W + 9 * n;
+  k.pk = k.F + 3 * n;
+  k.pj = (int*)(k.pk + 5 * ADJ_NP * n);
+  k.np = k.pj + ADJ_NP * n;
+  return k;
+}
+
+// coef of the LJ force coef d and twice its derivative with respect to r^2.
+__device__ inline void lj_coef(const MdParams& P, double r2, double& coef, double& c2) {
+  const double sr2 = P.sig2 / r2, sr6 = sr2 * sr2 * sr2, sr12 = sr6 * sr6;
+  coef = P.eps24 * (2.0 * sr12 - sr6) / r2;
+  c2 = 2.0 * (P.eps24 * (4.0 * sr6 - 14.0 * sr12) / r2) / r2;
+}
+
+// Row blockIdx.y of the coefficients: sub-step s0 - blockIdx.y.
+__global__ __launch_bounds__(AT_WG) void k_adj_terms(Dev d, const int* __restrict__ lok, AdjCoef K,
+                                                     const double* __restrict__ mdt, int nb, int s0) {
+  __shared__ double G[AT_BPB + 2][9][6], Gv[AT_BPB + 2][9];       // angles: columns D1, D2; forces
+  __shared__ double B[AT_BPB + 1][3][3], Bv[AT_BPB + 1][3];       // bond of p0 + q to p0 + q - 1
+  __shared__ double N[AT_BPB][4][6];                              // pairs with p - 2, p - 1, p + 1, p + 2
+  __shared__ double W[AT_BPB][6], S[AT_BPB][3];                   // walls; pair, wall and field forces
+  const Rep& R = d.reps[0];
+  const MdParams P = R.mp;
+  const Geom g = R.g;
+  const int row = blockIdx.y, p0 = blockIdx.x * AT_BPB, t = threadIdx.x;
+  const double* x = mdt + (size_t)(s0 - row) * nb * 6;
+  const bool lists = *lok == 0;
+  for (int k = t; k < AT_BPB * 24; k += AT_WG) (&N[0][0][0])[k] = 0.0;
+  // component cmp of the angle centred at p0 - 1 + r, column k
+  if (t < 18 * (AT_BPB + 2)) {
+    const int r = t / 18, k = t % 18 / 3, cmp = t % 3, cen = p0 - 1 + r;
+    Dd o[3] = {mkd(0.0), mkd(0.0), mkd(0.0)};
+    if (cen >= 1 && cen <= nb - 2) {
+      Dd ra[3], rb[3], rc[3];
+      for (int c = 0; c < 3; ++c) {
+        ra[c] = Dd{x[6 * (size_t)(cen - 1) + c], k == c ? -1.0 : 0.0};
+        rb[c] = Dd{x[6 * (size_t)cen + c], 0.0};
+        rc[c] = Dd{x[6 * (size_t)(cen + 1) + c], k == 3 + c ? 1.0 : 0.0};
+      }
+      angle_dd_comp(P, ra, rb, rc, cmp, o);
+    }
+    for (int w = 0; w < 3; ++w) {
+      G[r][3 * w + cmp][k] = o[w].d;
+      if (k == 0) Gv[r][3 * w + cmp] = o[w].v;
+    }
+  }
+  if (t < 3 * (AT_BPB + 1)) {
+    const int q = t / 3, k = t % 3, p = p0 + q;
+    Dd T[3] = {mkd(0.0), mkd(0.0), mkd(0.0)};
+    if (p > 0 && p < nb) {
+      Dd rp[3], rq[3];
+      for (int c = 0; c < 3; ++c) {
+        rp[c] = Dd{x[6 * (size_t)p + c], k == c ? 1.0 : 0.0};
+        rq[c] = Dd{x[6 * (size_t)(p - 1) + c], 0.0};
+      }
+      bond_dd(P, rp, rq, T);
+    }
+    for (int c = 0; c < 3; ++c) {
+      B[q][c][k] = T[c].d;
+      if (k == 0) Bv[q][c] = T[c].v;
+    }
+  }
+  __syncthreads();
+  // pairs and wall sites, ADJ_LANES lanes per bead
+  const int b = t / ADJ_LANES, lane = t % ADJ_LANES, p = p0 + b;
+  const bool on = b < AT_BPB && p < nb;
+  double xp[3] = {0.0, 0.0, 0.0}, F[3] = {0.0, 0.0, 0.0}, w6[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  int cand = 0;
+  if (on) {
+    for (int c = 0; c < 3; ++c) xp[c] = x[6 * (size_t)p + c];
+    cand = lists ? d.ncnt[p] : nb;
+  }
+  int far = 0;
+  const uint64_t mine = ((1ull << ADJ_LANES) - 1ull) << (t & 63 & ~(ADJ_LANES - 1));
+  int most = cand;                               // over the wave, so that its lanes vote together
+  for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+  for (int i0 = 0; i0 < most; i0 += ADJ_LANES) {
+    const int i = i0 + lane;
+    bool keep = false;
+    double e[3] = {0.0, 0.0, 0.0}, coef = 0.0, c2 = 0.0;
+    int j = p;
+    if (i < cand) j = lists ? d.nbr[(size_t)p * MAXNBR + i] : i;
+    if (j != p) {
+      e[0] = min_image(xp[0] - x[6 * (size_t)j], g.nx);
+      e[1] = min_image(xp[1] - x[6 * (size_t)j + 1], g.ny);
+      e[2] = min_image(xp[2] - x[6 * (size_t)j + 2], g.nz);
+      const double r2 = e[0] * e[0] + e[1] * e[1] + e[2] * e[2];
+      if (r2 < P.rc2) {
+        lj_coef(P, r2, coef, c2);
+        for (int c = 0; c < 3; ++c) F[c] += coef * e[c];
+        const int o = j - p;
+        if (o >= -2 && o <= 2) {
+          double* n = N[b][o < 0 ? o + 2 : o + 1];
+          n[0] = coef + c2 * e[0] * e[0]; n[1] = c2 * e[0] * e[1]; n[2] = c2 * e[0] * e[2];
+          n[3] = coef + c2 * e[1] * e[1]; n[4] = c2 * e[1] * e[2]; n[5] = coef + c2 * e[2] * e[2];
+        } else {
+          keep = true;
+        }
+      }
+    }
+    const uint64_t m = __ballot(keep) & mine;
+    const int at = far + __builtin_popcountll(m & ((1ull << (t & 63)) - 1ull));
+    if (keep && at < ADJ_NP) {
+      const size_t n = (size_t)row * ADJ_NP + at;
+      K.pj[n * nb + p] = j;
+      double* q = K.pk + n * 5 * nb + p;
+      q[0] = coef; q[nb] = c2; q[2 * (size_t)nb] = e[0]; q[3 * (size_t)nb] = e[1]; q[4 * (size_t)nb] = e[2];
+    }
+    far += __builtin_popcountll(m);
+  }
+  bool field = false;
+  if (on && g.wall_axis >= 0) {
+    // the window of wall_terms
+    const double w[3] = {wrapc(xp[0], g.nx), wrapc(xp[1], g.ny), wrapc(xp[2], g.nz)};
+    const int n[3] = {g.nx, g.ny, g.nz};
+    const int a = g.wall_axis, t0 = g.t0, t1 = g.t1, nw = P.whi - P.wlo + 1;
+    int off = g.wall_pos - (int)floor(w[a]);
+    if (off < -2) off += n[a];
+    if (off > 3) off -= n[a];
+    if (off >= P.wlo && off <= P.whi)
+      for (int num = lane; num < nw * nw; num += ADJ_LANES) {
+        const int u1 = (int)floor(w[t1]) + P.wlo + num / nw, u0 = (int)floor(w[t0]) + P.wlo + num % nw;
+        const int v1 = u1 < 0 ? u1 + n[t1] : (u1 >= n[t1] ? u1 - n[t1] : u1);
+        const int v0 = u0 < 0 ? u0 + n[t0] : (u0 >= n[t0] ? u0 - n[t0] : u0);
+        if (v1 >= g.lo1 && v1 <= g.hi1 && v0 >= g.lo0 && v0 <= g.hi0) continue;   // pore node: fluid
+        double e[3];
+        e[a] = w[a] - (double)((int)floor(w[a]) + off);
+        e[t0] = w[t0] - (double)u0;
+        e[t1] = w[t1] - (double)u1;
+        const double r2 = e[0] * e[0] + e[1] * e[1] + e[2] * e[2];
+        if (!(r2 < P.rc2)) continue;
+        double coef, c2;
+        lj_coef(P, r2, coef, c2);
+        for (int c = 0; c < 3; ++c) F[c] += coef * e[c];
+        w6[0] += coef + c2 * e[0] * e[0]; w6[1] += c2 * e[0] * e[1]; w6[2] += c2 * e[0] * e[2];
+        w6[3] += coef + c2 * e[1] * e[1]; w6[4] += c2 * e[1] * e[2]; w6[5] += coef + c2 * e[2] * e[2];
+      }
+    field = P.field_on && in_field(g, xp);
+    if (field && lane == 0) F[a] += P.f_drive;
+  }
+  for (int o = ADJ_LANES / 2; o > 0; o >>= 1) {
+    for (int c = 0; c < 3; ++c) F[c] += __shfl_xor(F[c], o, 64);
+    for (int c = 0; c < 6; ++c) w6[c] += __shfl_xor(w6[c], o, 64);
+  }
+  if (on && lane == 0) {
+    for (int c = 0; c < 3; ++c) S[b][c] = F[c];
+    for (int c = 0; c < 6; ++c) W[b][c] = w6[c];
+    K.np[(size_t)row * nb + p] = (far > ADJ_NP ? 255 : far) + (field ? 256 : 0);
+  }
+  __syncthreads();
+  constexpr int sym[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
+  for (int i = t; i < 16 * 3 * AT_BPB; i += AT_WG) {
+    const int e = i % (3 * AT_BPB), j = i / (3 * AT_BPB), q = e / 3, c = e % 3;
+    if (p0 + q >= nb) continue;
+    const size_t at = (size_t)3 * nb, col = (size_t)3 * (p0 + q) + c;
+    if (j < 12) {
+      const int k = j % 3, z = sym[c][k];
+      double v;
+      if (j < 3) v = G[q][6 + c][k] + N[q][0][z];
+      else if (j < 6) v = B[q][c][k] + G[q][6 + c][3 + k] + G[q + 1][3 + c][k] + N[q][0][z] + N[q][1][z];
+      else if (j < 9) v = G[q + 1][3 + c][3 + k] + G[q + 2][c][k] - B[q + 1][c][k] - N[q][2][z] - N[q][3][z];
+      else v = G[q + 2][c][3 + k] - N[q][3][z];
+      K.M[((size_t)row * 12 + j) * at + col] = v;
+    } else if (j < 15) {
+      K.W[((size_t)row * 3 + (j - 12)) * at + col] = W[q][sym[c][j - 12]];
+    } else {
+      K.F[(size_t)row * at + col] = Bv[q][c] - Bv[q + 1][c] + Gv[q][6 + c] + Gv[q + 1][3 + c] + Gv[q + 2][c] + S[q][c];
+    }
+  }
+}
+
+// The serial part for rows 0 .. rows - 1 (sub-steps s0, s0 - 1, ...): thread t
+// has components t, t + blockDim.x, ... (E of them) of the chain's 3 nb, in
+// registers throughout; the directions are in LDS.  A row's coefficients are
+// requested while the row before is worked on (two rows before for E = 1: a
+// row takes less than a load).  first: the cycle starts here.
+constexpr int AC_WG = 512;                   // 256 registers per thread
+static_assert(3 * ADJ_CHAIN <= 2 * AC_WG, "at most two components per thread");
+struct AdjRow {
+  double m[12], w[3], f, vo, xi;
+  int np;
+};
+template <int E>
+__global__ __launch_bounds__(AC_WG) void k_adj_chain(Dev d, AdjBufs a, AdjCoef K, const double* __restrict__ mdt,
+                                                    const double* __restrict__ upt, int nb, int s0, int rows, int first,
+                                                    double kT) {
+  constexpr int PAD = 6;                         // two beads beyond each end (their coefficients are 0)
+  __shared__ double dir[2][3 * ADJ_CHAIN + 2 * PAD];
+  const MdParams P = d.reps[0].mp;
+  const Geom g = d.reps[0].g;
+  const int t = threadIdx.x, n3 = 3 * nb;
+  const double h = 2.0 * P.hh, gam = P.gamma, de = -h * P.e, domE = h * P.e;
+  const double dcf = (h * P.e) / (P.m * gam) - P.omE / (P.m * gam * gam);
+  const double dsig = P.sig > 0.0 ? ((kT / P.m) * (h * P.e * P.e)) / P.sig : 0.0;
+  const bool lists = *a.lok == 0;
+  double lr[E], lv[E], lJ[E], u[E], lu[E], ag[E], af[E];
+  if (t < PAD)
+    for (int q = 0; q < 2; ++q) dir[q][t] = dir[q][PAD + n3 + t] = 0.0;
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    const int e = t + k * (int)blockDim.x;
+    lr[k] = lv[k] = lJ[k] = u[k] = lu[k] = ag[k] = af[k] = 0.0;
+    if (e >= n3) continue;
+    lr[k] = a.lr[e]; lv[k] = a.lv[e]; lJ[k] = a.lJ[e]; u[k] = upt[e];
+    if (!first) lu[k] = a.lup[e];
+    dir[0][PAD + e] = P.cf * (lv[k] + P.hh * lr[k]);
+  }
+  auto fetch = [&](int r, int e, AdjRow& o) {
+    o.np = 0;
+    if (r >= rows || e >= n3) return;
+    const size_t at = (size_t)n3;
+    const int s = s0 - r, p = e / 3;
+#pragma unroll
+    for (int j = 0; j < 12; ++j) o.m[j] = K.M[((size_t)r * 12 + j) * at + e];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) o.w[j] = K.W[((size_t)r * 3 + j) * at + e];
+    o.f = K.F[(size_t)r * at + e];
+    o.np = K.np[(size_t)r * nb + p];
+    o.vo = mdt[((size_t)s * nb + p) * 6 + 3 + (e - 3 * p)];
+    o.xi = kT != 0.0 ? a.xi[(size_t)s * n3 + e] : 0.0;
+  };
+  AdjRow c0[E], c1[E];
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    fetch(0, t + k * (int)blockDim.x, c0[k]);
+    if (E == 1) fetch(1, t + k * (int)blockDim.x, c1[k]);
+  }
+  __syncthreads();
+  for (int r = 0; r < rows; ++r) {
+    const double* D = dir[r & 1];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int e = t + k * (int)blockDim.x;
+      const AdjRow q = c0[k];
+      if (E == 1) {
+        c0[k] = c1[k];
+        fetch(r + 2, e, c1[k]);
+      } else {
+        fetch(r + 1, e, c0[k]);
+      }
+      if (e >= n3) continue;
+      const int p = e / 3, c = e - 3 * p;
+      const double* x = D + PAD + 3 * p;         // the bead's direction
+      double df = 0.0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) df += q.m[3 * j + i] * (x[3 * (j - 1) + i] - x[3 * (j - 2) + i]);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) df += q.w[i] * x[i];
+      const int np = q.np & 255;
+      if (np == 255) {
+        const double* xs = mdt + (size_t)(s0 - r) * nb * 6;
+        const int cand = lists ? d.ncnt[p] : nb;
+        for (int i = 0; i < cand; ++i) {
+          const int j = lists ? d.nbr[(size_t)p * MAXNBR + i] : i;
+          if (j >= p - 2 && j <= p + 2) continue;
+          double z[3];
+          z[0] = min_image(xs[6 * (size_t)p] - xs[6 * (size_t)j], g.nx);
+          z[1] = min_image(xs[6 * (size_t)p + 1] - xs[6 * (size_t)j + 1], g.ny);
+          z[2] = min_image(xs[6 * (size_t)p + 2] - xs[6 * (size_t)j + 2], g.nz);
+          const double r2 = z[0] * z[0] + z[1] * z[1] + z[2] * z[2];
+          if (!(r2 < P.rc2)) continue;
+          double coef, c2;
+          lj_coef(P, r2, coef, c2);
+          const double* y = D + PAD + 3 * j;
+          df += coef * (x[c] - y[c]) +
+                c2 * (z[0] * (x[0] - y[0]) + z[1] * (x[1] - y[1]) + z[2] * (x[2] - y[2])) * (c == 0 ? z[0] : (c == 1 ? z[1] : z[2]));
+        }
+      } else {
+        for (int i = 0; i < np; ++i) {
+          const size_t n = (size_t)r * ADJ_NP + i;
+          const double* z = K.pk + n * 5 * nb + p;
+          const double z0 = z[2 * (size_t)nb], z1 = z[3 * (size_t)nb], z2 = z[4 * (size_t)nb];
+          const double* y = D + PAD + 3 * K.pj[n * nb + p];
+          df += z[0] * (x[c] - y[c]) +
+                z[nb] * (z0 * (x[0] - y[0]) + z1 * (x[1] - y[1]) + z2 * (x[2] - y[2])) * (c == 0 ? z0 : (c == 1 ? z1 : z2));
+        }
+      }
+      const double lvt = lv[k] + P.hh * lr[k];
+      ag[k] += lvt * (q.vo * de + (q.f + gam * u[k]) * dcf + P.cf * u[k] + q.xi * dsig);
+      ag[k] += lJ[k] * (-P.m) * ((u[k] - q.vo) * domE + q.xi * dsig);
+      lu[k] = lu[k] + (P.cf * gam * lvt - P.m * P.omE * lJ[k]);
+      if ((q.np & 256) && c == g.wall_axis) af[k] += x[c];
+      const double lrm = lr[k] + df;
+      lv[k] = P.e * lvt + P.m * P.omE * lJ[k] + P.hh * lrm;
+      lr[k] = lrm;
+      dir[(r & 1) ^ 1][PAD + e] = P.cf * (lv[k] + P.hh * lrm);
+    }
+    __syncthreads();
+  }
+  // per bead the parameter terms, its components in order
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    const int e = t + k * (int)blockDim.x;
+    if (e >= n3) continue;
+    a.lr[e] = lr[k]; a.lv[e] = lv[k]; a.lup[e] = lu[k];
+    dir[0][e] = ag[k];
+    dir[1][e] = af[k];
+  }
+  __syncthreads();
+  for (int p = t; p < nb; p += (int)blockDim.x)
+    for (int z = 0; z < 2; ++z) {
+      double* o = a.gacc + 3 * p + z;
+      const double* v = dir[z] + 3 * p;
+      *o = (first ? 0.0 : *o) + (v[0] + v[1] + v[2]);
+    }
+}
+
 // After the reversed cycle: lr, lv from the pair the last launch wrote, and
 // the parameter terms added over the beads in a fixed order (beads p, p + M,
 // ... summed per slot, then a tree over M = the least power of two >= nb,
@@ -744,10 +1090,25 @@ void launch_adj_reverse_step(const void* A, const void* lamB, void* lamA, const 
   if (kT != 0.0) {   // sigma > 0 exactly when kT > 0 (gamma > 0 here)
     hipLaunchKernelGGL(k_adj_noise, dim3(nblk((long)nb * n_sub, 256)), dim3(256), 0, s, d, a.xi, step, nb, n_sub);
   }
-  for (int k = 0; k < n_sub; ++k)
-    hipLaunchKernelGGL(k_adj_sub, dim3(nblk(nb, AS_BPB)), dim3(AS_WG), 0, s, d, a, mdt, upt, nb, n_sub - 1 - k, k,
-                       kT);
-  hipLaunchKernelGGL(k_adj_md_fin, dim3(1), dim3(AS_FIN), 0, s, a, nb, n_sub);
+  const int C = adj_chunk(nb, n_sub);
+  if (C > 0) {
+    const AdjCoef K = adj_coef(a.coef, nb, C);
+    for (int r = 0; r < n_sub; r += C) {
+      const int rows = n_sub - r < C ? n_sub - r : C, s0 = n_sub - 1 - r;
+      hipLaunchKernelGGL(k_adj_terms, dim3(nblk(nb, AT_BPB), (unsigned)rows), dim3(AT_WG), 0, s, d, (const int*)a.lok, K,
+                         mdt, nb, s0);
+      const int E = (3 * nb + AC_WG - 1) / AC_WG;
+      const auto chain = E == 1 ? k_adj_chain<1> : k_adj_chain<2>;
+      hipLaunchKernelGGL(chain, dim3(1), dim3(64 * nblk(3 * nb, 64 * E)), 0, s, d, a, K, mdt, upt, nb, s0, rows,
+                         r == 0 ? 1 : 0, kT);
+    }
+  } else {
+    for (int k = 0; k < n_sub; ++k)
+      hipLaunchKernelGGL(k_adj_sub, dim3(nblk(nb, AS_BPB)), dim3(AS_WG), 0, s, d, a, mdt, upt, nb, n_sub - 1 - k, k,
+                         kT);
+  }
+  // k_adj_chain leaves lr, lv in place
+  hipLaunchKernelGGL(k_adj_md_fin, dim3(1), dim3(AS_FIN), 0, s, a, nb, C > 0 ? 0 : n_sub);
   hipLaunchKernelGGL((k_adj_gather_t<T, DEV>), dim3(nblk(nb, 64)), dim3(64), 0, s, (const T*)A, d, a, nb);
   launch_spread<T>(dspread, nslots, s);
   hipLaunchKernelGGL((k_adj_lb<T, DEV>), dim3((unsigned)ntiles), dim3(256), 0, s, (const T*)A, (const T*)lamB,

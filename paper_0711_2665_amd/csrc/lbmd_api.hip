@@ -731,7 +731,7 @@ int build_graph(lb_ctx* c) {
 // Workspace of the adjoint: checkpoints every K steps (and the final state),
 // the per-step tape of one segment, adjoint fields.
 struct AdjLayout {
-  size_t ckpt, tape_pops, tape_beads, lamA, lamB, lamu, lbead, mdtape, xi, par, total;
+  size_t ckpt, tape_pops, tape_beads, lamA, lamB, lamu, lbead, mdtape, xi, coef, par, total;
   size_t pops_slot, bead_arr, md_arr;
   size_t upj_arr;      // u_p and J of every slot, one block (they lie together in the bead buffer)
   size_t tape_entry;   // one step's bead tape: r, then u_p and J
@@ -757,6 +757,7 @@ AdjLayout adj_layout(const lb_ctx* c, int nsteps, int K) {
   L.lbead = o; o += 10 * L.bead_arr;
   L.mdtape = o; o += (size_t)K * L.md_arr;
   L.xi = o; o += align256(sizeof(double) * 3 * (size_t)c->d[0].nb * (size_t)c->n_sub);
+  L.coef = o; o += align256(adj_row_bytes(c->d[0].nb) * (size_t)adj_chunk(c->d[0].nb, c->n_sub));
   L.par = o; o += 256;
   L.total = o;
   return L;
@@ -1635,6 +1636,7 @@ int lb_adjoint_backward(lb_ctx* c, const double* dLdr, const double* dLdv, doubl
   a.par = (double*)(w + L.par);
   a.lok = (int*)(w + L.par + 128);
   a.xi = (double*)(w + L.xi);
+  a.coef = (double*)(w + L.coef);
   void* lamB = w + L.lamB;   // adjoint of the populations after the step being reversed
   void* lamA = w + L.lamA;
   acc(hipMemsetAsync(lamB, 0, L.pops_slot, c->s));

@@ -197,7 +197,19 @@ struct AdjBufs {
   void* lamu;       // [3][N] (storage type) adjoint of the gathered node velocity
   double* par;      // [4]: dL/dgamma, dL/dF_drive accumulators
   double* xi;       // [n_sub][nb][3] the bead noise of the step being reversed
+  double* coef;     // adj_coef_bytes: the force derivative of adj_chunk sub-steps
 };
+// Sub-steps reversed by one pair of launches (0: one launch each): chains that one
+// workgroup holds (one or two components per thread), within ADJ_COEF_BYTES.
+constexpr int ADJ_CHAIN = 341;
+constexpr int ADJ_NP = 8;                      // far pairs kept per bead and sub-step
+constexpr size_t ADJ_COEF_BYTES = (size_t)64 << 20;
+inline size_t adj_row_bytes(int nb) { return (sizeof(double) * (48 + 5 * ADJ_NP) + sizeof(int) * (ADJ_NP + 1)) * (size_t)nb; }
+inline int adj_chunk(int nb, int n_sub) {
+  if (nb > ADJ_CHAIN) return 0;
+  const size_t most = ADJ_COEF_BYTES / adj_row_bytes(nb);
+  return most < (size_t)n_sub ? (int)most : n_sub;
+}
 void launch_adj_init(const double* dLdr, const double* dLdv, const AdjBufs& a, int nb, hipStream_t s);
 template <typename T, bool DEV>
 void launch_adj_reverse_step(const void* A, const void* lamB, void* lamA, const Dev& d, const Dev& dspread,

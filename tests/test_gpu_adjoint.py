@@ -230,3 +230,30 @@ def test_adjoint_all_pairs_when_the_lists_do_not_hold(orc):
     moved = np.abs(probe.beads()["r"].cpu().numpy() - r0).max()
     assert moved > 0.6, moved                 # beyond half the skin within the first step
     _jvp_check(orc, CFG, r0, v0, NSTEPS, 5, "drifting chain")
+
+
+@pytest.mark.parametrize("nb,n_sub", [(1, 25), (2, 25), (3, 24), (11, 25), (12, 25), (13, 25), (25, 25), (170, 40),
+                                      (171, 40), (341, 40), (342, 40), (341, 300)])
+def test_adjoint_chain_lengths_match_oracle_jvp(orc, nb, n_sub):
+    """Chain lengths at the edges of the reversed sub-cycle's workgroups (12
+    beads evaluate the force derivative together; 170, 171, 341: one or two
+    components per thread of the serial part; 342: one launch per sub-step)
+    and a sub-cycle whose coefficients are evaluated in two parts."""
+    _torch()
+    cfg = scaled(C4, shape=(40, 40, 40), wall_axis=2, wall_pos=20, pore_h=3, nb=nb, n_sub=n_sub, init_seed=31)
+    r0 = _start(orc, cfg)
+    _jvp_check(orc, cfg, r0, np.zeros_like(r0), 3, 2, f"{nb} beads, {n_sub} sub-steps")
+
+
+def test_adjoint_of_a_dense_chain_matches_oracle_jvp(orc):
+    """A folded chain with r_c = 2.3: beads with more pairs than are kept per
+    bead and sub-step, wall sites in the 6 x 6 window."""
+    _torch()
+    cfg = scaled(C4, shape=(24, 24, 30), wall_axis=2, wall_pos=15, nb=90, n_sub=50, rc=2.3, eps=0.05, r0=1.5, kappa=0.5)
+    r0 = []
+    for k in range(90):
+        row, x = divmod(k, 5)
+        z, y = divmod(row, 5)
+        r0.append((4 - x if row % 2 else x, 4 - y if z % 2 else y, z))
+    r0 = np.asarray(r0, dtype=np.float64) * 1.5 + np.array([8.3137, 8.1282, 16.4931])
+    _jvp_check(orc, cfg, r0, np.zeros_like(r0), 3, 2, "dense chain")
