@@ -175,24 +175,38 @@ __device__ inline double dweight(const Stencil& s, int k, int a) {
   return a == 0 ? dw[0] * w[1] * w[2] : (a == 1 ? w[0] * dw[1] * w[2] : w[0] * w[1] * dw[2]);
 }
 
+// 0 + the values of the group's eight lanes where on, in order, on every lane.
+__device__ inline double corner_sum(double x, bool on) {
+  const int base = threadIdx.x & 63 & ~7;
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const double y = __shfl(x, base + k, 64);
+    if (__shfl(on ? 1 : 0, base + k, 64)) s += y;
+  }
+  return s;
+}
+
 // ---------------------------------------------------------------------------
-// Spreading transpose, one thread per bead: lam_J and the position term of
-// the spreading (J_p of the step from the tape).
+// Spreading transpose, eight lanes per bead (one per corner; the terms are
+// then added in corner order): lam_J and the position term of the spreading
+// (J_p of the step from the tape).  With one thread per bead, the corners'
+// loads one after the other, 22 us (the gather transpose 37) at 100 beads.
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ void k_adj_spread_t(const T* __restrict__ lamB, Dev d, AdjBufs a, const double* __restrict__ Jt, int nb) {
-  int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p == 0) *a.lok = 0;                      // the list check of this step follows
-  if (p >= nb) return;
+  const int e = blockIdx.x * blockDim.x + threadIdx.x, p = e >> 3, k = e & 7;
+  if (e == 0) *a.lok = 0;                      // the list check of this step follows
+  if (p >= nb) return;                         // whole groups of eight lanes
   const Rep& R = d.reps[0];
   const size_t N = (size_t)R.lp.N;
   double rp[3] = {d.rs[3 * p], d.rs[3 * p + 1], d.rs[3 * p + 2]};
   Stencil st = make_stencil(R.g, rp);
   double lJ[3] = {0.0, 0.0, 0.0}, lr[3] = {0.0, 0.0, 0.0};
   const double J[3] = {Jt[3 * p], Jt[3 * p + 1], Jt[3 * p + 2]};
-  for (int k = 0; k < 8; ++k) {
-    int n = (int)corner_node(R.g, st, k);
-    if (d.flags[n] & F_SOLID) continue;
+  const int n = (int)corner_node(R.g, st, k);
+  const bool fluid = !(d.flags[n] & F_SOLID);
+  if (fluid) {
     double lf[Q];
     for (int i = 0; i < Q; ++i) lf[i] = (double)lamB[(size_t)i * N + n];
     double lF[3];
@@ -202,13 +216,16 @@ __global__ void k_adj_spread_t(const T* __restrict__ lamB, Dev d, AdjBufs a, con
     double W = corner_weight(st, k);
     double JdotL = J[0] * lF[0] + J[1] * lF[1] + J[2] * lF[2];
     for (int b = 0; b < 3; ++b) {
-      lJ[b] += W * lF[b];
-      lr[b] += dweight(st, k, b) * JdotL;
+      lJ[b] = W * lF[b];
+      lr[b] = dweight(st, k, b) * JdotL;
     }
   }
   for (int b = 0; b < 3; ++b) {
-    a.lJ[3 * p + b] = lJ[b];
-    a.lrs[3 * p + b] = lr[b];
+    const double sJ = corner_sum(lJ[b], fluid), sr = corner_sum(lr[b], fluid);
+    if (k == b) {
+      a.lJ[3 * p + b] = sJ;
+      a.lrs[3 * p + b] = sr;
+    }
   }
 }
 
@@ -947,26 +964,25 @@ __global__ __launch_bounds__(AS_FIN) void k_adj_md_fin(AdjBufs a, int nb, int n_
 }
 
 // ---------------------------------------------------------------------------
-// Gather transpose, position term, one thread per bead; adds the spreading
-// and gathering position terms to lam_r.
+// Gather transpose, position term, eight lanes per bead as above; adds the
+// spreading and gathering position terms to lam_r.
 // ---------------------------------------------------------------------------
 template <typename T, bool DEV>
 __global__ void k_adj_gather_t(const T* __restrict__ A, Dev d, AdjBufs a, int nb) {
-  int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= nb) return;
+  const int e = blockIdx.x * blockDim.x + threadIdx.x, p = e >> 3, k = e & 7;
+  if (p >= nb) return;                         // whole groups of eight lanes
   const Rep& R = d.reps[0];
   double rp[3] = {d.rs[3 * p], d.rs[3 * p + 1], d.rs[3 * p + 2]};
   Stencil st = make_stencil(R.g, rp);
   const double lu[3] = {a.lup[3 * p], a.lup[3 * p + 1], a.lup[3 * p + 2]};
-  double lr[3] = {0.0, 0.0, 0.0};
-  for (int k = 0; k < 8; ++k) {
-    int n = (int)corner_node(R.g, st, k);
-    double u[3];
-    node_velocity<T, DEV>(A, d.flags, R.lp, n, u);
-    double ul = u[0] * lu[0] + u[1] * lu[1] + u[2] * lu[2];
-    for (int b = 0; b < 3; ++b) lr[b] += dweight(st, k, b) * ul;
+  const int n = (int)corner_node(R.g, st, k);
+  double u[3];
+  node_velocity<T, DEV>(A, d.flags, R.lp, n, u);
+  const double ul = u[0] * lu[0] + u[1] * lu[1] + u[2] * lu[2];
+  for (int b = 0; b < 3; ++b) {
+    const double s = corner_sum(dweight(st, k, b) * ul, true);
+    if (k == b) a.lr[3 * p + b] += a.lrs[3 * p + b] + s;
   }
-  for (int b = 0; b < 3; ++b) a.lr[3 * p + b] += a.lrs[3 * p + b] + lr[b];
 }
 
 // ---------------------------------------------------------------------------
@@ -1082,7 +1098,7 @@ void launch_adj_reverse_step(const void* A, const void* lamB, void* lamA, const 
                              const double* Jt, uint32_t step, double kT, int ntiles, int tile_nodes, int nslots,
                              int nb, int n_sub, hipStream_t s) {
   launch_bead_prep(d, nslots, 0, s);
-  hipLaunchKernelGGL((k_adj_spread_t<T>), dim3(nblk(nb, 64)), dim3(64), 0, s, (const T*)lamB, d, a, Jt, nb);
+  hipLaunchKernelGGL((k_adj_spread_t<T>), dim3(nblk(8L * nb, 64)), dim3(64), 0, s, (const T*)lamB, d, a, Jt, nb);
   // neighbour lists at the step's start positions (d.r is the tape's r_n),
   // checked against every sub-step's force positions
   launch_nbr_build(d, nslots, 1, s);
@@ -1109,7 +1125,7 @@ void launch_adj_reverse_step(const void* A, const void* lamB, void* lamA, const 
   }
   // k_adj_chain leaves lr, lv in place
   hipLaunchKernelGGL(k_adj_md_fin, dim3(1), dim3(AS_FIN), 0, s, a, nb, C > 0 ? 0 : n_sub);
-  hipLaunchKernelGGL((k_adj_gather_t<T, DEV>), dim3(nblk(nb, 64)), dim3(64), 0, s, (const T*)A, d, a, nb);
+  hipLaunchKernelGGL((k_adj_gather_t<T, DEV>), dim3(nblk(8L * nb, 64)), dim3(64), 0, s, (const T*)A, d, a, nb);
   launch_spread<T>(dspread, nslots, s);
   hipLaunchKernelGGL((k_adj_lb<T, DEV>), dim3((unsigned)ntiles), dim3(256), 0, s, (const T*)A, (const T*)lamB,
                      (T*)lamA, d, (const T*)a.lamu, ntiles, tile_nodes);
