@@ -635,7 +635,7 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
     launch_md_cycle_fused(D, c->fb, c->pk.nseg, c->nslots, c->nrep, c->n_sub, c->fusedK, st);
   else if (resident)
     launch_md_cycle_resident(D, c->fb.ang, c->rseg, c->nrtab, c->pk.nrseg, c->nslots, c->n_sub, c->mts, none, c->md_wait,
-                             c->resident_own, st);
+                             c->resident_own, c->any_constrained, st);
   else if (c->mts > 0) launch_md_cycle_mts(D, c->nslots, c->n_sub, c->mts, st);
   else launch_md_cycle(D, c->nslots, c->nrep, c->n_sub, none, st, false, c->any_constrained);
   if (resident) sweep_side();
@@ -909,13 +909,21 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
       for (int K = FUSED_K; K >= 2; --K)
         if (d[0].n_sub % K == 0) { c->fusedK_max = K; break; }
     c->fusedK = 0;
-    c->resident = !rigid && c->pk.nrseg > 0 && c->pk.nrseg <= RES_MAX_WG &&
+    c->resident = c->pk.nrseg > 0 && c->pk.nrseg <= RES_MAX_WG &&
                   c->n_sub >= RES_MIN_SUB;
     // the sweep reads and writes every population once
     rsegs = res_place(d, nrep, c->pk);
     c->nrtab = (int)rsegs.size();
     c->resident_own = c->pk.nrseg <= RES_OWN_WG && c->nrtab <= RES_OWN_XCD * XCDS &&
                       2.0 * Q * (double)elem_size(d) * (double)c->pk.nodes <= RES_OWN_BYTES * (c->n_sub + c->mts);
+    if (rigid) {
+      // every chain rigid and of a length that a workgroup projects, on a CU of
+      // its own (the launches take 20 us per sub-step: more than any sweep's loss)
+      for (int r = 0; r < nrep; ++r)
+        c->resident = c->resident && (d[r].nb == 0 || (d[r].constraints == 1 && d[r].nb >= 2 && d[r].nb <= RIG_MAX));
+      c->resident = c->resident && c->pk.nrseg <= RES_OWN_WG && c->nrtab <= RES_OWN_XCD * XCDS;
+      c->resident_own = true;
+    }
     // a shorter limit sends every wait to the redo (tests)
     if (const char* e = std::getenv("LBMD_MD_WAIT_TICKS")) c->md_wait = std::strtoull(e, nullptr, 10);
   }
@@ -1209,7 +1217,7 @@ int md_relax(lb_ctx* c, int nsub_total, double gamma_relax) {
       launch_md_begin(c->D, c->nrep, c->s);
       launch_md_start(c->D, c->nslots, ov, c->s);
       launch_md_cycle_resident(c->D, c->fb.ang, c->rseg, c->nrtab, c->pk.nrseg, c->nslots, n, 0, ov, c->md_wait,
-                               c->resident_own, c->s);
+                               c->resident_own, c->any_constrained, c->s);
     } else {
       launch_md_cycle(c->D, c->nslots, c->nrep, n, ov, c->s, true, c->any_constrained);
     }

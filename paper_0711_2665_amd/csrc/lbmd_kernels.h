@@ -300,12 +300,13 @@ constexpr int RES_BLOCK = 10;
 constexpr int RES_MAX_WG = 512;
 constexpr int RES_MIN_SUB = 3;
 constexpr int RES_OWN_WG = 128;
+constexpr int RIG_MAX = 512;                   // beads of a chain with rigid bonds
 constexpr int RES_OWN_XCD = 24;                // of the 32 CUs of an XCD
 constexpr int RES_XCD = 16;
 constexpr double RES_OWN_BYTES = 16e6;
 constexpr uint64_t RES_PLACE = 200000;   // 2 ms
 void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int ntab, int nseg, int nslots, int n_sub,
-                              int mts, const MdOverride& ov, uint64_t wait, bool own, hipStream_t s);
+                              int mts, const MdOverride& ov, uint64_t wait, bool own, bool rigid, hipStream_t s);
 void launch_md_gate(const Dev& d, int nseg, hipStream_t s);
 // Noise of one sub-cycle into d.xi, for the step counter + step_offset.
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s);

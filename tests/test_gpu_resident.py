@@ -291,3 +291,37 @@ def test_mts_against_single_launches(monkeypatch, M):
                 _same((group[k],), (e, k), f"M {M}, chain {k}, {tag} against launches")
     print({k: sims[0][3].diagnostics()[k] for k in ("nbr_max", "rebuilds")}, flush=True)
     assert sims[0][3].diagnostics()["rebuilds"] > 0
+
+
+@pytest.mark.parametrize("nb,speed", [(2, 0.0), (31, 0.0), (32, 0.0), (33, 0.0), (64, 0.0), (65, 0.0), (150, 0.0),
+                                      (181, 0.0), (200, 0.9), (200, 9.0), (512, 0.0)])
+def test_rigid_chains_against_single_launches(monkeypatch, nb, speed):
+    """Rigid bonds in the resident cycle and in its redo against the launches
+    that a context with a harmonic chain beside the rigid one takes: chain
+    lengths at the edges of the segments, of the serial solve (32 beads) and
+    of the largest chain; chains that leave their lists' range."""
+    _torch()
+    from paper_0711_2665_amd import lbmd
+    cfg = scaled(C0, shape=(40, 40, 40), wall_pos=20, nb=nb, init_seed=7, seed=5, replica=0, constraints=1)
+    other = scaled(C0, shape=(20, 20, 20), wall_pos=10, nb=3, seed=6, replica=1)
+    r = initial_chain(cfg)[0]
+    e = lbmd.Ensemble([cfg, other], [r, initial_chain(other)[0]])
+    sims = [lbmd.Simulation(cfg, r, None)]
+    monkeypatch.setenv("LBMD_MD_WAIT_TICKS", "0")
+    sims.append(lbmd.Simulation(cfg, r, None))
+    monkeypatch.delenv("LBMD_MD_WAIT_TICKS")
+    for s in (e, *sims):
+        s.relax(250, 1.0)
+    for tag, s in zip(("resident", "redo"), sims):
+        _same((s,), (e, 0), f"{nb} rigid beads, relaxed, {tag}")
+        s.beads()["v"][:, 1] = speed
+    e.beads(0)["v"][:, 1] = speed
+    for n in (1, 2):
+        e.couple_step(n)
+        for tag, s in zip(("resident", "redo"), sims):
+            s.couple_step(n)
+            _same((s,), (e, 0), f"{nb} rigid beads, {tag} against launches")
+    for s in (e, *sims):
+        s.check()
+    if speed:
+        assert sims[0].diagnostics()["rebuilds"] > 0
