@@ -255,7 +255,8 @@ int lb_ensemble_translocation(lb_ctx* ctx, int64_t* out_host);
 
 /* The uniform MD sub-cycle (mts_outer = 0, harmonic bonds) can run in
  * blocks of K sub-steps, one launch per block (off by default: on the
- * workloads measured it is slower than one launch per sub-step): each
+ * workloads measured it is slower than the default, one launch per cycle or,
+ * for more than 16384 beads, per sub-step): each
  * workgroup advances a chain segment and recomputes the beads that can reach
  * it within the block (chain neighbours, and pair partners closer than
  * r_c + 0.2 from the step's neighbour lists), then certifies the result (no
@@ -263,8 +264,8 @@ int lb_ensemble_translocation(lb_ctx* ctx, int64_t* out_host);
  * the list skin less 0.1 of where the lists were built).  A replica whose
  * block cannot be certified is redone from that block's start by one
  * workgroup (a launch that returns at once when nothing is to be redone), so
- * results equal the per-sub-step cycle bit for bit.  lb_md_fused(ctx, 0)
- * switches back to one launch per sub-step.  Drops the captured graph.
+ * results equal the default's bit for bit.  lb_md_fused(ctx, 0) switches
+ * back to it.  Drops the captured graph.
  * LB_ERR_UNSUPPORTED: K > 0 and the context has no chain, or uses the
  * multiple-time-step cycle or rigid bonds; LB_ERR_ARG: K < 0, or K not
  * dividing n_sub, below 2 or above 10. */

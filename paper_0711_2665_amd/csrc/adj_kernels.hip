@@ -230,7 +230,8 @@ __global__ void k_adj_spread_t(const T* __restrict__ lamB, Dev d, AdjBufs a, con
 }
 
 // ---------------------------------------------------------------------------
-// MD sub-cycle transpose, one launch per sub-step (in reverse order), four
+// MD sub-cycle transpose.  Up to ADJ_CHAIN beads k_adj_terms and k_adj_chain,
+// below; longer chains one launch per sub-step (in reverse order), four
 // beads per three-wave workgroup.  The force positions r_mid and the
 // velocities at the start of every sub-step come from the tape the forward
 // sub-cycle wrote (while the segment was recomputed, or in the forward pass
@@ -598,8 +599,9 @@ __global__ __launch_bounds__(AS_WG) void k_adj_sub(Dev d, AdjBufs a, const doubl
 // serial part (k_adj_chain, one workgroup) is a product with a band per
 // sub-step.  One launch per sub-step (k_adj_sub) evaluated the force law in
 // dual numbers between two directions: 8.5 us of latency each, at 100 beads
-// 0.85 of 1.5 ms per reversed step; the two launches take 14 and 125 us. From
-// 400 beads on, three components per thread spill and the launches are faster.
+// 0.85 of 1.5 ms per reversed step; the two launches take 14 and 125 us.  At 341
+// beads, two components per thread, a gradient step takes 1.14 instead of 1.52
+// ms; at 400, three per thread spill: 1.86 against 1.50.
 //
 // The chain's directions enter as differences of neighbours, D_q = dir_q -
 // dir_{q-1}, as in the dual evaluation (a common translation of the beads then

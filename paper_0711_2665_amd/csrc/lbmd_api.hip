@@ -424,7 +424,7 @@ struct lb_ctx {
   SweepCfg sweep;
   int ntiles = 0;
   int wl_blocks = 0;         // blocks of the wall-link list (bounce-back ledger)
-  int fusedK = 0;            // sub-steps per fused block of the uniform sub-cycle (0: one launch per sub-step)
+  int fusedK = 0;            // sub-steps per fused block of the uniform sub-cycle (0: not in blocks)
   int fusedK_max = 0;        // the block length the context supports (0: none)
   FusedBufs fb{};
   bool resident = false;     // the sub-cycle runs in one launch of co-resident workgroups

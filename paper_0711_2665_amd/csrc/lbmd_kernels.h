@@ -232,8 +232,8 @@ void launch_md_start(const Dev& d, int nslots, const MdOverride& ov, hipStream_t
 // The multiple-time-step sub-cycle of a coupled step: M outer steps of
 // n_sub / M SPV sub-steps with the bonded forces, between kicks of the slow
 // forces (bead LJ, wall, field); noise from d.xi as in launch_md_cycle.
-constexpr int MTS_MAX_INNER = 40;
-constexpr int MAX_CONSTRAINED_BEADS = 1024;   // rigid bonds: one workgroup per chain   // inner sub-steps per outer step (the inner kernel's halo is 2 per sub-step)
+constexpr int MTS_MAX_INNER = 40;             // inner sub-steps per outer step (the inner kernel's halo is 2 per sub-step)
+constexpr int MAX_CONSTRAINED_BEADS = 1024;   // rigid bonds: one workgroup per chain
 void launch_md_cycle_mts(const Dev& d, int nslots, int n_sub, int M, hipStream_t s);
 
 // The uniform sub-cycle in blocks of K sub-steps, one launch per block:
@@ -264,21 +264,23 @@ constexpr double FUSED_DELTA = 0.1;          // displacement bound within a bloc
 void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslots, int nrep, int n_sub, int K,
                            hipStream_t s);
 
-// The uniform sub-cycle (harmonic bonds) in one launch: workgroup w owns the
-// chain segment [a, b) of up to RES_OWN beads for the whole cycle and
-// exchanges the positions its neighbours need through d.xring (see
-// k_md_resident).  Measured per coupled step against one launch per sub-step:
-// 20 beads on 32^3 0.20 against 0.75 ms, 400 beads on 128^3 0.22 against 0.78,
-// 8000 beads on 512 x 256 x 256 (FP32) 1.12 against 1.66, 64 uneven replicas
-// 0.97 against 1.66.
+// The sub-cycle in one launch (uniform, with mts > 0 the multiple-time-step
+// one, with rigid that of rigid bonds): entry w of the table seg (ntab entries,
+// nseg of them in use) is the chain segment [a, b) of up to RES_OWN beads that
+// workgroup w owns for the whole cycle; it exchanges the positions its
+// neighbours need through d.xring (see k_md_resident).  Measured per coupled
+// step against single launches: 20 beads on 32^3 0.20 against 0.75 ms, 400
+// beads on 128^3 0.22 against 0.78, 8000 beads on 512 x 256 x 256 (FP32) 1.11
+// against 1.66, 64 uneven replicas 0.96 against 1.66, 2000 beads with M = 5 on
+// 256 x 256 x 128 0.35 against 0.63, 150 rigid beads 1.25 against 2.15.
 // Its workgroups wait for each other, so all of them have to be on the GPU at
 // once: 768 fit (three per CU by registers), at most RES_MAX_WG are used, so
 // that contexts of up to 256 segments fit beside any other.  A wait that
 // lasts longer than `wait` ticks of the 100 MHz clock, or RES_PLACE while some
 // workgroup has not found room, hands the replica to one workgroup that
 // redoes the cycle from its start; a bead that leaves the range of the step's
-// neighbour lists, to a second pass with new lists where one needs them, every RES_BLOCK sub-steps
-// (8000 beads of a walk that was not relaxed, step by step: 3.1 ms, as with one
+// neighbour lists, to a second pass with new lists where one needs them, every
+// RES_BLOCK sub-steps (8000 beads of a walk that was not relaxed, step by step: 3.1 ms, as with one
 // launch per sub-step; the one workgroup takes 94).  At n_sub = 1 and 2 the
 // single launches cost no more.
 // own: every workgroup takes a CU for itself.  An exchange beside the sweep's
@@ -286,9 +288,9 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
 // 1.0 to 1.3).  That is worth while the beads outlast the sweep, which then has
 // fewer CUs: 400 beads on 128^3 0.27 against 0.29 ms per step (0.22 with the
 // exchange within an XCD), 32 x 100 beads 0.34 against 0.38 (0.30), 2000 beads
-// with M = 5 on 256 x 256 x 128 (FP32) 0.35 against 0.47; but 4000 beads there in FP64 0.64 against 0.60, 8000 beads on 512 x 256 x
-// 256 1.60 against 1.11, 64 uneven replicas (432 segments) 1.28 against 0.96.  So:
-// up to RES_OWN_WG segments (half of the CUs; two contexts fit beside each
+// with M = 5 on 256 x 256 x 128 (FP32) 0.35 against 0.47; but 4000 beads there
+// in FP64 0.64 against 0.60, 8000 beads on 512 x 256 x 256 1.60 against 1.11, 64
+// uneven replicas (432 segments) 1.28 against 0.96.  So: up to RES_OWN_WG segments (half of the CUs; two contexts fit beside each
 // other) that leave a quarter of every XCD's CUs to the sweep, and at most
 // RES_OWN_BYTES of populations per sub-step (about what the sweep moves in that
 // time).

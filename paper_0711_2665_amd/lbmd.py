@@ -301,8 +301,8 @@ class Context:
         return out
 
     def md_fused(self, K):
-        """Sub-steps per fused launch of the uniform MD sub-cycle (0: one
-        launch per sub-step); see lb_md_fused."""
+        """Sub-steps per fused launch of the uniform MD sub-cycle (0: the
+        default cycle); see lb_md_fused."""
         _raise(lib().lb_md_fused(self.ctx, int(K)))
 
     def sweep_config(self, tile_nodes, order=0, grid=0, cap=0):
