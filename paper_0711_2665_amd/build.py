@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbmd.so")
 SOURCES = ["lbmd_api.hip", "lb_kernels.hip", "md_kernels.hip", "adj_kernels.hip"]
-HEADERS = ["lbmd_dev.h", "lbmd_kernels.h", "lbmd_lattice.h"]
+HEADERS = ["lbmd_dev.h", "lbmd_kernels.h", "lbmd_lattice.h", "lbmd_tag.h"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -21,6 +21,7 @@
 // after any bead has moved more than skin/2 since the last build; the flag is
 // carried between launches in three rotating words.
 #include "lbmd_kernels.h"
+#include "lbmd_tag.h"
 
 namespace lbmd {
 
@@ -2131,8 +2132,8 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
 //
 // The exchange has no fence and no flag (an agent-scope release would write
 // the L2 back).  A position component travels as two 64-bit words, its bits and
-// its bits XOR a tag that no other sub-step of any cycle uses, written and
-// read by relaxed agent-scope atomics, which bypass the L2s that the XCDs do
+// its bits XOR a tag that no other sub-step of any pass of any cycle uses
+// (lbmd_tag.h), written and read by relaxed agent-scope atomics, which bypass the L2s that the XCDs do
 // not share: a reader takes the pair when the two words differ by the tag, so
 // it needs no order between them.  Two slots suffice: segments depend on each
 // other symmetrically, so a segment publishes x(s + 2) over x(s) only after
@@ -2364,11 +2365,9 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     give_up();
     sh.lost = 1;
   };
-  // The tag of sub-step s of this cycle is (2^32 cycle + s) TAG, so that no two
-  // sub-steps share one, whatever the cycles' lengths; those of a block's
-  // start differ by MARK.
-  constexpr uint64_t TAG = 0x9E3779B97F4A7C15ull, MARK = 0x5851F42D4C957F2Dull;
-  const uint64_t tag0 = ((uint64_t)load_uniform(&d.ctrl->cycles) << 32) * TAG;
+  // The XCDs are published by the first pass, for both.
+  const uint64_t cycle = load_uniform(&d.ctrl->cycles);
+  const uint64_t tag0 = res_tag(cycle, BLOCKS, 0), tagx = res_tag(cycle, 0, 0);
 
   // ---- the lanes of the sum: component c of bead i
   const int i = 16 * wave + lane / 3, c = lane % 3;
@@ -2398,7 +2397,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
       if (seg.id == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)n_sub);
       const unsigned long long w = res_xcd();
       res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id, w);
-      res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id + 1, w ^ tag0);
+      res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id + 1, w ^ tagx);
     }
     if (!BLOCKS && d.rb[4 * rep] != 0u) lose();  // the lists are not valid at the start
     if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & RES_FAIL) sh.lost = 1;
@@ -2414,7 +2413,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
   const int lb = t / LL, ll = t % LL;
   bool fresh = BLOCKS && s0 == 0 && (RIGID || d.rb[4 * rep] != 0u);   // build new lists
   const unsigned long long* xb = nullptr;
-  const uint64_t tagb = tag0 + (uint64_t)s0 * TAG + MARK;
+  const uint64_t tagb = tag0 + (uint64_t)s0 * RES_TAG + RES_MARK;
   if (BLOCKS && (s0 > 0 || fresh)) {
     unsigned long long* xw = d.xring + (size_t)(4 + (blk & 1)) * 6 * nslots;
     xb = xw;
@@ -2602,7 +2601,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
   for (int k = t; k < RES_HALO + min(sh.nrem, RES_REM); k += RES_WG) {
     const int sl = sh.rslot[k];
     unsigned long long w = 0;
-    if (sl >= 0 && !res_poll(d.xflag + 4 * (size_t)nseg + 2 * (g0 + (sl - so) / RES_OWN), tag0, word, d.ctrl, wait, nseg, w))
+    if (sl >= 0 && !res_poll(d.xflag + 4 * (size_t)nseg + 2 * (g0 + (sl - so) / RES_OWN), tagx, word, d.ctrl, wait, nseg, w))
       lose();
     const bool near = w == (unsigned long long)res_xcd();
     sh.rnear[k] = near;
@@ -2626,7 +2625,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     // every segment's velocities are read; the lists at the opening's positions
     for (int k = t; k < (int)ng; k += RES_WG) {
       unsigned long long w = 0;
-      if (!res_poll(d.xflag + 4 * (size_t)nseg + 2 * (g0 + k), tag0, word, d.ctrl, wait, nseg, w)) lose();
+      if (!res_poll(d.xflag + 4 * (size_t)nseg + 2 * (g0 + k), tagx, word, d.ctrl, wait, nseg, w)) lose();
       const bool near = w == (unsigned long long)res_xcd();
       sh.snear[k] = near;
       if (g0 + k != seg.id) atomicOr(&sh.links, near ? 2 : 1);
@@ -2659,7 +2658,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
   // the other segments, its projections, and the positions of s + 1.
   auto rigid = [&](int s) {
     const int cb = s & 1;
-    const uint64_t tag = tag0 + (uint64_t)(s + 1) * TAG;
+    const uint64_t tag = tag0 + (uint64_t)(s + 1) * RES_TAG;
     const unsigned long long* from = d.xring + (cb ? 0 : half);
     for (int k = t; k < 3 * nb; k += RES_WG) {
       const int q = k / 3;
@@ -2703,14 +2702,14 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     const int j0 = ang ? at(k - 2) : 0, j1 = ang ? at(k - 1) : 0, j2 = ang ? at(k) : 0;
     double* tape = mine && d.mdtape ? d.mdtape + (size_t)p * 6 + c : nullptr;
     unsigned long long* ring = d.xring + ((size_t)slot * 3 + c) * 2;
-    uint64_t tag = tag0 + (uint64_t)sa * TAG;
+    uint64_t tag = tag0 + (uint64_t)sa * RES_TAG;
     int q = 0, o = MTS ? s0 / (Mb + 1) : 0;
     for (int s = sa; s < sb; ++s) {
       const int cb = s & 1, was = sh.dead[cb ^ 1];
       const bool last = s == end - 1;
       const bool kick = MTS && q == 0;
       if (MTS && q++ == Mb) { q = 0; ++o; }      // of stage s + 1
-      tag += TAG;                                // of sub-step s + 1
+      tag += RES_TAG;                                // of sub-step s + 1
       if (ang && !kick) {
         const ResAngle A = res_angle(sh.pos[cb][j0], sh.pos[cb][j1], sh.pos[cb][j2]);
         double d1, d2;
@@ -3012,13 +3011,13 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     }
     const int rs0 = lane < 3 * nrem ? sh.rslot[lane / 3] : -1;
     const bool rn0 = lane < 3 * nrem && sh.rnear[lane / 3];
-    uint64_t tag = tag0 + (uint64_t)sa * TAG;
+    uint64_t tag = tag0 + (uint64_t)sa * RES_TAG;
     int q = 0, o = MTS ? s0 / (Mb + 1) : 0;
     for (int s = sa; s < sb; ++s) {
       const int cb = s & 1, was = sh.dead[cb ^ 1];
       const bool kick = MTS && q == 0;
       if (MTS && q++ == Mb) { q = 0; ++o; }      // of stage s + 1
-      tag += TAG;
+      tag += RES_TAG;
       if (!kick) {
         if (lane < nx) sh.xi[lane] = xa;
         if (lane + 64 < nx) sh.xi[lane + 64] = xc;
