@@ -265,7 +265,8 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
                            hipStream_t s);
 
 // The sub-cycle in one launch (uniform, with mts > 0 the multiple-time-step
-// one, with rigid that of rigid bonds): entry w of the table seg (ntab entries,
+// one, with rigid that of rigid bonds, with win6 with memory for the wall sites
+// of some chain with r_c > 2): entry w of the table seg (ntab entries,
 // nseg of them in use) is the chain segment [a, b) of up to RES_OWN beads that
 // workgroup w owns for the whole cycle; it exchanges the positions its
 // neighbours need through d.xring (see k_md_resident).  Measured per coupled
@@ -308,7 +309,7 @@ constexpr int RES_XCD = 16;
 constexpr double RES_OWN_BYTES = 16e6;
 constexpr uint64_t RES_PLACE = 200000;   // 2 ms
 void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int ntab, int nseg, int nslots, int n_sub,
-                              int mts, const MdOverride& ov, uint64_t wait, bool own, bool rigid, hipStream_t s);
+                              int mts, const MdOverride& ov, uint64_t wait, bool own, bool rigid, bool win6, hipStream_t s);
 void launch_md_gate(const Dev& d, int nseg, hipStream_t s);
 // Noise of one sub-cycle into d.xi, for the step counter + step_offset.
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s);

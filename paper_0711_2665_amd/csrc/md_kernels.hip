@@ -2208,7 +2208,10 @@ constexpr int RES_REM = 144;                   // other remote beads
 constexpr int RES_IDX = RES_OWN + RES_HALO + RES_REM;
 constexpr int RES_PL = 4;                      // lanes per bead of the pair waves
 constexpr int RES_PH = 4;                      // pair forces kept per lane
-constexpr int RES_WH = 416;                    // wall-site forces kept (13 per bead at most for r_c <= 2)
+// Wall-site forces of a segment: no disk of radius 2 has more than 14 points of the
+// unit square lattice inside, none of radius 3 more than 32 (every position of
+// the centre, in ever smaller squares), so no row is tested against its end.
+constexpr int RES_WH = 14 * RES_OWN, RES_WH6 = 32 * RES_OWN;
 constexpr int RES_HASH = 512;
 constexpr uint32_t RES_FAIL = 0x80000000u;
 constexpr int RES_TILE = 256;                  // beads scanned together by a full list build
@@ -2222,19 +2225,6 @@ struct ResShared {
   double bnd[RES_OWN + 1][3];                  // row k: force on a + k of its bond to a + k - 1
   double ref[RES_OWN][3];                      // where the lists were built
   double xi[3 * RES_OWN];                      // the sub-step's noise
-  union {
-    struct {
-      double pairF[RES_PL][RES_PH][RES_OWN][3];   // pair forces of each lane's part of the list, in order
-      double wallF[RES_WH + 3][3];             // wall-site forces, bead by bead in site order
-    };
-    struct {                                   // set-up
-      int key[RES_HASH], val[RES_HASH];        // local index of a remote chain bead
-      int list[RES_OWN][MAXNBR];               // new lists (partner slots)
-      uint32_t bk[RES_OWN][27];                // the 27 buckets around a bead
-      double tile[RES_TILE][3];                // positions of RES_TILE chain beads
-      double vel[RES_OWN][3];
-    } h;
-  };
   uint8_t lst[RES_OWN][MAXNBR];                // the beads' lists as local indices, ascending chain order
   int lcnt[RES_OWN];
   uint8_t pcnt[RES_OWN][RES_PL];               // pair forces found (one beyond RES_PH: the sum evaluates them again)
@@ -2252,10 +2242,31 @@ struct ResShared {
   int owner;                                   // this workgroup set the failure bit
   int done;
   int ncand[RES_OWN];
+  union {
+    struct {
+      double pairF[RES_PL][RES_PH][RES_OWN][3];   // pair forces of each lane's part of the list, in order
+      double wallF[RES_WH + 3][3];             // wall-site forces, bead by bead in site order; last: the
+                                               // rows of r_c > 2 go on beyond the struct
+    };
+    struct {                                   // set-up
+      int key[RES_HASH], val[RES_HASH];        // local index of a remote chain bead
+      int list[RES_OWN][MAXNBR];               // new lists (partner slots)
+      uint32_t bk[RES_OWN][27];                // the 27 buckets around a bead
+      double tile[RES_TILE][3];                // positions of RES_TILE chain beads
+      double vel[RES_OWN][3];
+    } h;
+  };
 };
-static_assert(4 * sizeof(ResShared) <= (size_t)LDS_PER_CU, "four resident workgroups per CU");
-static_assert(sizeof(ResShared) % 16 == 0 && sizeof(ResShared) + sizeof(RigShared) <= (size_t)LDS_PER_CU && RES_WG == RIG_WG,
-              "one with rigid bonds");
+// The memory of a workgroup: with rigid bonds RigShared, then ResShared, then for
+// r_c > 2 more wall rows.  Dynamic, so that the kernel and its rescue share it.
+extern __shared__ __align__(16) unsigned char res_lds[];
+constexpr size_t res_base(bool rigid) { return rigid ? sizeof(RigShared) : 0; }
+constexpr size_t res_bytes(bool rigid, bool win6) {
+  return res_base(rigid) + (win6 ? offsetof(ResShared, wallF) + 3 * sizeof(double) * (RES_WH6 + 3) : sizeof(ResShared));
+}
+static_assert(sizeof(RigShared) % 16 == 0 && RES_WG == RIG_WG, "ResShared follows");
+static_assert(3 * res_bytes(false, false) <= (size_t)LDS_PER_CU && 2 * res_bytes(false, true) <= (size_t)LDS_PER_CU &&
+              res_bytes(true, true) <= (size_t)LDS_PER_CU, "RES_MAX_WG workgroups fit on the GPU; one with rigid bonds on a CU");
 
 // Orders one wave's LDS accesses (which the LDS executes in order) for the compiler.
 __device__ inline void wave_lds() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
@@ -2651,6 +2662,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
   }
   if (t <= n && (P.constrained || p0 + t == 0 || p0 + t == nb))
     for (int a = 0; a < 3; ++a) sh.bnd[t][a] = 0.0;
+  double (*const wallF)[3] = reinterpret_cast<double (*)[3]>(res_lds + res_base(RIGID) + offsetof(ResShared, wallF));
   const int links = sh.links;                    // 0: no other segment needs this one's positions
   const size_t half = (size_t)6 * nslots;        // words of one slot of the ring
   const bool noisy = P.sig != 0.0;
@@ -2766,11 +2778,11 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         }
         if (__any((wl & 0xff) != 0))
         for (int m = wl >> 8, m1 = m + (wl & 0xff); m < m1; m += 4) {   // four loads in flight
-          const double w0 = sh.wallF[m][c], w1 = sh.wallF[m + 1][c], w2 = sh.wallF[m + 2][c], w3 = sh.wallF[m + 3][c];
-          F += w0;
-          if (m + 1 < m1) F += w1;
-          if (m + 2 < m1) F += w2;
-          if (m + 3 < m1) F += w3;
+          const double f0 = wallF[m][c], f1 = wallF[m + 1][c], f2 = wallF[m + 2][c], f3 = wallF[m + 3][c];
+          F += f0;
+          if (m + 1 < m1) F += f1;
+          if (m + 2 < m1) F += f2;
+          if (m + 3 < m1) F += f3;
         }
         if (fl && c == g.wall_axis) F += P.f_drive;
         }
@@ -2976,10 +2988,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         }
         const uint64_t hm = __ballot(hit);
         const int o = total + __builtin_popcountll(hm & below);
-        if (hit) {
-          if (o < RES_WH) { sh.wallF[o][0] = d0; sh.wallF[o][1] = d1; sh.wallF[o][2] = d2; }
-          else fail(s);
-        }
+        if (hit) { wallF[o][0] = d0; wallF[o][1] = d1; wallF[o][2] = d2; }
         if (on && num == 0) {
           const uint64_t own = per == 64 ? hm : (hm >> lane) & 0xffffull;
           sh.wall[sh.wbead[r]] = (o << 8) | __builtin_popcountll(own);
@@ -2987,8 +2996,8 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
         total += __builtin_popcountll(hm);
       }
       wave_lds();
-      for (int o = lane; o < min(total, RES_WH); o += 64) {
-        double* w = sh.wallF[o];
+      for (int o = lane; o < total; o += 64) {
+        double* w = wallF[o];
         double Fs[3] = {0.0, 0.0, 0.0};
         lj_add(P, w[0], w[1], w[2], Fs);
         w[0] = Fs[0]; w[1] = Fs[1]; w[2] = Fs[2];
@@ -3077,10 +3086,6 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
   return 0;
 }
 
-// The memory of a workgroup (sizeof(ResShared) bytes of dynamic LDS, so that
-// the kernel and the function below share it).
-extern __shared__ __align__(16) unsigned char res_lds[];
-
 struct ResArgs {
   Dev d;
   double* ang;
@@ -3095,12 +3100,12 @@ struct ResArgs {
 // kernel's arguments in memory, so that none is copied for this call.
 template <bool MTS, bool RIGID>
 __device__ __attribute__((noinline)) void res_rescue(const ResArgs* a) {
-  ResShared& sh = *reinterpret_cast<ResShared*>(res_lds);
+  ResShared& sh = *reinterpret_cast<ResShared*>(res_lds + res_base(RIGID));
   const Dev& d = a->d;
   const FusedSeg seg = load_uniform(&a->segs[blockIdx.x]);
   const Rep& R = d.reps[seg.rep];
   const MdParams P = md_override(load_uniform(&R.mp), a->ov);
-  RigShared& rig = *reinterpret_cast<RigShared*>(res_lds + sizeof(ResShared));   // RIGID
+  RigShared& rig = *reinterpret_cast<RigShared*>(res_lds);   // RIGID
   if (res_pass<true, MTS, RIGID>(d, seg, R, P, sh, rig, a->nslots, a->nseg, a->n_sub, a->mts, a->wait) != 2) return;
   // the pass's failure was this workgroup's decision: it alone goes on.  No
   // other stores anything that the redo reads.
@@ -3113,12 +3118,12 @@ __device__ __attribute__((noinline)) void res_rescue(const ResArgs* a) {
 template <bool MTS, bool OWN, bool RIGID>
 __global__ __launch_bounds__(RES_WG, OWN ? 2 : 6) void k_md_resident(ResArgs a) {
   if (OWN) asm volatile("" ::: "v255");
-  ResShared& sh = *reinterpret_cast<ResShared*>(res_lds);
+  ResShared& sh = *reinterpret_cast<ResShared*>(res_lds + res_base(RIGID));
   const FusedSeg seg = load_uniform(&a.segs[blockIdx.x]);
   if (seg.rep < 0) return;                       // fills the table (see res_place)
   const Rep& R = a.d.reps[seg.rep];
   const MdParams P = md_override(load_uniform(&R.mp), a.ov);
-  RigShared& rig = *reinterpret_cast<RigShared*>(res_lds + sizeof(ResShared));   // RIGID
+  RigShared& rig = *reinterpret_cast<RigShared*>(res_lds);   // RIGID
   if (__builtin_expect(res_pass<false, MTS, RIGID>(a.d, seg, R, P, sh, rig, a.nslots, a.nseg, a.n_sub, a.mts, a.wait) == 0, 1)) return;
   __syncthreads();                               // sh.done and sh.owner are read
   res_rescue<MTS, RIGID>((const ResArgs*)__builtin_amdgcn_kernarg_segment_ptr());
@@ -3148,12 +3153,12 @@ void launch_md_gate(const Dev& d, int nseg, hipStream_t s) {
 }
 
 void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int ntab, int nseg, int nslots, int n_sub,
-                              int mts, const MdOverride& ov, uint64_t wait, bool own, bool rigid, hipStream_t s) {
+                              int mts, const MdOverride& ov, uint64_t wait, bool own, bool rigid, bool win6, hipStream_t s) {
   if (nslots <= 0 || n_sub <= 0 || nseg <= 0 || ntab < nseg) return;
   const auto k = rigid ? k_md_resident<false, true, true>
                        : (mts > 0 ? (own ? k_md_resident<true, true, false> : k_md_resident<true, false, false>)
                                   : (own ? k_md_resident<false, true, false> : k_md_resident<false, false, false>));
-  hipLaunchKernelGGL(k, dim3((unsigned)ntab), dim3(RES_WG), sizeof(ResShared) + (rigid ? sizeof(RigShared) : 0), s,
+  hipLaunchKernelGGL(k, dim3((unsigned)ntab), dim3(RES_WG), res_bytes(rigid, win6), s,
                      (ResArgs{d, ang, seg, nslots, nseg, n_sub, mts, ov, wait}));
 }
 

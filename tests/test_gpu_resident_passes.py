@@ -1,0 +1,58 @@
+"""What the resident MD sub-cycle's first pass holds, and what takes over
+where it does not: bit for bit the other forms of the cycle, through the C
+ABI, for chains that lie along the wall."""
+import numpy as np
+import pytest
+
+from paper_0711_2665_amd.workloads import C0, scaled
+
+pytestmark = pytest.mark.gpu
+
+
+def _torch():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _state(ctx, r=0):
+    ctx.torch.cuda.synchronize()
+    b = {k: t.cpu().numpy().copy() for k, t in ctx.beads(r).items()}
+    return ctx.pops(r).double().cpu().numpy(), b
+
+
+def _same(a, b, tag):
+    (pa, ba), (pb, bb) = _state(*a), _state(*b)
+    diff = {k: int((ba[k] != bb[k]).sum()) for k in ("r", "v", "up", "J")}
+    print(f"{tag}: pops differing {int((pa != pb).sum())}, beads {diff}", flush=True)
+    assert np.array_equal(pa, pb), tag
+    for k in ("r", "v", "up", "J"):
+        assert np.isfinite(ba[k]).all() and np.array_equal(ba[k], bb[k]), (tag, k)
+
+
+def _flat(n, a, row, origin):
+    """n beads in rows of `row`, forth and back, spacing a, in the plane z = origin[2]."""
+    out = [(k % row if k // row % 2 == 0 else row - 1 - k % row, k // row, 0) for k in range(n)]
+    return np.asarray(out, dtype=np.float64) * a + np.asarray(origin)
+
+
+@pytest.mark.parametrize("rc,spacing,offset,height", [
+    (2.0, 1.0, (0.07, 0.48), 0.0),     # 14 wall sites within r_c of every bead, the most there are
+    (2.5, 1.25, (0.1, 0.2), 0.9),
+    (2.5, 2.0, (0.5, 0.5), 0.0),       # 21 within 2.5
+    (3.0, 2.0, (0.5, 0.5), 0.0),       # 32 within 3, the most there are
+])
+def test_chain_along_the_wall(rc, spacing, offset, height):
+    _torch()
+    from paper_0711_2665_amd import lbmd
+    cfg = scaled(C0, shape=(64, 64, 24), wall_pos=12, nb=100, rc=rc, eps=1e-6, r0=spacing, kappa=0.5)
+    r = _flat(100, spacing, 12, (2 + offset[0], 2 + offset[1], 12 + height))
+    sims = [lbmd.Simulation(cfg, r, None) for _ in range(2)]
+    sims[1].md_fused(2)
+    for n in (1, 2):
+        for s in sims:
+            s.couple_step(n)
+        _same((sims[0],), (sims[1],), f"r_c {rc}, resident against fused")
+    for s in sims:
+        s.check()
