@@ -191,7 +191,7 @@ WorkLayout work_layout(const lb_desc* d, int nrep, const Packing& pk) {
   w.JS = take(sizeof(double) * 3 * ns);
   w.fang = take(sizeof(double) * 9 * ns);
   w.redo = take(sizeof(int) * R);
-  w.rsync = take(sizeof(uint32_t) * 2 * R);
+  w.rsync = take(sizeof(uint32_t) * 3 * R);
   w.rseg = take(sizeof(FusedSeg) * std::max<size_t>(res_place(d, nrep, pk).size(), 1));
   w.xring = take(sizeof(uint64_t) * xring_slots(pk) * 2 * 3 * ns);
   w.xflag = take(sizeof(uint64_t) * XFLAG * 2 * (size_t)(pk.nrseg > 0 ? pk.nrseg : 1));

@@ -123,7 +123,8 @@ struct Dev {
                     // kicks of the multiple-time-step cycle; 4, 5: the start of a block; 6 to 9:
                     // the copies of 0 to 3 for readers on the same XCD)
   unsigned long long* xflag;   // [3][segments][2]: a word per segment, likewise (0, 1: the start of a block; 2: its XCD)
-  uint32_t* rsync;  // [R][2]: per pass of the resident cycle, segments done and the failure bit
+  uint32_t* rsync;  // [R][3]: per pass of the resident cycle, segments done and the failure bit; segments
+                    // that left the last pass without a result
   Ctrl* ctrl;
   int* redo;        // per replica: first sub-step the fused sub-cycle leaves to the per-sub-step
                     // launches (-1: none); reset at every cycle's opening
@@ -329,8 +330,9 @@ __device__ inline void md_begin(const Dev& d, int nrep, int t, int nt) {
   }
   for (int r = t; r < nrep; r += nt) {
     d.redo[r] = -1;
-    d.rsync[2 * r] = 0u;
-    d.rsync[2 * r + 1] = 0u;
+    d.rsync[3 * r] = 0u;
+    d.rsync[3 * r + 1] = 0u;
+    d.rsync[3 * r + 2] = 0u;
     uint32_t* w = d.rb + 4 * r;
     w[0] = w[3];
     w[1] = 0u;

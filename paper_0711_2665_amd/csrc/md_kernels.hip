@@ -2177,7 +2177,7 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
 // their results only when all of them have finished.  Else a second pass takes
 // the replica from the cycle's start in blocks of RES_BLOCK sub-steps, with new
 // lists where one needs them, so a bead may travel half the skin per block
-// instead of per cycle.  When that fails too, the workgroup that set the bit advances the
+// instead of per cycle.  When that fails too, the workgroup that leaves last advances the
 // replica alone (md_redo).  Every wait ends: the polled value arrives, the bit
 // is set, or the clock runs out.  All of this is one launch: a second one that
 // finds nothing to do would wait for room beside the sweep (0.49 ms of a
@@ -2239,7 +2239,6 @@ struct ResShared {
   int nrem;
   int dead[2];                                 // by parity of the sub-step
   int lost;                                    // a set-up failed
-  int owner;                                   // this workgroup set the failure bit
   int done;
   int ncand[RES_OWN];
   union {
@@ -2342,10 +2341,9 @@ __device__ inline bool res_poll(const unsigned long long* o, uint64_t tag, const
   }
 }
 
-// One pass of the cycle (see above); 0: done, 1: failed, 2: failed, by this
-// workgroup's decision.
+// One pass of the cycle (see above); false: it failed.
 template <bool BLOCKS, bool MTS, bool RIGID>
-__device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const Rep& R, const MdParams& P, ResShared& sh,
+__device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const Rep& R, const MdParams& P, ResShared& sh,
                                         RigShared& rig, int nslots, int nseg, int n_sub, int mts, uint64_t wait) {
   const int rep = seg.rep;
   const int Mb = MTS ? n_sub / mts : 0;          // sub-steps between two kicks
@@ -2355,7 +2353,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
   const int p0 = seg.a, n = seg.b - seg.a;
   const int t = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(t) >> 6, lane = t & 63;
-  uint32_t* word = &d.rsync[2 * rep + BLOCKS];
+  uint32_t* word = &d.rsync[3 * rep + BLOCKS];
   const uint32_t ng = (uint32_t)((nb + RES_OWN - 1) / RES_OWN);   // the replica's segments
   // Failure ends the pass for the whole replica.  It is decided on one word:
   // the number of segments that have finished, and a failure bit that can
@@ -2364,7 +2362,7 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     uint32_t w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     while (w < ng) {
       const uint32_t was = atomicCAS(word, w, w | RES_FAIL);
-      if (was == w) { sh.owner = 1; break; }
+      if (was == w) break;
       w = was;
     }
   };
@@ -2402,7 +2400,6 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
   const int g0 = seg.id - p0 / RES_OWN;          // the replica's first segment
   if (t == 0) {
     sh.lost = 0;
-    sh.owner = 0;
     if (!BLOCKS) {
       __hip_atomic_fetch_add(&d.ctrl->placed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (seg.id == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)n_sub);
@@ -3076,14 +3073,14 @@ __device__ __forceinline__ int res_pass(const Dev& d, const FusedSeg seg, const 
     sh.done = !dead && __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ng;
   }
   __syncthreads();
-  if (!sh.done) return sh.owner ? 2 : 1;
+  if (!sh.done) return false;
   if (mine) {
     d.r[3 * slot + c] = x;
     d.v[3 * slot + c] = v;
     d.J[3 * slot + c] = J;
     if (!fin) atomicOr(&d.ctrl->err, E_BEADS);
   }
-  return 0;
+  return true;
 }
 
 struct ResArgs {
@@ -3106,10 +3103,18 @@ __device__ __attribute__((noinline)) void res_rescue(const ResArgs* a) {
   const Rep& R = d.reps[seg.rep];
   const MdParams P = md_override(load_uniform(&R.mp), a->ov);
   RigShared& rig = *reinterpret_cast<RigShared*>(res_lds);   // RIGID
-  if (res_pass<true, MTS, RIGID>(d, seg, R, P, sh, rig, a->nslots, a->nseg, a->n_sub, a->mts, a->wait) != 2) return;
-  // the pass's failure was this workgroup's decision: it alone goes on.  No
-  // other stores anything that the redo reads.
+  if (res_pass<true, MTS, RIGID>(d, seg, R, P, sh, rig, a->nslots, a->nseg, a->n_sub, a->mts, a->wait)) return;
+  // The redo stores the state, the positions and the lists that every segment's
+  // passes start from, and one of them may not have begun (it finds no room while
+  // another context's cycle has its place): so the segment that leaves last
+  // goes on.  Nobody waits.  The segments' stores (the adjoint's tape) are
+  // released before they count themselves, so that the redo's come after them.
+  const uint32_t ng = (uint32_t)((P.nb + RES_OWN - 1) / RES_OWN);
   __syncthreads();
+  if (threadIdx.x == 0)
+    sh.done = __hip_atomic_fetch_add(&d.rsync[3 * seg.rep + 2], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u == ng;
+  __syncthreads();
+  if (!sh.done) return;
   md_redo<RES_WG, MTS, RIGID>(d, R, P, seg.rep, a->ang, a->nslots, 0, a->n_sub, a->mts, &rig, sh.dead[0], sh.dead[1]);
 }
 
@@ -3124,8 +3129,8 @@ __global__ __launch_bounds__(RES_WG, OWN ? 2 : 6) void k_md_resident(ResArgs a) 
   const Rep& R = a.d.reps[seg.rep];
   const MdParams P = md_override(load_uniform(&R.mp), a.ov);
   RigShared& rig = *reinterpret_cast<RigShared*>(res_lds);   // RIGID
-  if (__builtin_expect(res_pass<false, MTS, RIGID>(a.d, seg, R, P, sh, rig, a.nslots, a.nseg, a.n_sub, a.mts, a.wait) == 0, 1)) return;
-  __syncthreads();                               // sh.done and sh.owner are read
+  if (__builtin_expect(res_pass<false, MTS, RIGID>(a.d, seg, R, P, sh, rig, a.nslots, a.nseg, a.n_sub, a.mts, a.wait), 1)) return;
+  __syncthreads();                               // sh.done is read
   res_rescue<MTS, RIGID>((const ResArgs*)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
