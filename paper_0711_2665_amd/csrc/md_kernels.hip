@@ -1842,7 +1842,8 @@ __device__ inline void rig_solve(RigShared& q, int n, double ai, double bi, doub
 
 // The opening of a sub-step (START of k_md_constraint): r, v of thread k's bead
 // to the positions x and velocities of the next sub-step, in q.x and q.v.
-__device__ inline void rig_open(RigShared& q, int nb, double hh, double d2, const double* r, double* v, uint32_t* err) {
+// False: the bonds could not be met (E_BEADS, if the result is kept).
+__device__ inline bool rig_open(RigShared& q, int nb, double hh, double d2, const double* r, double* v) {
   const int k = threadIdx.x, nbond = nb - 1;
   const bool own = k < nb;
   double xd[3] = {0.0, 0.0, 0.0}, e[3] = {0.0, 0.0, 0.0};
@@ -1857,6 +1858,7 @@ __device__ inline void rig_open(RigShared& q, int nb, double hh, double d2, cons
   if (k < nbond)
     for (int a = 0; a < 3; ++a) e[a] = q.e[k][a] = q.v[k][a] - q.v[k + 1][a];
   lds_barrier();
+  bool met = true;
   for (int it = 0;; ++it) {
     double sv[3] = {0.0, 0.0, 0.0}, sig = 0.0;
     if (k < nbond) {
@@ -1865,10 +1867,7 @@ __device__ inline void rig_open(RigShared& q, int nb, double hh, double d2, cons
     }
     const double worst = rig_max(fabs(sig), q, it & 1);
     if (worst <= CON_TOL * d2) break;
-    if (it == CON_MAXIT) {
-      if (k == 0) atomicOr(err, E_BEADS);
-      break;
-    }
+    if (it == CON_MAXIT) { met = false; break; }
     double a_ = 0.0, b_ = 1.0, c_ = 0.0;
     if (k < nbond) {
       b_ = 4.0 * dot3v(sv, e);
@@ -1892,12 +1891,13 @@ __device__ inline void rig_open(RigShared& q, int nb, double hh, double d2, cons
       q.v[k][a] = v[a] + dx / hh;
     }
   lds_barrier();
+  return met;
 }
 
 // After the kick (q.x the sub-step's positions, q.v the kicked velocities of
 // every bead): RATTLE, the second half drift, and unless last the opening of
 // the next sub-step; last: q.x, q.v are the step's end.
-__device__ inline void rig_step(RigShared& q, int nb, double hh, double d2, bool last, uint32_t* err) {
+__device__ inline bool rig_step(RigShared& q, int nb, double hh, double d2, bool last) {
   const int k = threadIdx.x, nbond = nb - 1;
   double v[3] = {0.0, 0.0, 0.0}, r[3] = {0.0, 0.0, 0.0}, rv[3] = {0.0, 0.0, 0.0};
   double a_ = 0.0, b_ = 1.0, c_ = 0.0, r_ = 0.0;
@@ -1926,9 +1926,9 @@ __device__ inline void rig_step(RigShared& q, int nb, double hh, double d2, bool
     if (k < nb)
       for (int a = 0; a < 3; ++a) { q.x[k][a] = r[a]; q.v[k][a] = v[a]; }
     lds_barrier();
-    return;
+    return true;
   }
-  rig_open(q, nb, hh, d2, r, v, err);
+  return rig_open(q, nb, hh, d2, r, v);
 }
 
 // Sub-steps sp .. n_sub - 1 of replica rep by one workgroup of WG threads, from
@@ -1947,7 +1947,7 @@ __device__ inline void md_redo(const Dev& d, const Rep& R, const MdParams& P, in
     double r[3] = {0.0, 0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
     if (t < nb)
       for (int a = 0; a < 3; ++a) { r[a] = d.r[3 * (so + t) + a]; v[a] = d.v[3 * (so + t) + a]; }
-    rig_open(*rig, nb, P.hh, P.r0 * P.r0, r, v, &d.ctrl->err);
+    fin = rig_open(*rig, nb, P.hh, P.r0 * P.r0, r, v);
     if (t < nb)
       for (int a = 0; a < 3; ++a) { d.rmid0[3 * (so + t) + a] = rig->x[t][a]; d.v[3 * (so + t) + a] = rig->v[t][a]; }
     __syncthreads();
@@ -2072,7 +2072,7 @@ __device__ inline void md_redo(const Dev& d, const Rep& R, const MdParams& P, in
       if (t < nb)
         for (int a = 0; a < 3; ++a) rig->x[t][a] = cur[3 * (so + t) + a];
       lds_barrier();
-      rig_step(*rig, nb, P.hh, P.r0 * P.r0, s == end - 1, &d.ctrl->err);
+      fin = rig_step(*rig, nb, P.hh, P.r0 * P.r0, s == end - 1) && fin;
       if (t < nb)
         for (int a = 0; a < 3; ++a) {
           (s == end - 1 ? d.r : nxt)[3 * (so + t) + a] = rig->x[t][a];
@@ -2383,11 +2383,12 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
   const bool mine = wave < 2 && lane < 48 && i < n;
   const int slot = so + p0 + (mine ? i : 0), p = p0 + i;
   double x = 0.0, v = 0.0, J = 0.0, u = 0.0;
+  bool fin = true;                               // of the pass; an error only if its result is kept
   if (RIGID) {
     double r3[3] = {0.0, 0.0, 0.0}, v3[3] = {0.0, 0.0, 0.0};
     if (t < nb)
       for (int a = 0; a < 3; ++a) { r3[a] = d.r[3 * (so + t) + a]; v3[a] = d.v[3 * (so + t) + a]; }
-    rig_open(rig, nb, P.hh, P.r0 * P.r0, r3, v3, &d.ctrl->err);
+    fin = rig_open(rig, nb, P.hh, P.r0 * P.r0, r3, v3);
   }
   if (mine) {
     x = RIGID ? rig.x[p][c] : d.rmid0[3 * slot + c];
@@ -2410,7 +2411,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     if (!BLOCKS && d.rb[4 * rep] != 0u) lose();  // the lists are not valid at the start
     if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & RES_FAIL) sh.lost = 1;
   }
-  bool fin = true, dead = false;
+  bool dead = false;
   const int len = !BLOCKS ? end : (MTS ? Mb + 1 : RES_BLOCK);
   for (int s0 = 0, blk = 0;; s0 += len, ++blk) {
   const int s1 = BLOCKS ? min(s0 + len, end) : end;
@@ -2681,7 +2682,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     }
     lds_barrier();
     if (__builtin_amdgcn_readfirstlane(sh.dead[cb])) return;   // uniform: the next writes follow the barriers below
-    rig_step(rig, nb, P.hh, P.r0 * P.r0, s == end - 1, &d.ctrl->err);
+    fin = rig_step(rig, nb, P.hh, P.r0 * P.r0, s == end - 1) && fin;
     if (s < end - 1) {
       for (int k = t; k < 3 * (RES_OWN + nrem); k += RES_WG) {
         const int l = k / 3, q = l < RES_OWN ? (l < n ? p0 + l : -1) : sh.rslot[l - RES_OWN] - so;

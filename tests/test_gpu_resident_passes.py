@@ -88,3 +88,24 @@ def test_redos_of_contexts_side_by_side(monkeypatch, rigid):
         _same((s,), (want,), f"context {k}, redo against resident")
         s.check()
         assert s.diagnostics()["rebuilds"] > 0
+
+
+def test_bonds_that_cannot_be_met_are_flagged(monkeypatch):
+    """Beads thrown 300 bond lengths apart in half a sub-step: the projection
+    does not converge, and the watchdog says so in the resident cycle, in its
+    redo and in the launches (with a harmonic chain beside)."""
+    torch = _torch()
+    from paper_0711_2665_amd import lbmd
+    cfg = scaled(C0, shape=(40, 40, 40), wall_pos=20, nb=70, init_seed=7, constraints=1, kT=0.0)
+    other = scaled(C0, shape=(20, 20, 20), wall_pos=10, nb=3, replica=1)
+    r = initial_chain(cfg)[0]
+    sims = [lbmd.Ensemble([cfg, other], [r, initial_chain(other)[0]]), lbmd.Simulation(cfg, r, None)]
+    monkeypatch.setenv("LBMD_MD_WAIT_TICKS", "0")
+    sims.append(lbmd.Simulation(cfg, r, None))
+    v = np.random.default_rng(1).normal(0.0, 6e4, (70, 3))
+    for s in sims:
+        s.relax(100, 1.0)
+        assert s.diagnostics()["watchdog"] == 0
+        s.beads(0)["v"].copy_(torch.as_tensor(v, device=s.device))
+        s.couple_step(1)
+        assert s.diagnostics()["watchdog"] & 2
