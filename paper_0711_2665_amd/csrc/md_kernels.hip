@@ -1750,7 +1750,6 @@ __global__ __launch_bounds__(FU_WG) void k_md_fused(Dev d, FusedBufs fb, int nsl
 // beads of the chain.  A replica whose last block wrote the shadow set gets v
 // and J copied back.
 constexpr int RD_WG = 1024;
-constexpr int RD_NC = 32;          // pair partners within r_c of one bead
 
 // A workgroup barrier that orders LDS only: __syncthreads would also wait for
 // every outstanding global access (the published positions on their way to
@@ -2014,19 +2013,7 @@ __device__ inline void md_redo(const Dev& d, const Rep& R, const MdParams& P, in
     for (int q = t; q < nb; q += WG) {
       const int sl = so + q;
       const double rp[3] = {cur[3 * sl], cur[3 * sl + 1], cur[3 * sl + 2]};
-      int part[RD_NC];
-      int np = 0;
       const int cnt = !MTS || kick ? d.ncnt[sl] : 0;
-      for (int k = 0; k < cnt && np <= RD_NC; ++k) {
-        const int j = d.nbr[(size_t)sl * MAXNBR + k] - so;   // list entries are slots
-        const double e0 = min_image(rp[0] - cur[3 * (so + j)], g.nx);
-        const double e1 = min_image(rp[1] - cur[3 * (so + j) + 1], g.ny);
-        const double e2 = min_image(rp[2] - cur[3 * (so + j) + 2], g.nz);
-        if (!(e0 * e0 + e1 * e1 + e2 * e2 < P.rc2)) continue;
-        if (np < RD_NC) part[np] = j;
-        ++np;
-      }
-      if (np > RD_NC) { over = true; np = RD_NC; }
       const double* a3 = (q - 1 >= 1 && q - 1 <= nb - 2) ? &ang[9 * (size_t)(sl - 1)] : nullptr;
       const double* ac = (q >= 1 && q <= nb - 2) ? &ang[9 * (size_t)sl] : nullptr;
       const double* a1 = (q + 1 >= 1 && q + 1 <= nb - 2) ? &ang[9 * (size_t)(sl + 1)] : nullptr;
@@ -2034,7 +2021,7 @@ __device__ inline void md_redo(const Dev& d, const Rep& R, const MdParams& P, in
       const bool fast = !kick, slow = !MTS || kick;
       fu_force(P, g, q, rp, fast && q > 0 ? &cur[3 * (sl - 1)] : nullptr,
                fast && q < nb - 1 ? &cur[3 * (sl + 1)] : nullptr, fast ? a3 : nullptr, fast ? ac : nullptr,
-               fast ? a1 : nullptr, cur + 3 * (size_t)so, part, np, F, slow);
+               fast ? a1 : nullptr, cur, d.nbr + (size_t)sl * MAXNBR, cnt, F, slow);   // list entries are slots
       double v[3] = {d.v[3 * sl], d.v[3 * sl + 1], d.v[3 * sl + 2]};
       double J[3] = {d.J[3 * sl], d.J[3 * sl + 1], d.J[3 * sl + 2]};
       double u[3] = {d.up[3 * sl], d.up[3 * sl + 1], d.up[3 * sl + 2]};

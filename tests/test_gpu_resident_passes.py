@@ -109,3 +109,35 @@ def test_bonds_that_cannot_be_met_are_flagged(monkeypatch):
         s.beads(0)["v"].copy_(torch.as_tensor(v, device=s.device))
         s.couple_step(1)
         assert s.diagnostics()["watchdog"] & 2
+
+
+def test_more_than_32_pairs_of_a_bead_in_a_redo(orc, monkeypatch):
+    """45 beads within r_c of one another (44 list partners each, within the 48
+    that a list holds): the resident cycle, its redo and the fused cycle (whose
+    blocks hold 16 close partners, so one workgroup redoes them) equal the
+    oracle bit for bit, without noise and bending."""
+    _torch()
+    from paper_0711_2665_amd import lbmd
+    cfg = scaled(C0, shape=(24, 24, 24), wall_axis=-1, wall_pos=0, pore_h=0, nb=45, rc=3.0, sigma=0.4, eps=0.01, r0=0.5,
+                 kT=0.0, kappa=0.0)
+    r = []
+    for k in range(45):
+        row, x = divmod(k, 4)
+        z, y = divmod(row, 4)
+        r.append((3 - x if row % 2 else x, 3 - y if z % 2 else y, z))
+    r = np.asarray(r, dtype=np.float64) * 0.5 + np.array([11.13, 10.37, 11.29])
+    assert np.linalg.norm(r[:, None] - r[None], axis=2).max() < 2.9
+    o = orc.Oracle(cfg, r, np.zeros_like(r))
+    sims = [lbmd.Simulation(cfg, r, None) for _ in range(2)]
+    sims[1].md_fused(2)
+    monkeypatch.setenv("LBMD_MD_WAIT_TICKS", "0")
+    sims.append(lbmd.Simulation(cfg, r, None))
+    o.couple_step(3)
+    ob = o.beads()
+    for tag, s in zip(("resident", "fused", "redo"), sims):
+        s.couple_step(3)
+        b = _state(s)[1]
+        print(tag, {k: int((b[k] != ob[k]).sum()) for k in ("r", "v", "up", "J")}, s.diagnostics()["nbr_max"], flush=True)
+        s.check()
+        for k in ("r", "v", "up", "J"):
+            assert np.array_equal(b[k], ob[k]), (tag, k)
