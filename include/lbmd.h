@@ -454,6 +454,15 @@ int lb_profile_stop(lb_ctx* ctx, double* mean_lb_ms, double* mean_bead_ms, int* 
  * the watchdog, bit 4, which lb_check reports as LB_ERR_UNSTABLE). */
 int lb_diagnostics(lb_ctx* ctx, int64_t* out);
 
+/* Diagnostics of the sub-cycle in one launch (workgroups that stay for the
+ * whole cycle; used up to 512 segments of 32 beads): synchronises the stream
+ * and writes three int64, counted per replica and cycle: out[0] = cycles begun
+ * that way (relaxation included; 0: single launches or fused blocks), out[1] =
+ * those whose first pass could not hold (a bead beyond half the list skin, too
+ * many partners, a workgroup that waited too long) and went on in a second,
+ * out[2] = those that one workgroup redid, which is much slower. */
+int lb_md_passes(lb_ctx* ctx, int64_t* out);
+
 /* Message of the last failed call on this thread (never NULL). */
 const char* lb_last_error(void);
 

@@ -1330,13 +1330,29 @@ int lb_check(lb_ctx* c) {
 
 int64_t lb_step_count(lb_ctx* c) { return c ? c->steps : -1; }
 
-int lb_diagnostics(lb_ctx* c, int64_t* out) {
-  if (!c || !out) return fail(LB_ERR_ARG, "bad arguments");
+// The control block, once the stream is done.
+static int read_ctrl(lb_ctx* c, Ctrl& h) {
   hipError_t e = hipStreamSynchronize(c->s);
   if (e != hipSuccess) return fail(LB_ERR_DEVICE, "stream: %s", hipGetErrorString(e));
-  Ctrl h;
   e = hipMemcpy(&h, c->D.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost);
   if (e != hipSuccess) return fail(LB_ERR_DEVICE, "diagnostics read: %s", hipGetErrorString(e));
+  return LB_OK;
+}
+
+int lb_md_passes(lb_ctx* c, int64_t* out) {
+  if (!c || !out) return fail(LB_ERR_ARG, "bad arguments");
+  Ctrl h;
+  if (int rc = read_ctrl(c, h)) return rc;
+  out[0] = (int64_t)h.res_cycles;
+  out[1] = (int64_t)h.res_second;
+  out[2] = (int64_t)h.res_redone;
+  return LB_OK;
+}
+
+int lb_diagnostics(lb_ctx* c, int64_t* out) {
+  if (!c || !out) return fail(LB_ERR_ARG, "bad arguments");
+  Ctrl h;
+  if (int rc = read_ctrl(c, h)) return rc;
   out[0] = (int64_t)h.rebuilds;
   out[1] = (int64_t)h.substeps;
   out[2] = (int64_t)c->ntiles;

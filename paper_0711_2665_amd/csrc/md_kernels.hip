@@ -2349,7 +2349,10 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     uint32_t w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     while (w < ng) {
       const uint32_t was = atomicCAS(word, w, w | RES_FAIL);
-      if (was == w) break;
+      if (was == w) {
+        if (!BLOCKS) atomicAdd((unsigned long long*)&d.ctrl->res_second, 1ull);
+        break;
+      }
       w = was;
     }
   };
@@ -2391,6 +2394,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     if (!BLOCKS) {
       __hip_atomic_fetch_add(&d.ctrl->placed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (seg.id == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)n_sub);
+      if (p0 == 0) atomicAdd((unsigned long long*)&d.ctrl->res_cycles, 1ull);
       const unsigned long long w = res_xcd();
       res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id, w);
       res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id + 1, w ^ tagx);
@@ -3103,6 +3107,7 @@ __device__ __attribute__((noinline)) void res_rescue(const ResArgs* a) {
     sh.done = __hip_atomic_fetch_add(&d.rsync[3 * seg.rep + 2], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u == ng;
   __syncthreads();
   if (!sh.done) return;
+  if (threadIdx.x == 0) atomicAdd((unsigned long long*)&d.ctrl->res_redone, 1ull);
   md_redo<RES_WG, MTS, RIGID>(d, R, P, seg.rep, a->ang, a->nslots, 0, a->n_sub, a->mts, &rig, sh.dead[0], sh.dead[1]);
 }
 

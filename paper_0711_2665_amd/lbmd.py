@@ -111,6 +111,7 @@ def _declare(L):
     L.lb_step_count.argtypes = [P]
     L.lb_step_count.restype = C.c_int64
     L.lb_diagnostics.argtypes = [P, C.POINTER(C.c_int64)]
+    L.lb_md_passes.argtypes = [P, C.POINTER(C.c_int64)]
     L.lb_profile_start.argtypes = [P, C.c_int]
     L.lb_profile_stop.argtypes = [P, C.POINTER(C.c_double), C.POINTER(C.c_double), C.POINTER(C.c_int)]
 
@@ -344,6 +345,13 @@ class Context:
         return dict(zip(("rebuilds", "substeps", "sweep_tiles", "watchdog", "steps", "forced_total",
                          "cell_rebuilds", "fused_blocks", "fused_redos", "why_moved", "why_partners",
                          "why_capacity", "why_unsettled", "why_displacement", "nbr_max"), list(out)))
+
+    def md_passes(self):
+        """Replica cycles run in one launch, those that needed a second pass
+        and those that one workgroup redid; see lb_md_passes."""
+        out = (C.c_int64 * 3)()
+        _raise(lib().lb_md_passes(self.ctx, out))
+        return dict(zip(("cycles", "second", "redone"), list(out)))
 
     def step_count(self):
         return int(lib().lb_step_count(self.ctx))

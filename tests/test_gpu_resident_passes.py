@@ -4,7 +4,7 @@ ABI, for chains that lie along the wall."""
 import numpy as np
 import pytest
 
-from paper_0711_2665_amd.workloads import C0, initial_chain, scaled
+from paper_0711_2665_amd.workloads import C0, PAPER_LJ, initial_chain, scaled
 
 pytestmark = pytest.mark.gpu
 
@@ -141,3 +141,47 @@ def test_more_than_32_pairs_of_a_bead_in_a_redo(orc, monkeypatch):
         s.check()
         for k in ("r", "v", "up", "J"):
             assert np.array_equal(b[k], ob[k]), (tag, k)
+
+
+def _passes(s, n):
+    """Passes of n coupled steps."""
+    a = s.md_passes()
+    s.couple_step(n)
+    return {k: x - a[k] for k, x in s.md_passes().items()}
+
+
+def test_which_pass_ran(monkeypatch):
+    """The counters of the passes: an ordinary chain stays in the first one, a
+    drifting one goes on in the second, a very fast one and every chain of more
+    than one segment that may not wait end in the redo; the fused cycle and a
+    context with too many segments run no pass."""
+    _torch()
+    from paper_0711_2665_amd import lbmd
+
+    def make(nb, speed=0.0, **kw):
+        cfg = scaled(C0, shape=(40, 40, 40), wall_pos=20, nb=nb, init_seed=9, **kw)
+        s = lbmd.Simulation(cfg, initial_chain(cfg)[0], None)
+        s.relax(1000, 1.0)
+        if speed:
+            s.beads()["v"][:, 1] = speed
+        return s
+    for nb, kw in ((20, {}), (300, {}), (300, dict(constraints=1)), (300, dict(mts_outer=5, **PAPER_LJ))):
+        assert _passes(make(nb, **kw), 3) == {"cycles": 3, "second": 0, "redone": 0}, (nb, kw)
+    assert _passes(make(300, 2.0), 3) == {"cycles": 3, "second": 3, "redone": 0}
+    assert _passes(make(300, 9.0), 3) == {"cycles": 3, "second": 3, "redone": 3}
+    assert _passes(make(300, 0.9, constraints=1), 2) == {"cycles": 2, "second": 2, "redone": 0}
+    fused = make(300)
+    fused.md_fused(10)
+    assert _passes(fused, 2) == {"cycles": 0, "second": 0, "redone": 0}
+    monkeypatch.setenv("LBMD_MD_WAIT_TICKS", "0")
+    assert _passes(make(32), 2) == {"cycles": 2, "second": 0, "redone": 0}
+    assert _passes(make(33), 2) == {"cycles": 2, "second": 2, "redone": 2}
+
+
+@pytest.mark.parametrize("rc,spacing,height", [(2.0, 1.0, 0.0), (2.5, 1.25, 0.9), (3.0, 2.0, 0.0)])
+def test_chain_along_the_wall_stays_in_the_first_pass(rc, spacing, height):
+    _torch()
+    from paper_0711_2665_amd import lbmd
+    cfg = scaled(C0, shape=(64, 64, 24), wall_pos=12, nb=100, rc=rc, eps=1e-6, r0=spacing, kappa=0.5)
+    s = lbmd.Simulation(cfg, _flat(100, spacing, 12, (2.5, 2.5, 12 + height)), None)
+    assert _passes(s, 3) == {"cycles": 3, "second": 0, "redone": 0}
