@@ -200,8 +200,13 @@ int lb_ensemble_sizes(const lb_desc* d, int nrep, lb_sizes* out);
  * zero velocity) and uploads the bead positions r0_host and velocities
  * v0_host ([nb][3] doubles, host memory; v0_host may be NULL for zero;
  * positions are unwrapped).  stream is a hipStream_t (NULL: the default
- * stream).  Synchronises the stream before returning.  LB_ERR_ARG: as
- * lb_buffer_sizes, a NULL or misaligned buffer, or non-finite bead state. */
+ * stream).  Synchronises the stream before returning.  The environment
+ * variable LBMD_MD_WAIT_TICKS (a whole number from 0 to 10^9, ticks of 10 ns;
+ * 0.1 s without it), read here, limits how long a workgroup of the sub-cycle
+ * waits for another before one workgroup redoes the chain's cycle: the results
+ * are the same, the redo is much slower (lb_md_passes).  LB_ERR_ARG: as
+ * lb_buffer_sizes, a NULL or misaligned buffer, non-finite bead state, or
+ * another value of that variable. */
 int lb_init(const lb_desc* d, const lb_buffers* b, const double* r0_host, const double* v0_host,
             void* stream, lb_ctx** out);
 

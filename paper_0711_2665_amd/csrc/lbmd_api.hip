@@ -397,6 +397,21 @@ struct SweepCfg {
 // A wait inside the resident sub-cycle normally lasts microseconds; longer
 // ones mean that the GPU is shared.
 constexpr uint64_t RES_WAIT = 10000000;   // 0.1 s
+constexpr uint64_t RES_WAIT_MOST = 1000000000;   // 10 s
+
+// The limit that LBMD_MD_WAIT_TICKS asks for, in *ticks (as it is without it).
+int wait_limit(uint64_t* ticks) {
+  const char* e = std::getenv("LBMD_MD_WAIT_TICKS");
+  if (!e) return LB_OK;
+  uint64_t v = 0;
+  const char* p = e;
+  for (; *p >= '0' && *p <= '9' && v <= RES_WAIT_MOST; ++p) v = 10 * v + (uint64_t)(*p - '0');
+  if (p == e || *p || v > RES_WAIT_MOST)
+    return fail(LB_ERR_ARG, "LBMD_MD_WAIT_TICKS is not a whole number from 0 to %llu: \"%.40s\"",
+                (unsigned long long)RES_WAIT_MOST, e);
+  *ticks = v;
+  return LB_OK;
+}
 
 struct lb_ctx {
   std::vector<lb_desc> d;
@@ -882,6 +897,8 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
     if (!std::isfinite(r0_host[k]) || (v0_host && !std::isfinite(v0_host[k])))
       return fail(LB_ERR_ARG, "non-finite bead state");
   }
+  uint64_t wait_ticks = RES_WAIT;
+  if (int rc2 = wait_limit(&wait_ticks)) return rc2;
   lb_ctx* c = new lb_ctx();
   c->d.assign(d, d + nrep);
   c->nrep = nrep;
@@ -939,8 +956,7 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
       c->resident = c->resident && c->pk.nrseg <= RES_OWN_WG && c->nrtab <= RES_OWN_XCD * XCDS;
       c->resident_own = true;
     }
-    // a shorter limit sends every wait to the redo (tests)
-    if (const char* e = std::getenv("LBMD_MD_WAIT_TICKS")) c->md_wait = std::strtoull(e, nullptr, 10);
+    c->md_wait = wait_ticks;
   }
   const double skin = SKIN_STEP;
   const size_t ns = (size_t)c->pk.slots_alloc;
