@@ -463,9 +463,11 @@ int lb_diagnostics(lb_ctx* ctx, int64_t* out);
  * whole cycle; used up to 512 segments of 32 beads): synchronises the stream
  * and writes three int64, counted per replica and cycle: out[0] = cycles begun
  * that way (relaxation included; 0: single launches or fused blocks), out[1] =
- * those whose first pass could not hold (a bead beyond half the list skin, too
- * many partners, a workgroup that waited too long) and went on in a second,
- * out[2] = those that one workgroup redid, which is much slower. */
+ * those that the first pass could not hold (a bead beyond half the list skin,
+ * many partners or wall sites, a workgroup that waited too long) and that went on
+ * in a second one (about as long as single launches), out[2] = those that one
+ * workgroup redid, which is much slower (no room on the GPU beside other work, a
+ * list overflow, more than 1024 partners of 32 beads in other segments). */
 int lb_md_passes(lb_ctx* ctx, int64_t* out);
 
 /* Message of the last failed call on this thread (never NULL). */

@@ -435,7 +435,6 @@ struct lb_ctx {
   bool any_fluct = false;    // some replica has a fluctuating fluid
   int mts = 0;               // outer steps of the multiple-time-step sub-cycle (0: uniform sub-steps)
   bool any_constrained = false;  // some replica has rigid bonds
-  bool any_win6 = false;     // some chain's wall-site window is 6 x 6 (r_c > 2)
   bool noise_ready = false;  // the noise slot of the current population parity holds this step's noise
   SweepCfg sweep;
   int ntiles = 0;
@@ -665,7 +664,7 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
     launch_md_cycle_fused(D, c->fb, c->pk.nseg, c->nslots, c->nrep, c->n_sub, c->fusedK, st);
   else if (resident)
     launch_md_cycle_resident(D, c->fb.ang, c->rseg, c->nrtab, c->pk.nrseg, c->nslots, c->n_sub, c->mts, none, c->md_wait,
-                             c->resident_own, c->any_constrained, c->any_win6, st);
+                             c->resident_own, c->any_constrained, st);
   else if (c->mts > 0) launch_md_cycle_mts(D, c->nslots, c->n_sub, c->mts, st);
   else launch_md_cycle(D, c->nslots, c->nrep, c->n_sub, none, st, false, c->any_constrained);
   if (resident) sweep_side();
@@ -982,7 +981,6 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
     if (R.mp.nb > 0 && R.mp.sig != 0.0) c->any_noise = true;
     if (R.lp.fluct) c->any_fluct = true;
     if (R.mp.constrained && R.mp.nb >= 2) c->any_constrained = true;
-    if (R.mp.nb > 0 && R.mp.whi - R.mp.wlo + 1 > 4) c->any_win6 = true;
     R.node_off = c->pk.node_off[r];
     R.slot_off = c->pk.slot_off[r];
     R.nslot = (int)round_up(d[r].nb, MD_BPB);
@@ -1249,7 +1247,7 @@ int md_relax(lb_ctx* c, int nsub_total, double gamma_relax) {
       launch_md_begin(c->D, c->nrep, c->s);
       launch_md_start(c->D, c->nslots, ov, c->s);
       launch_md_cycle_resident(c->D, c->fb.ang, c->rseg, c->nrtab, c->pk.nrseg, c->nslots, n, 0, ov, c->md_wait,
-                               c->resident_own, c->any_constrained, c->any_win6, c->s);
+                               c->resident_own, c->any_constrained, c->s);
     } else {
       launch_md_cycle(c->D, c->nslots, c->nrep, n, ov, c->s, true, c->any_constrained);
     }

@@ -118,11 +118,12 @@ struct Dev {
   uint32_t* cst;    // per replica, 3 rotating words: some bead is farther than CELL_MARGIN
                     // from its binned position at that sub-step (the table is not usable)
   uint32_t cmask;   // buckets - 1 (a power of two minus one)
-  unsigned long long* xring;   // [10][slots][3][2]: positions exchanged inside a resident cycle, each as its
-                    // bits and its bits XOR the sub-step's tag (slots 0, 1: every sub-step; 2, 3: the
-                    // kicks of the multiple-time-step cycle; 4, 5: the start of a block; 6 to 9:
-                    // the copies of 0 to 3 for readers on the same XCD)
-  unsigned long long* xflag;   // [3][segments][2]: a word per segment, likewise (0, 1: the start of a block; 2: its XCD)
+  unsigned long long* xring;   // [8][slots][3][2]: positions exchanged inside a resident cycle, each as its
+                    // bits and its bits XOR the stage's tag (slots 0, 1: every sub-step; 2, 3: the
+                    // kicks of the multiple-time-step cycle; 4 to 7: the copies of 0 to 3 for
+                    // readers on the same XCD)
+  unsigned long long* xflag;   // [4][segments][2]: a word per segment, likewise (0, 1: the wide pass's synchronised
+                    // stages; 2: its XCD; 3, at a chain's first two segments: the sum of its words)
   uint32_t* rsync;  // [R][3]: per pass of the resident cycle, segments done and the failure bit; segments
                     // that left the last pass without a result
   Ctrl* ctrl;
@@ -266,8 +267,7 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
                            hipStream_t s);
 
 // The sub-cycle in one launch (uniform, with mts > 0 the multiple-time-step
-// one, with rigid that of rigid bonds, with win6 with memory for the wall sites
-// of some chain with r_c > 2): entry w of the table seg (ntab entries,
+// one, with rigid that of rigid bonds): entry w of the table seg (ntab entries,
 // nseg of them in use) is the chain segment [a, b) of up to RES_OWN beads that
 // workgroup w owns for the whole cycle; it exchanges the positions its
 // neighbours need through d.xring (see k_md_resident).  Measured per coupled
@@ -280,11 +280,9 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
 // that contexts of up to 256 segments fit beside any other.  A wait that
 // lasts longer than `wait` ticks of the 100 MHz clock, or RES_PLACE while some
 // workgroup has not found room, hands the replica to one workgroup that
-// redoes the cycle from its start; a bead that leaves the range of the step's
-// neighbour lists, to a second pass with new lists where one needs them, every
-// RES_BLOCK sub-steps (8000 beads of a walk that was not relaxed, step by step: 3.1 ms, as with one
-// launch per sub-step; the one workgroup takes 94).  At n_sub = 1 and 2 the
-// single launches cost no more.
+// redoes the cycle from its start (8000 beads: 60 to 94 ms); what the first pass
+// cannot hold goes on in the wide pass of the same launch.  At n_sub = 1 and 2
+// the single launches cost no more.
 // own: every workgroup takes a CU for itself.  An exchange beside the sweep's
 // waves on the same CU takes 2.4 to 2.8 us, on a CU of its own 1.4 to 1.8 (alone
 // 1.0 to 1.3).  That is worth while the beads outlast the sweep, which then has
@@ -296,11 +294,10 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
 // other) that leave a quarter of every XCD's CUs to the sweep, and at most
 // RES_OWN_BYTES of populations per sub-step (about what the sweep moves in that
 // time).
-constexpr int XRING = 10;                      // slots of xring
-constexpr int XFLAG = 3;
+constexpr int XRING = 8;                       // slots of xring
+constexpr int XFLAG = 4;
 constexpr int XCDS = 8;
 constexpr int RES_OWN = 32;
-constexpr int RES_BLOCK = 10;
 constexpr int RES_MAX_WG = 512;
 constexpr int RES_MIN_SUB = 3;
 constexpr int RES_OWN_WG = 128;
@@ -310,7 +307,7 @@ constexpr int RES_XCD = 16;
 constexpr double RES_OWN_BYTES = 16e6;
 constexpr uint64_t RES_PLACE = 200000;   // 2 ms
 void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int ntab, int nseg, int nslots, int n_sub,
-                              int mts, const MdOverride& ov, uint64_t wait, bool own, bool rigid, bool win6, hipStream_t s);
+                              int mts, const MdOverride& ov, uint64_t wait, bool own, bool rigid, hipStream_t s);
 void launch_md_gate(const Dev& d, int nseg, hipStream_t s);
 // Noise of one sub-cycle into d.xi, for the step counter + step_offset.
 void launch_md_noise(const Dev& d, int nslots, int n_sub, int step_offset, hipStream_t s);

@@ -46,6 +46,14 @@ __device__ inline T load_uniform(const T* p) {
   return out;
 }
 
+// A pointer in a kernel's arguments, read from memory: a scalar load, and known to
+// be global (else every access through it is a flat one).
+template <typename T>
+__device__ inline T* load_global(T* const* p) {
+  typedef const __attribute__((address_space(4))) uint64_t Word;
+  return (T*)(__attribute__((address_space(1))) T*)*(Word*)(uintptr_t)p;
+}
+
 // Coefficients of the sub-cycle for one replica: its own, or the
 // relaxation's (no coupling, no field, no noise).
 __device__ inline MdParams md_override(MdParams P, const MdOverride& ov) {
@@ -1739,7 +1747,7 @@ __global__ __launch_bounds__(FU_WG) void k_md_fused(Dev d, FusedBufs fb, int nsl
 }
 
 // After the fused blocks, one workgroup per replica (and one workgroup of a
-// replica that the resident cycle could not take).  A replica whose block
+// replica whose resident cycle waited too long).  A replica whose block
 // failed at sub-step sp is redone from that block's start state to the end of
 // the cycle, sub-step by sub-step, with barriers: the angles of every centre,
 // then every bead's force, kick and drifts; the positions alternate between
@@ -1781,6 +1789,7 @@ struct RigShared {
   double w[RIG_MAX][3];
   double row[2][4][RIG_MAX];   // a, b, c, r of the tridiagonal rows
   double lam[RIG_MAX];
+  double ref[RIG_MAX][3];      // where the lists were built (wide pass)
   double red[2][RIG_WG / 64];
 };
 
@@ -2120,9 +2129,9 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
 // The exchange has no fence and no flag (an agent-scope release would write
 // the L2 back).  A position component travels as two 64-bit words, its bits and
 // its bits XOR a tag that no other sub-step of any pass of any cycle uses
-// (lbmd_tag.h), written and read by relaxed agent-scope atomics, which bypass the L2s that the XCDs do
-// not share: a reader takes the pair when the two words differ by the tag, so
-// it needs no order between them.  Two slots suffice: segments depend on each
+// (lbmd_tag.h), written and read by relaxed agent-scope atomics, which bypass the
+// L2s that the XCDs do not share: a reader takes the pair when the two words
+// differ by the tag, so it needs no order between them.  Two slots suffice: segments depend on each
 // other symmetrically, so a segment publishes x(s + 2) over x(s) only after
 // it has read x(s + 1) of a segment that has read its x(s).
 //
@@ -2158,17 +2167,33 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
 //
 // The lists hold every pair within r_c while no bead is farther than half
 // the skin from where they were built.  A workgroup whose bead leaves that
-// range, whose lists are not valid at the start, whose remote beads exceed
-// RES_REM, or whose wait exceeds its limit sets the replica's failure bit;
-// the others see it while they poll, and leave the pass.  The segments store
-// their results only when all of them have finished.  Else a second pass takes
-// the replica from the cycle's start in blocks of RES_BLOCK sub-steps, with new
-// lists where one needs them, so a bead may travel half the skin per block
-// instead of per cycle.  When that fails too, the workgroup that leaves last advances the
-// replica alone (md_redo).  Every wait ends: the polled value arrives, the bit
-// is set, or the clock runs out.  All of this is one launch: a second one that
-// finds nothing to do would wait for room beside the sweep (0.49 ms of a
-// 1.1 ms step).
+// range, whose lists are not valid at the start, whose remote beads, wall sites
+// or pairs exceed what the first pass keeps, or whose wait exceeds its limit sets
+// the replica's failure bit; the others see it while they poll, and leave the
+// pass.  The segments store their results only when all of them have finished.
+// Else the wide pass takes the replica from the cycle's start; when that fails
+// too, the workgroup that leaves it last advances the replica alone (md_redo).
+// Every wait ends: the polled value arrives, the bit is set, or the clock runs
+// out.  All of this is one launch: a second one that finds nothing to do would
+// wait for room beside the sweep (0.49 ms of a 1.1 ms step).
+//
+// The wide pass takes any density and any displacement.  Sixteen lanes per bead
+// evaluate its terms side by side, whatever their kind, and its lanes 0 to 2 add
+// them in the fixed order; a segment may have WIDE_REM remote partners, each
+// fetched once per stage.  Every few stages (synchronised ones: as many apart as
+// no bead can use up the lists' range in at twice its present speed) each segment
+// publishes a word that says whether its beads are within CELL_MARGIN of where
+// the cell table binned them, whether one is beyond the lists' range, and how long
+// the others hold, and takes every segment's: where some word asks for new lists,
+// all segments build them there, from positions that all have published, from the
+// cell table if every word allows it, else from all beads of the chain.  No
+// segment passes a synchronised stage before all have left the one before, so two
+// slots suffice for the words too.  ms per step in the wide pass / with single
+// launches: 2000 beads folded into a cube of spacing 1.1 0.73 / 0.84, 8000 1.05 /
+// 1.01 (80 registers per lane), 2000 along the wall with r_c = 2.5 1.03 / 1.28,
+// 8000 of a walk that was not relaxed 2.07 / 2.34, 2000 that drift by 3 per step
+// 0.94 / 1.29, 300 rigid ones by 9 2.6 / 3.3; one workgroup alone takes 14 for
+// the first and 60 for the second.
 //
 // The multiple-time-step cycle (MTS) is the same loop over n_sub + M + 1
 // stages: kicks of the slow forces (pairs, walls, field) at r, and between two
@@ -2176,30 +2201,28 @@ __global__ __launch_bounds__(RD_WG) void k_md_redo(Dev d, FusedBufs fb, double* 
 // no chain neighbours exchange positions for the kicks only, so those travel in
 // slots of their own (2, 3, by the kick's parity: the argument above holds
 // for the kicks alone, and for every stage between chain neighbours).  The
-// lists are checked at the kicks, and a block is a kick and the sub-steps up
-// to the next, so the second pass takes any displacement.  2000 beads, M = 5,
-// n_sub = 100: 0.47 ms per step; with a launch per kick and one for the
-// sub-steps between (k_md_inner) 0.63.
-//
-// At a block's start each segment publishes its positions (tagged like the
-// exchange) and a word that says whether its beads are within CELL_MARGIN of
-// where the cell table binned them and whether one may leave the lists' range
-// within the block, and reads every segment's word -- so no segment enters a
-// block before all have left the one before, and two slots suffice here as
-// well.  Where some word asks for new lists, their candidates come from the
-// cell table if every word allows it, else from all beads of the chain.
+// lists are checked at the kicks, which are the wide pass's synchronised stages.
+// 2000 beads, M = 5, n_sub = 100: 0.35 ms per step; with a launch per kick and
+// one for the sub-steps between (k_md_inner) 0.63.
 // ---------------------------------------------------------------------------
 constexpr int RES_WG = 512;
 constexpr int RES_HALO = 4;                    // local indices RES_OWN + 0..3: chain beads a-2, a-1, b, b+1
-constexpr int RES_REM = 144;                   // other remote beads
+constexpr int RES_REM = 144;                   // other remote beads (more: the wide pass)
 constexpr int RES_IDX = RES_OWN + RES_HALO + RES_REM;
 constexpr int RES_PL = 4;                      // lanes per bead of the pair waves
 constexpr int RES_PH = 4;                      // pair forces kept per lane
-// Wall-site forces of a segment: no disk of radius 2 has more than 14 points of the
-// unit square lattice inside, none of radius 3 more than 32 (every position of
-// the centre, in ever smaller squares), so no row is tested against its end.
-constexpr int RES_WH = 14 * RES_OWN, RES_WH6 = 32 * RES_OWN;
+// Wall-site forces of a segment in the first pass: no disk of radius 2 has more than
+// 14 points of the unit square lattice inside (every position of the centre, in ever
+// smaller squares).  r_c up to 3 reaches 32, but with so many the wide pass, which
+// spreads a bead's terms over 16 lanes, is the faster one: 400 beads along the
+// wall at r_c = 2.5 and 3 0.91 and 0.99 against 1.35 and 1.57 ms per step.
+constexpr int RES_WH = 14 * RES_OWN;
+constexpr int RES_WH_START = 12 * RES_OWN;     // at the first sub-step, for r_c > 2: they may become more
 constexpr int RES_HASH = 512;
+// Up to RES_ALL segments read each other's words, of more the first one reads them
+// and publishes their sum: 250 segments' loads of one another's meet at the few
+// channels that hold them.
+constexpr uint32_t RES_ALL = 64;
 constexpr uint32_t RES_FAIL = 0x80000000u;
 constexpr int RES_TILE = 256;                  // beads scanned together by a full list build
 static_assert(RES_IDX <= 255, "local indices fit in a byte");
@@ -2227,32 +2250,60 @@ struct ResShared {
   int dead[2];                                 // by parity of the sub-step
   int lost;                                    // a set-up failed
   int done;
-  int ncand[RES_OWN];
   union {
     struct {
       double pairF[RES_PL][RES_PH][RES_OWN][3];   // pair forces of each lane's part of the list, in order
-      double wallF[RES_WH + 3][3];             // wall-site forces, bead by bead in site order; last: the
-                                               // rows of r_c > 2 go on beyond the struct
+      double wallF[RES_WH + 3][3];             // wall-site forces, bead by bead in site order
     };
     struct {                                   // set-up
       int key[RES_HASH], val[RES_HASH];        // local index of a remote chain bead
-      int list[RES_OWN][MAXNBR];               // new lists (partner slots)
-      uint32_t bk[RES_OWN][27];                // the 27 buckets around a bead
-      double tile[RES_TILE][3];                // positions of RES_TILE chain beads
-      double vel[RES_OWN][3];
     } h;
   };
 };
-// The memory of a workgroup: with rigid bonds RigShared, then ResShared, then for
-// r_c > 2 more wall rows.  Dynamic, so that the kernel and its rescue share it.
+// The wide pass's memory.  A list holds chain indices,
+// then places: own beads' index, WIDE_FAR + the place in rem (rigid bonds: chain
+// indices throughout).
+constexpr int WIDE_REM = 1024;                 // remote partners of a segment
+constexpr int WIDE_FAR = 64;
+constexpr uint16_t WIDE_NONE = 0xffffu;
+struct WideShared {
+  double pos[2][RES_OWN + RES_HALO][3];        // by parity of the stage: own beads, chain beads a-2, a-1, b, b+1
+  double far[WIDE_REM][3];                     // the stage's positions of the remote partners
+  double ref[RES_OWN][3];                      // where the lists were built
+  double v[RES_OWN][3], J[RES_OWN][3], u[RES_OWN][3];
+  uint16_t rem[WIDE_REM];                      // their chain indices, ascending
+  uint16_t list[RES_OWN][MAXNBR];              // WIDE_NONE beyond a list's end
+  union {
+    double row[RES_OWN][RES_WG / RES_OWN][3];  // force terms of a bead, in the order of the sum
+    struct {                                   // new lists
+      uint32_t bk[RES_OWN][27];                // the 27 buckets around a bead
+      double tile[RES_TILE][3];                // positions of RES_TILE chain beads
+      int ncand[RES_OWN];
+    } h;
+    struct {                                   // the remote partners among the chain's beads
+      uint32_t set[RES_WG];                    // a bit per bead
+      int pre[RES_WG];                         // set bits before this word
+      int wsum[RES_WG / 64];
+    } m;
+  };
+  int nrem;
+  uint32_t bits[2], all[2];                    // by parity of the stage: this segment's word, every segment's
+  int lost[2];                                 // failed before / after the barrier that opens a stage of this parity
+  int done, off, near;
+  MdParams P;
+};
+static_assert(32 * RES_WG >= RES_MAX_WG * RES_OWN, "a bit for every bead of a chain");
+
+// The memory of a workgroup: with rigid bonds RigShared, then ResShared or
+// WideShared.  Dynamic, so that the kernel and what follows a failed pass share it.
 extern __shared__ __align__(16) unsigned char res_lds[];
 constexpr size_t res_base(bool rigid) { return rigid ? sizeof(RigShared) : 0; }
-constexpr size_t res_bytes(bool rigid, bool win6) {
-  return res_base(rigid) + (win6 ? offsetof(ResShared, wallF) + 3 * sizeof(double) * (RES_WH6 + 3) : sizeof(ResShared));
+constexpr size_t res_bytes(bool rigid) {
+  return res_base(rigid) + (sizeof(ResShared) > sizeof(WideShared) ? sizeof(ResShared) : sizeof(WideShared));
 }
 static_assert(sizeof(RigShared) % 16 == 0 && RES_WG == RIG_WG, "ResShared follows");
-static_assert(3 * res_bytes(false, false) <= (size_t)LDS_PER_CU && 2 * res_bytes(false, true) <= (size_t)LDS_PER_CU &&
-              res_bytes(true, true) <= (size_t)LDS_PER_CU, "RES_MAX_WG workgroups fit on the GPU; one with rigid bonds on a CU");
+static_assert(3 * res_bytes(false) <= (size_t)LDS_PER_CU && res_bytes(true) <= (size_t)LDS_PER_CU,
+              "as many fit on a CU as by registers; one with rigid bonds");
 
 // Orders one wave's LDS accesses (which the LDS executes in order) for the compiler.
 __device__ inline void wave_lds() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
@@ -2328,8 +2379,32 @@ __device__ inline bool res_poll(const unsigned long long* o, uint64_t tag, const
   }
 }
 
-// One pass of the cycle (see above); false: it failed.
-template <bool BLOCKS, bool MTS, bool RIGID>
+// Failure ends a pass for the whole replica.  It is decided on one word: the
+// number of segments that have finished, and a failure bit that can only be set
+// while that number is below ng.  True: this call set the bit.
+__device__ inline bool res_give_up(uint32_t* word, uint32_t ng) {
+  uint32_t w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  while (w < ng) {
+    const uint32_t was = atomicCAS(word, w, w | RES_FAIL);
+    if (was == w) return true;
+    w = was;
+  }
+  return false;
+}
+// One thread of each segment, at a pass's end: every segment of the replica, or
+// none, stores its result.
+__device__ inline bool res_close(uint32_t* word, uint32_t ng, bool dead, uint64_t wait) {
+  if (dead) return false;
+  if (atomicAdd(word, 1u) + 1u != ng) {
+    const uint64_t t0 = wall_clock64();
+    while (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < ng)
+      if (wall_clock64() - t0 >= wait) res_give_up(word, ng);   // the word reaches ng or gets the failure bit
+  }
+  return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ng;
+}
+
+// The first pass of the cycle (see above); false: it failed.
+template <bool MTS, bool RIGID>
 __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const Rep& R, const MdParams& P, ResShared& sh,
                                         RigShared& rig, int nslots, int nseg, int n_sub, int mts, uint64_t wait) {
   const int rep = seg.rep;
@@ -2340,21 +2415,10 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
   const int p0 = seg.a, n = seg.b - seg.a;
   const int t = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(t) >> 6, lane = t & 63;
-  uint32_t* word = &d.rsync[3 * rep + BLOCKS];
+  uint32_t* word = &d.rsync[3 * rep];
   const uint32_t ng = (uint32_t)((nb + RES_OWN - 1) / RES_OWN);   // the replica's segments
-  // Failure ends the pass for the whole replica.  It is decided on one word:
-  // the number of segments that have finished, and a failure bit that can
-  // only be set while that number is below ng.
   auto give_up = [&]() {
-    uint32_t w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    while (w < ng) {
-      const uint32_t was = atomicCAS(word, w, w | RES_FAIL);
-      if (was == w) {
-        if (!BLOCKS) atomicAdd((unsigned long long*)&d.ctrl->res_second, 1ull);
-        break;
-      }
-      w = was;
-    }
+    if (res_give_up(word, ng)) atomicAdd((unsigned long long*)&d.ctrl->res_second, 1ull);
   };
   auto fail = [&](int s) {
     give_up();
@@ -2364,9 +2428,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     give_up();
     sh.lost = 1;
   };
-  // The XCDs are published by the first pass, for both.
-  const uint64_t cycle = load_uniform(&d.ctrl->cycles);
-  const uint64_t tag0 = res_tag(cycle, BLOCKS, 0), tagx = res_tag(cycle, 0, 0);
+  const uint64_t tag0 = res_tag(load_uniform(&d.ctrl->cycles), 0, 0);
 
   // ---- the lanes of the sum: component c of bead i
   const int i = 16 * wave + lane / 3, c = lane % 3;
@@ -2391,156 +2453,24 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
   const int g0 = seg.id - p0 / RES_OWN;          // the replica's first segment
   if (t == 0) {
     sh.lost = 0;
-    if (!BLOCKS) {
-      __hip_atomic_fetch_add(&d.ctrl->placed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (seg.id == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)n_sub);
-      if (p0 == 0) atomicAdd((unsigned long long*)&d.ctrl->res_cycles, 1ull);
-      const unsigned long long w = res_xcd();
-      res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id, w);
-      res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id + 1, w ^ tagx);
-    }
-    if (!BLOCKS && d.rb[4 * rep] != 0u) lose();  // the lists are not valid at the start
+    __hip_atomic_fetch_add(&d.ctrl->placed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (seg.id == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)n_sub);
+    if (p0 == 0) atomicAdd((unsigned long long*)&d.ctrl->res_cycles, 1ull);
+    const unsigned long long w = res_xcd();
+    res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id, w);
+    res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id + 1, w ^ tag0);
+    if (d.rb[4 * rep] != 0u) lose();             // the lists are not valid at the start
     if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & RES_FAIL) sh.lost = 1;
   }
   bool dead = false;
-  const int len = !BLOCKS ? end : (MTS ? Mb + 1 : RES_BLOCK);
-  for (int s0 = 0, blk = 0;; s0 += len, ++blk) {
-  const int s1 = BLOCKS ? min(s0 + len, end) : end;
-  const int sp = s0 & 1;                         // parity of the block's first sub-step
+  do {
   // ---- set-up: the lists as local indices
-  __syncthreads();                               // the positions at s0 are there, the forces' memory is free
+  __syncthreads();                               // the positions are there
   constexpr int LL = RES_WG / RES_OWN, LE = MAXNBR / LL;   // 16 lanes per bead
   const int lb = t / LL, ll = t % LL;
-  bool fresh = BLOCKS && s0 == 0 && (RIGID || d.rb[4 * rep] != 0u);   // build new lists
-  const unsigned long long* xb = nullptr;
-  const uint64_t tagb = tag0 + (uint64_t)s0 * RES_TAG + RES_MARK;
-  if (BLOCKS && (s0 > 0 || fresh)) {
-    unsigned long long* xw = d.xring + (size_t)(4 + (blk & 1)) * 6 * nslots;
-    xb = xw;
-    unsigned long long* words = d.xflag + (size_t)2 * (blk & 1) * nseg;
-    if (mine) {
-      const unsigned long long bits = (unsigned long long)__double_as_longlong(x);
-      res_store(xw + ((size_t)slot * 3 + c) * 2, bits);
-      res_store(xw + ((size_t)slot * 3 + c) * 2 + 1, bits ^ tagb);
-    }
-    // bit 0: every bead near where the table binned it; bit 1: some bead may
-    // leave the lists' range within the block (at twice its present speed)
-    bool near = true, need = s0 == 0;
-    if (mine) sh.h.vel[i][c] = v;
-    __syncthreads();
-    if (t < n) {
-      double b2 = 0.0, f2 = 0.0, v2 = 0.0;
-      for (int a = 0; a < 3; ++a) {
-        const double y = sh.pos[sp][t][a], w = sh.h.vel[t][a];
-        const double db = y - d.rbin[3 * (so + p0 + t) + a], df = y - sh.ref[t][a];
-        b2 += db * db;
-        f2 += df * df;
-        v2 += w * w;
-      }
-      near = b2 <= CELL_MARGIN * CELL_MARGIN;
-      // (MTS: the lists serve the block's first stage only)
-      need = need || (MTS ? !(f2 <= P.halfskin2)
-                          : !(sqrt(f2) + 4.0 * P.hh * RES_BLOCK * sqrt(v2) <= 0.95 * sqrt(P.halfskin2)));
-      sh.ncand[t] = 0;
-    }
-    const int all_near = __syncthreads_and(near ? 1 : 0), any_need = __syncthreads_or(need ? 1 : 0);
-    if (t == 0) {
-      const unsigned long long w = (all_near ? 1ull : 0ull) | (any_need ? 2ull : 0ull);
-      res_store(words + 2 * seg.id, w);
-      res_store(words + 2 * seg.id + 1, w ^ tagb);
-    }
-    // every segment's word
-    bool table = true;
-    need = false;
-    for (int k = t; k < (int)ng; k += RES_WG) {
-      unsigned long long w = 0;
-      if (!res_poll(words + 2 * (g0 + k), tagb, word, d.ctrl, wait, nseg, w)) { lose(); break; }
-      table = table && (w & 1ull);
-      need = need || (w & 2ull);
-    }
-    table = __syncthreads_and(table ? 1 : 0) != 0;
-    fresh = __syncthreads_or(need ? 1 : 0) != 0;
-    if (__syncthreads_or(sh.lost)) { dead = true; break; }   // uniform, and read by all before the next write
-    if (fresh) {
-    auto partner = [&](int q, const double* y) {
-      if (q == so + p0 + lb) return;
-      const double* rp = sh.pos[sp][lb];
-      const double d0 = min_image(rp[0] - y[0], g.nx);
-      const double d1 = min_image(rp[1] - y[1], g.ny);
-      const double d2 = min_image(rp[2] - y[2], g.nz);
-      if (!(d0 * d0 + d1 * d1 + d2 * d2 < P.rlist2)) return;
-      const int o = atomicAdd(&sh.ncand[lb], 1);
-      if (o < MAXNBR) sh.h.list[lb][o] = q;
-    };
-    bool ok = true;
-    if (table) {
-      if (lb < n) {
-        int cell[3];
-        bead_cell(R, sh.pos[sp][lb], cell);
-        for (int k = ll; k < 27; k += LL) {
-          const int dx = k % 3 - 1, dy = (k / 3) % 3 - 1, dz = k / 9 - 1;
-          sh.h.bk[lb][k] = cell_bucket(rep, (cell[0] + dx + R.ncell[0]) % R.ncell[0],
-                                       (cell[1] + dy + R.ncell[1]) % R.ncell[1],
-                                       (cell[2] + dz + R.ncell[2]) % R.ncell[2], d.cmask);
-        }
-      }
-      __syncthreads();
-      if (lb < n)
-        for (int k = ll; k < 27 && ok; k += LL) {
-          const uint32_t b = sh.h.bk[lb][k];
-          bool dup = false;
-          for (int k2 = 0; k2 < k; ++k2) dup = dup || sh.h.bk[lb][k2] == b;
-          const int m = dup ? 0 : min(d.ccount[b], CELL_CAP);
-          for (int q = 0; q < m && ok; ++q) {
-            const int sl = d.cbuf[(size_t)b * CELL_CAP + q];
-            if (d.slot_rep[sl] != rep) continue;
-            double y[3];
-            for (int a = 0; a < 3 && ok; ++a) {
-              unsigned long long w = 0;
-              ok = res_poll(xb + ((size_t)sl * 3 + a) * 2, tagb, word, d.ctrl, wait, nseg, w);
-              y[a] = __longlong_as_double((long long)w);
-            }
-            if (ok) partner(sl, y);
-          }
-        }
-      if (!ok) lose();
-    } else {
-      for (int base = 0; base < nb; base += RES_TILE) {
-        const int m = min(RES_TILE, nb - base);
-        for (int k = t; k < 3 * m && ok; k += RES_WG) {
-          unsigned long long w = 0;
-          ok = res_poll(xb + ((size_t)(so + base + k / 3) * 3 + k % 3) * 2, tagb, word, d.ctrl, wait, nseg, w);
-          sh.h.tile[k / 3][k % 3] = __longlong_as_double((long long)w);
-        }
-        if (!ok) lose();
-        __syncthreads();
-        if (lb < n)
-          for (int k = ll; k < m; k += LL) partner(so + base + k, sh.h.tile[k]);
-        __syncthreads();
-      }
-    }
-    __syncthreads();
-    if (lb < n && ll == 0) {                     // ascending order
-      const int cnt = min(sh.ncand[lb], MAXNBR);
-      int* L = sh.h.list[lb];
-      for (int k = 1; k < cnt; ++k) {
-        const int q = L[k];
-        int m = k;
-        while (m > 0 && L[m - 1] > q) { L[m] = L[m - 1]; --m; }
-        L[m] = q;
-      }
-    }
-    if (t == 0 && p0 == 0) {
-      atomicAdd((unsigned long long*)&d.ctrl->rebuilds, 1ull);
-      if (table) atomicAdd((unsigned long long*)&d.ctrl->cell_rebuilds, 1ull);
-    }
-    __syncthreads();
-    }
-  }
-  if (!BLOCKS || s0 == 0 || fresh) {
-  const int cnt = lb >= n ? 0 : (BLOCKS && fresh ? min(sh.ncand[lb], MAXNBR) : d.ncnt[so + p0 + lb]);
+  const int cnt = lb < n ? d.ncnt[so + p0 + lb] : 0;
   if (t < n)
-    for (int a = 0; a < 3; ++a) sh.ref[t][a] = BLOCKS && fresh ? sh.pos[sp][t][a] : d.ref[3 * (so + p0 + t) + a];
+    for (int a = 0; a < 3; ++a) sh.ref[t][a] = d.ref[3 * (so + p0 + t) + a];
   if (t == 0) { sh.nrem = 0; sh.links = 0; }
   for (int k = t; k < RES_IDX - RES_OWN; k += RES_WG) {
     // chain beads a - 2, a - 1, b, b + 1 first
@@ -2548,20 +2478,33 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     sh.rslot[k] = k < RES_HALO && q >= 0 && q < nb ? so + q : -1;
   }
   for (int k = t; k < RES_HASH; k += RES_WG) { sh.h.key[k] = -1; sh.h.val[k] = -1; }
+  if (wave == 7) {
+    // the segment as a whole will leave the lists' range within the cycle: at
+    // once, not when it gets there (200 rigid beads at 0.9 per step, 2.9 against 1.9 ms)
+    double m2 = 0.0;
+    for (int a = 0; a < 3; ++a) {
+      double y = lane < n ? d.v[3 * (so + p0 + lane) + a] : 0.0;
+      for (int o = 16; o > 0; o >>= 1) y += __shfl_xor(y, o, 64);
+      m2 += y * y;
+    }
+    const double reach = 2.0 * P.hh * n_sub;
+    if (lane == 0 && m2 * reach * reach > P.halfskin2 * (double)(n * n)) lose();
+  }
   __syncthreads();
   // a remote bead's first finder gives it an index
-  if (cnt >= MAXNBR) lose();                     // a full list may have lost partners: segments need not depend on each other
+  // a full list may have lost partners: segments need not depend on each other
+  if (cnt >= MAXNBR && (__hip_atomic_load(&d.ctrl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & E_NBRLIST)) lose();
   int e[LE];
 #pragma unroll
   for (int m = 0; m < LE; ++m) {
     const int k = LL * m + ll;
-    e[m] = k < cnt ? (fresh ? sh.h.list[lb][k] : d.nbr[(size_t)(so + p0 + lb) * MAXNBR + k]) : -1;
+    e[m] = k < cnt ? d.nbr[(size_t)(so + p0 + lb) * MAXNBR + k] : -1;
   }
 #pragma unroll 1
   for (int m = 0; m < LE; ++m) {
     const int em = m == 0 ? e[0] : (m == 1 ? e[1] : e[2]);
     const int q = em - so;
-    if (em < 0 || (q >= p0 - 2 && q < seg.b + 2)) continue;
+    if (em < 0 || (q >= p0 - 2 && q < seg.b + 2) || sh.lost) continue;
     uint32_t h = ((uint32_t)q * 2654435761u) >> 23;          // RES_HASH = 2^9
     for (int tries = 0; tries < RES_HASH; ++tries, h = (h + 1) & (RES_HASH - 1)) {
       const int was = atomicCAS(&sh.h.key[h], -1, q);
@@ -2580,6 +2523,9 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     }
   }
   __syncthreads();
+  const int full = sh.lost;
+  __syncthreads();
+  if (full) { dead = true; break; }              // uniform
   if (lb < n && ll == 0) sh.lcnt[lb] = cnt;
 #pragma unroll 1
   for (int m = 0; m < LE; ++m) {
@@ -2601,7 +2547,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
   for (int k = t; k < RES_HALO + min(sh.nrem, RES_REM); k += RES_WG) {
     const int sl = sh.rslot[k];
     unsigned long long w = 0;
-    if (sl >= 0 && !res_poll(d.xflag + 4 * (size_t)nseg + 2 * (g0 + (sl - so) / RES_OWN), tagx, word, d.ctrl, wait, nseg, w))
+    if (sl >= 0 && !res_poll(d.xflag + 4 * (size_t)nseg + 2 * (g0 + (sl - so) / RES_OWN), tag0, word, d.ctrl, wait, nseg, w))
       lose();
     const bool near = w == (unsigned long long)res_xcd();
     sh.rnear[k] = near;
@@ -2609,36 +2555,25 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
   }
   for (int k = t; k < 3 * (RES_HALO + min(sh.nrem, RES_REM)); k += RES_WG) {
     const int sl = sh.rslot[k / 3];
-    double y = 0.0;
-    if (sl >= 0) {
-      if (fresh) {
-        unsigned long long w = 0;
-        if (!res_poll(xb + ((size_t)sl * 3 + k % 3) * 2, tagb, word, d.ctrl, wait, nseg, w)) lose();
-        y = __longlong_as_double((long long)w);
-      } else {
-        y = RIGID ? rig.x[sl - so][k % 3] : d.rmid0[3 * sl + k % 3];
-      }
-    }
-    sh.pos[sp][RES_OWN + k / 3][k % 3] = y;
+    sh.pos[0][RES_OWN + k / 3][k % 3] = sl < 0 ? 0.0 : (RIGID ? rig.x[sl - so][k % 3] : d.rmid0[3 * sl + k % 3]);
   }
   if (RIGID) {
     // every segment's velocities are read; the lists at the opening's positions
     for (int k = t; k < (int)ng; k += RES_WG) {
       unsigned long long w = 0;
-      if (!res_poll(d.xflag + 4 * (size_t)nseg + 2 * (g0 + k), tagx, word, d.ctrl, wait, nseg, w)) lose();
+      if (!res_poll(d.xflag + 4 * (size_t)nseg + 2 * (g0 + k), tag0, word, d.ctrl, wait, nseg, w)) lose();
       const bool near = w == (unsigned long long)res_xcd();
       sh.snear[k] = near;
       if (g0 + k != seg.id) atomicOr(&sh.links, near ? 2 : 1);
     }
-    if (!BLOCKS && t < n) {
+    if (t < n) {
       double d2 = 0.0;
-      for (int a = 0; a < 3; ++a) { const double dd = sh.pos[sp][t][a] - sh.ref[t][a]; d2 += dd * dd; }
+      for (int a = 0; a < 3; ++a) { const double dd = sh.pos[0][t][a] - sh.ref[t][a]; d2 += dd * dd; }
       if (d2 > P.halfskin2) lose();
     }
   }
-  }
   __syncthreads();
-  if (sh.lost) { dead = true; break; }           // uniform: the next writes follow many barriers
+  if (sh.lost) { dead = true; break; }           // uniform
   const int nrem = RES_HALO + min(sh.nrem, RES_REM);
 
   constexpr int HL = RES_OWN, HR = RES_OWN + 2;  // local indices of a - 2 and b
@@ -2651,7 +2586,6 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
   }
   if (t <= n && (P.constrained || p0 + t == 0 || p0 + t == nb))
     for (int a = 0; a < 3; ++a) sh.bnd[t][a] = 0.0;
-  double (*const wallF)[3] = reinterpret_cast<double (*)[3]>(res_lds + res_base(RIGID) + offsetof(ResShared, wallF));
   const int links = sh.links;                    // 0: no other segment needs this one's positions
   const size_t half = (size_t)6 * nslots;        // words of one slot of the ring
   const bool noisy = P.sig != 0.0;
@@ -2665,7 +2599,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
       const int q = k / 3;
       if (q >= p0 && q < seg.b) continue;
       unsigned long long w = 0;
-      if (!res_poll(from + ((size_t)so * 3 + k) * 2 + (sh.snear[q / RES_OWN] ? 6 * half : 0), tag, word, d.ctrl, wait, nseg, w)) {
+      if (!res_poll(from + ((size_t)so * 3 + k) * 2 + (sh.snear[q / RES_OWN] ? 4 * half : 0), tag, word, d.ctrl, wait, nseg, w)) {
         fail(s);
         break;
       }
@@ -2688,8 +2622,8 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     lds_barrier();
   };
   __builtin_amdgcn_s_setprio(2);
-  for (int sa = s0;; ++sa) {                     // RIGID: the loops below take one sub-step at a time
-  const int sb = RIGID ? sa + 1 : s1;
+  for (int sa = 0;; ++sa) {                      // RIGID: the loops below take one sub-step at a time
+  const int sb = RIGID ? sa + 1 : end;
   // Each kind of wave has a loop of its own (its registers then hold only
   // what it needs), with the same two barriers per sub-step.  A failure at
   // sub-step s is seen before the first barrier of s + 1, by all waves: s writes
@@ -2704,7 +2638,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     double* tape = mine && d.mdtape ? d.mdtape + (size_t)p * 6 + c : nullptr;
     unsigned long long* ring = d.xring + ((size_t)slot * 3 + c) * 2;
     uint64_t tag = tag0 + (uint64_t)sa * RES_TAG;
-    int q = 0, o = MTS ? s0 / (Mb + 1) : 0;
+    int q = 0, o = 0;
     for (int s = sa; s < sb; ++s) {
       const int cb = s & 1, was = sh.dead[cb ^ 1];
       const bool last = s == end - 1;
@@ -2767,7 +2701,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
         }
         if (__any((wl & 0xff) != 0))
         for (int m = wl >> 8, m1 = m + (wl & 0xff); m < m1; m += 4) {   // four loads in flight
-          const double f0 = wallF[m][c], f1 = wallF[m + 1][c], f2 = wallF[m + 2][c], f3 = wallF[m + 3][c];
+          const double f0 = sh.wallF[m][c], f1 = sh.wallF[m + 1][c], f2 = sh.wallF[m + 2][c], f3 = sh.wallF[m + 3][c];
           F += f0;
           if (m + 1 < m1) F += f1;
           if (m + 2 < m1) F += f2;
@@ -2800,8 +2734,8 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
           unsigned long long* w = ring + (MTS && q == 0 ? (2 + (o & 1)) * half : (cb ? 0 : half));
           const unsigned long long bits = (unsigned long long)__double_as_longlong(RIGID ? v : x);
           if (links & 2) {
-            res_store_near(w + 6 * half, bits);
-            res_store_near(w + 6 * half + 1, bits ^ tag);
+            res_store_near(w + 4 * half, bits);
+            res_store_near(w + 4 * half + 1, bits ^ tag);
           }
           if (links & 1) {
             res_store(w, bits);
@@ -2849,6 +2783,8 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
           o[0] = 0.0; o[1] = 0.0; o[2] = 0.0;
         }
         sh.pcnt[pb][pl] = (uint8_t)min(hits, RES_PH + 1);
+        if (s == 0 && hits > RES_PH) fail(s);    // the sum would evaluate the list again (2.3 against 0.97 ms per
+                                                 // step, 400 beads along the wall, r_c = 2.5): the wide pass
       }
       if (__builtin_amdgcn_readfirstlane(was)) { dead = true; break; }
       lds_barrier();
@@ -2890,7 +2826,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
         bond_add(P, sh.pos[cb][lane < n ? lane : HR], sh.pos[cb][lane ? lane - 1 : HL + 1], Fb);
         sh.bnd[lane][0] = Fb[0]; sh.bnd[lane][1] = Fb[1]; sh.bnd[lane][2] = Fb[2];
       }
-      if (lane < n && (MTS ? kick && s > s0 : !RIGID && (s > s0 || (BLOCKS && s > 0)))) {
+      if (lane < n && s > 0 && (MTS ? kick : !RIGID)) {
         double d2 = 0.0;
 #pragma unroll
         for (int a = 0; a < 3; ++a) { const double dd = sh.pos[cb][lane][a] - ref[a]; d2 += dd * dd; }
@@ -2977,7 +2913,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
         }
         const uint64_t hm = __ballot(hit);
         const int o = total + __builtin_popcountll(hm & below);
-        if (hit) { wallF[o][0] = d0; wallF[o][1] = d1; wallF[o][2] = d2; }
+        if (hit && o < RES_WH) { sh.wallF[o][0] = d0; sh.wallF[o][1] = d1; sh.wallF[o][2] = d2; }
         if (on && num == 0) {
           const uint64_t own = per == 64 ? hm : (hm >> lane) & 0xffffull;
           sh.wall[sh.wbead[r]] = (o << 8) | __builtin_popcountll(own);
@@ -2985,8 +2921,13 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
         total += __builtin_popcountll(hm);
       }
       wave_lds();
+      if (per == 64 && total > (s == 0 ? RES_WH_START : RES_WH)) {   // too many: the wide pass takes them
+        fail(s);
+        if (lane < n) sh.wall[lane] = 0;         // none is read
+        total = 0;
+      }
       for (int o = lane; o < total; o += 64) {
-        double* w = wallF[o];
+        double* w = sh.wallF[o];
         double Fs[3] = {0.0, 0.0, 0.0};
         lj_add(P, w[0], w[1], w[2], Fs);
         w[0] = Fs[0]; w[1] = Fs[1]; w[2] = Fs[2];
@@ -3000,7 +2941,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     // of its 3 n values per lane); the remote positions
     const int nx = noisy ? 3 * n : 0;
     const size_t row = (size_t)3 * nslots;
-    int left = n_sub - (MTS ? s0 - s0 / (Mb + 1) : sa);   // sub-steps from here on
+    int left = n_sub - sa;                       // sub-steps from here on
     const double* xn = d.xi + (size_t)3 * (so + p0) + (size_t)(n_sub - left) * row;
     double xa = 0.0, xc = 0.0;
     if (!MTS || left > 0) {
@@ -3010,7 +2951,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     const int rs0 = lane < 3 * nrem ? sh.rslot[lane / 3] : -1;
     const bool rn0 = lane < 3 * nrem && sh.rnear[lane / 3];
     uint64_t tag = tag0 + (uint64_t)sa * RES_TAG;
-    int q = 0, o = MTS ? s0 / (Mb + 1) : 0;
+    int q = 0, o = 0;
     for (int s = sa; s < sb; ++s) {
       const int cb = s & 1, was = sh.dead[cb ^ 1];
       const bool kick = MTS && q == 0;
@@ -3035,7 +2976,7 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
           const int sl = m == lane ? rs0 : sh.rslot[m / 3];
           if (sl < 0) continue;
           unsigned long long w = 0;
-          const size_t off = ((size_t)sl * 3 + m % 3) * 2 + ((m == lane ? rn0 : sh.rnear[m / 3] != 0) ? 6 * half : 0);
+          const size_t off = ((size_t)sl * 3 + m % 3) * 2 + ((m == lane ? rn0 : sh.rnear[m / 3] != 0) ? 4 * half : 0);
           if (!res_poll(from + off, tag, word, d.ctrl, wait, nseg, w)) {
             fail(s);
             break;
@@ -3049,27 +2990,518 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
   if (!RIGID || dead) break;
   rigid(sa);
   if (mine) { x = rig.x[p][c]; v = rig.v[p][c]; }
-  if (sa == s1 - 1) break;
+  if (sa == end - 1) break;
   }
-  if (__builtin_amdgcn_readfirstlane(sh.dead[(s1 - 1) & 1])) dead = true;   // the last sub-step's
-  if (dead || !BLOCKS || s1 == end) break;
-  }
+  if (__builtin_amdgcn_readfirstlane(sh.dead[(end - 1) & 1])) dead = true;   // the last sub-step's
+  } while (false);
   __builtin_amdgcn_s_setprio(0);
-  // every segment of the replica, or none, stores its result
-  if (t == 0) {
-    if (!dead && atomicAdd(word, 1u) + 1u != ng) {
-      const uint64_t t0 = wall_clock64();
-      while (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < ng)
-        if (wall_clock64() - t0 >= wait) give_up();          // the word reaches ng or gets the failure bit
-    }
-    sh.done = !dead && __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ng;
-  }
+  if (t == 0) sh.done = res_close(word, ng, dead, wait);
   __syncthreads();
   if (!sh.done) return false;
   if (mine) {
     d.r[3 * slot + c] = x;
     d.v[3 * slot + c] = v;
     d.J[3 * slot + c] = J;
+    if (!fin) atomicOr(&d.ctrl->err, E_BEADS);
+  }
+  return true;
+}
+
+// As res_poll for a published vector, its words requested together.
+__device__ inline bool res_poll_vec(const unsigned long long* o, uint64_t tag, const uint32_t* word, const Ctrl* ctrl,
+                                    uint64_t wait, int nseg, double y[3]) {
+  uint64_t t0 = 0;
+  for (int spin = 0;; ++spin) {
+    unsigned long long w[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) w[k] = res_load(o + k);
+    for (int a = 0; a < 3; ++a) y[a] = __longlong_as_double((long long)w[2 * a]);
+    if ((w[0] ^ w[1]) == tag && (w[2] ^ w[3]) == tag && (w[4] ^ w[5]) == tag) return true;
+    if (spin == 0) t0 = wall_clock64();
+    if ((spin & 15) == 15 || wait == 0) {
+      const uint64_t dt = wall_clock64() - t0;
+      if ((__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & RES_FAIL) || dt >= wait ||
+          (dt >= RES_PLACE &&
+           __hip_atomic_load(&ctrl->placed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)nseg))
+        return false;
+    }
+  }
+}
+
+// The bonded terms of chain bead q, in the first five rows of its lanes: bonds to
+// q - 1 and q + 1, the angles centred at q - 1 (third bead's part), q (centre) and
+// q + 1 (first); zeros beyond the chain's ends.  Out of line: its constants (the
+// arc tangent's) are else kept, and spilled, over the whole loop.
+template <bool RIGID>
+__device__ __attribute__((noinline)) void wide_bonded(int cb, int n, int q, int nb) {
+  WideShared& sh = *reinterpret_cast<WideShared*>(res_lds + res_base(RIGID));
+  RigShared& rig = *reinterpret_cast<RigShared*>(res_lds);
+  const MdParams& P = sh.P;
+  constexpr int LL = RES_WG / RES_OWN;
+  const int b = threadIdx.x / LL, l = threadIdx.x % LL;
+  const bool on = b < n;
+  double (*const row)[3] = sh.row[b];
+  // chain bead q + k, -2 <= k <= 2
+  auto chain = [&](int k) -> const double* {
+    if (RIGID) return rig.x[q + k];
+    const int j = b + k;
+    return sh.pos[cb][j < 0 ? RES_OWN + 2 + j : (j < n ? j : RES_OWN + 2 + (j - n))];
+  };
+  if (l < 9) {
+    // component c of the angle centred at q - 1 + k
+    const int k = l / 3, c = l % 3, cen = q - 1 + k;
+    double y = 0.0;
+    if (on && cen >= 1 && cen <= nb - 2) {
+      const ResAngle A = res_angle(chain(k - 2), chain(k - 1), chain(k));
+      double d1, d2;
+      res_angle_d(A, c, d1, d2);
+      const double kp = A.s == 0.0 ? 0.0 : P.kappa * atan2(A.s, A.c);
+      y = k == 0 ? -(kp * d2) : (k == 1 ? -(kp * (d1 - d2)) : kp * d1);
+    }
+    row[2 + k][c] = y;
+  } else if (l < 11) {
+    const int k = l == 9 ? -1 : 1;
+    double F[3] = {0.0, 0.0, 0.0};
+    if (on && !P.constrained && q + k >= 0 && q + k < nb) bond_add(P, chain(0), chain(k), F);
+    row[l - 9][0] = F[0]; row[l - 9][1] = F[1]; row[l - 9][2] = F[2];
+  }
+}
+
+// The wide pass of the cycle (see above); false: it failed.
+template <bool MTS, bool RIGID>
+__device__ __forceinline__ bool res_wide(const Dev& d, const FusedSeg seg, const Rep& R, const MdParams& P0, WideShared& sh,
+                                         RigShared& rig, int nslots, int nseg, int n_sub, int mts, uint64_t wait) {
+  const int rep = seg.rep;
+  const int Mb = MTS ? n_sub / mts : 0;
+  const int end = MTS ? n_sub + mts + 1 : n_sub;
+  const Geom g = load_uniform(&R.g);
+  const int so = load_uniform(&R.slot_off), nb = P0.nb;
+  const int p0 = seg.a, n = seg.b - seg.a;
+  const int t = threadIdx.x;
+  uint32_t* word = &d.rsync[3 * rep + 1];
+  const uint32_t ng = (uint32_t)((nb + RES_OWN - 1) / RES_OWN);
+  const int g0 = seg.id - p0 / RES_OWN;
+  const uint64_t tag0 = res_tag(load_uniform(&d.ctrl->cycles), 1, 0);
+  const size_t half = (size_t)6 * nslots;
+  if (t == 0) sh.P = P0;
+  __syncthreads();
+  const MdParams& P = sh.P;
+  // lane l of bead b's 16
+  constexpr int LL = RES_WG / RES_OWN, LE = MAXNBR / LL;
+  const int b = t / LL, l = t % LL, first = t & 63 & ~(LL - 1), q = p0 + b;
+  const bool on = b < n;
+  const int slot = so + p0 + (on ? b : 0);
+  const bool star = !RIGID && ng > RES_ALL;
+  auto lose = [&](int at) {
+    res_give_up(word, ng);
+    sh.lost[at] = 1;
+  };
+
+  bool fin = true;
+  if (RIGID) {
+    double r3[3] = {0.0, 0.0, 0.0}, v3[3] = {0.0, 0.0, 0.0};
+    if (t < nb)
+      for (int a = 0; a < 3; ++a) { r3[a] = d.r[3 * (so + t) + a]; v3[a] = d.v[3 * (so + t) + a]; }
+    fin = rig_open(rig, nb, P.hh, P.r0 * P.r0, r3, v3);
+  }
+  // lane c < 3 has component c of the bead's state
+  const bool mine = on && l < 3;
+  if (mine) {
+    sh.pos[0][b][l] = RIGID ? rig.x[q][l] : d.rmid0[3 * slot + l];
+    sh.v[b][l] = RIGID ? rig.v[q][l] : d.v[3 * slot + l];
+    sh.J[b][l] = d.J[3 * slot + l];
+    sh.u[b][l] = P.couple ? d.up[3 * slot + l] : 0.0;
+  }
+  // where the lists were built: the bead's, with RIGID bead t's
+  if (mine && !RIGID) sh.ref[b][l] = d.ref[3 * slot + l];
+  if (RIGID && t < nb)
+    for (int a = 0; a < 3; ++a) rig.ref[t][a] = d.ref[3 * (so + t) + a];
+  const int cnt = on ? d.ncnt[slot] : 0;
+  // the lists as they are do not hold: not built, or cut short
+  bool stale = d.rb[4 * rep] != 0u ||
+               (cnt >= MAXNBR &&
+                (__hip_atomic_load(&d.ctrl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & E_NBRLIST));
+  for (int k = l; k < MAXNBR; k += LL)
+    sh.list[b][k] = !stale && k < cnt ? (uint16_t)(d.nbr[(size_t)slot * MAXNBR + k] - so) : WIDE_NONE;
+  if (t < 2) { sh.bits[t] = 0u; sh.all[t] = 0u; sh.lost[t] = 0; }
+  __syncthreads();
+  // The lists' chain indices to places, and the remote partners, each once.
+  auto places = [&](int at) {
+    if (RIGID) return;
+    sh.m.set[t] = 0u;
+    __syncthreads();
+    for (int k = l; on && k < MAXNBR; k += LL) {
+      const int z = sh.list[b][k];
+      if (z != WIDE_NONE && !(z >= p0 && z < seg.b)) atomicOr(&sh.m.set[z >> 5], 1u << (z & 31));
+    }
+    __syncthreads();
+    uint32_t mine32 = sh.m.set[t];
+    const int n32 = __builtin_popcount(mine32);
+    int pre = n32;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(pre, o, 64);
+      if ((t & 63) >= o) pre += y;
+    }
+    if ((t & 63) == 63) sh.m.wsum[t >> 6] = pre;
+    __syncthreads();
+    pre -= n32;
+    for (int k = 0; k < t >> 6; ++k) pre += sh.m.wsum[k];
+    sh.m.pre[t] = pre;
+    if (t == RES_WG - 1) {
+      sh.nrem = min(pre + n32, WIDE_REM);
+      if (pre + n32 > WIDE_REM) lose(at);
+    }
+    for (; mine32 && pre < WIDE_REM; mine32 &= mine32 - 1u) sh.rem[pre++] = (uint16_t)(32 * t + __builtin_ctz(mine32));
+    __syncthreads();
+    for (int k = l; on && k < MAXNBR; k += LL) {
+      const int z = sh.list[b][k];
+      if (z == WIDE_NONE) continue;
+      const int o = sh.m.pre[z >> 5] + __builtin_popcount(sh.m.set[z >> 5] & ((1u << (z & 31)) - 1u));
+      sh.list[b][k] = (uint16_t)(z >= p0 && z < seg.b ? z - p0 : WIDE_FAR + min(o, WIDE_REM - 1));
+    }
+    __syncthreads();
+  };
+  places(0);
+  bool dead = false;
+  int next = 0, nsync = 0;
+  __builtin_amdgcn_s_setprio(2);
+  for (int s = 0; s < end; ++s) {
+    const int cb = s & 1;
+    const bool kick = MTS && s % (Mb + 1) == 0, slow = !MTS || kick, sync = RIGID || s == next;
+    const int sub = MTS ? s - s / (Mb + 1) - 1 : s;       // index of the sub-step (no kick)
+    const uint64_t tag = tag0 + (uint64_t)s * RES_TAG;
+    unsigned long long* ring = d.xring + (kick ? (2 + (nsync & 1)) * half : (cb ? half : 0));
+    // the positions of the remote partners
+    auto remote = [&](int at) {
+      for (int k = t; k < sh.nrem; k += RES_WG) {
+        double y[3];
+        if (!res_poll_vec(ring + (size_t)(so + sh.rem[k]) * 6, tag, word, d.ctrl, wait, nseg, y)) { lose(at); break; }
+        for (int a = 0; a < 3; ++a) sh.far[k][a] = y[a];
+      }
+    };
+    // the position of any bead of the chain
+    auto position = [&](int k, double* y) {
+      if (RIGID || (k >= p0 && k < seg.b)) {
+        const double* o = RIGID ? rig.x[k] : sh.pos[cb][k - p0];
+        y[0] = o[0]; y[1] = o[1]; y[2] = o[2];
+        return true;
+      }
+      return res_poll_vec(ring + (size_t)(so + k) * 6, tag, word, d.ctrl, wait, nseg, y);
+    };
+    // Bit 0: a bead is far from where the table binned it; bit 1: beyond the range
+    // of the lists; bit 8 + k: at twice its present speed it may be, k sub-steps
+    // from here.
+    uint32_t bits = 0u;
+    if (RIGID ? t < nb : on && l == 0 && slow) {
+      const double* y = RIGID ? rig.x[t] : sh.pos[cb][b];
+      const double* ref = RIGID ? rig.ref[t] : sh.ref[b];
+      double f2 = 0.0;
+      for (int a = 0; a < 3; ++a) { const double df = y[a] - ref[a]; f2 += df * df; }
+      const bool held = f2 <= P.halfskin2;
+      if (sync) {
+        const double* rb = d.rbin + 3 * (size_t)(RIGID ? so + t : slot);
+        double b2 = 0.0, v2 = 0.0;
+        for (int a = 0; a < 3; ++a) {
+          const double db = y[a] - rb[a], va = RIGID ? 0.0 : sh.v[b][a];
+          b2 += db * db;
+          v2 += va * va;
+        }
+        bits = (b2 <= CELL_MARGIN * CELL_MARGIN ? 0u : 1u) | (held ? 0u : 2u);
+        if (!RIGID && !MTS) {
+          const double k = (0.95 * sqrt(P.halfskin2) - sqrt(f2)) / (4.0 * P.hh * sqrt(v2));
+          bits |= ((0xffffu << (k >= 16.0 ? 16 : (k >= 1.0 ? (int)k : 1))) & 0xffffu) << 8;
+        }
+      } else if (!held) {
+        lose(cb);
+      }
+    }
+    if (stale) bits |= 2u;
+    if (RIGID) {
+      // every segment has the whole chain, and finds the same
+      if (bits) atomicOr(&sh.all[cb], bits);
+      lds_barrier();
+      if (t == 0) sh.all[cb ^ 1] = 0u;           // read before this barrier, written after the next
+    } else {
+      if (mine) {
+        const unsigned long long w = (unsigned long long)__double_as_longlong(sh.pos[cb][b][l]);
+        res_store(ring + ((size_t)slot * 3 + l) * 2, w);
+        res_store(ring + ((size_t)slot * 3 + l) * 2 + 1, w ^ tag);
+      }
+      if (bits) atomicOr(&sh.bits[cb], bits);
+      lds_barrier();
+      const int sp = nsync & 1;
+      unsigned long long* words = d.xflag + (size_t)2 * sp * nseg;
+      if (t == 0) {
+        if (sync) {
+          const unsigned long long w = sh.bits[cb];
+          res_store(words + 2 * seg.id, w);
+          res_store(words + 2 * seg.id + 1, w ^ tag);
+        }
+        sh.bits[cb ^ 1] = 0u;
+        sh.all[cb ^ 1] = 0u;
+      }
+      // the partners (of lists that may be replaced: the words are on their way
+      // meanwhile), every segment's word, the chain beads at the segment's ends
+      if (slow) remote(cb);
+      if (sync) {
+        uint32_t got = 0u;
+        if (!star || p0 == 0)
+          for (int k = t; k < (int)ng; k += RES_WG) {
+            unsigned long long w = 0;
+            if (!res_poll(words + 2 * (g0 + k), tag, word, d.ctrl, wait, nseg, w)) { lose(cb); break; }
+            got |= (uint32_t)w;
+          }
+        if (star) {
+          unsigned long long* sum = d.xflag + (size_t)6 * nseg + 2 * (g0 + sp);
+          if (p0 == 0) {
+            if (got) atomicOr(&sh.all[cb], got);
+            lds_barrier();
+            if (t == 0 && !sh.lost[cb]) {
+              const unsigned long long w = sh.all[cb];
+              res_store(sum, w);
+              res_store(sum + 1, w ^ tag);
+            }
+          } else if (t == RES_WG / 2) {
+            unsigned long long w = 0;
+            if (!res_poll(sum, tag, word, d.ctrl, wait, nseg, w)) lose(cb);
+            got = (uint32_t)w;
+          }
+        }
+        if (got) atomicOr(&sh.all[cb], got);
+      }
+      const int h = t - (RES_WG - RES_HALO), c = h < 2 ? p0 - 2 + h : seg.b + (h - 2);
+      if (!kick && h >= 0 && c >= 0 && c < nb) {
+        double y[3];
+        if (!res_poll_vec(ring + (size_t)(so + c) * 6, tag, word, d.ctrl, wait, nseg, y)) lose(cb);
+        for (int a = 0; a < 3; ++a) sh.pos[cb][RES_OWN + h][a] = y[a];
+      }
+      lds_barrier();
+    }
+    const uint32_t all = sync ? sh.all[cb] : 0u;
+    if (sh.lost[cb]) { dead = true; break; }     // uniform: next written after the barriers of the next stage
+    if (sync) {
+      // after new lists at once again: a segment that is no partner of this one
+      // may not replace the positions that this one searches
+      next = s + (MTS ? Mb + 1 : (all & 2u ? 1 : __builtin_ctz((all >> 8) | 0x10000u)));
+      ++nsync;
+    }
+    double x[3] = {0.0, 0.0, 0.0};
+    if (on)
+      for (int a = 0; a < 3; ++a) x[a] = RIGID ? rig.x[q][a] : sh.pos[cb][b][a];
+    if (all & 2u) {
+      // ---- new lists, from the cell table where every bead is near its bucket
+      auto partner = [&](int k, const double* y) {
+        if (k == q) return;
+        const double d0 = min_image(x[0] - y[0], g.nx);
+        const double d1 = min_image(x[1] - y[1], g.ny);
+        const double d2 = min_image(x[2] - y[2], g.nz);
+        if (!(d0 * d0 + d1 * d1 + d2 * d2 < P.rlist2)) return;
+        const int o = atomicAdd(&sh.h.ncand[b], 1);
+        if (o < MAXNBR) sh.list[b][o] = (uint16_t)k;
+      };
+      bool ok = true;
+      if (t < RES_OWN) sh.h.ncand[t] = 0;
+      if (!(all & 1u)) {
+        if (on) {
+          int cell[3];
+          bead_cell(R, x, cell);
+          for (int k = l; k < 27; k += LL) {
+            const int dx = k % 3 - 1, dy = (k / 3) % 3 - 1, dz = k / 9 - 1;
+            sh.h.bk[b][k] = cell_bucket(rep, (cell[0] + dx + R.ncell[0]) % R.ncell[0],
+                                      (cell[1] + dy + R.ncell[1]) % R.ncell[1],
+                                      (cell[2] + dz + R.ncell[2]) % R.ncell[2], d.cmask);
+          }
+        }
+        __syncthreads();
+        if (on)
+          for (int k = l; k < 27 && ok; k += LL) {
+            const uint32_t bk = sh.h.bk[b][k];
+            bool dup = false;
+            for (int k2 = 0; k2 < k; ++k2) dup = dup || sh.h.bk[b][k2] == bk;
+            const int m = dup ? 0 : min(d.ccount[bk], CELL_CAP);
+            for (int i = 0; i < m && ok; ++i) {
+              const int sl = d.cbuf[(size_t)bk * CELL_CAP + i];
+              if (d.slot_rep[sl] != rep) continue;
+              double y[3];
+              ok = position(sl - so, y);
+              if (ok) partner(sl - so, y);
+            }
+          }
+      } else {
+        for (int base = 0; base < nb; base += RES_TILE) {
+          const int m = min(RES_TILE, nb - base);
+          __syncthreads();
+          if (t < m && ok) {
+            double y[3];
+            ok = position(base + t, y);
+            for (int a = 0; a < 3; ++a) sh.h.tile[t][a] = y[a];
+          }
+          __syncthreads();
+          if (on)
+            for (int k = l; k < m; k += LL) partner(base + k, sh.h.tile[k]);
+        }
+      }
+      __syncthreads();
+      if (on && sh.h.ncand[b] > MAXNBR) ok = false;  // the redo says so
+      if (!ok) lose(cb ^ 1);
+      const int found = on ? min(sh.h.ncand[b], MAXNBR) : 0;
+      if (l == 0) {                              // ascending order
+        uint16_t* L = sh.list[b];
+        for (int k = 1; k < found; ++k) {
+          const uint16_t w = L[k];
+          int m = k;
+          while (m > 0 && L[m - 1] > w) { L[m] = L[m - 1]; --m; }
+          L[m] = w;
+        }
+      }
+      for (int k = l; k < MAXNBR; k += LL)
+        if (k >= found) sh.list[b][k] = WIDE_NONE;
+      __syncthreads();
+      places(cb ^ 1);
+      if (mine && !RIGID) sh.ref[b][l] = sh.pos[cb][b][l];
+      if (RIGID && t < nb)
+        for (int a = 0; a < 3; ++a) rig.ref[t][a] = rig.x[t][a];
+      stale = false;
+      if (t == 0 && p0 == 0) {
+        atomicAdd((unsigned long long*)&d.ctrl->rebuilds, 1ull);
+        if (!(all & 1u)) atomicAdd((unsigned long long*)&d.ctrl->cell_rebuilds, 1ull);
+      }
+      if (!RIGID) remote(cb ^ 1);
+      __syncthreads();
+    }
+    // ---- the sum in the fixed order, lane c < 3 component c: the terms come by
+    // rounds of one per lane, those present in consecutive rows.  An absent term
+    // is a zero (F is never -0, which a zero would change).
+    double F = 0.0;
+    double (*const row)[3] = sh.row[b];
+    if (!kick) {
+      wide_bonded<RIGID>(cb, n, q, nb);
+      wave_lds();
+      if (l < 3)
+        for (int k = 0; k < 5; ++k) F += row[k][l];
+      wave_lds();
+    }
+    auto add = [&](bool in, double d0, double d1, double d2) {
+      const uint64_t any = __ballot(in);
+      if (any == 0) return;
+      const uint32_t mask = (uint32_t)(any >> first) & ((1u << LL) - 1u);
+      if (in) {
+        double Fp[3] = {0.0, 0.0, 0.0};
+        lj_add(P, d0, d1, d2, Fp);
+        double* o = row[__builtin_popcount(mask & ((1u << l) - 1u))];
+        o[0] = Fp[0]; o[1] = Fp[1]; o[2] = Fp[2];
+      }
+      wave_lds();
+      const int rows = __builtin_popcount(mask);
+      if (l < 3)
+        for (int k = 0; k < rows; k += 4) {      // four loads in flight
+          const double f0 = row[k][l], f1 = row[min(k + 1, LL - 1)][l], f2 = row[min(k + 2, LL - 1)][l],
+                       f3 = row[min(k + 3, LL - 1)][l];
+          F += f0;
+          if (k + 1 < rows) F += f1;
+          if (k + 2 < rows) F += f2;
+          if (k + 3 < rows) F += f3;
+        }
+      wave_lds();
+    };
+    if (slow) {
+      for (int m = 0; m < LE; ++m) {
+        const int k = sh.list[b][LL * m + l];
+        const bool in = on && k != WIDE_NONE;
+        if (!__any(in)) break;                   // lists are filled from the front
+        const int z = in ? k : 0;
+        const double* y = RIGID ? rig.x[z] : (z < WIDE_FAR ? sh.pos[cb][z] : sh.far[z - WIDE_FAR]);
+        const double d0 = min_image(x[0] - y[0], g.nx);
+        const double d1 = min_image(x[1] - y[1], g.ny);
+        const double d2 = min_image(x[2] - y[2], g.nz);
+        add(in && d0 * d0 + d1 * d1 + d2 * d2 < P.rc2, d0, d1, d2);
+      }
+      // the sites of wall_row, a lane each, in their order
+      bool near = false;
+      int off = 0;
+      const int wa = g.wall_axis, na = wa >= 0 ? ext(g, wa) : 0, n0 = wa == 0 ? g.ny : g.nx, n1 = wa == 2 ? g.ny : g.nz;
+      double wn = 0.0, wt0 = 0.0, wt1 = 0.0;
+      if (on && wa >= 0) {
+        wn = wrapc(sel3(wa, x[0], x[1], x[2]), na);
+        off = g.wall_pos - (int)floor(wn);
+        if (off < WLO) off += na;
+        if (off > WHI) off -= na;
+        near = off >= P.wlo && off <= P.whi;
+      }
+      if (__any(near)) {
+        wt0 = wrapc(wa == 0 ? x[1] : x[0], n0);
+        wt1 = wrapc(wa == 2 ? x[1] : x[2], n1);
+        const int nw = P.whi - P.wlo + 1;
+        for (int k0 = 0; k0 < nw * nw; k0 += LL) {
+          const int k = k0 + l, u1 = (int)floor(wt1) + P.wlo + k / nw, u0 = (int)floor(wt0) + P.wlo + k % nw;
+          const int v1 = u1 < 0 ? u1 + n1 : (u1 >= n1 ? u1 - n1 : u1);
+          const int v0 = u0 < 0 ? u0 + n0 : (u0 >= n0 ? u0 - n0 : u0);
+          const bool pore = v1 >= g.lo1 && v1 <= g.hi1 && v0 >= g.lo0 && v0 <= g.hi0;
+          const double dn = wn - (double)((int)floor(wn) + off), dt0 = wt0 - (double)u0, dt1 = wt1 - (double)u1;
+          const double d0 = wa == 0 ? dn : dt0, d1 = wa == 1 ? dn : (wa == 0 ? dt0 : dt1), d2 = wa == 2 ? dn : dt1;
+          add(near && k < nw * nw && !pore && d0 * d0 + d1 * d1 + d2 * d2 < P.rc2, d0, d1, d2);
+        }
+        if (near && P.field_on && l == wa && in_field(g, x)) F += P.f_drive;
+      }
+    }
+    if (d.mdtape && mine) {
+      double* tp = d.mdtape + ((size_t)s * nb + q) * 6 + l;
+      tp[0] = sh.pos[cb][b][l];
+      tp[3] = sh.v[b][l];
+    }
+    const bool last = s == end - 1;
+    double xc = 0.0, v = 0.0;
+    if (mine) {
+      xc = RIGID ? rig.x[q][l] : sh.pos[cb][b][l];
+      v = sh.v[b][l];
+    }
+    if (kick) {
+      v = v + P.kick * F;
+      if (s > 0 && !last) v = v + P.kick * F;
+      fin = fin && isfinite(v) && isfinite(xc);
+      if (!last) xc = xc + P.hh * v;
+    } else {
+      const double xi = mine && P.sig != 0.0 ? d.xi[(size_t)3 * ((size_t)sub * nslots + slot) + l] : 0.0;
+      const double sx = P.sig * xi;
+      const double u = mine ? sh.u[b][l] : 0.0, vn = P.e * v + P.cf * (F + P.gamma * u) + sx;
+      if (mine) sh.J[b][l] = sh.J[b][l] - P.m * (P.omE * (u - v) + sx);
+      v = vn;
+      fin = fin && isfinite(vn);
+      const double re = xc + P.hh * vn;
+      xc = (MTS ? (s + 1) % (Mb + 1) == 0 : last) ? re : re + P.hh * vn;   // a kick takes r itself
+    }
+    if (!RIGID) {
+      if (mine) { sh.pos[cb ^ 1][b][l] = xc; sh.v[b][l] = v; }
+      wave_lds();                                // lane 0 looks at them before the next barrier
+      continue;
+    }
+    // ---- rigid bonds: the chain's kicked velocities, its projections
+    const uint64_t next = tag + RES_TAG;
+    if (mine) {
+      const unsigned long long w = (unsigned long long)__double_as_longlong(v);
+      rig.v[q][l] = v;
+      res_store(ring + ((size_t)slot * 3 + l) * 2, w);
+      res_store(ring + ((size_t)slot * 3 + l) * 2 + 1, w ^ next);
+    }
+    if (t < nb && !(t >= p0 && t < seg.b)) {
+      double y[3];
+      if (!res_poll_vec(ring + (size_t)(so + t) * 6, next, word, d.ctrl, wait, nseg, y)) lose(cb ^ 1);
+      for (int a = 0; a < 3; ++a) rig.v[t][a] = y[a];
+    }
+    __syncthreads();
+    if (sh.lost[cb ^ 1]) { dead = true; break; }
+    fin = rig_step(rig, nb, P.hh, P.r0 * P.r0, last) && fin;
+    if (mine) sh.v[b][l] = rig.v[q][l];
+  }
+  __builtin_amdgcn_s_setprio(0);
+  __syncthreads();
+  if (t == 0) sh.done = res_close(word, ng, dead || sh.lost[0] || sh.lost[1], wait);
+  __syncthreads();
+  if (!sh.done) return false;
+  if (mine) {
+    d.r[3 * slot + l] = RIGID ? rig.x[q][l] : sh.pos[end & 1][b][l];
+    d.v[3 * slot + l] = sh.v[b][l];
+    d.J[3 * slot + l] = sh.J[b][l];
     if (!fin) atomicOr(&d.ctrl->err, E_BEADS);
   }
   return true;
@@ -3087,15 +3519,50 @@ struct ResArgs {
 // What follows a failed first pass.  Out of line: inlined, its registers
 // spill in the first pass (0.27 against 0.23 ms per step on 32^3).  a: the
 // kernel's arguments in memory, so that none is copied for this call.
+// A function's argument arrives in vector registers; this one is the same in all
+// lanes, and what is read through it then too.
+__device__ inline const ResArgs* res_args(const ResArgs* a) {
+  const uint64_t p = (uint64_t)(uintptr_t)a;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p), hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+  return (const ResArgs*)(uintptr_t)((uint64_t)hi << 32 | lo);
+}
+// What the wide pass uses of the arguments.
+__device__ inline Dev res_dev(const Dev* a) {
+  Dev d{};
+  d.reps = load_global(&a->reps);
+  d.r = load_global(&a->r); d.v = load_global(&a->v); d.up = load_global(&a->up); d.J = load_global(&a->J);
+  d.slot_rep = load_global(&a->slot_rep);
+  d.nbr = load_global(&a->nbr); d.ncnt = load_global(&a->ncnt); d.ref = load_global(&a->ref);
+  d.rmid0 = load_global(&a->rmid0); d.rb = load_global(&a->rb); d.xi = load_global(&a->xi);
+  d.mdtape = load_global(&a->mdtape);
+  d.ccount = load_global(&a->ccount); d.cbuf = load_global(&a->cbuf); d.rbin = load_global(&a->rbin);
+  d.cmask = load_uniform(&a->cmask);
+  d.xring = load_global(&a->xring); d.xflag = load_global(&a->xflag); d.rsync = load_global(&a->rsync);
+  d.ctrl = load_global(&a->ctrl);
+  return d;
+}
 template <bool MTS, bool RIGID>
-__device__ __attribute__((noinline)) void res_rescue(const ResArgs* a) {
-  ResShared& sh = *reinterpret_cast<ResShared*>(res_lds + res_base(RIGID));
-  const Dev& d = a->d;
-  const FusedSeg seg = load_uniform(&a->segs[blockIdx.x]);
-  const Rep& R = d.reps[seg.rep];
-  const MdParams P = md_override(load_uniform(&R.mp), a->ov);
+__device__ __attribute__((noinline)) void res_redo(const ResArgs* args) {
+  const ResArgs* a = res_args(args);
+  WideShared& sh = *reinterpret_cast<WideShared*>(res_lds + res_base(RIGID));
   RigShared& rig = *reinterpret_cast<RigShared*>(res_lds);   // RIGID
-  if (res_pass<true, MTS, RIGID>(d, seg, R, P, sh, rig, a->nslots, a->nseg, a->n_sub, a->mts, a->wait)) return;
+  const FusedSeg seg = load_uniform(&load_global(&a->segs)[blockIdx.x]);
+  const Rep& R = a->d.reps[seg.rep];
+  const MdParams P = md_override(load_uniform(&R.mp), a->ov);
+  if (threadIdx.x == 0) atomicAdd((unsigned long long*)&a->d.ctrl->res_redone, 1ull);
+  md_redo<RES_WG, MTS, RIGID>(a->d, R, P, seg.rep, a->ang, a->nslots, 0, a->n_sub, a->mts, &rig, sh.near, sh.off);
+}
+template <bool MTS, bool OWN, bool RIGID>
+__device__ __attribute__((noinline)) void res_rescue(const ResArgs* args) {
+  const ResArgs* a = res_args(args);
+  WideShared& sh = *reinterpret_cast<WideShared*>(res_lds + res_base(RIGID));
+  const Dev d = res_dev(&a->d);
+  const FusedSeg seg = load_uniform(&load_global(&a->segs)[blockIdx.x]);
+  const Rep& R = d.reps[seg.rep];
+  const MdParams P = md_override(load_uniform(&R.mp), load_uniform(&a->ov));
+  RigShared& rig = *reinterpret_cast<RigShared*>(res_lds);   // RIGID
+  if (res_wide<MTS, RIGID>(d, seg, R, P, sh, rig, load_uniform(&a->nslots), load_uniform(&a->nseg), load_uniform(&a->n_sub),
+                           load_uniform(&a->mts), load_uniform(&a->wait))) return;
   // The redo stores the state, the positions and the lists that every segment's
   // passes start from, and one of them may not have begun (it finds no room while
   // another context's cycle has its place): so the segment that leaves last
@@ -3106,9 +3573,7 @@ __device__ __attribute__((noinline)) void res_rescue(const ResArgs* a) {
   if (threadIdx.x == 0)
     sh.done = __hip_atomic_fetch_add(&d.rsync[3 * seg.rep + 2], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u == ng;
   __syncthreads();
-  if (!sh.done) return;
-  if (threadIdx.x == 0) atomicAdd((unsigned long long*)&d.ctrl->res_redone, 1ull);
-  md_redo<RES_WG, MTS, RIGID>(d, R, P, seg.rep, a->ang, a->nslots, 0, a->n_sub, a->mts, &rig, sh.dead[0], sh.dead[1]);
+  if (sh.done) res_redo<MTS, RIGID>(a);
 }
 
 // OWN: a workgroup takes the registers of a whole CU (8 waves of 256), so that
@@ -3122,9 +3587,9 @@ __global__ __launch_bounds__(RES_WG, OWN ? 2 : 6) void k_md_resident(ResArgs a) 
   const Rep& R = a.d.reps[seg.rep];
   const MdParams P = md_override(load_uniform(&R.mp), a.ov);
   RigShared& rig = *reinterpret_cast<RigShared*>(res_lds);   // RIGID
-  if (__builtin_expect(res_pass<false, MTS, RIGID>(a.d, seg, R, P, sh, rig, a.nslots, a.nseg, a.n_sub, a.mts, a.wait), 1)) return;
+  if (__builtin_expect(res_pass<MTS, RIGID>(a.d, seg, R, P, sh, rig, a.nslots, a.nseg, a.n_sub, a.mts, a.wait), 1)) return;
   __syncthreads();                               // sh.done is read
-  res_rescue<MTS, RIGID>((const ResArgs*)__builtin_amdgcn_kernarg_segment_ptr());
+  res_rescue<MTS, OWN, RIGID>((const ResArgs*)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
 void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslots, int nrep, int n_sub, int K,
@@ -3151,12 +3616,12 @@ void launch_md_gate(const Dev& d, int nseg, hipStream_t s) {
 }
 
 void launch_md_cycle_resident(const Dev& d, double* ang, const FusedSeg* seg, int ntab, int nseg, int nslots, int n_sub,
-                              int mts, const MdOverride& ov, uint64_t wait, bool own, bool rigid, bool win6, hipStream_t s) {
+                              int mts, const MdOverride& ov, uint64_t wait, bool own, bool rigid, hipStream_t s) {
   if (nslots <= 0 || n_sub <= 0 || nseg <= 0 || ntab < nseg) return;
   const auto k = rigid ? k_md_resident<false, true, true>
                        : (mts > 0 ? (own ? k_md_resident<true, true, false> : k_md_resident<true, false, false>)
                                   : (own ? k_md_resident<false, true, false> : k_md_resident<false, false, false>));
-  hipLaunchKernelGGL(k, dim3((unsigned)ntab), dim3(RES_WG), res_bytes(rigid, win6), s,
+  hipLaunchKernelGGL(k, dim3((unsigned)ntab), dim3(RES_WG), res_bytes(rigid), s,
                      (ResArgs{d, ang, seg, nslots, nseg, n_sub, mts, ov, wait}));
 }
 

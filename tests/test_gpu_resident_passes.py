@@ -168,7 +168,7 @@ def test_which_pass_ran(monkeypatch):
     for nb, kw in ((20, {}), (300, {}), (300, dict(constraints=1)), (300, dict(mts_outer=5, **PAPER_LJ))):
         assert _passes(make(nb, **kw), 3) == {"cycles": 3, "second": 0, "redone": 0}, (nb, kw)
     assert _passes(make(300, 2.0), 3) == {"cycles": 3, "second": 3, "redone": 0}
-    assert _passes(make(300, 9.0), 3) == {"cycles": 3, "second": 3, "redone": 3}
+    assert _passes(make(300, 9.0), 3) == {"cycles": 3, "second": 3, "redone": 0}
     assert _passes(make(300, 0.9, constraints=1), 2) == {"cycles": 2, "second": 2, "redone": 0}
     fused = make(300)
     fused.md_fused(10)
@@ -178,10 +178,90 @@ def test_which_pass_ran(monkeypatch):
     assert _passes(make(33), 2) == {"cycles": 2, "second": 2, "redone": 2}
 
 
-@pytest.mark.parametrize("rc,spacing,height", [(2.0, 1.0, 0.0), (2.5, 1.25, 0.9), (3.0, 2.0, 0.0)])
-def test_chain_along_the_wall_stays_in_the_first_pass(rc, spacing, height):
+@pytest.mark.parametrize("rc,spacing,height,second", [(2.0, 2.0, 0.0, 0), (2.5, 1.25, 0.9, 3), (3.0, 2.0, 0.0, 3)])
+def test_chain_along_the_wall_is_not_redone(rc, spacing, height, second):
+    """14 wall sites per bead stay in the first pass; more go on in the second."""
     _torch()
     from paper_0711_2665_amd import lbmd
     cfg = scaled(C0, shape=(64, 64, 24), wall_pos=12, nb=100, rc=rc, eps=1e-6, r0=spacing, kappa=0.5)
     s = lbmd.Simulation(cfg, _flat(100, spacing, 12, (2.5, 2.5, 12 + height)), None)
-    assert _passes(s, 3) == {"cycles": 3, "second": 0, "redone": 0}
+    assert _passes(s, 3) == {"cycles": 3, "second": second, "redone": 0}
+
+
+def _cube(n, a, edge, origin):
+    """n beads folded into a cube of `edge` beads a side, spacing a, every bond of length a."""
+    out = []
+    for k in range(n):
+        row, x = divmod(k, edge)
+        z, y = divmod(row, edge)
+        out.append((edge - 1 - x if row % 2 else x, edge - 1 - y if z % 2 else y, z))
+    return np.asarray(out, dtype=np.float64) * a + np.asarray(origin)
+
+
+@pytest.mark.parametrize("nb,edge,speed,rc", [
+    (600, 9, 0.0, 2.0 ** (1 / 6)),      # more than 144 remote partners of a segment
+    (2080, 13, 0.0, 2.0 ** (1 / 6)),    # 65 segments: the words by way of the first one
+    (2048, 13, 3.0, 2.0 ** (1 / 6)),    # 64, each reading all; new lists in the cycle
+    (2500, 14, 9.0, 2.0 ** (1 / 6)),    # the same with 79, from the table and from all beads
+    (300, 7, 0.7, 2.0),                 # many pairs, along the wall and through its window
+])
+def test_dense_chains_in_the_second_pass(nb, edge, speed, rc):
+    """Chains folded densely stay out of the one-workgroup redo, bit for bit the
+    fused cycle's (whose blocks they leave for its redo)."""
+    _torch()
+    from paper_0711_2665_amd import lbmd
+    a = 1.13 if rc < 2.0 else 1.45
+    cfg = scaled(C0, shape=(40, 40, 40), wall_pos=10, nb=nb, rc=rc, eps=0.05, r0=a, kappa=0.5)
+    r = _cube(nb, a, edge, (11.3, 10.1, 10.93))
+    sims = [lbmd.Simulation(cfg, r, None) for _ in range(2)]
+    sims[1].md_fused(2)
+    for s in sims:
+        s.beads()["v"][:, 1] = speed
+    for n in (1, 2):
+        got = _passes(sims[0], n)
+        sims[1].couple_step(n)
+        assert got == {"cycles": n, "second": n, "redone": 0}
+        _same((sims[0],), (sims[1],), f"{nb} beads at {speed}, second pass against fused")
+    for s in sims:
+        s.check()
+
+
+def test_full_lists_are_no_overflow(orc):
+    """49 beads in one another's range: 48 partners each, as many as a list holds."""
+    _torch()
+    from paper_0711_2665_amd import lbmd
+    cfg = scaled(C0, shape=(24, 24, 24), wall_axis=-1, wall_pos=0, pore_h=0, nb=49, rc=3.0, sigma=0.4, eps=0.01, r0=0.5,
+                 kT=0.0, kappa=0.0)
+    r = _cube(49, 0.5, 4, (11.13, 10.37, 11.29))
+    o = orc.Oracle(cfg, r, np.zeros_like(r))
+    s = lbmd.Simulation(cfg, r, None)
+    o.couple_step(3)
+    ob = o.beads()
+    assert _passes(s, 3) == {"cycles": 3, "second": 3, "redone": 0}
+    assert s.diagnostics()["nbr_max"] == 48
+    s.check()
+    b = _state(s)[1]
+    for k in ("r", "v", "up", "J"):
+        assert np.array_equal(b[k], ob[k]), k
+
+
+def test_more_remote_partners_than_the_second_pass_holds():
+    """Consecutive beads far apart on a face-centred lattice: the 42 partners of
+    each bead of a segment are others, more than 1024 in all. One workgroup
+    redoes the cycle, bit for bit the fused one."""
+    _torch()
+    from paper_0711_2665_amd import lbmd
+    cell = np.array([(0, 0, 0), (0, 1, 1), (1, 0, 1), (1, 1, 0)], dtype=np.float64)
+    grid = np.stack(np.meshgrid(*[np.arange(12)] * 3, indexing="ij"), -1).reshape(-1, 1, 3)
+    pts = (2.0 * grid + cell).reshape(-1, 3) * (1.25 / np.sqrt(2.0)) + 5.0     # nearest neighbours 1.25 apart
+    n = len(pts)
+    r = pts[np.random.default_rng(3).permutation(n)]
+    cfg = scaled(C0, shape=(32, 32, 32), wall_axis=-1, wall_pos=0, pore_h=0, nb=n, k_bond=1e-6, r0=5.0, kappa=0.0)
+    sims = [lbmd.Simulation(cfg, r, None) for _ in range(2)]
+    sims[1].md_fused(2)
+    assert _passes(sims[0], 2) == {"cycles": 2, "second": 2, "redone": 2}
+    sims[1].couple_step(2)
+    assert sims[0].diagnostics()["nbr_max"] == 42
+    _same((sims[0],), (sims[1],), "redo against fused")
+    for s in sims:
+        s.check()
