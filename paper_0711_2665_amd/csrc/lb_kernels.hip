@@ -413,8 +413,7 @@ __global__ void k_spread_lb(const T* __restrict__ A, T* __restrict__ B, Dev d, i
   Fr[n] = (T)F[0];
   Fr[N + n] = (T)F[1];
   Fr[2 * N + n] = (T)F[2];
-  int s = atomicAdd(&d.ctrl->touched, 1u);
-  d.touched[s] = make_int2(rep, n);
+  atomicAdd(&d.ctrl->touched, 1u);             // one per wave, by the compiler
   const long no = R.node_off;
   lb_node<T, DEV>(A + (size_t)Q * no, B + (size_t)Q * no, fr, Fr, R.lp, d.ctrl, n, fr[n]);
 }
