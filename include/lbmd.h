@@ -284,10 +284,8 @@ int lb_md_fused(lb_ctx* ctx, int K);
  * nodes of a tile (at most 4 per pass, their loads issued together).  cap 0
  * leaves the occupancy to the hardware; cap in [2, 8] lets at most cap sweep
  * workgroups share a CU (each reserves LDS it does not use), which leaves
- * the rest of the CU to the bead phase running beside the sweep.  A context
- * starts with tiles of 256 nodes, grid 0 and cap 0, in order 1 where its two
- * population arrays take 100 to 256 MB, else 0.  Results do not depend on the
- * layout.  Synchronises the stream (uploads the tile
+ * the rest of the CU to the bead phase running beside the sweep.  Results do
+ * not depend on the layout.  Synchronises the stream (uploads the tile
  * table).  LB_ERR_ARG: order not 0 or 1, grid < 0, cap outside {0, 2..8},
  * tile_nodes not a positive multiple of 256. */
 int lb_sweep_config(lb_ctx* ctx, int tile_nodes, int order, int grid, int cap);

@@ -524,20 +524,6 @@ std::vector<Tile> tile_table(const lb_ctx* c, const SweepCfg& sc) {
   return t;
 }
 
-// The layout a context starts with.  Chunks where the two population arrays are
-// a few times the L2s' 32 MB but fit in the 256 MB behind them: a tile's
-// neighbours in y and z are then read again while one XCD's L2 still has them.
-// us per fluid step, order 0 / 1: 64^3 FP64 (80 MB) 17 / 19, 96^3 FP32 (134 MB)
-// 26.9 / 26.7, 201 x 97 x 53 FP32 (158 MB) 41 / 38, 301 x 77 x 59 (208 MB) 57 / 52.
-// Above it depends: 128^3 FP32 (319 MB) 60 / 57 athermal, in runs of four thermal
-// steps on new populations 65 / 67; 160^3 120 / 122, 256^3 442 / 480.
-SweepCfg default_sweep(const lb_ctx* c) {
-  SweepCfg sc;
-  const double bytes = 2.0 * Q * (c->dev ? 4.0 : 8.0) * (double)c->pk.nodes;
-  sc.order = bytes >= 100e6 && bytes <= 256e6 ? 1 : 0;
-  return sc;
-}
-
 int upload_tiles(lb_ctx* c, const SweepCfg& sc) {
   if (sc.tile_nodes < TILE_MIN || sc.tile_nodes % TILE_MIN) return fail(LB_ERR_ARG, "tile size must be a multiple of %d", TILE_MIN);
   std::vector<Tile> t = tile_table(c, sc);
@@ -1113,7 +1099,7 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   }
   rc = take_acc("init");
   if (rc) { lb_destroy(c); return rc; }
-  rc = upload_tiles(c, default_sweep(c));
+  rc = upload_tiles(c, SweepCfg{});
   if (rc) { lb_destroy(c); return rc; }
   rc = check_hip("init");
   if (rc) { lb_destroy(c); return rc; }
