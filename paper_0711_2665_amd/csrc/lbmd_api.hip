@@ -448,6 +448,8 @@ struct lb_ctx {
   int nrtab = 0;             // its entries
   uint64_t md_wait = RES_WAIT;   // longest wait inside it, ticks of the 100 MHz clock
   int64_t steps = 0;
+  int nchain = 0;            // replicas with beads
+  int64_t res_cycles = 0;    // replica cycles enqueued as resident ones
   // second stream for the sweep over the nodes without bead force, which
   // runs concurrently with the bead phase on the caller's; fork/join events
   hipStream_t s2 = nullptr;
@@ -648,9 +650,11 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
   MdOverride none{};
   if (c->fusedK > 0 && !D.mdtape)
     launch_md_cycle_fused(D, c->fb, c->pk.nseg, c->nslots, c->nrep, c->n_sub, c->fusedK, st);
-  else if (resident)
+  else if (resident) {
+    if (!c->capturing) c->res_cycles += c->nchain;
     launch_md_cycle_resident(D, c->fb.ang, c->rseg, c->nrtab, c->pk.nrseg, c->nslots, c->n_sub, c->mts, none, c->md_wait,
                              c->resident_own, c->any_constrained, st);
+  }
   else if (c->mts > 0) launch_md_cycle_mts(D, c->nslots, c->n_sub, c->mts, st);
   else launch_md_cycle(D, c->nslots, c->nrep, c->n_sub, none, st, false, c->any_constrained);
   if (resident) sweep_side();
@@ -912,6 +916,7 @@ int lb_ensemble_init(const lb_desc* d, int nrep, const lb_buffers* b, const doub
   c->wl = work_layout(d, nrep, c->pk);
   c->sl = state_layout(d, nrep, c->pk);
   c->nslots = c->pk.slots;
+  for (int r = 0; r < nrep; ++r) c->nchain += d[r].nb > 0 ? 1 : 0;
   // every chain's neighbour lists are built from the cell table at every
   // coupled step, beside the spreading, with a skin wide enough that a
   // step's motion rarely forces a rebuild inside the sub-cycle
@@ -1204,6 +1209,7 @@ int lb_ensemble_run(lb_ctx* c, int nsteps, int use_graph) {
       ensure_noise(c, c->s);
       ensure_lists(c, c->s);
     }
+    if (c->resident && c->fusedK == 0) c->res_cycles += (int64_t)(left / 2) * 2 * c->nchain;
     for (; left >= 2; left -= 2) acc(hipGraphLaunch(c->gexec, c->s));
   }
   for (; left > 0; --left) enqueue_coupled_step(c, c->s);
@@ -1229,6 +1235,7 @@ int md_relax(lb_ctx* c, int nsub_total, double gamma_relax) {
   while (left > 0) {
     int n = left < c->n_sub ? left : c->n_sub;
     if (c->resident && n >= RES_MIN_SUB) {
+      c->res_cycles += c->nchain;
       launch_nbr_build(c->D, c->nslots, c->nrep, c->s);
       launch_md_begin(c->D, c->nrep, c->s);
       launch_md_start(c->D, c->nslots, ov, c->s);
@@ -1343,7 +1350,7 @@ int lb_md_passes(lb_ctx* c, int64_t* out) {
   if (!c || !out) return fail(LB_ERR_ARG, "bad arguments");
   Ctrl h;
   if (int rc = read_ctrl(c, h)) return rc;
-  out[0] = (int64_t)h.res_cycles;
+  out[0] = c->res_cycles;
   out[1] = (int64_t)h.res_second;
   out[2] = (int64_t)h.res_redone;
   return LB_OK;
@@ -1427,7 +1434,7 @@ struct Snapshot {
   char* mem = nullptr;
   size_t pops = 0, beads = 0, work = 0, force = 0;
   int cur = 0;
-  int64_t steps = 0;
+  int64_t steps = 0, res_cycles = 0;
   bool lists_stale = true;
   bool noise_ready = false;
 };
@@ -1453,6 +1460,7 @@ int snapshot_take(lb_ctx* c, Snapshot& S, char* mem) {
                      hipMemcpyDeviceToDevice, c->s));
   S.cur = c->cur;
   S.steps = c->steps;
+  S.res_cycles = c->res_cycles;
   S.lists_stale = c->lists_stale;
   S.noise_ready = c->noise_ready;
   return take_acc("snapshot");
@@ -1462,6 +1470,7 @@ void snapshot_restore(lb_ctx* c, const Snapshot& S) {
   const size_t es = c->dev ? sizeof(float) : sizeof(double);
   c->cur = S.cur;
   c->steps = S.steps;
+  c->res_cycles = S.res_cycles;
   c->lists_stale = S.lists_stale;
   c->noise_ready = S.noise_ready;
   const char* o = S.mem;

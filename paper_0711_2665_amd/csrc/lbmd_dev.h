@@ -118,10 +118,10 @@ struct Ctrl {
   uint64_t cycles;           // sub-cycles opened so far: the tag of the resident cycle's exchanges
   uint32_t placed;           // workgroups of the current resident cycle that have started
   uint32_t pad0;
-  // resident cycles of a replica, those whose first pass failed, and those that
-  // one workgroup redid (diagnostic)
-  uint64_t res_cycles, res_second, res_redone;
-  uint32_t pad[32];
+  // resident cycles of a replica whose first pass failed, and those that one
+  // workgroup redid (diagnostic)
+  uint64_t res_second, res_redone;
+  uint32_t pad[34];
 };
 static_assert(sizeof(Ctrl) == 256, "control block is one 256-byte line");
 

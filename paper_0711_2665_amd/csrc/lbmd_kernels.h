@@ -290,10 +290,12 @@ void launch_md_cycle_fused(const Dev& d, const FusedBufs& fb, int nseg, int nslo
 // exchange within an XCD), 32 x 100 beads 0.34 against 0.38 (0.30), 2000 beads
 // with M = 5 on 256 x 256 x 128 (FP32) 0.35 against 0.47; but 4000 beads there
 // in FP64 0.64 against 0.60, 8000 beads on 512 x 256 x 256 1.60 against 1.11, 64
-// uneven replicas (432 segments) 1.28 against 0.96.  So: up to RES_OWN_WG segments (half of the CUs; two contexts fit beside each
-// other) that leave a quarter of every XCD's CUs to the sweep, and at most
-// RES_OWN_BYTES of populations per sub-step (about what the sweep moves in that
-// time).
+// uneven replicas (432 segments) 1.28 against 0.96.  So: up to RES_OWN_WG
+// segments (half of the CUs; two contexts fit beside each other) that leave a
+// quarter of every XCD's CUs to the sweep, and at most RES_OWN_BYTES of
+// populations per sub-step (about what the sweep moves in that time).  2000 beads
+// in FP64 on 256 x 256 x 128, 1.6 times over that limit, lie between: 0.563
+// against 0.576.
 constexpr int XRING = 8;                       // slots of xring
 constexpr int XFLAG = 4;
 constexpr int XCDS = 8;

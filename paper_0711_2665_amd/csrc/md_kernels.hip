@@ -2455,7 +2455,6 @@ __device__ __forceinline__ bool res_pass(const Dev& d, const FusedSeg seg, const
     sh.lost = 0;
     __hip_atomic_fetch_add(&d.ctrl->placed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (seg.id == 0) atomicAdd((unsigned long long*)&d.ctrl->substeps, (unsigned long long)n_sub);
-    if (p0 == 0) atomicAdd((unsigned long long*)&d.ctrl->res_cycles, 1ull);
     const unsigned long long w = res_xcd();
     res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id, w);
     res_store(d.xflag + 4 * (size_t)nseg + 2 * seg.id + 1, w ^ tag0);
