@@ -654,9 +654,11 @@ void enqueue_coupled_step_ab(lb_ctx* c, const void* A, void* B, hipStream_t st) 
     if (!c->capturing) c->res_cycles += c->nchain;
     launch_md_cycle_resident(D, c->fb.ang, c->rseg, c->nrtab, c->pk.nrseg, c->nslots, c->n_sub, c->mts, none, c->md_wait,
                              c->resident_own, c->any_constrained, st);
+  } else if (c->mts > 0) {
+    launch_md_cycle_mts(D, c->nslots, c->n_sub, c->mts, st);
+  } else {
+    launch_md_cycle(D, c->nslots, c->nrep, c->n_sub, none, st, false, c->any_constrained);
   }
-  else if (c->mts > 0) launch_md_cycle_mts(D, c->nslots, c->n_sub, c->mts, st);
-  else launch_md_cycle(D, c->nslots, c->nrep, c->n_sub, none, st, false, c->any_constrained);
   if (resident) sweep_side();
   if (c->dev) launch_spread_lb<float, true>(A, B, D, c->nslots, c->nrep, st);
   else launch_spread_lb<double, false>(A, B, D, c->nslots, c->nrep, st);
